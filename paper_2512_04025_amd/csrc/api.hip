@@ -281,7 +281,7 @@ int psa_attention_fwd(const psa_params* p, const void* Q, const void* K, const v
   uint32_t* desc = reinterpret_cast<uint32_t*>(at(scratch, pl.off_desc));
   if (pl.desc_pitch > 0 && launch_tiles(pl, idx, cnt, desc, s) != hipSuccess) return PSA_ELAUNCH;
   const hipError_t e = pl.use_mfma ? launch_attn_mfma(pl, Q, K, V, Kpyr, Vpyr, idx, cnt, desc, O, lse, s)
-                                   : launch_attn_rows(pl, Q, K, V, Kpyr, Vpyr, idx, cnt, O, lse, s);
+                                   : launch_attn_f32(pl, Q, K, V, Kpyr, Vpyr, idx, cnt, O, lse, s);
   return e == hipSuccess ? PSA_OK : PSA_ELAUNCH;
 }
 
@@ -291,7 +291,7 @@ int psa_dense_ref(const psa_params* p, const void* Q, const void* K, const void*
   const int rc = make_plan(p, &pl);
   if (rc != PSA_OK) return rc;
   if (!Q || !K || !V || !O) return PSA_EINVAL;
-  const hipError_t e = launch_attn_rows(pl, Q, K, V, nullptr, nullptr, nullptr, nullptr, O, lse,
+  const hipError_t e = launch_attn_f32(pl, Q, K, V, nullptr, nullptr, nullptr, nullptr, O, lse,
                                         static_cast<hipStream_t>(stream));
   return e == hipSuccess ? PSA_OK : PSA_ELAUNCH;
 }
@@ -388,7 +388,7 @@ int psa_attention_fwd_static(const psa_params* p, const void* Q, const void* K, 
   if (launch_schedule(pl, M, idx, cnt, s) != hipSuccess) return PSA_ELAUNCH;
   if (pl.desc_pitch > 0 && launch_tiles(pl, idx, cnt, desc, s) != hipSuccess) return PSA_ELAUNCH;
   const hipError_t e = pl.use_mfma ? launch_attn_mfma(pl, Q, K, V, Kpyr, Vpyr, idx, cnt, desc, O, lse, s)
-                                   : launch_attn_rows(pl, Q, K, V, Kpyr, Vpyr, idx, cnt, O, lse, s);
+                                   : launch_attn_f32(pl, Q, K, V, Kpyr, Vpyr, idx, cnt, O, lse, s);
   return e == hipSuccess ? PSA_OK : PSA_ELAUNCH;
 }
 

@@ -79,7 +79,7 @@ hipError_t launch_schedule(const Plan& pl, const uint8_t* M, uint16_t* idx, int3
 // load instructions, level and irregularity (Plan::off_desc; only when Plan::desc_pitch > 0)
 hipError_t launch_tiles(const Plan& pl, const uint16_t* idx, const int32_t* cnt, uint32_t* desc, hipStream_t s);
 // idx == nullptr selects dense attention (every key block at level 1)
-hipError_t launch_attn_rows(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp,
+hipError_t launch_attn_f32(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp,
                             const void* Vp, const uint16_t* idx, const int32_t* cnt, void* O, float* lse,
                             hipStream_t s);
 hipError_t launch_attn_mfma(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp,

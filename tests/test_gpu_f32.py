@@ -1,0 +1,84 @@
+"""The fp32 matrix-core kernels at the sizes where their tiles and teams end, against the oracle.
+
+Tolerance: fp32 products and sums of at most a few thousand terms with accurate exp: the fp32 bar of the
+parity tests (1e-5); bfloat16 inputs through the same arithmetic are rounded once on the way out (2^-9 of
+values below 4)."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+from oracle import psa_oracle as orc
+from tests.psa_testlib import Buffers, from_dev, gpu_params, to_dev
+
+pytestmark = pytest.mark.gpu
+
+psa = pytest.importorskip("paper_2512_04025_amd")
+
+
+def _problem(dtype, B, Hq, Hkv, N, d, bq, bk, levels, causal, seed=3):
+    op = orc.Params(B=B, Hq=Hq, Hkv=Hkv, N=N, d=d, bq=bq, bk=bk, levels=levels, dtype=dtype, causal=causal, sq=8, sk=1)
+    host = si.random_qkv(seed, B, Hq, Hkv, N, d, dtype)
+    rng = np.random.default_rng(seed + 1)
+    vis = orc.block_visibility(op)
+    M = rng.integers(0, levels + 1, size=(B, Hq, op.nq, op.nk)).astype(np.uint8)
+    M[..., 0] = 1
+    M = np.where(vis[None, None] == 0, 0, np.where(vis[None, None] == 2, 1, M)).astype(np.uint8)
+    return op, gpu_params(op), host, M
+
+
+# (dtype, B, Hq, Hkv, N, d, bq, bk, levels, causal): teams of 1, 2 and 4; ragged tails; blocks of one pooled key, of more
+# keys than a tile; query blocks that are no multiple of a team's rows
+SHAPES = [
+    ("f32", 1, 2, 1, 333, 64, 64, 64, 4, False),
+    ("f32", 1, 2, 2, 40, 128, 32, 8, 4, False),
+    ("f32", 2, 2, 1, 515, 128, 24, 16, 5, True),
+    ("f32", 1, 12, 12, 1000, 64, 128, 64, 3, False),
+    ("f32", 1, 12, 4, 1021, 128, 64, 32, 3, True),
+    ("f32", 2, 16, 4, 1001, 64, 128, 256, 4, True),
+    ("f32", 1, 32, 8, 1023, 128, 128, 64, 4, False),
+    ("bf16", 1, 2, 2, 700, 128, 96, 64, 3, True),
+    ("bf16", 1, 32, 8, 1530, 64, 192, 32, 2, False),
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "-".join(map(str, s)))
+def test_attention_and_dense_at_the_edges(shape):
+    import torch
+    op, gp, host, M = _problem(*shape)
+    Q64, K64, V64 = (si.to_f64(x, op.dtype) for x in host)
+    Qd, Kd, Vd = (to_dev(x, op.dtype) for x in host)
+    buf = Buffers(gp)
+    tol = 1e-5 if op.dtype == "f32" else 1e-2
+    psa.psa_build_pyramid(gp, Kd, Vd, buf.Kpyr, buf.Vpyr)
+    buf.O.fill_(float("nan"))
+    psa.psa_attention_fwd(gp, Qd, Kd, Vd, buf.Kpyr, buf.Vpyr, torch.from_numpy(M).cuda(), buf.O, buf.scratch, lse=buf.lse)
+    torch.cuda.synchronize()
+    O, lse = orc.psa_attention(Q64, orc.build_pyramid(K64, op), orc.build_pyramid(V64, op), M, op)
+    assert np.abs(from_dev(buf.O, op.dtype) - O).max() <= tol
+    assert np.abs(buf.lse.cpu().numpy() - lse).max() <= 1e-4
+    buf.O.fill_(float("nan"))
+    psa.psa_dense_ref(gp, Qd, Kd, Vd, buf.O, lse=buf.lse)
+    torch.cuda.synchronize()
+    O, lse = orc.dense_attention(Q64, K64, V64, op)
+    assert np.abs(from_dev(buf.O, op.dtype) - O).max() <= tol
+    assert np.abs(buf.lse.cpu().numpy() - lse).max() <= 1e-4
+
+
+@pytest.mark.parametrize("N,Hq,bq", [(333, 2, 64), (1000, 12, 64), (1000, 32, 128)])
+def test_values_hidden_by_the_causal_mask_may_be_infinite(N, Hq, bq):
+    """The last token's value is infinite: no row before it sees that token, so no row before it changes."""
+    import torch
+    op, gp, host, M = _problem("f32", 1, Hq, 1, N, 64, bq, 64, 3, True)
+    Qd, Kd, Vd = (to_dev(x, "f32") for x in host)
+    outs = []
+    for bad in (None, float("inf")):
+        V = Vd.clone()
+        if bad is not None:
+            V[:, :, -1] = bad
+        buf = Buffers(gp)
+        psa.psa_build_pyramid(gp, Kd, V, buf.Kpyr, buf.Vpyr)
+        psa.psa_attention_fwd(gp, Qd, Kd, V, buf.Kpyr, buf.Vpyr, torch.from_numpy(M).cuda(), buf.O, buf.scratch)
+        torch.cuda.synchronize()
+        outs.append(from_dev(buf.O, "f32"))
+    assert np.abs(outs[1][:, :, :-1] - outs[0][:, :, :-1]).max() <= 1e-5
+    assert np.all(np.isinf(outs[1][:, :, -1]) | np.isnan(outs[1][:, :, -1]))
