@@ -5,38 +5,29 @@
 //   dP_g = dO . vbar_g,  D = dO . O,  dS_g = P_g (dP_g - D),
 //   dq = scale sum_g dS_g kbar_g,  dkbar_g = scale sum_rows dS_g q,  dvbar_g = sum_rows P_g dO,
 // and the gradient of a pooled token is shared equally by the c_g tokens under it (Eq. 2-3).
-// The level map is a constant.  Everything is fp32 on the vector unit (a correctness-first path that
-// serves both element types and every shape), deterministic, without atomics:
+// The level map is a constant.  Everything is in fp32 arithmetic, deterministic, without atomics; it serves
+// float32 and the bfloat16 shapes that attn_bwd_mfma.hip does not take:
 //   rowdot_kernel   D = dO . O per query row
-//   bwd_dq_kernel   one workgroup per 64 query rows, walking the row's level-sorted block list
-//   bwd_dkv_kernel  one workgroup per (key head, key block, level), walking the column of the level
-//                   map; writes the gradient of every pooled token of every level (fp32)
+//   bwd_dq_kernel   one workgroup per 32, 64 or 128 query rows, walking the row's level-sorted block list
+//   bwd_dkv_kernel  one workgroup per (key head, up to 32 pooled keys of a block, level), walking the column
+//                   of the level map; writes the gradient of every pooled token of every level (fp32)
 //   unpool_kernel   dK, dV = sum over the levels of the pooled gradients / c_g
-// Four lanes share a row (of queries or of pooled keys), each owning every fourth 16-byte group of
-// channels; dot products are completed with two lane exchanges inside the quad.
+// The products run on v_mfma_f32_32x32x2_f32 and are bound by its rate (64 FLOP per cycle and SIMD); the
+// operands of a 32 x 32 tile are read from LDS in an eighth of that time, so tiles are staged through registers
+// during the products and one wavefront per SIMD (up to 512 registers at d = 128) keeps the pipe busy.
+// Measured against four lanes per row on the vector unit, which this replaces (2 heads x 1000 tokens, d = 64,
+// four levels): dK, dV 641 -> 45 us (four launches -> one), dQ 78 -> 16 us, the whole call 735 -> 62 us.
 #include "psa_dev.h"
 #include "psa_internal.h"
 
 namespace psa {
 
 struct BwdArgs {
-  int N, Hq, Hkv, nq, nk, bq, bk, H, causal;
+  int N, Hq, Hkv, nq, nk, bq, bk, lg_bk, H, causal;
   float scale;
   int64_t lvl_off[PSA_MAX_LEVELS + 2];   // level h >= 2 inside one pyramid buffer (elements)
   int64_t glvl_off[PSA_MAX_LEVELS + 2];  // level h >= 1 inside one pooled-gradient buffer (elements)
 };
-
-constexpr int BWD_TK = 32;   // pooled keys / query rows staged per step
-
-__device__ __forceinline__ float quad_sum(float x) {
-  x += __shfl_xor(x, 1, 64);
-  x += __shfl_xor(x, 2, 64);
-  return x;
-}
-
-// channel of element e (0 .. D/4-1) of quarter qd: groups of four consecutive channels are dealt
-// round-robin to the four lanes of a quad, so a quad reads 16 consecutive floats of an LDS row at once
-__device__ __forceinline__ int quad_channel(int e, int qd) { return (e >> 2) * 16 + qd * 4 + (e & 3); }
 
 // out[r] = A[r] . B[r] (D = dO . O of the softmax backward).  A row is shared by d / VEC consecutive lanes
 // (8, 16 or 32), each with one 16-byte load per tensor; the partial sums meet in a butterfly.
@@ -60,215 +51,459 @@ __global__ __launch_bounds__(256) void rowdot_kernel(const T* __restrict__ A, co
   if (r < rows && c == 0) out[r] = acc;
 }
 
-// Stage `seg` pooled rows [prow0, prow0 + seg) of level h (K and V of one key head) into LDS as fp32,
-// with the additive term ln(count) (-inf: the row covers no valid token) and the last covered token.
-template <typename T, int D>
-__device__ __forceinline__ void stage_keys(const T* kbase, const T* vbase, int prow0, int seg, int h, int N,
-                                           float (*Ks)[D], float (*Vs)[D], float* bias_s, int* last_s, int tid, int nt) {
-  const int span = 1 << (h - 1);
-  for (int x = tid; x < seg * D; x += nt) {
-    const int r = x / D, c = x % D;
-    const int prow = prow0 + r;
-    float kv = 0.f, vv = 0.f;
-    if (prow * span < N) {
-      kv = Elem<T>::to_f32(kbase[(int64_t)prow * D + c]);
-      vv = Elem<T>::to_f32(vbase[(int64_t)prow * D + c]);
-    }
-    Ks[r][c] = kv;
-    Vs[r][c] = vv;
-  }
-  if (tid < seg) {
-    const int first = (prow0 + tid) * span;
-    int c = N - first;
-    c = c < 0 ? 0 : (c > span ? span : c);
-    bias_s[tid] = c > 0 ? logf((float)c) : -INFINITY;
-    last_s[tid] = first + (c > 0 ? c : 1) - 1;
-  }
-}
+// LDS rows carry four floats of padding: the 16-byte reads of 16 rows then cover every bank once.
+template <int D, int TEAM>
+struct BwdDqShape {
+  static constexpr int KS = 4 / TEAM, ROWS = 32 * TEAM, PITCH = D + 4;
+  static constexpr int TILEF = 2 * 32 * PITCH + 64;                    // K | V | bias [32] | last token [32]
+  static constexpr int MERGEF = KS * ROWS * PITCH;
+  static constexpr size_t BYTES = sizeof(float) * (KS * TILEF > MERGEF ? KS * TILEF : MERGEF);
+};
 
-template <typename T, int D>
-__global__ __launch_bounds__(256) void bwd_dq_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
-                                                     const T* __restrict__ Kp, const T* __restrict__ Vp,
-                                                     const uint16_t* __restrict__ idx, const int32_t* __restrict__ cnt,
-                                                     const float* __restrict__ lse, const float* __restrict__ Dr,
-                                                     const T* __restrict__ dO, T* __restrict__ dQ, BwdArgs a) {
-  constexpr int DQ = D / 4;
-  __shared__ __attribute__((aligned(16))) float Ks[BWD_TK][D];
-  __shared__ __attribute__((aligned(16))) float Vs[BWD_TK][D];
-  __shared__ float bias_s[BWD_TK];
-  __shared__ int last_s[BWD_TK];
-  const int tid = threadIdx.x, qd = tid & 3;
-  const int slices = (a.bq + 63) / 64;
-  const int i = blockIdx.x / slices, slice = blockIdx.x % slices;
-  const int hq = blockIdx.y, b = blockIdx.z;
-  const int hk = hq / (a.Hq / a.Hkv);
+// dQ.  Operand roles, tiles and teams as in attn_f32_kernel: S^T = K Q^T and dP^T = V dO^T put one query row in
+// each lane, register v of dS^T is the B operand of dQ^T += K^T dS^T for the two keys of the lane's halves.
+template <typename T, int D, int TEAM>
+__global__ __launch_bounds__(256, (D == 64 && TEAM > 1 ? 2 : 1))
+void bwd_dq_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ Kp,
+                   const T* __restrict__ Vp, const uint16_t* __restrict__ idx, const int32_t* __restrict__ cnt,
+                   const float* __restrict__ lse, const float* __restrict__ Dr, const T* __restrict__ dO, T* __restrict__ dQ,
+                   BwdArgs a) {
+  using S = BwdDqShape<D, TEAM>;
+  constexpr int KS = S::KS, ROWS = S::ROWS, PITCH = S::PITCH, CPR = D / 4, MD = D / 32, TT = 64 * TEAM, NCH = 32 * CPR / TT;
+  extern __shared__ __attribute__((aligned(16))) float fsm[];
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int team = wave / TEAM, wr = wave % TEAM, tt = tid & (TT - 1);
+  float* Ks = fsm + team * S::TILEF;
+  float* Vs = Ks + 32 * PITCH;
+  float* bias_s = Vs + 32 * PITCH;
+  int* last_s = reinterpret_cast<int*>(bias_s + 32);
+  const int slices = (a.bq + ROWS - 1) / ROWS;
+  const int slice = blockIdx.x % slices;
+  int i = blockIdx.x / slices;
+  if (a.causal) i = a.nq - 1 - i;                        // longest rows first
+  const int hq = blockIdx.y, b = blockIdx.z, hk = hq / (a.Hq / a.Hkv);
+  const int64_t qhead = (int64_t)b * a.Hq + hq, khead = (int64_t)b * a.Hkv + hk;
   int row_end = (i + 1) * a.bq;
   row_end = row_end < a.N ? row_end : a.N;
-  const int row = i * a.bq + slice * 64 + (tid >> 2);
+  const int row0 = i * a.bq + slice * ROWS;
+  if (row0 >= row_end) return;
+  const int row = row0 + wr * 32 + l32;
   const bool active = row < row_end;
-  const int64_t qhead = (int64_t)b * a.Hq + hq, khead = (int64_t)b * a.Hkv + hk;
 
-  float q[DQ], go[DQ], dq[DQ];
+  float q[D / 2], go[D / 2];
 #pragma unroll
-  for (int e = 0; e < DQ; ++e) {
-    const int c = quad_channel(e, qd);
-    q[e] = active ? Elem<T>::to_f32(Q[(qhead * a.N + row) * D + c]) : 0.f;
-    go[e] = active ? Elem<T>::to_f32(dO[(qhead * a.N + row) * D + c]) : 0.f;
-    dq[e] = 0.f;
+  for (int k8 = 0; k8 < D / 8; ++k8) {
+    f32x4 x = {0.f, 0.f, 0.f, 0.f}, y = x;
+    if (active) {
+      x = Four<T>::widen(Four<T>::load(Q + (qhead * a.N + row) * D + k8 * 8 + hf * 4));
+      y = Four<T>::widen(Four<T>::load(dO + (qhead * a.N + row) * D + k8 * 8 + hf * 4));
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      q[k8 * 4 + e] = x[e];
+      go[k8 * 4 + e] = y[e];
+    }
   }
-  const float my_lse = active ? lse[qhead * a.N + row] : 0.f;
+  const float my_lse = active ? lse[qhead * a.N + row] : INFINITY;     // a row that does not exist: all weights 0
   const float my_D = active ? Dr[qhead * a.N + row] : 0.f;
+  f32x16 dq[MD];
+#pragma unroll
+  for (int md = 0; md < MD; ++md)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) dq[md][v] = 0.f;
 
   const int64_t srow = qhead * a.nq + i;
   const uint16_t* my_idx = idx + srow * a.nk;
   const int32_t* my_cnt = cnt + srow * CNT_STRIDE;
-  int list_pos = 0;
-  for (int h = 1; h <= a.H; ++h) {
-    const int nblk = my_cnt[h - 1];
-    const int th = a.bk >> (h - 1);
-    const T* kbase = h == 1 ? K + khead * (int64_t)a.N * D : Kp + a.lvl_off[h] + khead * (int64_t)a.nk * th * D;
-    const T* vbase = h == 1 ? V + khead * (int64_t)a.N * D : Vp + a.lvl_off[h] + khead * (int64_t)a.nk * th * D;
-    for (int e2 = 0; e2 < nblk; ++e2) {
-      const int j = (int)my_idx[list_pos + e2];
-      for (int t0 = 0; t0 < th; t0 += BWD_TK) {
-        const int seg = th - t0 < BWD_TK ? th - t0 : BWD_TK;
-        __syncthreads();
-        stage_keys<T, D>(kbase, vbase, j * th + t0, seg, h, a.N, Ks, Vs, bias_s, last_s, tid, 256);
-        __syncthreads();
-        for (int g = 0; g < seg; ++g) {
-          float s = 0.f, dp = 0.f;
+  struct Tile { int h, tl, ntl, nblk, start; bool ok; };
+  auto enter = [&](Tile& t) __attribute__((always_inline)) {
+    t.nblk = my_cnt[t.h - 1];
+    t.ntl = ((t.nblk << (a.lg_bk - (t.h - 1))) + 31) >> 5;
+  };
+  auto settle = [&](Tile& t) __attribute__((always_inline)) {          // carry tl over to the level that holds it
+    for (;;) {
+      if (t.tl < t.ntl) { t.ok = true; return; }
+      t.tl -= t.ntl;
+      t.start += t.nblk;
+      if (++t.h > a.H) { t.h = a.H; t.ok = false; t.ntl = 0; t.nblk = 0; return; }
+      enter(t);
+    }
+  };
+  auto locate = [&](const Tile& t) __attribute__((always_inline)) -> int {   // pooled row of tile row l32; -1: none
+    if (!t.ok) return -1;
+    const int lg_th = a.lg_bk - (t.h - 1), g = (t.tl << 5) + l32, e = g >> lg_th;
+    return e < t.nblk ? ((int)my_idx[t.start + e] << lg_th) | (g & ((1 << lg_th) - 1)) : -1;
+  };
+  typename Four<T>::raw kreg[NCH], vreg[NCH];
+  auto fetch = [&](const Tile& t, int prow) __attribute__((always_inline)) {
+    const int lg_th = a.lg_bk - (t.h - 1), hm1 = t.h - 1;
+    const int64_t off = a.lvl_off[t.h] + khead * ((int64_t)a.nk << lg_th) * D;
+    const T* kbase = hm1 == 0 ? K + khead * (int64_t)a.N * D : Kp + off;
+    const T* vbase = hm1 == 0 ? V + khead * (int64_t)a.N * D : Vp + off;
 #pragma unroll
-          for (int m = 0; m < DQ / 4; ++m) {
-            const f32x4 kk = *reinterpret_cast<const f32x4*>(&Ks[g][m * 16 + qd * 4]);
-            const f32x4 vv = *reinterpret_cast<const f32x4*>(&Vs[g][m * 16 + qd * 4]);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              s = fmaf(q[m * 4 + u], kk[u], s);
-              dp = fmaf(go[m * 4 + u], vv[u], dp);
-            }
-          }
-          s = quad_sum(s);
-          dp = quad_sum(dp);
-          float logit = s * a.scale + bias_s[g];
-          if (a.causal && last_s[g] > row) logit = -INFINITY;
-          const float p = active ? expf(logit - my_lse) : 0.f;    // -inf -> 0
-          const float ds = p * (dp - my_D);
-#pragma unroll
-          for (int m = 0; m < DQ / 4; ++m) {
-            const f32x4 kk = *reinterpret_cast<const f32x4*>(&Ks[g][m * 16 + qd * 4]);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) dq[m * 4 + u] = fmaf(ds, kk[u], dq[m * 4 + u]);
-          }
-        }
+    for (int c = 0; c < NCH; ++c) {
+      const int x = tt + TT * c, pr = __shfl(prow, x / CPR, 64), ch = (x % CPR) * 4;
+      kreg[c] = typename Four<T>::raw{0, 0, 0, 0};
+      vreg[c] = typename Four<T>::raw{0, 0, 0, 0};
+      if (pr >= 0 && ((int64_t)pr << hm1) < a.N) {
+        kreg[c] = Four<T>::load(kbase + (int64_t)pr * D + ch);
+        vreg[c] = Four<T>::load(vbase + (int64_t)pr * D + ch);
       }
     }
-    list_pos += nblk;
-  }
-  if (active) {
+  };
+  auto deposit = [&](const Tile& t, int prow) __attribute__((always_inline)) {
 #pragma unroll
-    for (int e = 0; e < DQ; ++e) dQ[(qhead * a.N + row) * D + quad_channel(e, qd)] = Elem<T>::from_f32(dq[e] * a.scale);
+    for (int c = 0; c < NCH; ++c) {
+      const int x = tt + TT * c, at = (x / CPR) * PITCH + (x % CPR) * 4;
+      *reinterpret_cast<f32x4*>(Ks + at) = Four<T>::widen(kreg[c]);
+      *reinterpret_cast<f32x4*>(Vs + at) = Four<T>::widen(vreg[c]);
+    }
+    if (tt < 32) {
+      const int span = 1 << (t.h - 1);
+      const int64_t first = (int64_t)prow * span;
+      int64_t c = a.N - first;
+      c = prow < 0 || c < 0 ? 0 : (c > span ? span : c);
+      bias_s[tt] = c > 0 ? logf((float)c) : -INFINITY;
+      last_s[tt] = (int)(first + (c > 0 ? c : 1) - 1);
+    }
+  };
+  // a team of one wavefront owns its buffer: its LDS operations complete in order, nothing to wait for
+  auto barrier = [&]() __attribute__((always_inline)) {
+    if constexpr (TEAM == 1) asm volatile("" ::: "memory");
+    else asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  };
+  int total = 0;
+  for (int h = 1; h <= a.H; ++h) {
+    Tile t;
+    t.h = h;
+    enter(t);
+    total += t.ntl;
+  }
+  Tile cur = {1, team, 0, 0, 0, false};
+  enter(cur);
+  settle(cur);
+  int pc = locate(cur);
+  fetch(cur, pc);
+  deposit(cur, pc);
+  Tile nxt = cur;
+  nxt.tl += KS;
+  if (nxt.ok) settle(nxt);
+  int pn = locate(nxt);
+  for (int step = 0; step < total; step += KS) {
+    barrier();                                           // the tile's rows are in LDS
+    Tile nn = nxt;
+    int pnn = -1;
+    if (nxt.ok) {
+      fetch(nxt, pn);
+      nn.tl += KS;
+      settle(nn);
+      pnn = locate(nn);
+    }
+    if (cur.ok) {
+      f32x16 sc, dp;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) { sc[v] = 0.f; dp[v] = 0.f; }
+      f32x4 kk = *reinterpret_cast<const f32x4*>(Ks + l32 * PITCH + hf * 4), vv = *reinterpret_cast<const f32x4*>(Vs + l32 * PITCH + hf * 4);
+#pragma unroll
+      for (int k8 = 0; k8 < D / 8; ++k8) {               // one fragment ahead of the products, no more
+        const f32x4 k0 = kk, v0 = vv;
+        if (k8 + 1 < D / 8) {
+          kk = *reinterpret_cast<const f32x4*>(Ks + l32 * PITCH + (k8 + 1) * 8 + hf * 4);
+          vv = *reinterpret_cast<const f32x4*>(Vs + l32 * PITCH + (k8 + 1) * 8 + hf * 4);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          sc = __builtin_amdgcn_mfma_f32_32x32x2f32(k0[e], q[k8 * 4 + e], sc, 0, 0, 0);
+          dp = __builtin_amdgcn_mfma_f32_32x32x2f32(v0[e], go[k8 * 4 + e], dp, 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const f32x4 bs = *reinterpret_cast<const f32x4*>(bias_s + g4 * 8 + hf * 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float x = bs[e] == -INFINITY ? -INFINITY : fmaf(sc[g4 * 4 + e], a.scale, bs[e]);
+          if (a.causal && last_s[g4 * 8 + hf * 4 + e] > row) x = -INFINITY;
+          sc[g4 * 4 + e] = expf(x - my_lse) * (dp[g4 * 4 + e] - my_D);
+        }
+      }
+      float ka[MD], kn[MD];
+#pragma unroll
+      for (int md = 0; md < MD; ++md) ka[md] = Ks[hf * 4 * PITCH + md * 32 + l32];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        if (v + 1 < 16) {
+#pragma unroll
+          for (int md = 0; md < MD; ++md) kn[md] = Ks[(((v + 1) >> 2) * 8 + hf * 4 + ((v + 1) & 3)) * PITCH + md * 32 + l32];
+        }
+#pragma unroll
+        for (int md = 0; md < MD; ++md) {
+          dq[md] = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[md], sc[v], dq[md], 0, 0, 0);
+          ka[md] = kn[md];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    barrier();                                           // everyone has read it
+    if (nxt.ok) deposit(nxt, pn);
+    cur = nxt;
+    nxt = nn;
+    pn = pnn;
+  }
+  // the teams' sums through LDS, added in a fixed order
+  __syncthreads();
+  const int slot = team * ROWS + wr * 32 + l32;
+#pragma unroll
+  for (int md = 0; md < MD; ++md)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<f32x4*>(fsm + slot * PITCH + md * 32 + g * 8 + hf * 4) =
+          f32x4{dq[md][4 * g], dq[md][4 * g + 1], dq[md][4 * g + 2], dq[md][4 * g + 3]};
+  __syncthreads();
+  for (int x = tid; x < ROWS * CPR; x += 256) {
+    const int r = x / CPR, c = (x % CPR) * 4;
+    if (row0 + r >= row_end) continue;
+    f32x4 sum = *reinterpret_cast<const f32x4*>(fsm + r * PITCH + c);
+#pragma unroll
+    for (int k = 1; k < KS; ++k) sum += *reinterpret_cast<const f32x4*>(fsm + (k * ROWS + r) * PITCH + c);
+    Four<T>::store(dQ + (qhead * a.N + row0 + r) * D + c, sum * a.scale);
   }
 }
 
-// One workgroup per (key block j, key head, batch) and level h (a launch per level): 4 lanes per pooled
-// key of the block.  The column j of the level map is walked for every query head of the group; query
-// blocks that use this block at this level are staged through LDS, 32 rows at a time.
-template <typename T, int D>
-__global__ __launch_bounds__(512) void bwd_dkv_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
-                               const T* __restrict__ Kp, const T* __restrict__ Vp, const uint8_t* __restrict__ M,
-                               const float* __restrict__ lse, const float* __restrict__ Dr, const T* __restrict__ dO,
-                               float* __restrict__ dKp, float* __restrict__ dVp, int h, BwdArgs a) {
-  constexpr int DQ = D / 4;
-  __shared__ __attribute__((aligned(16))) float Qs[BWD_TK][D];
-  __shared__ __attribute__((aligned(16))) float Gs[BWD_TK][D];
-  __shared__ float lse_s[BWD_TK], D_s[BWD_TK];
-  const int tid = threadIdx.x, nt = blockDim.x, qd = tid & 3;
-  const int j = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
-  const int th = a.bk >> (h - 1), span = 1 << (h - 1);
-  const int g = tid >> 2;                       // pooled key of this block
-  const bool have = g < th;
-  const int group = a.Hq / a.Hkv;
-  const int64_t khead = (int64_t)b * a.Hkv + hk;
-  const int prow = j * th + g;
-  const int first = prow * span;
-  int c = a.N - first;
-  c = c < 0 ? 0 : (c > span ? span : c);
-  const bool valid = have && c > 0;
-  const float bias = valid ? logf((float)c) : -INFINITY;
-  const int last = first + (c > 0 ? c : 1) - 1;
-  const T* kbase = h == 1 ? K + khead * (int64_t)a.N * D : Kp + a.lvl_off[h] + khead * (int64_t)a.nk * th * D;
-  const T* vbase = h == 1 ? V + khead * (int64_t)a.N * D : Vp + a.lvl_off[h] + khead * (int64_t)a.nk * th * D;
+template <int D>
+struct BwdDkvShape {
+  static constexpr int PITCH = D + 4;
+  static constexpr int WAVEF = 2 * 32 * PITCH + 64;                    // Q | dO | lse [32] | D [32] of one wavefront
+  static constexpr int LIST = 256;                                     // column entries tested at a time
+  static constexpr size_t BYTES = sizeof(float) * (4 * WAVEF + LIST + 4);
+};
 
-  float k[DQ], v[DQ], dk[DQ], dv[DQ];
-#pragma unroll
-  for (int e = 0; e < DQ; ++e) {
-    const int ch = quad_channel(e, qd);
-    k[e] = valid ? Elem<T>::to_f32(kbase[(int64_t)prow * D + ch]) : 0.f;
-    v[e] = valid ? Elem<T>::to_f32(vbase[(int64_t)prow * D + ch]) : 0.f;
-    dk[e] = 0.f;
-    dv[e] = 0.f;
+// Pooled dK, dV of up to 32 pooled keys of a key block at one level (all levels in one launch, the coarsest first: their
+// columns are the longest).  Larger blocks are split over several workgroups; smaller ones leave lanes idle and are
+// not packed together, because a query row that is not finite would reach the blocks that do not use it as 0 * inf.
+// Queries and keys exchanged: the keys and values sit in registers as B operands (one key per lane), the four
+// wavefronts take the 32-row chunks of the query blocks that use the block at this level in turn, each
+// through an LDS buffer of its own (no barrier in between), and their sums meet at the end in a fixed order.
+// The column of the level map is tested 256 entries at a time, so its length is not limited.
+template <typename T, int D>
+__global__ __launch_bounds__(256, (D == 64 ? 2 : 1))
+void bwd_dkv_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ Kp,
+                    const T* __restrict__ Vp, const uint8_t* __restrict__ M, const float* __restrict__ lse,
+                    const float* __restrict__ Dr, const T* __restrict__ dO, float* __restrict__ dKp, float* __restrict__ dVp,
+                    BwdArgs a) {
+  using S = BwdDkvShape<D>;
+  constexpr int PITCH = S::PITCH, CPR = D / 4, MD = D / 32, NCH = 32 * CPR / 64;
+  extern __shared__ __attribute__((aligned(16))) float fsm[];
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  float* Qs = fsm + wave * S::WAVEF;
+  float* Gs = Qs + 32 * PITCH;
+  float* lse_s = Gs + 32 * PITCH;
+  float* D_s = lse_s + 32;
+  int* kept = reinterpret_cast<int*>(fsm + 4 * S::WAVEF);
+  int* wcount = kept + S::LIST;
+  const int hk = blockIdx.y, b = blockIdx.z, group = a.Hq / a.Hkv;
+  int h = a.H, pieces = 1, bx = blockIdx.x;
+  for (;; --h) {
+    const int th = a.bk >> (h - 1);
+    pieces = th > 32 ? th / 32 : 1;
+    if (bx < pieces * a.nk || h == 1) break;
+    bx -= pieces * a.nk;
   }
-  for (int gq = 0; gq < group; ++gq) {
-    const int hq = hk * group + gq;
-    const int64_t qhead = (int64_t)b * a.Hq + hq;
-    const uint8_t* mcol = M + (qhead * a.nq) * a.nk + j;
-    for (int i = 0; i < a.nq; ++i) {
-      if ((int)mcol[(int64_t)i * a.nk] != h) continue;             // uniform over the workgroup
-      int row_end = (i + 1) * a.bq;
-      row_end = row_end < a.N ? row_end : a.N;
-      for (int r0 = i * a.bq; r0 < row_end; r0 += BWD_TK) {
-        const int seg = row_end - r0 < BWD_TK ? row_end - r0 : BWD_TK;
-        __syncthreads();
-        for (int x = tid; x < seg * D; x += nt) {
-          const int r = x / D, ch = x % D;
-          Qs[r][ch] = Elem<T>::to_f32(Q[(qhead * a.N + r0 + r) * D + ch]);
-          Gs[r][ch] = Elem<T>::to_f32(dO[(qhead * a.N + r0 + r) * D + ch]);
-        }
-        if (tid < seg) {
-          lse_s[tid] = lse[qhead * a.N + r0 + tid];
-          D_s[tid] = Dr[qhead * a.N + r0 + tid];
-        }
-        __syncthreads();
-        for (int r = 0; r < seg; ++r) {
-          float s = 0.f, dp = 0.f;
+  const int lg_th = a.lg_bk - (h - 1), span = 1 << (h - 1);
+  const int j = bx / pieces, koff = (bx % pieces) * 32;                // key block; first key inside it
+  const int64_t khead = (int64_t)b * a.Hkv + hk;
+  const int prow = (j << lg_th) + koff + l32;
+  const int64_t first = (int64_t)prow * span;
+  int64_t c64 = a.N - first;
+  c64 = c64 < 0 ? 0 : (c64 > span ? span : c64);
+  const bool valid = koff + l32 < (1 << lg_th) && c64 > 0;
+  const float bias = valid ? logf((float)c64) : -INFINITY;
+  const int last = (int)(first + (c64 > 0 ? c64 : 1) - 1);
+  const int64_t off = a.lvl_off[h] + khead * ((int64_t)a.nk << lg_th) * D;
+  const T* kbase = h == 1 ? K + khead * (int64_t)a.N * D : Kp + off;
+  const T* vbase = h == 1 ? V + khead * (int64_t)a.N * D : Vp + off;
+
+  float k[D / 2], v[D / 2];
 #pragma unroll
-          for (int m = 0; m < DQ / 4; ++m) {
-            const f32x4 qq = *reinterpret_cast<const f32x4*>(&Qs[r][m * 16 + qd * 4]);
-            const f32x4 gg = *reinterpret_cast<const f32x4*>(&Gs[r][m * 16 + qd * 4]);
+  for (int k8 = 0; k8 < D / 8; ++k8) {
+    f32x4 x = {0.f, 0.f, 0.f, 0.f}, y = x;
+    if (valid) {
+      x = Four<T>::widen(Four<T>::load(kbase + (int64_t)prow * D + k8 * 8 + hf * 4));
+      y = Four<T>::widen(Four<T>::load(vbase + (int64_t)prow * D + k8 * 8 + hf * 4));
+    }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              s = fmaf(qq[u], k[m * 4 + u], s);
-              dp = fmaf(gg[u], v[m * 4 + u], dp);
-            }
-          }
-          s = quad_sum(s);
-          dp = quad_sum(dp);
-          float logit = s * a.scale + bias;
-          if (a.causal && last > r0 + r) logit = -INFINITY;
-          const float p = expf(logit - lse_s[r]);
-          const float ds = p * (dp - D_s[r]);
-#pragma unroll
-          for (int m = 0; m < DQ / 4; ++m) {
-            const f32x4 qq = *reinterpret_cast<const f32x4*>(&Qs[r][m * 16 + qd * 4]);
-            const f32x4 gg = *reinterpret_cast<const f32x4*>(&Gs[r][m * 16 + qd * 4]);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              dk[m * 4 + u] = fmaf(ds, qq[u], dk[m * 4 + u]);
-              dv[m * 4 + u] = fmaf(p, gg[u], dv[m * 4 + u]);
-            }
-          }
-        }
-      }
+    for (int e = 0; e < 4; ++e) {
+      k[k8 * 4 + e] = x[e];
+      v[k8 * 4 + e] = y[e];
     }
   }
-  if (have) {
-    float* dkp = dKp + a.glvl_off[h] + (khead * (int64_t)a.nk * th + prow) * D;
-    float* dvp = dVp + a.glvl_off[h] + (khead * (int64_t)a.nk * th + prow) * D;
+  f32x16 dk[MD], dv[MD];
 #pragma unroll
-    for (int e = 0; e < DQ; ++e) {
-      const int ch = quad_channel(e, qd);
-      dkp[ch] = dk[e] * a.scale;
-      dvp[ch] = dv[e];
+  for (int md = 0; md < MD; ++md)
+#pragma unroll
+    for (int u = 0; u < 16; ++u) { dk[md][u] = 0.f; dv[md][u] = 0.f; }
+
+  const int E = group * a.nq, nchunk = (a.bq + 31) / 32;
+  struct Chunk { int64_t row0; int r0, seg; };
+  typename Four<T>::raw reg[NCH];                                      // the Q or dO rows on their way into LDS
+  float lreg = INFINITY, dreg = 0.f;
+  auto place = [&](int f) __attribute__((always_inline)) -> Chunk {    // chunk f of the batch's list
+    Chunk c;
+    const int e = __builtin_amdgcn_readfirstlane(kept[f / nchunk]);
+    const int i = e % a.nq;
+    c.r0 = i * a.bq + (f % nchunk) * 32;
+    int row_end = (i + 1) * a.bq;
+    row_end = row_end < a.N ? row_end : a.N;
+    c.seg = row_end - c.r0 < 32 ? row_end - c.r0 : 32;                 // <= 0: past the end of a short last block
+    c.row0 = ((int64_t)b * a.Hq + hk * group + e / a.nq) * a.N + c.r0;
+    return c;
+  };
+  auto fetch = [&](const T* src, const Chunk& c) __attribute__((always_inline)) {
+#pragma unroll
+    for (int n = 0; n < NCH; ++n) {
+      const int x = lane + 64 * n, r = x / CPR;
+      reg[n] = typename Four<T>::raw{0, 0, 0, 0};
+      if (r < c.seg) reg[n] = Four<T>::load(src + (c.row0 + r) * D + (x % CPR) * 4);
+    }
+  };
+  auto deposit = [&](float* dst) __attribute__((always_inline)) {
+#pragma unroll
+    for (int n = 0; n < NCH; ++n) {
+      const int x = lane + 64 * n;
+      *reinterpret_cast<f32x4*>(dst + (x / CPR) * PITCH + (x % CPR) * 4) = Four<T>::widen(reg[n]);
+    }
+  };
+  auto fetch_stats = [&](const Chunk& c) __attribute__((always_inline)) {
+    lreg = l32 < c.seg ? lse[c.row0 + l32] : INFINITY;
+    dreg = l32 < c.seg ? Dr[c.row0 + l32] : 0.f;
+  };
+  // acc += tile^T w: 32 rows of the tile, w[u] = weight of row (u/4)*8 + hf*4 + u%4 for this lane's key
+  auto accumulate = [&](f32x16 (&acc)[MD], const float* tile, const f32x16& w) __attribute__((always_inline)) {
+    float now[MD], nxt[MD];
+#pragma unroll
+    for (int md = 0; md < MD; ++md) now[md] = tile[hf * 4 * PITCH + md * 32 + l32];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      if (u + 1 < 16) {
+#pragma unroll
+        for (int md = 0; md < MD; ++md) nxt[md] = tile[(((u + 1) >> 2) * 8 + hf * 4 + ((u + 1) & 3)) * PITCH + md * 32 + l32];
+      }
+#pragma unroll
+      for (int md = 0; md < MD; ++md) {
+        acc[md] = __builtin_amdgcn_mfma_f32_32x32x2f32(now[md], w[u], acc[md], 0, 0, 0);
+        now[md] = nxt[md];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  for (int e0 = 0; e0 < E; e0 += S::LIST) {
+    // which of the next column entries (query head of the group, query block) use this block at this level
+    const int e = e0 + tid;
+    const bool hit = e < E && (int)M[(((int64_t)b * a.Hq + hk * group) * a.nq + e) * a.nk + j] == h;
+    const uint64_t mask = __ballot(hit);
+    __syncthreads();                                                   // the list of the batch before is done with
+    if (lane == 0) wcount[wave] = __popcll(mask);
+    __syncthreads();
+    int base = 0, nkept = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      base += w < wave ? wcount[w] : 0;
+      nkept += wcount[w];
+    }
+    if (hit) kept[base + __popcll(mask & ((1ull << lane) - 1ull))] = e;
+    __syncthreads();
+    const int nf = nkept * nchunk;
+    // dO is done with before Q is, so its next rows travel during the product with dO^T and those of Q during the one
+    // with Q^T, through the same registers.
+    Chunk c = {};
+    if (wave < nf) {
+      c = place(wave);
+      fetch(dO, c);
+      fetch_stats(c);
+      deposit(Gs);
+      fetch(Q, c);
+    }
+    for (int f = wave; f < nf; f += 4) {
+      deposit(Qs);
+      if (hf == 0) {
+        lse_s[l32] = lreg;
+        D_s[l32] = dreg;
+      }
+      asm volatile("" ::: "memory");                                   // this wavefront's LDS operations complete in order
+      f32x16 sc, dp;
+#pragma unroll
+      for (int u = 0; u < 16; ++u) { sc[u] = 0.f; dp[u] = 0.f; }
+      f32x4 qa = *reinterpret_cast<const f32x4*>(Qs + l32 * PITCH + hf * 4), ga = *reinterpret_cast<const f32x4*>(Gs + l32 * PITCH + hf * 4);
+#pragma unroll
+      for (int k8 = 0; k8 < D / 8; ++k8) {
+        const f32x4 q0 = qa, g0 = ga;
+        if (k8 + 1 < D / 8) {
+          qa = *reinterpret_cast<const f32x4*>(Qs + l32 * PITCH + (k8 + 1) * 8 + hf * 4);
+          ga = *reinterpret_cast<const f32x4*>(Gs + l32 * PITCH + (k8 + 1) * 8 + hf * 4);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          sc = __builtin_amdgcn_mfma_f32_32x32x2f32(q0[u], k[k8 * 4 + u], sc, 0, 0, 0);
+          dp = __builtin_amdgcn_mfma_f32_32x32x2f32(g0[u], v[k8 * 4 + u], dp, 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // this lane: its key, rows (u/4)*8 + hf*4 + u%4; sc becomes dS, dp becomes P
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const int r = g4 * 8 + hf * 4;
+        const f32x4 ls = *reinterpret_cast<const f32x4*>(lse_s + r), dd = *reinterpret_cast<const f32x4*>(D_s + r);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          float x = valid ? fmaf(sc[g4 * 4 + u], a.scale, bias) : -INFINITY;
+          if (a.causal && last > c.r0 + r + u) x = -INFINITY;
+          const float p = expf(x - ls[u]);
+          sc[g4 * 4 + u] = p * (dp[g4 * 4 + u] - dd[u]);
+          dp[g4 * 4 + u] = p;
+        }
+      }
+      const bool more = f + 4 < nf;
+      if (more) {
+        c = place(f + 4);
+        fetch(dO, c);
+        fetch_stats(c);
+      }
+      accumulate(dv, Gs, dp);
+      asm volatile("" ::: "memory");
+      if (more) {
+        deposit(Gs);
+        fetch(Q, c);
+      }
+      accumulate(dk, Qs, sc);
+      asm volatile("" ::: "memory");
+    }
+  }
+  // the wavefronts' sums through LDS, first dK, then dV; every pooled key of the group is written
+#pragma unroll
+  for (int which = 0; which < 2; ++which) {
+    __syncthreads();
+#pragma unroll
+    for (int md = 0; md < MD; ++md)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        f32x4 x;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = which ? dv[md][4 * g + u] : dk[md][4 * g + u];
+        *reinterpret_cast<f32x4*>(fsm + (wave * 32 + l32) * PITCH + md * 32 + g * 8 + hf * 4) = x;
+      }
+    __syncthreads();
+    float* dst = (which ? dVp : dKp) + a.glvl_off[h] + (khead * ((int64_t)a.nk << lg_th) + ((int64_t)j << lg_th) + koff) * D;
+    const float mul = which ? 1.f : a.scale;
+    for (int x = tid; x < 32 * CPR; x += 256) {
+      const int kk = x / CPR, c = (x % CPR) * 4;
+      if (koff + kk >= (1 << lg_th)) break;
+      f32x4 sum = *reinterpret_cast<const f32x4*>(fsm + kk * PITCH + c);
+#pragma unroll
+      for (int w = 1; w < 4; ++w) sum += *reinterpret_cast<const f32x4*>(fsm + (w * 32 + kk) * PITCH + c);
+      *reinterpret_cast<f32x4*>(dst + (int64_t)kk * D + c) = sum * mul;
     }
   }
 }
@@ -319,6 +554,19 @@ size_t bwd_pooled_grad_elems(const Plan& pl) {      // one tensor: levels 1..H, 
   return n;
 }
 
+template <typename T, int D, int TEAM>
+static hipError_t launch_dq_t(const Plan& pl, const BwdArgs& a, const T* q, const T* k, const T* v, const T* kp, const T* vp,
+                              const uint16_t* idx, const int32_t* cnt, const float* lse, const float* Dr, const T* go, T* dq,
+                              hipStream_t s) {
+  using S = BwdDqShape<D, TEAM>;
+  auto kern = bwd_dq_kernel<T, D, TEAM>;
+  static LdsOptIn optin;
+  const hipError_t e = allow_max_lds(reinterpret_cast<const void*>(kern), &optin);
+  if (e != hipSuccess) return e;
+  kern<<<dim3(pl.nq * ((pl.bq + S::ROWS - 1) / S::ROWS), pl.Hq, pl.B), 256, S::BYTES, s>>>(q, k, v, kp, vp, idx, cnt, lse, Dr, go, dq, a);
+  return hipGetLastError();
+}
+
 template <typename T, int D>
 static hipError_t launch_bwd_t(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp, const void* Vp,
                                const uint8_t* M, const uint16_t* idx, const int32_t* cnt, const void* O, const float* lse,
@@ -327,6 +575,8 @@ static hipError_t launch_bwd_t(const Plan& pl, const void* Q, const void* K, con
   BwdArgs a;
   a.N = pl.N; a.Hq = pl.Hq; a.Hkv = pl.Hkv; a.nq = pl.nq; a.nk = pl.nk; a.bq = pl.bq; a.bk = pl.bk;
   a.H = pl.H; a.causal = pl.causal; a.scale = pl.scale;
+  a.lg_bk = 0;
+  while ((1 << a.lg_bk) < pl.bk) ++a.lg_bk;
   const int parts = use_mfma ? pl.group : 1;
   int64_t off = 0;
   for (int h = 0; h < PSA_MAX_LEVELS + 2; ++h) { a.lvl_off[h] = pl.lvl_off[h]; a.glvl_off[h] = 0; }
@@ -349,18 +599,26 @@ static hipError_t launch_bwd_t(const Plan& pl, const void* Q, const void* K, con
     e = launch_attn_bwd_mfma(pl, Q, K, V, Kp, Vp, M, idx, cnt, lse, dO, Dr, dKp, dVp, dQ, s);
     if (e != hipSuccess) return e;
   } else {
-    const int slices = (pl.bq + 63) / 64;
-    bwd_dq_kernel<T, D><<<dim3(pl.nq * slices, pl.Hq, pl.B), 256, 0, s>>>(q, k, v, kp, vp, idx, cnt, lse, Dr, go,
-                                                                          static_cast<T*>(dQ), a);
+    // rows per workgroup: the largest that still fills the chip (see launch_f32_d)
+    const int64_t blocks = (int64_t)pl.B * pl.Hq * pl.nq;
+    auto groups = [&](int rows_wg) { return blocks * ((pl.bq + rows_wg - 1) / rows_wg); };
+    const int team = pl.bq > 64 && groups(128) >= 256 ? 4 : (pl.bq > 32 && groups(64) >= 192 ? 2 : 1);
+    T* dq = static_cast<T*>(dQ);
+    e = team == 4 ? launch_dq_t<T, D, 4>(pl, a, q, k, v, kp, vp, idx, cnt, lse, Dr, go, dq, s)
+      : team == 2 ? launch_dq_t<T, D, 2>(pl, a, q, k, v, kp, vp, idx, cnt, lse, Dr, go, dq, s)
+                  : launch_dq_t<T, D, 1>(pl, a, q, k, v, kp, vp, idx, cnt, lse, Dr, go, dq, s);
+    if (e != hipSuccess) return e;
+    static LdsOptIn optin;
+    e = allow_max_lds(reinterpret_cast<const void*>(bwd_dkv_kernel<T, D>), &optin);
+    if (e != hipSuccess) return e;
+    int wgs = 0;                                   // as the kernel counts them
+    for (int h = 1; h <= pl.H; ++h) {
+      const int th = pl.bk >> (h - 1);
+      wgs += (th > 32 ? th / 32 : 1) * pl.nk;
+    }
+    bwd_dkv_kernel<T, D><<<dim3(wgs, pl.Hkv, pl.B), 256, BwdDkvShape<D>::BYTES, s>>>(q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    for (int h = 1; h <= pl.H; ++h) {
-      int threads = 4 * (pl.bk >> (h - 1));
-      threads = threads < 64 ? 64 : threads;
-      bwd_dkv_kernel<T, D><<<dim3(pl.nk, pl.Hkv, pl.B), threads, 0, s>>>(q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h, a);
-      e = hipGetLastError();
-      if (e != hipSuccess) return e;
-    }
   }
   const int heads = pl.B * pl.Hkv;
   const int64_t n = (int64_t)heads * pl.N * (pl.d / 4);

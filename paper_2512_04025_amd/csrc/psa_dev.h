@@ -63,6 +63,36 @@ template <> struct Elem<bf16_t> {
   __device__ static __forceinline__ bf16_t from_f32(float x) { return f32_to_bf16(x); }
 };
 
+// Four consecutive elements for the fp32-arithmetic kernels.  The caller's tensors need no more than element
+// alignment there (the memory pipeline takes 16-byte accesses at any address), so the vector types do not
+// claim more.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint16_t u16x4_any __attribute__((ext_vector_type(4), aligned(2)));
+template <typename T> struct Four;
+template <> struct Four<float> {
+  typedef f32x4 raw;
+  __device__ static __forceinline__ raw load(const float* p) { return *reinterpret_cast<const f32x4_any*>(p); }
+  __device__ static __forceinline__ f32x4 widen(raw r) { return r; }
+  __device__ static __forceinline__ void store(float* p, f32x4 x) { *reinterpret_cast<f32x4_any*>(p) = x; }
+};
+template <> struct Four<bf16_t> {
+  typedef uint16_t raw __attribute__((ext_vector_type(4)));
+  __device__ static __forceinline__ raw load(const bf16_t* p) { return *reinterpret_cast<const u16x4_any*>(p); }
+  __device__ static __forceinline__ f32x4 widen(raw r) {
+    return f32x4{bf16_to_f32(r[0]), bf16_to_f32(r[1]), bf16_to_f32(r[2]), bf16_to_f32(r[3])};
+  }
+  __device__ static __forceinline__ void store(bf16_t* p, f32x4 x) {
+    *reinterpret_cast<u16x4_any*>(p) = u16x4_any{f32_to_bf16(x[0]), f32_to_bf16(x[1]), f32_to_bf16(x[2]), f32_to_bf16(x[3])};
+  }
+};
+
+__device__ __forceinline__ bool not_finite(f32x4 x) {
+  bool bad = false;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) bad |= (__float_as_uint(x[u]) & 0x7f800000u) == 0x7f800000u;
+  return bad;
+}
+
 __device__ __forceinline__ int ilog2(int x) { return 31 - __clz(x); }
 
 }  // namespace psa

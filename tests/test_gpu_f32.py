@@ -64,6 +64,35 @@ def test_attention_and_dense_at_the_edges(shape):
     assert np.abs(buf.lse.cpu().numpy() - lse).max() <= 1e-4
 
 
+BWD_SHAPES = [s for s in SHAPES if s[0] == "f32" and s[7] <= 128] + [
+    ("f32", 1, 4, 2, 2070, 64, 8, 8, 4, True),            # more column entries than are tested at a time; blocks of one pooled key
+    ("bf16", 1, 2, 2, 300, 128, 64, 4, 3, False),         # key blocks smaller than the bfloat16 kernels take
+]
+
+
+@pytest.mark.parametrize("shape", BWD_SHAPES, ids=lambda s: "-".join(map(str, s)))
+def test_backward_at_the_edges(shape):
+    """Gradients against the oracle: 1e-5 of the largest entry for float32, one bfloat16 rounding otherwise (O, which
+    enters through dO . O, is rounded too: the bar of the backward tests)."""
+    import torch
+    op, gp, host, M = _problem(*shape)
+    dO = si.random_qkv(9, op.B, op.Hq, op.Hq, op.N, op.d, op.dtype)[0]
+    Q64, K64, V64, dO64 = (si.to_f64(x, op.dtype) for x in (*host, dO))
+    Qd, Kd, Vd, dOd = (to_dev(x, op.dtype) for x in (*host, dO))
+    buf = Buffers(gp)
+    Md = torch.from_numpy(M).cuda()
+    psa.psa_build_pyramid(gp, Kd, Vd, buf.Kpyr, buf.Vpyr)
+    psa.psa_attention_fwd(gp, Qd, Kd, Vd, buf.Kpyr, buf.Vpyr, Md, buf.O, buf.scratch, lse=buf.lse)
+    grads = [torch.full_like(x, float("nan")) for x in (Qd, Kd, Vd)]
+    scratch = torch.full((psa.psa_query_bwd_sizes(gp),), 255, dtype=torch.uint8, device="cuda")
+    psa.psa_attention_bwd(gp, Qd, Kd, Vd, buf.Kpyr, buf.Vpyr, Md, buf.O, buf.lse, dOd, *grads, scratch)
+    torch.cuda.synchronize()
+    ref = orc.psa_attention_backward(Q64, orc.build_pyramid(K64, op), orc.build_pyramid(V64, op), M, dO64, op)
+    for name, got, want in zip(("dQ", "dK", "dV"), grads, ref):
+        bar = (1e-5 if op.dtype == "f32" else 2e-2) * max(1.0, float(np.abs(want).max()))
+        assert np.abs(from_dev(got, op.dtype) - want).max() <= bar, name
+
+
 @pytest.mark.parametrize("N,Hq,bq", [(333, 2, 64), (1000, 12, 64), (1000, 32, 128)])
 def test_values_hidden_by_the_causal_mask_may_be_infinite(N, Hq, bq):
     """The last token's value is infinite: no row before it sees that token, so no row before it changes."""
