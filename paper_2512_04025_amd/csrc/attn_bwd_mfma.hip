@@ -1,10 +1,10 @@
 // Backward pass of the adaptive pyramid attention on the gfx950 matrix cores, bfloat16 (the chain rule
 // through Eq. 8 and the mean pooling of Eq. 2-3; see attn_bwd.hip for the formulas and for the fp32
-// vector-unit version that serves float32 and the shapes this one does not take).
+// version that serves float32 and the shapes this one does not take).
 //
 // Two kernels, both on 32x32x16 MFMAs with fp32 accumulation, P and dS rounded to bfloat16 for the
 // products that consume them, no atomics, two wavefronts per SIMD (at most 256 registers per lane),
-// tiles double-buffered through registers into LDS:
+// double-buffered tiles in LDS (dQ: through registers; dK, dV: loaded directly):
 //   bwd_dq_mfma_kernel   one workgroup per 128 query rows (a wavefront per 32), walking the row's
 //        level-sorted block list in tiles of 64 pooled keys gathered into LDS.  Same operand roles as the
 //        forward kernel: S^T = Kbar Q^T and dP^T = Vbar dO^T put one query row in each lane (lse and
@@ -17,18 +17,19 @@
 //        level (a walk down the level map's columns) are staged through LDS 64 rows at a time; S = Q Kbar^T and dP = dO Vbar^T, then dVbar^T += dO^T P and
 //        dKbar^T += Q^T dS with the transposing load on the staged dO and Q.  Half of the wavefronts
 //        accumulate dKbar, the other half dVbar.
-// LDS rows carry padding that spreads the rows of an operand read over the banks: 16 bytes serve the
+// The dQ kernel's LDS rows carry padding that spreads the rows of an operand read over the banks: 16 bytes serve the
 // row-wise fragments (eight rows x 16 bytes) at either head dimension and, at d = 64, the transposing
 // load too (four rows x 32 bytes); at d = 128 that load wants the rows 8 banks apart and the fragments
-// an odd multiple of 4, which 48 bytes give (measured: bank conflicts a third, 3 % less time), and 48
-// are used wherever two workgroups still fit a compute unit's LDS.
+// an odd multiple of 4, which 48 bytes give.
+#include <type_traits>
+
 #include "psa_dev.h"
 #include "psa_internal.h"
 
 namespace psa {
 
 struct BwdMfmaArgs {
-  int N, Hq, Hkv, nq, nk, bq, bk, lg_bk, H, causal;
+  int B, N, Hq, Hkv, nq, nk, bq, bk, lg_bk, H, causal;
   float scale, scale_log2;
   int64_t lvl_off[PSA_MAX_LEVELS + 2];   // level h >= 2 inside one pyramid buffer (elements)
   int64_t glvl_off[PSA_MAX_LEVELS + 2];  // level h >= 1 inside one pooled-gradient buffer (elements)
@@ -37,6 +38,8 @@ struct BwdMfmaArgs {
 typedef __attribute__((ext_vector_type(4))) short bs16x4;
 typedef __attribute__((ext_vector_type(8))) short bs16x8;
 typedef __attribute__((address_space(3))) bs16x4 lds_bs16x4;
+typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
 
 constexpr float LOG2E = 1.44269504088896340736f;
 
@@ -288,44 +291,76 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(const bf16_t* __res
 // workgroups of four per compute unit, or one of eight for KH = 4) and the matrix pipe works for one
 // while the other is in its exponentials, its LDS reads or a barrier.  Wavefronts of the same half
 // that share a key tile (KH = 1: two of them) split the 32-row chunks of a staged tile.
-template <int D, int KH, int PAD>
+//
+// The rows of a stage go straight into LDS (buffer_load ... lds), one stage ahead, with one barrier per stage.  The
+// two buffers are separate objects on purpose: that is what lets the compiler see that reads of one do not depend
+// on the loads in flight into the other, and count its waits instead of draining them.  The 16-byte chunks of a
+// row are stored at chunk ^ row_swizzle(row), which serves both ways a tile is read without padding: the row-wise
+// fragments want 16 consecutive rows at 16 different places, the transposing load wants the four rows of a group
+// in four different 64-byte groups.
+//
+// Measured at 12 heads x 32760 tokens, d = 128 (through registers and padded rows -> directly, swizzled): level 1
+// 2.83 -> 2.73 ms, levels 2-4 3.97 -> 3.65 ms, LDS cycles halved, no bank conflicts; causal, 28 heads x 8000: 1.04 -> 0.86 ms;
+// d = 64, 16 heads x 16384: 8-20 % of the whole call.  With everything but the products switched off the stages of
+// levels 2-4 alone take 2.6 ms (1.5 when every row hits the L2), the products alone 2.3: the two overlap only in
+// part, because one stage is all that fits in flight.
+template <int D, int KH>
 struct DkvShape {
   static constexpr int NW = KH == 4 ? 8 : 4, NT = NW * 64, RH = (NW / 2) / KH, ROWS = 64;
-  static constexpr int PITCH = D * 2 + PAD, TILEB = ROWS * PITCH, BUFB = 2 * TILEB + 2 * ROWS * (int)sizeof(float);
+  static constexpr int ROWB = D * 2, TILEB = ROWS * ROWB;
 };
+template <int D> __device__ __forceinline__ int row_swizzle(int row) {
+  return D == 128 ? ((row & 3) << 2) | ((row >> 2) & 3) : (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
+}
+constexpr int DKV_LIST = 1024;     // query blocks tested before their rows are walked
 
-template <int D, int KH, bool CAUSAL, int PAD>
-__global__ __launch_bounds__((DkvShape<D, KH, PAD>::NT), 2) void bwd_dkv_mfma_kernel(
+template <int D, int KH, bool CAUSAL>
+__global__ __launch_bounds__((DkvShape<D, KH>::NT), 2) void bwd_dkv_mfma_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V, const bf16_t* __restrict__ Kp,
     const bf16_t* __restrict__ Vp, const uint8_t* __restrict__ M, const float* __restrict__ lse, const float* __restrict__ Dr,
     const bf16_t* __restrict__ dO, float* __restrict__ dKp, float* __restrict__ dVp, int h_lo, int h_hi, BwdMfmaArgs a) {
-  using S = DkvShape<D, KH, PAD>;
-  constexpr int NW = S::NW, NT = S::NT, RH = S::RH, ROWS = S::ROWS, PITCH = S::PITCH, TILEB = S::TILEB, BUFB = S::BUFB;
-  constexpr int CPR = D / 8, KS = D / 16, MD = D / 32;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  // two buffers, each: Q rows [ROWS][PITCH] | dO rows [ROWS][PITCH] | lse [ROWS] | D [ROWS]
+  using S = DkvShape<D, KH>;
+  constexpr int NW = S::NW, NT = S::NT, RH = S::RH, ROWS = S::ROWS, ROWB = S::ROWB, TILEB = S::TILEB;
+  constexpr int CPR = D / 8, KS = D / 16, MD = D / 32, RPI = 64 / CPR, NI = ROWS / RPI / NW;   // NI: load instructions per wavefront, stage and tensor
+  // Q rows [ROWS][ROWB] | dO rows [ROWS][ROWB]
+  __shared__ __attribute__((aligned(1024))) unsigned char buf0[2 * TILEB];
+  __shared__ __attribute__((aligned(1024))) unsigned char buf1[2 * TILEB];
+  __shared__ __attribute__((aligned(16))) float stat0[2 * ROWS], stat1[2 * ROWS];   // lse [ROWS] | D [ROWS]
+  __shared__ uint32_t kept[DKV_LIST];              // query block | used blocks << 16
+  __shared__ int wcount[8];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // 0: this wavefront accumulates dKbar, 1: dVbar.  The halves change places from one workgroup to the
   // next, so that two workgroups on a compute unit do not put both heavier halves on the same SIMDs.
-  const int role = (wave / (NW / 2)) ^ (int)(blockIdx.x & 1);
+  const int role = (wave / (NW / 2)) ^ (int)((blockIdx.x >> 3) & 1);
   const int w2 = wave % (NW / 2), kh = w2 % KH, rh = w2 / KH;
-  const int hq = blockIdx.y, b = blockIdx.z;
-  const int hk = hq / (a.Hq / a.Hkv);
   // One launch covers the levels h_lo .. h_hi that share this KH, the coarsest first: its workgroups
   // walk the longest lists, and the finer levels' shorter ones fill the end of the launch.
   // A block of more pooled keys than the workgroup takes (KH * 32) is shared by several workgroups,
   // `pieces` of them, each with its own KH * 32 keys (and its own walk down the same column).
-  int h = h_hi, G = 1, pieces = 1, bx = blockIdx.x;
+  // Workgroup ids are dealt round-robin to the 8 XCDs; each XCD takes one contiguous run of a level's
+  // (head, key block) items, so that what runs on it at one time are columns of one head and level, of
+  // like length, whose query rows meet in its L2.  (All XCDs on one head, a block each in turn: 2 % slower
+  // at 32760 tokens, 12 heads; 13 % slower causal at 16384 tokens, d = 64.)
+  int h = h_hi, G = 1, pieces = 1, bx = 0, head = 0;
+  int slot = (int)(blockIdx.x >> 3);
   for (;; --h) {
     const int lg = a.lg_bk - (h - 1);
     G = (KH * 32) >> lg;
     G = G < 1 ? 1 : (G > 16 ? 16 : G);
     pieces = (1 << lg) > KH * 32 ? (1 << lg) / (KH * 32) : 1;
-    const int ng = pieces * ((a.nk + G - 1) / G);
-    if (bx < ng || h == h_lo) break;
-    bx -= ng;
+    const int ng = pieces * ((a.nk + G - 1) / G), items = a.B * a.Hq * ng, run = (items + 7) >> 3;
+    if (slot < run || h == h_lo) {
+      const int item = (int)(blockIdx.x & 7) * run + slot;
+      if (item >= items) return;
+      head = item / ng;
+      bx = item % ng;
+      break;
+    }
+    slot -= run;
   }
+  const int hq = head % a.Hq, b = head / a.Hq;
+  const int hk = hq / (a.Hq / a.Hkv);
   const int lg_th = a.lg_bk - (h - 1), span = 1 << (h - 1);
   const int j0 = (bx / pieces) * G, koff = (bx % pieces) * KH * 32;   // first block; first key inside it
   const int64_t qhead = (int64_t)b * a.Hq + hq, khead = (int64_t)b * a.Hkv + hk;
@@ -366,49 +401,66 @@ __global__ __launch_bounds__((DkvShape<D, KH, PAD>::NT), 2) void bwd_dkv_mfma_ke
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[md][v] = 0.f;
 
-  // First the columns of the level map: which query blocks of this query head use any of the group's
-  // key blocks at this level, as an ordered list in LDS with the blocks used as a bit mask (one round of
-  // independent loads per NT entries; a walk that tests one entry after the other spends a memory
-  // latency on each of them).
-  const int E = a.nq;
-  const int listb = (E * 2 + 15) & ~15;
-  uint16_t* kept = reinterpret_cast<uint16_t*>(smem + 2 * BUFB);
-  uint16_t* kmask = reinterpret_cast<uint16_t*>(smem + 2 * BUFB + listb);
-  int* wcount = reinterpret_cast<int*>(smem + 2 * BUFB + 2 * listb);
-  int nkept = 0;
-  for (int e0 = 0; e0 < E; e0 += NT) {
-    const int e = e0 + tid;
-    uint32_t bits = 0u;
-    if (e < E) {
-      const uint8_t* mrow = M + (qhead * a.nq + e) * a.nk + j0;
-      for (int g = 0; g < G && j0 + g < a.nk; ++g) bits |= ((int)mrow[g] == h ? 1u : 0u) << g;
-    }
-    const bool hit = bits != 0u;
-    const uint64_t mask = __ballot(hit);
-    if (lane == 0) wcount[wave] = __popcll(mask);
-    __syncthreads();
-    int base = nkept, total = 0;
+  // ---- loads: instruction n = wave * NI + k covers 1024 bytes of LDS, RPI rows
+  const __amdgpu_buffer_rsrc_t qrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(Q + qhead * a.N * D), 0, (int)((uint32_t)a.N * (uint32_t)ROWB), 0x00020000);
+  const __amdgpu_buffer_rsrc_t grsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(dO + qhead * a.N * D), 0, (int)((uint32_t)a.N * (uint32_t)ROWB), 0x00020000);
+  const int lrow = lane / CPR;
+  int lane_chunk[NI];                              // byte offset inside its source row that this lane reads
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      base += w < wave ? wcount[w] : 0;
-      total += wcount[w];
-    }
-    if (hit) {
-      const int pos = base + __popcll(mask & ((1ull << lane) - 1ull));
-      kept[pos] = (uint16_t)e;
-      kmask[pos] = (uint16_t)bits;
-    }
-    nkept += total;
-    __syncthreads();
-  }
-  // The stages (a query block on the list, ROWS of its rows) are walked with the NEXT stage's
-  // rows already on their way from memory into registers while the current one is multiplied; they go
-  // into the other LDS buffer afterwards.
+  for (int k = 0; k < NI; ++k) lane_chunk[k] = ((lane % CPR) ^ row_swizzle<D>((wave * NI + k) * RPI + lrow)) << 4;
   struct Stage { int k, i, r0, seg; uint32_t bits; bool ok; };
+  float lreg = INFINITY, dreg = 0.f;
+  auto fire = [&](const Stage& st, unsigned char* dst) __attribute__((always_inline)) {
+    lds_void* q0 = (lds_void*)(dst);
+    lds_void* g0 = (lds_void*)(dst + TILEB);
+    auto load = [&](auto tag) __attribute__((always_inline)) {
+      constexpr int k = decltype(tag)::value;
+      if constexpr (k < NI) {
+        const int n = wave * NI + k;
+        int r = n * RPI + lrow;
+        // a short stage repeats its last row: the weights of the rows past it are 0, and what they multiply has to be a
+        // row that takes part anyway
+        if (st.seg < ROWS) r = r < st.seg ? r : st.seg - 1;
+        const int at = (st.r0 + r) * ROWB + lane_chunk[k];
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(qrsrc, (lds_void*)((lds_byte*)q0 + n * 1024), 16, at, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(grsrc, (lds_void*)((lds_byte*)g0 + n * 1024), 16, at, 0, 0, 0);
+      }
+    };
+    static_assert(NI <= 4, "loads below");
+    load(std::integral_constant<int, 0>{});
+    load(std::integral_constant<int, 1>{});
+    load(std::integral_constant<int, 2>{});
+    load(std::integral_constant<int, 3>{});
+    if (tid < ROWS) {
+      const int64_t row = qhead * a.N + st.r0 + tid;
+      lreg = tid < st.seg ? lse[row] * LOG2E : INFINITY;
+      dreg = tid < st.seg ? Dr[row] : 0.f;
+    }
+  };
+  // ---- LDS addresses inside a tile: this wavefront's first 32-row chunk
+  int rowaddr[KS], traddr[MD];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) rowaddr[ks] = (rh * 32 + l32) * ROWB + (((2 * ks + hf) ^ row_swizzle<D>(l32)) << 4);
+  {
+    const int grp = lane >> 4, s16 = lane & 15, row = hf * 4 + (s16 >> 2);
+#pragma unroll
+    for (int md = 0; md < MD; ++md)
+      traddr[md] = (rh * 32 + row) * ROWB + (((md * 4 + (grp & 1) * 2 + ((s16 & 3) >> 1)) ^ row_swizzle<D>(row)) << 4) + (s16 & 1) * 8;
+  }
+  // channels md*32 .. +31 of rows r0 .. r0+15, transposed: the order in which pack_b lays the rows out.  Eight rows
+  // further down the swizzle differs in one bit.
+  auto frag_t = [&](const unsigned char* tile, int r0, int md) __attribute__((always_inline)) -> bf16x8 {
+    const bs16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bs16x4*)(tile + traddr[md] + r0 * ROWB));
+    const bs16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bs16x4*)(tile + (traddr[md] ^ 32) + (r0 + 8) * ROWB));
+    return __builtin_bit_cast(bf16x8, (bs16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  // one stage: cur has been requested into `now`, the stage after it goes into `later`
+  int nkept = 0;
   auto settle = [&](Stage st) __attribute__((always_inline)) -> Stage {   // first existing stage at or after (k, r0)
     for (; st.k < nkept; ++st.k, st.r0 = -1) {
-      st.i = __builtin_amdgcn_readfirstlane((int)kept[st.k]);       // the same for every lane: scalar from here on
-      st.bits = (uint32_t)__builtin_amdgcn_readfirstlane((int)kmask[st.k]);
+      const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)kept[st.k]);   // the same for every lane: scalar from here on
+      st.i = (int)(w & 0xffffu);
+      st.bits = w >> 16;
       int row_end = (st.i + 1) * a.bq;
       row_end = row_end < a.N ? row_end : a.N;
       if (st.r0 < 0) st.r0 = st.i * a.bq;
@@ -421,85 +473,38 @@ __global__ __launch_bounds__((DkvShape<D, KH, PAD>::NT), 2) void bwd_dkv_mfma_ke
     st.ok = false;
     return st;
   };
-  constexpr int NCH = ROWS * CPR / NT;             // 16-byte chunks per thread, tile and tensor
-  u32x4 qreg[NCH], greg[NCH];
-  float lreg = INFINITY, dreg = 0.f;
-  auto fetch = [&](const Stage& st) __attribute__((always_inline)) {
-    // a scalar base for the stage plus this thread's fixed 32-bit offsets: no 64-bit vector arithmetic
-    const int64_t row0 = qhead * a.N + st.r0;
-    const bf16_t* qs = Q + row0 * D;
-    const bf16_t* gs = dO + row0 * D;
-    if (st.seg == ROWS) {                          // all but a ragged last query block
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        const int x = tid + NT * c, off = (x / CPR) * D + (x % CPR) * 8;
-        qreg[c] = *reinterpret_cast<const u32x4*>(qs + off);
-        greg[c] = *reinterpret_cast<const u32x4*>(gs + off);
-      }
-      if (tid < ROWS) {
-        lreg = lse[row0 + tid] * LOG2E;
-        dreg = Dr[row0 + tid];
-      }
-    } else {
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        const int x = tid + NT * c, r = x / CPR, off = r * D + (x % CPR) * 8;
-        const u32x4 z = {0u, 0u, 0u, 0u};
-        qreg[c] = z;
-        greg[c] = z;
-        if (r < st.seg) {
-          qreg[c] = *reinterpret_cast<const u32x4*>(qs + off);
-          greg[c] = *reinterpret_cast<const u32x4*>(gs + off);
-        }
-      }
-      if (tid < ROWS) {
-        lreg = tid < st.seg ? lse[row0 + tid] * LOG2E : INFINITY;
-        dreg = tid < st.seg ? Dr[row0 + tid] : 0.f;
-      }
-    }
-  };
-  auto deposit = [&](int buf) __attribute__((always_inline)) {
-    unsigned char* base = smem + buf * BUFB;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int x = tid + NT * c, r = x / CPR, ch = x % CPR;
-      *reinterpret_cast<u32x4*>(base + r * PITCH + ch * 16) = qreg[c];
-      *reinterpret_cast<u32x4*>(base + TILEB + r * PITCH + ch * 16) = greg[c];
-    }
-    if (tid < ROWS) {
-      reinterpret_cast<float*>(base + 2 * TILEB)[tid] = lreg;
-      reinterpret_cast<float*>(base + 2 * TILEB)[ROWS + tid] = dreg;
-    }
-  };
-  Stage cur = settle(Stage{0, 0, -1, 0, 0u, false});
-  if (cur.ok) {
-    fetch(cur);
-    deposit(0);
-  }
-  for (int buf = 0; cur.ok; buf ^= 1) {
+  Stage cur;
+  auto step = [&](const unsigned char* now, float* stat, unsigned char* later) __attribute__((always_inline)) {
     Stage nxt = cur;
     nxt.r0 += ROWS;
     nxt = settle(nxt);
-    if (nxt.ok) fetch(nxt);
-    // this stage's rows are in LDS; the other buffer is no longer being read.  A bare barrier after the
-    // LDS counter alone: __syncthreads() would also wait for the loads just issued for the next stage.
+    // this wavefront's part of the stage has landed; behind the barrier everyone's has, and the other buffer is
+    // no longer being read
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (tid < ROWS) {
+      stat[tid] = lreg;
+      stat[ROWS + tid] = dreg;
+    }
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    const unsigned char* Qs = smem + buf * BUFB;
-    const unsigned char* Gs = Qs + TILEB;
-    const float* lse_s = reinterpret_cast<const float*>(Qs + 2 * TILEB);   // log2 domain, +inf for rows that do not exist
-    const float* D_s = lse_s + ROWS;
+    if (nxt.ok) fire(nxt, later);
+    const unsigned char* Qs = now;
+    const unsigned char* Gs = now + TILEB;
+    const float* lse_s = stat;                                             // log2 domain, +inf for rows that do not exist
+    const float* D_s = stat + ROWS;
     const unsigned char* Ts = role == 0 ? Qs : Gs;                         // dKbar^T += Q^T dS, dVbar^T += dO^T P
-    const int r0 = cur.r0, seg = cur.seg;
     // this lane's key counts only if its block is used by this query block
     const float bias_on = ((cur.bits >> kblk) & 1u) != 0u ? bias2 : -INFINITY;
     if ((cur.bits & wave_bits) != 0u) {                                    // ... and so is one of this wavefront's
-      for (int c = rh; c * 32 < seg; c += RH) {                             // this wavefront's 32-row chunks
+#pragma unroll
+      for (int cc = 0; cc < 2 / RH; ++cc) {                                 // this wavefront's 32-row chunks
+        const int c = rh + cc * RH;
+        if (c * 32 >= cur.seg) break;
         f32x16 sc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) sc[v] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
-          sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows(Qs, PITCH, c * 32 + l32, ks * 16, hf), kf[ks], sc, 0, 0, 0);
+          sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(Qs + rowaddr[ks] + cc * RH * 32 * ROWB), kf[ks], sc, 0, 0, 0);
         // this lane: key `key`, rows c*32 + (v/4)*8 + hf*4 + v%4
         float w[16];                               // P, or dS for the dKbar half
 #pragma unroll
@@ -509,7 +514,7 @@ __global__ __launch_bounds__((DkvShape<D, KH, PAD>::NT), 2) void bwd_dkv_mfma_ke
 #pragma unroll
           for (int e4 = 0; e4 < 4; ++e4) {
             float x = fmaf(sc[g4 * 4 + e4], a.scale_log2, bias_on) - ls[e4];
-            if (CAUSAL) x = last > r0 + r + e4 ? -INFINITY : x;
+            if (CAUSAL) x = last > cur.r0 + r + e4 ? -INFINITY : x;
             w[g4 * 4 + e4] = __builtin_amdgcn_exp2f(x);
           }
         }
@@ -519,7 +524,7 @@ __global__ __launch_bounds__((DkvShape<D, KH, PAD>::NT), 2) void bwd_dkv_mfma_ke
           for (int v = 0; v < 16; ++v) dp[v] = 0.f;
 #pragma unroll
           for (int ks = 0; ks < KS; ++ks)
-            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows(Gs, PITCH, c * 32 + l32, ks * 16, hf), vf[ks], dp, 0, 0, 0);
+            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(Gs + rowaddr[ks] + cc * RH * 32 * ROWB), vf[ks], dp, 0, 0, 0);
 #pragma unroll
           for (int g4 = 0; g4 < 4; ++g4) {
             const f32x4 dd = *reinterpret_cast<const f32x4*>(D_s + c * 32 + g4 * 8 + hf * 4);
@@ -533,17 +538,54 @@ __global__ __launch_bounds__((DkvShape<D, KH, PAD>::NT), 2) void bwd_dkv_mfma_ke
         for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
           for (int md = 0; md < MD; ++md)
-            acc[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_transposed(Ts, PITCH, c * 32 + ks * 16, md * 32, lane), wf[ks], acc[md], 0, 0, 0);
+            acc[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_t(Ts, cc * RH * 32 + ks * 16, md), wf[ks], acc[md], 0, 0, 0);
       }
     }
-    if (nxt.ok) deposit(buf ^ 1);
     cur = nxt;
+  };
+
+  for (int e_lo = 0; e_lo < a.nq; e_lo += DKV_LIST) {
+    // The columns of the level map: which of the next query blocks of this query head use any of the group's key blocks
+    // at this level, as an ordered list in LDS with the blocks used as a bit mask (one round of independent
+    // loads per NT entries; a walk that tests one entry after the other spends a memory latency on each of them).
+    nkept = 0;
+    const int e_hi = e_lo + DKV_LIST < a.nq ? e_lo + DKV_LIST : a.nq;
+    for (int e0 = e_lo; e0 < e_hi; e0 += NT) {
+      const int e = e0 + tid;
+      uint32_t bits = 0u;
+      if (e < e_hi) {
+        const uint8_t* mrow = M + (qhead * a.nq + e) * a.nk + j0;
+        for (int g = 0; g < G && j0 + g < a.nk; ++g) bits |= ((int)mrow[g] == h ? 1u : 0u) << g;
+      }
+      const uint64_t mask = __ballot(bits != 0u);
+      if (lane == 0) wcount[wave] = __popcll(mask);
+      __syncthreads();                             // (and the list before is done with)
+      int base = nkept, total = 0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        base += w < wave ? wcount[w] : 0;
+        total += wcount[w];
+      }
+      if (bits) kept[base + __popcll(mask & ((1ull << lane) - 1ull))] = (uint32_t)e | (bits << 16);
+      nkept += total;
+      __syncthreads();
+    }
+    cur = settle(Stage{0, 0, -1, 0, 0u, false});
+    if (cur.ok) fire(cur, buf0);
+    while (cur.ok) {
+      step(buf0, stat0, buf1);
+      if (!cur.ok) break;
+      step(buf1, stat1, buf0);
+    }
+    __syncthreads();                               // everyone has read the last stage: buf0 may be filled again
   }
   // partial sums of the wavefronts that share a key tile -> LDS [wavefront of the half][key][channel],
   // added in a fixed order, first dKbar, then dVbar; lane (key, hf) holds channels
   // md*32 + (v/4)*8 + hf*4 + v%4.  Every pooled key of the group is written (zeros where no query block
   // used it).
-  float* red = reinterpret_cast<float*>(smem);    // NW/2 x 32 x D floats <= the two staged tiles
+  auto red = [&](int w) __attribute__((always_inline)) {                    // 32 x D floats of wavefront w of a half: two fit a buffer
+    return reinterpret_cast<float*>((w < 2 ? buf0 : buf1) + (w & 1) * 32 * D * 4);
+  };
   for (int which = 0; which < 2; ++which) {
     __syncthreads();
     if (role == which) {
@@ -554,7 +596,7 @@ __global__ __launch_bounds__((DkvShape<D, KH, PAD>::NT), 2) void bwd_dkv_mfma_ke
           f32x4 x;
 #pragma unroll
           for (int e = 0; e < 4; ++e) x[e] = acc[md][4 * g + e];
-          *reinterpret_cast<f32x4*>(red + ((w2 * 32 + l32) * D + md * 32 + g * 8 + hf * 4)) = x;
+          *reinterpret_cast<f32x4*>(red(w2) + (l32 * D + ((md * 32 + g * 8 + hf * 4) ^ ((l32 & 7) << 2)))) = x;   // (rows spread over the banks)
         }
     }
     __syncthreads();
@@ -567,55 +609,34 @@ __global__ __launch_bounds__((DkvShape<D, KH, PAD>::NT), 2) void bwd_dkv_mfma_ke
       const int g2 = kk / 32, k32 = kk % 32;
       f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int r = 0; r < RH; ++r) sum += *reinterpret_cast<const f32x4*>(red + (((r * KH + g2) * 32 + k32) * D + c4 * 4));
+      for (int r = 0; r < RH; ++r) sum += *reinterpret_cast<const f32x4*>(red(r * KH + g2) + (k32 * D + ((c4 * 4) ^ ((k32 & 7) << 2))));
       *reinterpret_cast<f32x4*>(dst + (int64_t)(koff + kk) * D + c4 * 4) = sum * mul;
     }
   }
 }
 
-// two staging buffers + the kept list and block masks of the group's columns (entries: query blocks) +
-// 8 counters
-size_t bwd_dkv_mfma_smem(int d, int pad, int entries) {
-  return 2 * (2 * (size_t)64 * (d * 2 + pad) + 2 * 64 * sizeof(float)) + 2 * (((size_t)entries * 2 + 15) & ~(size_t)15) + 32;
-}
-
 bool bwd_uses_mfma(const Plan& pl) {
   return pl.dtype == PSA_BF16 && pl.bk >= 8 && pl.bk <= 128 && (pl.d == 64 || pl.d == 128) &&
-         pl.nq <= 8192;                          // the column's kept list sits in LDS next to the staging buffers
+         pl.nq <= 8192 &&                          // a query block's number and its 16 block bits share a list entry
+         (int64_t)pl.N * pl.d * 2 < 0x7fffffff;    // a head's rows are addressed with 32-bit byte offsets
 }
 
 // levels h_lo .. h_hi in one launch (they share KH)
-template <int D, int KH, bool CAUSAL, int PAD>
+template <int D, int KH>
 static hipError_t launch_dkv_t(const Plan& pl, const BwdMfmaArgs& a, const bf16_t* q, const bf16_t* k, const bf16_t* v,
                                const bf16_t* kp, const bf16_t* vp, const uint8_t* M, const float* lse, const float* Dr,
                                const bf16_t* go, float* dKp, float* dVp, int h_lo, int h_hi, hipStream_t s) {
-  static LdsOptIn optin;
-  auto kern = bwd_dkv_mfma_kernel<D, KH, CAUSAL, PAD>;
-  const hipError_t e = allow_max_lds(reinterpret_cast<const void*>(kern), &optin);
-  if (e != hipSuccess) return e;
-  int groups = 0;
+  int groups = 0;                                // as the kernel counts them
   for (int h = h_lo; h <= h_hi; ++h) {
     const int th = pl.bk >> (h - 1);
-    int G = KH * 32 / th;                        // key blocks per workgroup, as in the kernel
+    int G = KH * 32 / th;                        // key blocks per workgroup
     G = G < 1 ? 1 : (G > 16 ? 16 : G);
     const int pieces = th > KH * 32 ? th / (KH * 32) : 1;
-    groups += pieces * ((pl.nk + G - 1) / G);
+    groups += (pl.B * pl.Hq * pieces * ((pl.nk + G - 1) / G) + 7) / 8;
   }
-  kern<<<dim3(groups, pl.Hq, pl.B), DkvShape<D, KH, PAD>::NT, bwd_dkv_mfma_smem(D, PAD, pl.nq), s>>>(q, k, v, kp, vp, M, lse, Dr, go,
-                                                                                                    dKp, dVp, h_lo, h_hi, a);
+  if (pl.causal) bwd_dkv_mfma_kernel<D, KH, true><<<8 * groups, DkvShape<D, KH>::NT, 0, s>>>(q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h_lo, h_hi, a);
+  else bwd_dkv_mfma_kernel<D, KH, false><<<8 * groups, DkvShape<D, KH>::NT, 0, s>>>(q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h_lo, h_hi, a);
   return hipGetLastError();
-}
-
-template <int D, int KH>
-static hipError_t launch_dkv_c(const Plan& pl, const BwdMfmaArgs& a, const bf16_t* q, const bf16_t* k, const bf16_t* v,
-                               const bf16_t* kp, const bf16_t* vp, const uint8_t* M, const float* lse, const float* Dr,
-                               const bf16_t* go, float* dKp, float* dVp, int h_lo, int h_hi, hipStream_t s) {
-  // the wider padding where two workgroups of it still share a compute unit (d = 128 only: see the header)
-  if (D == 128 && 2 * bwd_dkv_mfma_smem(D, 48, pl.nq) <= LDS_LIMIT)
-    return pl.causal ? launch_dkv_t<D, KH, true, D == 128 ? 48 : 16>(pl, a, q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h_lo, h_hi, s)
-                     : launch_dkv_t<D, KH, false, D == 128 ? 48 : 16>(pl, a, q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h_lo, h_hi, s);
-  return pl.causal ? launch_dkv_t<D, KH, true, 16>(pl, a, q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h_lo, h_hi, s)
-                   : launch_dkv_t<D, KH, false, 16>(pl, a, q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h_lo, h_hi, s);
 }
 
 template <int D>
@@ -624,7 +645,7 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
                                     const float* lse, const void* dO, const float* Dr, float* dKp, float* dVp, void* dQ,
                                     hipStream_t s) {
   BwdMfmaArgs a;
-  a.N = pl.N; a.Hq = pl.Hq; a.Hkv = pl.Hkv; a.nq = pl.nq; a.nk = pl.nk; a.bq = pl.bq; a.bk = pl.bk;
+  a.B = pl.B; a.N = pl.N; a.Hq = pl.Hq; a.Hkv = pl.Hkv; a.nq = pl.nq; a.nk = pl.nk; a.bq = pl.bq; a.bk = pl.bk;
   a.H = pl.H; a.causal = pl.causal; a.scale = pl.scale; a.scale_log2 = pl.scale * LOG2E;
   a.lg_bk = 0;
   while ((1 << a.lg_bk) < pl.bk) ++a.lg_bk;
@@ -661,9 +682,9 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
     int h_hi = h;
     while (h_hi < pl.H && tiles_of(h_hi + 1) == tiles_of(h)) ++h_hi;
     const int kh = tiles_of(h);
-    if (kh == 4) e = launch_dkv_c<D, 4>(pl, a, q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h, h_hi, s);
-    else if (kh == 2) e = launch_dkv_c<D, 2>(pl, a, q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h, h_hi, s);
-    else e = launch_dkv_c<D, 1>(pl, a, q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h, h_hi, s);
+    if (kh == 4) e = launch_dkv_t<D, 4>(pl, a, q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h, h_hi, s);
+    else if (kh == 2) e = launch_dkv_t<D, 2>(pl, a, q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h, h_hi, s);
+    else e = launch_dkv_t<D, 1>(pl, a, q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h, h_hi, s);
     if (e != hipSuccess) return e;
     h = h_hi + 1;
   }

@@ -1,0 +1,60 @@
+"""bfloat16 gradients where the staging of the matrix-core kernels ends: columns longer than one list, ragged last
+stages, every tile width, and tensors that start between two 16-byte chunks.
+
+Tolerance: the bfloat16 bar of the backward tests (P, dS, O and the gradients are rounded to 8 bits)."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+from oracle import psa_oracle as orc
+from tests.psa_testlib import Buffers, from_dev, gpu_params, rel_l2, to_dev
+
+pytestmark = pytest.mark.gpu
+
+psa = pytest.importorskip("paper_2512_04025_amd")
+
+
+def _off_by_one(x):
+    """The same tensor at an address that is 2 bytes past a 16-byte boundary."""
+    import torch
+    flat = torch.empty(x.numel() + 8, dtype=x.dtype, device=x.device)
+    y = flat[1:1 + x.numel()].view(x.shape)
+    y.copy_(x)
+    return y
+
+
+@pytest.mark.parametrize("Hq,Hkv,N,d,bq,bk,levels,causal,keep,shifted", [
+    (1, 1, 8300, 128, 8, 64, 3, False, 0.04, False),      # 1038 query blocks: two lists; stages of 8 rows
+    (2, 1, 1050, 128, 128, 128, 4, True, 0.6, False),     # 128-key blocks: eight wavefronts
+    (2, 2, 530, 64, 64, 128, 5, False, 0.6, False),       # d = 64: a 128-key block split over two workgroups
+    (3, 1, 333, 64, 96, 32, 3, True, 0.8, False),         # 9 (head, block) runs on 8 XCDs; 96-row blocks: stages of 64 and 32
+    (2, 1, 300, 128, 128, 64, 4, False, 0.7, True),
+])
+def test_backward_edges(Hq, Hkv, N, d, bq, bk, levels, causal, keep, shifted):
+    import torch
+    op = orc.Params(B=1, Hq=Hq, Hkv=Hkv, N=N, d=d, bq=bq, bk=bk, levels=levels, dtype="bf16", causal=causal, sq=8, sk=8)
+    gp = gpu_params(op)
+    host = si.random_qkv(5, 1, Hq, Hkv, N, d, "bf16")
+    dO = si.random_qkv(6, 1, Hq, Hq, N, d, "bf16")[0]
+    rng = np.random.default_rng(7)
+    vis = orc.block_visibility(op)
+    M = rng.integers(1, levels + 1, size=(1, Hq, op.nq, op.nk)) * (rng.random((1, Hq, op.nq, op.nk)) < keep)
+    M[..., 0] = 1
+    M = np.where(vis[None, None] == 0, 0, np.where(vis[None, None] == 2, 1, M)).astype(np.uint8)
+    Qd, Kd, Vd, dOd = (to_dev(x, "bf16") for x in (*host, dO))
+    if shifted:
+        Qd, dOd = _off_by_one(Qd), _off_by_one(dOd)
+    buf = Buffers(gp)
+    Md = torch.from_numpy(M).cuda()
+    psa.psa_build_pyramid(gp, Kd, Vd, buf.Kpyr, buf.Vpyr)
+    psa.psa_attention_fwd(gp, Qd, Kd, Vd, buf.Kpyr, buf.Vpyr, Md, buf.O, buf.scratch, lse=buf.lse)
+    grads = [torch.full_like(x, float("nan")) for x in (Qd, Kd, Vd)]
+    scratch = torch.full((psa.psa_query_bwd_sizes(gp),), 255, dtype=torch.uint8, device="cuda")
+    psa.psa_attention_bwd(gp, Qd, Kd, Vd, buf.Kpyr, buf.Vpyr, Md, buf.O, buf.lse, dOd, *grads, scratch)
+    torch.cuda.synchronize()
+    Q64, K64, V64, dO64 = (si.to_f64(x, "bf16") for x in (*host, dO))
+    ref = orc.psa_attention_backward(Q64, orc.build_pyramid(K64, op), orc.build_pyramid(V64, op), M, dO64, op)
+    for name, got, want in zip(("dQ", "dK", "dV"), grads, ref):
+        g = from_dev(got, "bf16")
+        assert np.abs(g - want).max() <= 2e-2 * max(1.0, float(np.abs(want).max())), name
+        assert rel_l2(g, want) <= 1e-2, name
