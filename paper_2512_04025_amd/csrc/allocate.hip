@@ -354,94 +354,8 @@ hipError_t launch_rho(const Plan& pl, const uint32_t* rowcnt, float* rho, hipStr
   return hipGetLastError();
 }
 
-// Per query block: the kept key blocks grouped by level (ascending block index inside a level)
-// and the number of blocks per level.  One wavefront per row; the row of levels is loaded once
-// into NCH registers per lane (block c*64 + lane in register c).
-template <int NCH>
-__global__ __launch_bounds__(256) void schedule_kernel(const uint8_t* __restrict__ M, uint16_t* __restrict__ idx,
-                                                       int32_t* __restrict__ cnt, int64_t rows, int nk, int H) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  const uint8_t* m = M + row * nk;
-  uint16_t* out = idx + row * nk;
-  int lv[NCH];
-#pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int j = c * 64 + lane;
-    lv[c] = j < nk ? (int)m[j] : 0;
-  }
-  const uint64_t below = (1ull << lane) - 1ull;
-  int pos = 0;
-  for (int h = 1; h <= PSA_MAX_LEVELS; ++h) {
-    int n = 0;
-    if (h <= H) {
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        const bool hit = lv[c] == h;
-        const uint64_t mask = __ballot(hit);
-        if (hit) out[pos + n + __popcll(mask & below)] = (uint16_t)(c * 64 + lane);
-        n += __popcll(mask);
-      }
-    }
-    if (lane == 0) cnt[row * CNT_STRIDE + (h - 1)] = n;
-    pos += n;
-  }
-}
-
-// The same for rows of more than 4096 blocks: the row is re-read from memory for every level.
-__global__ __launch_bounds__(256) void schedule_sweep_kernel(const uint8_t* __restrict__ M, uint16_t* __restrict__ idx,
-                                                             int32_t* __restrict__ cnt, int64_t rows, int nk, int H) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  const uint8_t* m = M + row * nk;
-  uint16_t* out = idx + row * nk;
-  int pos = 0;
-  for (int h = 1; h <= PSA_MAX_LEVELS; ++h) {
-    int c = 0;
-    if (h <= H) {
-      for (int j0 = 0; j0 < nk; j0 += 64) {
-        const int j = j0 + lane;
-        const bool hit = j < nk && m[j] == h;
-        const uint64_t mask = __ballot(hit);
-        if (hit) out[pos + c + __popcll(mask & ((1ull << lane) - 1ull))] = (uint16_t)j;
-        c += __popcll(mask);
-      }
-    }
-    if (lane == 0) cnt[row * CNT_STRIDE + (h - 1)] = c;
-    pos += c;
-  }
-}
-
-template <int NCH>
-static hipError_t launch_schedule_t(const uint8_t* M, uint16_t* idx, int32_t* cnt, int64_t rows, int nk, int H,
-                                    hipStream_t s) {
-  schedule_kernel<NCH><<<(unsigned)((rows + 3) / 4), 256, 0, s>>>(M, idx, cnt, rows, nk, H);
-  return hipGetLastError();
-}
-
-hipError_t launch_schedule(const Plan& pl, const uint8_t* M, uint16_t* idx, int32_t* cnt, hipStream_t s) {
-  const int64_t rows = (int64_t)pl.B * pl.Hq * pl.nq;
-  int nch = 1;
-  while (64 * nch < pl.nk) nch <<= 1;
-  switch (nch) {
-    case 1:  return launch_schedule_t<1>(M, idx, cnt, rows, pl.nk, pl.H, s);
-    case 2:  return launch_schedule_t<2>(M, idx, cnt, rows, pl.nk, pl.H, s);
-    case 4:  return launch_schedule_t<4>(M, idx, cnt, rows, pl.nk, pl.H, s);
-    case 8:  return launch_schedule_t<8>(M, idx, cnt, rows, pl.nk, pl.H, s);
-    case 16: return launch_schedule_t<16>(M, idx, cnt, rows, pl.nk, pl.H, s);
-    case 32: return launch_schedule_t<32>(M, idx, cnt, rows, pl.nk, pl.H, s);
-    case 64: return launch_schedule_t<64>(M, idx, cnt, rows, pl.nk, pl.H, s);
-    default: break;
-  }
-  // longer rows do not fit the registers of one wavefront: sweep the row once per level instead
-  schedule_sweep_kernel<<<(unsigned)((rows + 3) / 4), 256, 0, s>>>(M, idx, cnt, rows, pl.nk, pl.H);
-  return hipGetLastError();
-}
-
-// Tile descriptors for the matrix-core attention kernel.  The kept blocks of a level, in list order,
-// form one stream of pooled tokens that is cut into tiles of 64; tile row r of a tile comes from
+// Tile descriptors for the matrix-core attention kernel (only when Plan::desc_pitch > 0).  The kept blocks of a
+// level, in list order, form one stream of pooled tokens that is cut into tiles of 64; tile row r of a tile comes from
 // pooled row (block id << lg_th) | (stream position & (th - 1)) of the level's array.  A tile is
 // irregular when some row lies past the level's kept blocks, covers tokens past N, or (causal) is not
 // visible to every query row of the block.  One word per load instruction of the kernel (rpi tile
@@ -453,34 +367,74 @@ hipError_t launch_schedule(const Plan& pl, const uint8_t* M, uint16_t* idx, int3
 // each wavefront also carries level - 1 in bits 0..3 and the irregular flag in bit 4 (row offsets are
 // multiples of 128 bytes).  Four null tiles (level field 15) follow the last one: the kernel
 // requests tiles ahead of the one it computes (and touches one cache line further: the pitch leaves room).
-struct TileArgs {
-  int N, nq, nk, bq, lg_bk, H, causal, rowb, rpi, nw, ri, words, pitch, lg_ri, lg_words;
+struct ListArgs {
+  int64_t rows;
+  int N, nq, nk, bq, lg_bk, H, causal;
+  int rowb, rpi, ri, words, pitch, lg_ri, lg_words;   // descriptors; pitch 0: none
   uint32_t bias;
 };
 
-__global__ __launch_bounds__(256) void tiles_kernel(const uint16_t* __restrict__ idx, const int32_t* __restrict__ cnt,
-                                                    uint32_t* __restrict__ desc, TileArgs a) {
-  // one workgroup per query block; per level (wave-uniform constants), one thread per (tile, load
-  // instruction): every word is independent.  Pooled blocks hold at least rpi rows here, so the rpi
-  // rows of an instruction share their block.
-  extern __shared__ uint16_t lst[];                   // the row's block list: the gathers below hit LDS, not memory
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int64_t row = blockIdx.x;
-  const int32_t* c = cnt + row * CNT_STRIDE;
-  uint32_t* drow = desc + row * (int64_t)a.pitch * a.words;
-  const int i = (int)(row % a.nq);
-  {  // the whole list row (entries past the kept blocks are never used): no dependence on the counts
-    const uint16_t* src = idx + row * a.nk;
-    for (int x = tid; x < a.nk; x += 256) lst[x] = src[x];
-  }
-  __syncthreads();
-  const int q = tid & (a.words - 1), w = q >> a.lg_ri, k = q & (a.ri - 1);     // words, ri: powers of two
-  const int sub = tid >> a.lg_words, per_pass = 256 >> a.lg_words;               // tiles per pass of the workgroup
-  const uint64_t group_mask = ((1ull << a.words) - 1ull) << ((lane >> a.lg_words) << a.lg_words);
-  uint32_t* dmine = drow + (int64_t)w * a.pitch * a.ri + k;
-  int nb_h[PSA_MAX_LEVELS];                            // all counts first: one round trip to memory
+// Per query block: the kept key blocks grouped by level (ascending block index inside a level), the number of blocks
+// per level, and the tile descriptors.  One wavefront per query block does all three, so the descriptors read the
+// list from LDS where it was just made: two kernels with the list and the counts in between took 6 + 13 us at 12
+// heads x 256 query blocks x 512 key blocks and 3.3 + 3.7 at 12 x 8 x 16, this one 15 and 4.8.  NCH > 0: the row of levels is loaded once into NCH registers per
+// lane (block c*64 + lane in register c), four query blocks per workgroup.  NCH = 0 (rows of more than 4096 blocks):
+// the row is read again for every level, one query block per workgroup.
+template <int NCH>
+__global__ __launch_bounds__(NCH ? 256 : 64) void lists_kernel(const uint8_t* __restrict__ M, uint16_t* __restrict__ idx,
+                                                               int32_t* __restrict__ cnt, uint32_t* __restrict__ desc, ListArgs a) {
+  extern __shared__ uint16_t lists[];
+  constexpr int WAVES = NCH ? 4 : 1;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t row = (int64_t)blockIdx.x * WAVES + wave;
+  if (row >= a.rows) return;                           // (wavefronts of a workgroup do not wait for each other)
+  const uint8_t* m = M + row * a.nk;
+  uint16_t* out = idx + row * a.nk;
+  uint16_t* lst = lists + (int64_t)wave * ((a.nk + 7) & ~7);
+  int lv[NCH ? NCH : 1];
 #pragma unroll
-  for (int h = 0; h < PSA_MAX_LEVELS; ++h) nb_h[h] = h < a.H ? c[h] : 0;
+  for (int c = 0; c < NCH; ++c) {
+    const int j = c * 64 + lane;
+    lv[c] = j < a.nk ? (int)m[j] : 0;
+  }
+  const uint64_t below = (1ull << lane) - 1ull;
+  int nb_h[PSA_MAX_LEVELS];
+  int pos = 0;
+#pragma unroll
+  for (int h = 1; h <= PSA_MAX_LEVELS; ++h) {
+    int n = 0;
+    if (h <= a.H) {
+      auto take = [&](bool hit, int j) __attribute__((always_inline)) {
+        const uint64_t mask = __ballot(hit);
+        if (hit) {
+          const int at = pos + n + __popcll(mask & below);
+          out[at] = (uint16_t)j;
+          if (a.pitch) lst[at] = (uint16_t)j;
+        }
+        n += __popcll(mask);
+      };
+      if constexpr (NCH > 0) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) take(lv[c] == h, c * 64 + lane);
+      } else {
+        for (int j0 = 0; j0 < a.nk; j0 += 64) take(j0 + lane < a.nk && (int)m[j0 + lane] == h, j0 + lane);
+      }
+    }
+    if (lane == 0) cnt[row * CNT_STRIDE + (h - 1)] = n;
+    nb_h[h - 1] = n;
+    pos += n;
+  }
+  if (a.pitch == 0) return;
+  // the list passes between lanes of this one wavefront: LDS serves its accesses in order, the fences keep the
+  // compiler from moving the reads above the writes
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const int i = (int)(row % a.nq);
+  const int q = lane & (a.words - 1), w = q >> a.lg_ri, k = q & (a.ri - 1);     // words, ri: powers of two
+  const int sub = lane >> a.lg_words, per_pass = 64 >> a.lg_words;               // tiles per pass
+  const uint64_t group_mask = ((1ull << a.words) - 1ull) << ((lane >> a.lg_words) << a.lg_words);
+  uint32_t* dmine = desc + row * (int64_t)a.pitch * a.words + (int64_t)w * a.pitch * a.ri + k;
   int first = 0, start = 0;
 #pragma unroll
   for (int h = 0; h < PSA_MAX_LEVELS; ++h) {           // h = level - 1
@@ -507,30 +461,46 @@ __global__ __launch_bounds__(256) void tiles_kernel(const uint16_t* __restrict__
     first += ntl;
     start += nb;
   }
-  if (sub < 4) dmine[(int64_t)(first + sub) * a.ri] = k == 0 ? 15u : 0u;   // null tiles
+  for (int t = sub; t < 4; t += per_pass) dmine[(int64_t)(first + t) * a.ri] = k == 0 ? 15u : 0u;   // null tiles
 }
 
-hipError_t launch_tiles(const Plan& pl, const uint16_t* idx, const int32_t* cnt, uint32_t* desc, hipStream_t s) {
-  TileArgs a;
+template <int NCH>
+static hipError_t launch_lists_t(const uint8_t* M, uint16_t* idx, int32_t* cnt, uint32_t* desc, const ListArgs& a, hipStream_t s) {
+  constexpr int WAVES = NCH ? 4 : 1;
+  const size_t smem = a.pitch ? (size_t)WAVES * ((a.nk + 7) & ~7) * sizeof(uint16_t) : 0;
+  static LdsOptIn optin;
+  const hipError_t e = allow_max_lds(reinterpret_cast<const void*>(lists_kernel<NCH>), &optin);
+  if (e != hipSuccess) return e;
+  lists_kernel<NCH><<<(unsigned)((a.rows + WAVES - 1) / WAVES), 64 * WAVES, smem, s>>>(M, idx, cnt, desc, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_lists(const Plan& pl, const uint8_t* M, uint16_t* idx, int32_t* cnt, uint32_t* desc, hipStream_t s) {
+  ListArgs a;
+  a.rows = (int64_t)pl.B * pl.Hq * pl.nq;
   a.N = pl.N; a.nq = pl.nq; a.nk = pl.nk; a.bq = pl.bq; a.H = pl.H; a.causal = pl.causal;
   a.lg_bk = 0;
   while ((1 << a.lg_bk) < pl.bk) ++a.lg_bk;
   a.rowb = pl.d * 2;
   a.words = pl.desc_words;
   a.rpi = 64 / a.words;
-  a.nw = 4;
   a.lg_words = a.words == 16 ? 4 : 3;
-  a.ri = a.words / a.nw;
+  a.ri = a.words / 4;                                  // four wavefronts
   a.lg_ri = a.ri == 4 ? 2 : 1;
   a.bias = 1024u * (uint32_t)(a.ri - 1);
-  a.pitch = pl.desc_pitch;
-  const int64_t rows = (int64_t)pl.B * pl.Hq * pl.nq;
-  const size_t smem = ((size_t)pl.nk * sizeof(uint16_t) + 15) & ~(size_t)15;
-  static LdsOptIn optin;
-  const hipError_t e = allow_max_lds(reinterpret_cast<const void*>(tiles_kernel), &optin);
-  if (e != hipSuccess) return e;
-  tiles_kernel<<<(unsigned)rows, 256, smem, s>>>(idx, cnt, desc, a);
-  return hipGetLastError();
+  a.pitch = desc ? pl.desc_pitch : 0;
+  int nch = 1;
+  while (64 * nch < pl.nk) nch <<= 1;
+  switch (nch) {
+    case 1:  return launch_lists_t<1>(M, idx, cnt, desc, a, s);
+    case 2:  return launch_lists_t<2>(M, idx, cnt, desc, a, s);
+    case 4:  return launch_lists_t<4>(M, idx, cnt, desc, a, s);
+    case 8:  return launch_lists_t<8>(M, idx, cnt, desc, a, s);
+    case 16: return launch_lists_t<16>(M, idx, cnt, desc, a, s);
+    case 32: return launch_lists_t<32>(M, idx, cnt, desc, a, s);
+    case 64: return launch_lists_t<64>(M, idx, cnt, desc, a, s);
+    default: return launch_lists_t<0>(M, idx, cnt, desc, a, s);
+  }
 }
 
 }  // namespace psa

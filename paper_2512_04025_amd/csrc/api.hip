@@ -277,9 +277,8 @@ int psa_attention_fwd(const psa_params* p, const void* Q, const void* K, const v
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint16_t* idx = reinterpret_cast<uint16_t*>(at(scratch, pl.off_idx));
   int32_t* cnt = reinterpret_cast<int32_t*>(at(scratch, pl.off_cnt));
-  if (launch_schedule(pl, M, idx, cnt, s) != hipSuccess) return PSA_ELAUNCH;
   uint32_t* desc = reinterpret_cast<uint32_t*>(at(scratch, pl.off_desc));
-  if (pl.desc_pitch > 0 && launch_tiles(pl, idx, cnt, desc, s) != hipSuccess) return PSA_ELAUNCH;
+  if (launch_lists(pl, M, idx, cnt, desc, s) != hipSuccess) return PSA_ELAUNCH;
   const hipError_t e = pl.use_mfma ? launch_attn_mfma(pl, Q, K, V, Kpyr, Vpyr, idx, cnt, desc, O, lse, s)
                                    : launch_attn_f32(pl, Q, K, V, Kpyr, Vpyr, idx, cnt, O, lse, s);
   return e == hipSuccess ? PSA_OK : PSA_ELAUNCH;
@@ -335,7 +334,7 @@ int psa_attention_bwd(const psa_params* p, const void* Q, const void* K, const v
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint16_t* idx = reinterpret_cast<uint16_t*>(at(scratch, l.off_idx));
   int32_t* cnt = reinterpret_cast<int32_t*>(at(scratch, l.off_cnt));
-  if (launch_schedule(pl, M, idx, cnt, s) != hipSuccess) return PSA_ELAUNCH;
+  if (launch_lists(pl, M, idx, cnt, nullptr, s) != hipSuccess) return PSA_ELAUNCH;
   const hipError_t e = launch_attn_bwd(pl, Q, K, V, Kpyr, Vpyr, M, idx, cnt, O, lse, dO,
                                        reinterpret_cast<float*>(at(scratch, l.off_D)),
                                        reinterpret_cast<float*>(at(scratch, l.off_dkp)),
@@ -383,10 +382,9 @@ int psa_attention_fwd_static(const psa_params* p, const void* Q, const void* K, 
   uint16_t* idx = reinterpret_cast<uint16_t*>(at(base, off_idx));
   int32_t* cnt = reinterpret_cast<int32_t*>(at(base, off_cnt));
   uint32_t* desc = reinterpret_cast<uint32_t*>(at(base, off_desc));
-  // every word the attention kernel reads is rewritten by the two kernels below, so nothing needs
+  // every word the attention kernel reads is rewritten by the kernel below, so nothing needs
   // clearing between calls (what an earlier, larger call left behind is never read)
-  if (launch_schedule(pl, M, idx, cnt, s) != hipSuccess) return PSA_ELAUNCH;
-  if (pl.desc_pitch > 0 && launch_tiles(pl, idx, cnt, desc, s) != hipSuccess) return PSA_ELAUNCH;
+  if (launch_lists(pl, M, idx, cnt, desc, s) != hipSuccess) return PSA_ELAUNCH;
   const hipError_t e = pl.use_mfma ? launch_attn_mfma(pl, Q, K, V, Kpyr, Vpyr, idx, cnt, desc, O, lse, s)
                                    : launch_attn_f32(pl, Q, K, V, Kpyr, Vpyr, idx, cnt, O, lse, s);
   return e == hipSuccess ? PSA_OK : PSA_ELAUNCH;

@@ -97,7 +97,7 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   constexpr int NB = (BN / 16) * (D / 32);   // MFMAs of O^T += V^T P^T per tile
   constexpr int MPC = NPAIR / NB;            // 3-input maxima handled next to one MFMA of the second product
   // Full-size workgroups on shapes whose load instructions never straddle a pooled block read their
-  // load plan from per-tile descriptors made by tiles_kernel instead of deriving it per tile.
+  // load plan from per-tile descriptors made by lists_kernel instead of deriving it per tile.
   constexpr bool DESC = SC && BN == 64 && NW == 4;
   static_assert(BN == 64 || BN == 32, "tile width");
   static_assert(NINST % NW == 0, "tile rows must split evenly over the wavefronts");
@@ -312,7 +312,7 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
     else __builtin_amdgcn_s_waitcnt(0x0F70);
   };
 
-  // ---- tile descriptors (DESC).  tiles_kernel has worked out, per tile and load instruction, what the
+  // ---- tile descriptors (DESC).  lists_kernel has worked out, per tile and load instruction, what the
   // planner above derives: RI consecutive words per wavefront and tile, each the byte offset of the
   // source row of one of this wavefront's loads; the low bits of the first word carry the tile's
   // level - 1 (15: a null tile past the end of the row) and, in bit 4, whether the tile is irregular.

@@ -59,7 +59,19 @@ __global__ __launch_bounds__(256) void reps_kernel(const T* __restrict__ X, T* _
     cnt = cnt < 0 ? 0 : (cnt > g ? g : cnt);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) out[e] = 0.f;
-    for (int u = 0; u < cnt; ++u) {
+    // Four rows requested before the first is added (in order): bound by HBM on large inputs, by the latency of one
+    // row after the other on small ones (12 heads x 1000 tokens, 16 rows a group: 9.5 us one by one, 5.0 us so).
+    int u = 0;
+    for (; u + 4 <= cnt; u += 4) {
+      float x[4][VEC];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) Elem<T>::load(src + (int64_t)(start + u + v) * a.d, x[v]);
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) out[e] += x[v][e];
+    }
+    for (; u < cnt; ++u) {
       float x[VEC];
       Elem<T>::load(src + (int64_t)(start + u) * a.d, x);
 #pragma unroll

@@ -74,10 +74,9 @@ hipError_t launch_importance(const Plan& pl, const void* Qrep, const void* Krep,
 hipError_t launch_allocate(const Plan& pl, const float* S, const FactoredScores* factored, float* S_out,
                            const uint8_t* cap, uint8_t* M, uint32_t* rowcnt, hipStream_t s);
 hipError_t launch_rho(const Plan& pl, const uint32_t* rowcnt, float* rho, hipStream_t s);
-hipError_t launch_schedule(const Plan& pl, const uint8_t* M, uint16_t* idx, int32_t* cnt, hipStream_t s);
-// Per query block and 64-column tile of its level-sorted block list: source-row offsets of the tile's
-// load instructions, level and irregularity (Plan::off_desc; only when Plan::desc_pitch > 0)
-hipError_t launch_tiles(const Plan& pl, const uint16_t* idx, const int32_t* cnt, uint32_t* desc, hipStream_t s);
+// Per query block its level-sorted block list and level counts and, unless desc is null or Plan::desc_pitch is 0, per
+// 64-column tile of that list the source-row offsets of the tile's load instructions, level and irregularity (Plan::off_desc)
+hipError_t launch_lists(const Plan& pl, const uint8_t* M, uint16_t* idx, int32_t* cnt, uint32_t* desc, hipStream_t s);
 // idx == nullptr selects dense attention (every key block at level 1)
 hipError_t launch_attn_f32(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp,
                             const void* Vp, const uint16_t* idx, const int32_t* cnt, void* O, float* lse,
@@ -87,7 +86,7 @@ hipError_t launch_attn_mfma(const Plan& pl, const void* Q, const void* K, const 
                             float* lse, hipStream_t s);
 
 // Backward of the pyramid attention.  Dr: [B*Hq*N] floats; dKp, dVp: pooled gradients of levels 1..H
-// (bwd_pooled_grad_elems floats each); idx / cnt: the level-sorted block lists of launch_schedule.
+// (bwd_pooled_grad_elems floats each); idx / cnt: the level-sorted block lists of launch_lists.
 size_t bwd_pooled_grad_elems(const Plan& pl);
 hipError_t launch_attn_bwd(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp, const void* Vp,
                            const uint8_t* M, const uint16_t* idx, const int32_t* cnt, const void* O, const float* lse,
