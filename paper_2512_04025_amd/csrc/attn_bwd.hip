@@ -7,8 +7,8 @@
 // and the gradient of a pooled token is shared equally by the c_g tokens under it (Eq. 2-3).
 // The level map is a constant.  Everything is in fp32 arithmetic, deterministic, without atomics; it serves
 // float32 and the bfloat16 shapes that attn_bwd_mfma.hip does not take:
-//   rowdot_kernel   D = dO . O per query row
-//   bwd_dq_kernel   one workgroup per 32, 64 or 128 query rows, walking the row's level-sorted block list
+//   bwd_dq_kernel   one workgroup per 32, 64 or 128 query rows, walking the row's level-sorted block list; also
+//                   leaves D = dO . O per query row for the next kernel
 //   bwd_dkv_kernel  one workgroup per (key head, up to 32 pooled keys of a block, level), walking the column
 //                   of the level map; writes the gradient of every pooled token of every level (fp32)
 //   unpool_kernel   dK, dV = sum over the levels of the pooled gradients / c_g
@@ -29,28 +29,6 @@ struct BwdArgs {
   int64_t glvl_off[PSA_MAX_LEVELS + 2];  // level h >= 1 inside one pooled-gradient buffer (elements)
 };
 
-// out[r] = A[r] . B[r] (D = dO . O of the softmax backward).  A row is shared by d / VEC consecutive lanes
-// (8, 16 or 32), each with one 16-byte load per tensor; the partial sums meet in a butterfly.
-template <typename T>
-__global__ __launch_bounds__(256) void rowdot_kernel(const T* __restrict__ A, const T* __restrict__ Bm,
-                                                     float* __restrict__ out, int64_t rows, int d) {
-  constexpr int VEC = Elem<T>::VEC;
-  const int lpr = d / VEC;                         // lanes per row: a power of two that divides 64
-  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t r = gid / lpr;
-  const int c = (int)(gid % lpr) * VEC;
-  float acc = 0.f;
-  if (r < rows) {
-    float x[VEC], y[VEC];
-    Elem<T>::load(A + r * d + c, x);
-    Elem<T>::load(Bm + r * d + c, y);
-#pragma unroll
-    for (int u = 0; u < VEC; ++u) acc = fmaf(x[u], y[u], acc);
-  }
-  for (int o = 1; o < lpr; o <<= 1) acc += __shfl_xor(acc, o, 64);
-  if (r < rows && c == 0) out[r] = acc;
-}
-
 // LDS rows carry four floats of padding: the 16-byte reads of 16 rows then cover every bank once.
 template <int D, int TEAM>
 struct BwdDqShape {
@@ -66,8 +44,8 @@ template <typename T, int D, int TEAM>
 __global__ __launch_bounds__(256, (D == 64 && TEAM > 1 ? 2 : 1))
 void bwd_dq_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ Kp,
                    const T* __restrict__ Vp, const uint16_t* __restrict__ idx, const int32_t* __restrict__ cnt,
-                   const float* __restrict__ lse, const float* __restrict__ Dr, const T* __restrict__ dO, T* __restrict__ dQ,
-                   BwdArgs a) {
+                   const T* __restrict__ O, const float* __restrict__ lse, float* __restrict__ Dr, const T* __restrict__ dO,
+                   T* __restrict__ dQ, BwdArgs a) {
   using S = BwdDqShape<D, TEAM>;
   constexpr int KS = S::KS, ROWS = S::ROWS, PITCH = S::PITCH, CPR = D / 4, MD = D / 32, TT = 64 * TEAM, NCH = 32 * CPR / TT;
   extern __shared__ __attribute__((aligned(16))) float fsm[];
@@ -91,22 +69,30 @@ void bwd_dq_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* __
   const int row = row0 + wr * 32 + l32;
   const bool active = row < row_end;
 
-  float q[D / 2], go[D / 2];
+  float q[D / 2], go[D / 2], dots[D / 8];                // dots: dO . O, four channels at a time
 #pragma unroll
   for (int k8 = 0; k8 < D / 8; ++k8) {
-    f32x4 x = {0.f, 0.f, 0.f, 0.f}, y = x;
+    f32x4 x = {0.f, 0.f, 0.f, 0.f}, y = x, z = x;
     if (active) {
       x = Four<T>::widen(Four<T>::load(Q + (qhead * a.N + row) * D + k8 * 8 + hf * 4));
       y = Four<T>::widen(Four<T>::load(dO + (qhead * a.N + row) * D + k8 * 8 + hf * 4));
+      z = Four<T>::widen(Four<T>::load(O + (qhead * a.N + row) * D + k8 * 8 + hf * 4));
     }
+    dots[k8] = 0.f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       q[k8 * 4 + e] = x[e];
       go[k8 * 4 + e] = y[e];
+      dots[k8] = fmaf(y[e], z[e], dots[k8]);
     }
   }
+#pragma unroll
+  for (int w = 1; w < D / 8; w *= 2)
+#pragma unroll
+    for (int k8 = 0; k8 < D / 8; k8 += 2 * w) dots[k8] += dots[k8 + w];
+  const float my_D = dots[0] + __shfl_xor(dots[0], 32, 64);            // D of the row, also for bwd_dkv_kernel
+  if (active && team == 0 && hf == 0) Dr[qhead * a.N + row] = my_D;
   const float my_lse = active ? lse[qhead * a.N + row] : INFINITY;     // a row that does not exist: all weights 0
-  const float my_D = active ? Dr[qhead * a.N + row] : 0.f;
   f32x16 dq[MD];
 #pragma unroll
   for (int md = 0; md < MD; ++md)
@@ -542,8 +528,8 @@ __global__ __launch_bounds__(256) void unpool_kernel(const float* __restrict__ d
 
 bool bwd_uses_mfma(const Plan& pl);
 hipError_t launch_attn_bwd_mfma(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp, const void* Vp,
-                                const uint8_t* M, const uint16_t* idx, const int32_t* cnt, const float* lse, const void* dO,
-                                const float* Dr, float* dKp, float* dVp, void* dQ, hipStream_t s);
+                                const uint8_t* M, const uint16_t* idx, const int32_t* cnt, const void* O, const float* lse,
+                                const void* dO, float* Dr, float* dKp, float* dVp, void* dQ, hipStream_t s);
 
 // partial pooled-gradient tensors per key head: the matrix-core kernel writes one per query head of the group
 int bwd_parts(const Plan& pl) { return bwd_uses_mfma(pl) ? pl.group : 1; }
@@ -556,14 +542,14 @@ size_t bwd_pooled_grad_elems(const Plan& pl) {      // one tensor: levels 1..H, 
 
 template <typename T, int D, int TEAM>
 static hipError_t launch_dq_t(const Plan& pl, const BwdArgs& a, const T* q, const T* k, const T* v, const T* kp, const T* vp,
-                              const uint16_t* idx, const int32_t* cnt, const float* lse, const float* Dr, const T* go, T* dq,
-                              hipStream_t s) {
+                              const uint16_t* idx, const int32_t* cnt, const T* o, const float* lse, float* Dr, const T* go,
+                              T* dq, hipStream_t s) {
   using S = BwdDqShape<D, TEAM>;
   auto kern = bwd_dq_kernel<T, D, TEAM>;
   static LdsOptIn optin;
   const hipError_t e = allow_max_lds(reinterpret_cast<const void*>(kern), &optin);
   if (e != hipSuccess) return e;
-  kern<<<dim3(pl.nq * ((pl.bq + S::ROWS - 1) / S::ROWS), pl.Hq, pl.B), 256, S::BYTES, s>>>(q, k, v, kp, vp, idx, cnt, lse, Dr, go, dq, a);
+  kern<<<dim3(pl.nq * ((pl.bq + S::ROWS - 1) / S::ROWS), pl.Hq, pl.B), 256, S::BYTES, s>>>(q, k, v, kp, vp, idx, cnt, o, lse, Dr, go, dq, a);
   return hipGetLastError();
 }
 
@@ -590,13 +576,10 @@ static hipError_t launch_bwd_t(const Plan& pl, const void* Q, const void* K, con
   const T* kp = static_cast<const T*>(Kp);
   const T* vp = static_cast<const T*>(Vp);
   const T* go = static_cast<const T*>(dO);
-  const int64_t rows = (int64_t)pl.B * pl.Hq * pl.N;
-  const int64_t dot_threads = rows * (pl.d / Elem<T>::VEC);
-  rowdot_kernel<T><<<(unsigned)((dot_threads + 255) / 256), 256, 0, s>>>(go, static_cast<const T*>(O), Dr, rows, pl.d);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  const T* o = static_cast<const T*>(O);
+  hipError_t e = hipSuccess;
   if (use_mfma) {     // bfloat16: dQ and the pooled gradients on the matrix cores
-    e = launch_attn_bwd_mfma(pl, Q, K, V, Kp, Vp, M, idx, cnt, lse, dO, Dr, dKp, dVp, dQ, s);
+    e = launch_attn_bwd_mfma(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, dO, Dr, dKp, dVp, dQ, s);
     if (e != hipSuccess) return e;
   } else {
     // rows per workgroup: the largest that still fills the chip (see launch_f32_d)
@@ -604,9 +587,9 @@ static hipError_t launch_bwd_t(const Plan& pl, const void* Q, const void* K, con
     auto groups = [&](int rows_wg) { return blocks * ((pl.bq + rows_wg - 1) / rows_wg); };
     const int team = pl.bq > 64 && groups(128) >= 256 ? 4 : (pl.bq > 32 && groups(64) >= 192 ? 2 : 1);
     T* dq = static_cast<T*>(dQ);
-    e = team == 4 ? launch_dq_t<T, D, 4>(pl, a, q, k, v, kp, vp, idx, cnt, lse, Dr, go, dq, s)
-      : team == 2 ? launch_dq_t<T, D, 2>(pl, a, q, k, v, kp, vp, idx, cnt, lse, Dr, go, dq, s)
-                  : launch_dq_t<T, D, 1>(pl, a, q, k, v, kp, vp, idx, cnt, lse, Dr, go, dq, s);
+    e = team == 4 ? launch_dq_t<T, D, 4>(pl, a, q, k, v, kp, vp, idx, cnt, o, lse, Dr, go, dq, s)
+      : team == 2 ? launch_dq_t<T, D, 2>(pl, a, q, k, v, kp, vp, idx, cnt, o, lse, Dr, go, dq, s)
+                  : launch_dq_t<T, D, 1>(pl, a, q, k, v, kp, vp, idx, cnt, o, lse, Dr, go, dq, s);
     if (e != hipSuccess) return e;
     static LdsOptIn optin;
     e = allow_max_lds(reinterpret_cast<const void*>(bwd_dkv_kernel<T, D>), &optin);
