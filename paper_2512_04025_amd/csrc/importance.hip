@@ -671,15 +671,21 @@ static hipError_t launch_imp_tiles_t(const Plan& pl, const void* Qrep, const voi
   const int row_groups = (pl.nq * 8 + 127) / 128;
   const int ntile_all = (pl.nk * 8 + 63) / 64;
   // Key slices: the workgroups run in rounds of `slots` (what fits on the chip at once); pick the
-  // slice count with the least rounds x work-per-workgroup, preferring fewer slices on a tie.
+  // slice count with the least rounds x work-per-workgroup, preferring fewer slices on a tie, among those whose
+  // slices have at most 24 tiles: the more workgroups share a head's keys, the fewer heads are in flight and the
+  // more of their keys the L2 holds.  Measured for the whole allocation call, one slice / the rule / eight slices:
+  // 40 heads x 148 tiles 1882 / 1427 / 1424 us, 12 heads x 128 tiles 951 / 724 / 729, causal 28 heads x 64 tiles 225 / 210 / 214,
+  // 32 heads x 128 tiles at d = 64 1254 / 1145 / 1148 (two slices: 1145).
   const int smem = 4 * 64 * D * 2 + 16 * 8 * 16 * (int)sizeof(float);   // sweep 2: ring of 4 tiles + staged scores
   const int smem1 = 3 * 64 * D * 2;                                      // sweep 1: ring of 3 tiles
   const int per_cu = 160 * 1024 / smem1 < 3 ? 160 * 1024 / smem1 : 3;
   const int slots = 256 * per_cu;
   const int base = row_groups * pl.Hq * pl.B;
-  int ksplit = 1;
+  int least = (ntile_all + 23) / 24;
+  least = least < IMP_MAX_SPLIT ? least : IMP_MAX_SPLIT;
+  int ksplit = least;
   double best = 1e30;
-  for (int ks = 1; ks <= IMP_MAX_SPLIT && ks <= ntile_all; ++ks) {
+  for (int ks = least; ks <= IMP_MAX_SPLIT && ks <= ntile_all; ++ks) {
     const int tiles = (ntile_all + ks - 1) / ks;
     const double cost = (double)((base * ks + slots - 1) / slots) * (tiles + 2.0);   // +2: start-up of a workgroup
     if (cost < best - 1e-9) { best = cost; ksplit = ks; }
