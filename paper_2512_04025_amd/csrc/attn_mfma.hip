@@ -46,9 +46,6 @@ struct MfmaArgs {
   int64_t lvl_off[PSA_MAX_LEVELS + 2];
 };
 
-#ifndef PSA_ATTN_TILE
-#define PSA_ATTN_TILE 64
-#endif
 constexpr float LAZY_RESCALE = 8.0f;
 // word 3 of a raw (untyped, stride 0) buffer descriptor on gfx9-family targets: 32-bit data format
 constexpr int RSRC_FLAGS = 0x00020000;
@@ -74,9 +71,16 @@ struct LevelState {
 
 // D: head dimension; NW: wavefronts per workgroup (each owns 32 query rows); SC: every level's pooled
 // block holds at least as many rows as one load instruction covers
-// BN: key columns per tile (64, or 32: fewer registers, three wavefronts per SIMD)
+// BN: key columns per tile: 64 for workgroups of four wavefronts, 32 for those of one or two, whose tiles serve fewer
+// rows, so that LDS holds four of them per compute unit at d = 128 (eight at d = 64) instead of two (four).
+// Wavefronts per SIMD: as many as LDS lets in, and NOT more registers free than that: with room for more, the
+// one- and two-wavefront workgroups of a compute unit were put on few of its four SIMDs.  Measured, 12 heads x 32760
+// tokens (pyramid included), tiles of 64 and two wavefronts per SIMD allowed -> tiles of 32, no tight limit -> this:
+// 32-row blocks d = 128 4104 -> 3915 -> 2360 us, d = 64 1752 -> 1685 -> 1180; 64-row blocks d = 128 2142 -> 1777 -> 1765,
+// d = 64 1160 -> 1118 -> 1040.
+constexpr int waves_per_simd(int d, int nw) { return nw == 4 ? (d == 64 ? 3 : 2) : (d == 64 ? nw + 1 : nw); }
 template <int D, int NW, bool SC, int BN>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(BN == 32 ? 3 : 2, (D == 64 || BN == 32) ? 3 : 2)))
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((NW == 4 ? 2 : waves_per_simd(D, NW)), waves_per_simd(D, NW))))
 void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
                       const bf16_t* __restrict__ Kp, const bf16_t* __restrict__ Vp,
                       const uint16_t* __restrict__ idx, const int32_t* __restrict__ cnt,
@@ -98,8 +102,8 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   constexpr int MPC = NPAIR / NB;            // 3-input maxima handled next to one MFMA of the second product
   // Full-size workgroups on shapes whose load instructions never straddle a pooled block read their
   // load plan from per-tile descriptors made by lists_kernel instead of deriving it per tile.
-  constexpr bool DESC = SC && BN == 64 && NW == 4;
-  static_assert(BN == 64 || BN == 32, "tile width");
+  constexpr bool DESC = SC && NW == 4;
+  static_assert(BN == (NW == 4 ? 64 : 32), "tile width");
   static_assert(NINST % NW == 0, "tile rows must split evenly over the wavefronts");
   static_assert(MPC * NB == NPAIR, "chunking of the softmax work");
   // LDS map: K[2] | V[2] | per-wavefront table for irregular tiles | block list
@@ -442,7 +446,7 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   for (int ks = 0; ks < D / 16; ++ks) kaddr[ks] = kaddr0 ^ (uint32_t)(ks << 5);
   auto read_k_asm = [&](bf16x8& dst, int j, int flip) __attribute__((always_inline)) {
     const int mb = j % HALVES, ks = j / HALVES;
-    if (BN == 32) {   // three wavefronts per SIMD leave no room for one address register per k-step
+    if (BN == 32) {   // (tiles of 32 came with three wavefronts per SIMD: no room for one address register per k-step)
       uint32_t ad;
       asm volatile("v_xor_b32 %0, %1, %2" : "=v"(ad) : "n"(ks << 5), "v"(kaddr0));
       asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(ad), "n"(flip + mb * 32 * ROWB));
@@ -814,7 +818,7 @@ static hipError_t launch_mfma_d(const Plan& pl, const void* Q, const void* K, co
   constexpr int RPI = 64 / (D / 8);           // tile rows per wave-wide 16 B/lane load
   // (the scalar-plan variant of full workgroups reads tile descriptors; without them take the general one)
   const bool blocks_cover_a_load = (pl.bk >> (pl.H - 1)) >= RPI && (NW != 4 || pl.desc_pitch > 0);
-  constexpr int BN = PSA_ATTN_TILE;
+  constexpr int BN = NW == 4 ? 64 : 32;
   return blocks_cover_a_load ? launch_mfma_t<D, NW, true, BN>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s)
                              : launch_mfma_t<D, NW, false, BN>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s);
 }

@@ -1,0 +1,39 @@
+"""32- and 64-row query blocks (tiles of 32 key columns) where tiles and levels end, against the oracle.
+
+Tolerance: the bfloat16 bar of the parity tests (P rounded to 8 bits, the result once more)."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+from oracle import psa_oracle as orc
+from tests.psa_testlib import Buffers, from_dev, gpu_params, rel_l2, to_dev
+
+pytestmark = pytest.mark.gpu
+
+psa = pytest.importorskip("paper_2512_04025_amd")
+
+
+@pytest.mark.parametrize("bq", [32, 64])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("N,bk,levels,causal", [(33, 32, 3, False), (96, 32, 1, True), (511, 64, 4, False), (700, 16, 5, True), (650, 128, 5, False)])
+def test_attention_small_query_blocks(bq, d, N, bk, levels, causal):
+    import torch
+    op = orc.Params(B=1, Hq=2, Hkv=1, N=N, d=d, bq=bq, bk=bk, levels=levels, dtype="bf16", causal=causal, sq=8, sk=8)
+    gp = gpu_params(op)
+    host = si.random_qkv(N + bk, 1, 2, 1, N, d, "bf16")
+    rng = np.random.default_rng(N)
+    vis = orc.block_visibility(op)
+    M = rng.integers(0, levels + 1, size=(1, 2, op.nq, op.nk))
+    M[..., 0] = 1
+    M = np.where(vis[None, None] == 0, 0, np.where(vis[None, None] == 2, 1, M)).astype(np.uint8)
+    Qd, Kd, Vd = (to_dev(x, "bf16") for x in host)
+    Q64, K64, V64 = (si.to_f64(x, "bf16") for x in host)
+    buf = Buffers(gp)
+    psa.psa_build_pyramid(gp, Kd, Vd, buf.Kpyr, buf.Vpyr)
+    buf.O.fill_(float("nan"))
+    psa.psa_attention_fwd(gp, Qd, Kd, Vd, buf.Kpyr, buf.Vpyr, torch.from_numpy(M).cuda(), buf.O, buf.scratch, lse=buf.lse)
+    torch.cuda.synchronize()
+    O, lse = orc.psa_attention(Q64, orc.build_pyramid(K64, op), orc.build_pyramid(V64, op), M, op)
+    got = from_dev(buf.O, "bf16")
+    assert np.abs(got - O).max() <= 2e-2 and rel_l2(got, O) <= 1e-2
+    assert np.abs(buf.lse.cpu().numpy() - lse).max() <= 2e-2
