@@ -148,7 +148,7 @@ __global__ __launch_bounds__(256) void importance_kernel(const T* __restrict__ Q
       for (int r = 0; r < IMP_ROWS; ++r) acc[r] = 0.f;
       if (kpos >= 0) {
         const T* kp = kbase + (int64_t)c * D;
-#pragma unroll 4
+#pragma unroll 16
         for (int ch = 0; ch < D / VEC; ++ch) {
           float kv[VEC];
           Elem<T>::load(kp + ch * VEC, kv);
@@ -158,20 +158,29 @@ __global__ __launch_bounds__(256) void importance_kernel(const T* __restrict__ Q
             for (int e = 0; e < VEC; ++e) acc[r] = fmaf(qs[r * D + ch * VEC + e], kv[e], acc[r]);
         }
       }
+      // The rows side by side, so that a step waits once for the lane exchanges of all of them: latency decides here (32
+      // workgroups for 2 heads x 1024 tokens: row by row 20 us, so 18.5; whole float32 forwards 1-4 % faster).
+      float gmax[IMP_ROWS], e[IMP_ROWS];
 #pragma unroll
       for (int r = 0; r < IMP_ROWS; ++r) {
-        float logit = acc[r] * a.scale;
         const bool dead = kpos < 0 || qpos[r] < 0 || (a.causal && kpos > qpos[r]);
-        if (dead) logit = -INFINITY;
-        float gmax = logit;
-        for (int off = 1; off < a.sk; off <<= 1) gmax = fmaxf(gmax, __shfl_xor(gmax, off, 64));
-        float e = gmax == -INFINITY ? 0.f : expf(logit - gmax);
-        for (int off = 1; off < a.sk; off <<= 1) e += __shfl_xor(e, off, 64);
-        if (r < nr && c < nkeys && (c % a.sk) == 0) {
-          bmax[(size_t)(r0 + r) * a.nk + j] = gmax;
-          bsum[(size_t)(r0 + r) * a.nk + j] = e;
-        }
+        acc[r] = dead ? -INFINITY : acc[r] * a.scale;
+        gmax[r] = acc[r];
       }
+      for (int off = 1; off < a.sk; off <<= 1)
+#pragma unroll
+        for (int r = 0; r < IMP_ROWS; ++r) gmax[r] = fmaxf(gmax[r], __shfl_xor(gmax[r], off, 64));
+#pragma unroll
+      for (int r = 0; r < IMP_ROWS; ++r) e[r] = gmax[r] == -INFINITY ? 0.f : expf(acc[r] - gmax[r]);
+      for (int off = 1; off < a.sk; off <<= 1)
+#pragma unroll
+        for (int r = 0; r < IMP_ROWS; ++r) e[r] += __shfl_xor(e[r], off, 64);
+#pragma unroll
+      for (int r = 0; r < IMP_ROWS; ++r)
+        if (r < nr && c < nkeys && (c % a.sk) == 0) {
+          bmax[(size_t)(r0 + r) * a.nk + j] = gmax[r];
+          bsum[(size_t)(r0 + r) * a.nk + j] = e[r];
+        }
     }
   }
   __syncthreads();
