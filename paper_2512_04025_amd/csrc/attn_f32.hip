@@ -314,9 +314,9 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int k = 0; k < KS; ++k) {
-      const float mk = ms[k * ROWS + r];
-      const float w = KS == 1 ? 1.f : expf(mk - (mm == -INFINITY ? 0.f : mm));
-      if (KS > 1 && mk == -INFINITY) continue;            // this team saw no key of the row
+      // A team that saw no key of the row adds 0 * 0.  None is left out for a maximum of -inf alone: fmaxf drops NaN, so
+      // a team all of whose scores are NaN has that maximum too, with a sum and outputs that are NaN and have to stay.
+      const float w = KS == 1 ? 1.f : expf(ms[k * ROWS + r] - (mm == -INFINITY ? 0.f : mm));
       ll += w * ms[KS * ROWS + k * ROWS + r];
       acc += w * *reinterpret_cast<const f32x4*>(os + (k * ROWS + r) * KPITCH + c);
     }

@@ -111,3 +111,32 @@ def test_values_hidden_by_the_causal_mask_may_be_infinite(N, Hq, bq):
         outs.append(from_dev(buf.O, "f32"))
     assert np.abs(outs[1][:, :, :-1] - outs[0][:, :, :-1]).max() <= 1e-5
     assert np.all(np.isinf(outs[1][:, :, -1]) | np.isnan(outs[1][:, :, -1]))
+
+
+@pytest.mark.parametrize("N,Hq,bq", [(97, 2, 64), (993, 12, 64), (993, 32, 128)])
+def test_a_key_that_is_not_a_number_reaches_every_row_that_keeps_it(N, Hq, bq):
+    """The last token's key is NaN, alone in the last key block and in the last tile of a row's list, at sizes that
+    deal out the wavefronts in teams of one, two and four: rows that keep the block are NaN, the others untouched."""
+    import torch
+    op = orc.Params(B=1, Hq=Hq, Hkv=1, N=N, d=64, bq=bq, bk=32, levels=1, dtype="f32", sq=8, sk=1)
+    gp = gpu_params(op)
+    Qd, Kd, Vd = (to_dev(x, "f32") for x in si.random_qkv(4, 1, Hq, 1, N, 64, "f32"))
+    M = np.zeros((1, Hq, op.nq, op.nk), np.uint8)
+    M[..., 0] = 1
+    M[:, :, ::2, -1] = 1
+    keeps = np.repeat(np.arange(op.nq) % 2 == 0, bq)[:N]
+    outs = []
+    for key in (None, float("nan")):
+        K = Kd.clone()
+        if key is not None:
+            K[:, :, -1] = key
+        buf = Buffers(gp)
+        psa.psa_attention_fwd(gp, Qd, K, Vd, None, None, torch.from_numpy(M).cuda(), buf.O, buf.scratch, lse=buf.lse)
+        torch.cuda.synchronize()
+        outs.append((from_dev(buf.O, "f32"), buf.lse.cpu().numpy()))
+    for clean, bad in zip(*outs):
+        assert np.all(np.isnan(bad[:, :, keeps]))
+        assert np.array_equal(bad[:, :, ~keeps], clean[:, :, ~keeps])
+    psa.psa_dense_ref(gp, Qd, K, Vd, buf.O, lse=buf.lse)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(buf.O).all()) and bool(torch.isnan(buf.lse).all())
