@@ -16,7 +16,8 @@
  *     `stream` (a hipStream_t passed as void*; NULL = the default stream) and the call returns.
  *   - Tensors are contiguous, row-major:  Q, O: [B, Hq, N, d];  K, V: [B, Hkv, N, d].
  *     Query head hq reads key/value head hq / (Hq / Hkv).  Element type is psa_params.dtype
- *     (bfloat16 or float32) for Q, K, V, the pyramids and O.
+ *     (bfloat16 or float32) for Q, K, V, the pyramids and O.  They need no more than the alignment of an
+ *     element: the same kernels run, with the same results, at any such address.
  *   - Blocks (Sec. 3.1): nq = ceil(N / bq) query blocks, nk = ceil(N / bk) key blocks; the last block
  *     of either kind may be short (the paper assumes divisibility; see psa_build_pyramid).
  *   - Levels follow Eq. 5:  M = 0 skip,  M = h in 1..H use level h (pooled by 2^(h-1)).

@@ -617,9 +617,7 @@ hipError_t launch_attn_bwd(const Plan& pl, const void* Q, const void* K, const v
   if (pl.dtype == PSA_F32)
     return pl.d == 64 ? launch_bwd_t<float, 64>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, dO, Dr, dKp, dVp, dQ, dK, dV, false, s)
                       : launch_bwd_t<float, 128>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, dO, Dr, dKp, dVp, dQ, dK, dV, false, s);
-  // (direct-to-LDS loads of Q and dO: rows of 16-byte chunks at aligned addresses)
-  const bool aligned = ((reinterpret_cast<uintptr_t>(Q) | reinterpret_cast<uintptr_t>(dO)) & 15) == 0;
-  const bool mfma = !vector_unit && aligned && bwd_uses_mfma(pl);
+  const bool mfma = !vector_unit && bwd_uses_mfma(pl);
   return pl.d == 64 ? launch_bwd_t<bf16_t, 64>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, dO, Dr, dKp, dVp, dQ, dK, dV, mfma, s)
                     : launch_bwd_t<bf16_t, 128>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, dO, Dr, dKp, dVp, dQ, dK, dV, mfma, s);
 }

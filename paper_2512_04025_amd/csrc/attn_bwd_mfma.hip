@@ -629,10 +629,11 @@ __global__ __launch_bounds__((DkvShape<D, KH>::NT), 2) void bwd_dkv_mfma_kernel(
   }
 }
 
+// (32-bit byte offsets reach every row of a head: at most 65535 key blocks of 128 keys of 256 bytes are less than 2^31.
+// Addresses need no more than element alignment, in the direct-to-LDS loads as in all others.)
 bool bwd_uses_mfma(const Plan& pl) {
   return pl.dtype == PSA_BF16 && pl.bk >= 8 && pl.bk <= 128 && (pl.d == 64 || pl.d == 128) &&
-         pl.nq <= 8192 &&                          // a query block's number and its 16 block bits share a list entry
-         (int64_t)pl.N * pl.d * 2 < 0x7fffffff;    // a head's rows are addressed with 32-bit byte offsets
+         pl.nq <= 8192;                            // a query block's number and its 16 block bits share a list entry
 }
 
 // levels h_lo .. h_hi in one launch (they share KH)
