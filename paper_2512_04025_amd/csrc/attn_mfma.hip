@@ -71,16 +71,18 @@ struct LevelState {
 
 // D: head dimension; NW: wavefronts per workgroup (each owns 32 query rows); SC: every level's pooled
 // block holds at least as many rows as one load instruction covers
-// BN: key columns per tile: 64 for workgroups of four wavefronts, 32 for those of one or two, whose tiles serve fewer
-// rows, so that LDS holds four of them per compute unit at d = 128 (eight at d = 64) instead of two (four).
-// Wavefronts per SIMD: as many as LDS lets in, and NOT more registers free than that: with room for more, the
-// one- and two-wavefront workgroups of a compute unit were put on few of its four SIMDs.  Measured, 12 heads x 32760
+// BN: key columns per tile, 64 or 32 (see launch_mfma_d).
+// Wavefronts per SIMD: with tiles of 64 as many as the registers of the loop allow.  Workgroups of one or two wavefronts
+// with tiles of 32: NOT more registers free than for one or two (d = 64: two or three) wavefronts per SIMD, since with
+// room for more the workgroups of a compute unit were put on few of its four SIMDs.  (LDS would take four per SIMD at
+// d = 64 and two wavefronts a workgroup; three is what was measured.)  Measured, 12 heads x 32760
 // tokens (pyramid included), tiles of 64 and two wavefronts per SIMD allowed -> tiles of 32, no tight limit -> this:
 // 32-row blocks d = 128 4104 -> 3915 -> 2360 us, d = 64 1752 -> 1685 -> 1180; 64-row blocks d = 128 2142 -> 1777 -> 1765,
 // d = 64 1160 -> 1118 -> 1040.
-constexpr int waves_per_simd(int d, int nw) { return nw == 4 ? (d == 64 ? 3 : 2) : (d == 64 ? nw + 1 : nw); }
+constexpr int most_waves(int d, int nw, int bn) { return bn == 64 ? (d == 64 ? 3 : 2) : (d == 64 ? nw + 1 : nw); }
+constexpr int least_waves(int d, int nw, int bn) { return bn == 64 ? 2 : most_waves(d, nw, bn); }
 template <int D, int NW, bool SC, int BN>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((NW == 4 ? 2 : waves_per_simd(D, NW)), waves_per_simd(D, NW))))
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((least_waves(D, NW, BN)), most_waves(D, NW, BN))))
 void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
                       const bf16_t* __restrict__ Kp, const bf16_t* __restrict__ Vp,
                       const uint16_t* __restrict__ idx, const int32_t* __restrict__ cnt,
@@ -103,7 +105,7 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   // Full-size workgroups on shapes whose load instructions never straddle a pooled block read their
   // load plan from per-tile descriptors made by lists_kernel instead of deriving it per tile.
   constexpr bool DESC = SC && NW == 4;
-  static_assert(BN == (NW == 4 ? 64 : 32), "tile width");
+  static_assert(BN == 64 || (BN == 32 && NW < 4), "tile width");
   static_assert(NINST % NW == 0, "tile rows must split evenly over the wavefronts");
   static_assert(MPC * NB == NPAIR, "chunking of the softmax work");
   // LDS map: K[2] | V[2] | per-wavefront table for irregular tiles | block list
@@ -818,9 +820,25 @@ static hipError_t launch_mfma_d(const Plan& pl, const void* Q, const void* K, co
   constexpr int RPI = 64 / (D / 8);           // tile rows per wave-wide 16 B/lane load
   // (the scalar-plan variant of full workgroups reads tile descriptors; without them take the general one)
   const bool blocks_cover_a_load = (pl.bk >> (pl.H - 1)) >= RPI && (NW != 4 || pl.desc_pitch > 0);
-  constexpr int BN = NW == 4 ? 64 : 32;
-  return blocks_cover_a_load ? launch_mfma_t<D, NW, true, BN>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s)
-                             : launch_mfma_t<D, NW, false, BN>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s);
+  // Key columns per tile.  64 for workgroups of four wavefronts.  The tiles of smaller workgroups serve fewer rows, and of 32
+  // columns twice as many workgroups fit the LDS of a compute unit (d = 128: four instead of two; d = 64: eight instead of four):
+  // what counts once the chip is full.  While all workgroups are resident at once either way, twice the tiles are only twice
+  // the steps of each, and longer rows take 64 columns too (short ones have few tiles, most of them partly empty).
+  // Attention alone, one head, a fifth of the keys, us for 64 / 32 columns, d = 64 and d = 128: 64-row blocks x 3000 tokens 19.1 / 20.0
+  // and 23.2 / 23.7, x 8000 31.8 / 38.1 and 41.7 / 46.6, x 15000 55.6 / 65.6 and 72.4 / 79.7; 32-row blocks x 3000 21.9 / 21.3 and 30.3 / 28.3,
+  // x 8000 35.4 / 39.2 and 51.2 / 54.9; more workgroups than fit (three tenths of the keys): d = 64, 12 heads x 6000 tokens in 64-row
+  // blocks 85 / 70, in 32-row blocks 128 / 95, d = 128 144 / 125 and 277 / 185.  Not with blocks of less than a load at d = 128
+  // in one wavefront, whose load plans of 64 rows do not fit its registers (x 8000 119 / 61).
+  constexpr bool WIDE = NW == 4 || !(D == 128 && NW == 1);
+  const int64_t wgs = (int64_t)pl.B * pl.Hq * pl.nq * ((pl.bq + NW * 32 - 1) / (NW * 32));
+  const int64_t resident = 256 * (int64_t)(LDS_LIMIT / attn_mfma_smem_bytes(D, pl.nk, 64));
+  const bool wide = NW == 4 || (wgs <= resident && pl.N >= (NW == 2 ? 4096 : 6144));
+  constexpr int NARROW = NW == 4 ? 64 : 32;
+  if (blocks_cover_a_load)
+    return wide ? launch_mfma_t<D, NW, true, 64>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s)
+                : launch_mfma_t<D, NW, true, NARROW>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s);
+  return wide && WIDE ? launch_mfma_t<D, NW, false, WIDE ? 64 : NARROW>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s)
+                      : launch_mfma_t<D, NW, false, NARROW>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s);
 }
 
 hipError_t launch_attn_mfma(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp,

@@ -37,3 +37,34 @@ def test_attention_small_query_blocks(bq, d, N, bk, levels, causal):
     got = from_dev(buf.O, "bf16")
     assert np.abs(got - O).max() <= 2e-2 and rel_l2(got, O) <= 1e-2
     assert np.abs(buf.lse.cpu().numpy() - lse).max() <= 2e-2
+
+
+@pytest.mark.parametrize("bq,N", [(64, 4096), (64, 5003), (32, 6144), (32, 6205)])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("bk,levels,causal", [(64, 3, False), (16, 5, True)])
+def test_attention_small_query_blocks_on_an_idle_chip(bq, N, d, bk, levels, causal):
+    """Long rows and fewer workgroups than fit at once: tiles of 64 key columns (the first, a middle and the last query
+    block against the oracle)."""
+    import torch
+    op = orc.Params(B=1, Hq=1, Hkv=1, N=N, d=d, bq=bq, bk=bk, levels=levels, dtype="bf16", causal=causal, sq=8, sk=1)
+    gp = gpu_params(op)
+    host = si.random_qkv(N + bk, 1, 1, 1, N, d, "bf16")
+    rng = np.random.default_rng(N)
+    vis = orc.block_visibility(op)
+    M = rng.integers(1, levels + 1, size=(1, 1, op.nq, op.nk)) * (rng.random((1, 1, op.nq, op.nk)) < 0.25)
+    M[..., 0] = 1
+    M = np.where(vis[None, None] == 0, 0, np.where(vis[None, None] == 2, 1, M)).astype(np.uint8)
+    Qd, Kd, Vd = (to_dev(x, "bf16") for x in host)
+    Q64, K64, V64 = (si.to_f64(x, "bf16") for x in host)
+    buf = Buffers(gp)
+    psa.psa_build_pyramid(gp, Kd, Vd, buf.Kpyr, buf.Vpyr)
+    buf.O.fill_(float("nan"))
+    psa.psa_attention_fwd(gp, Qd, Kd, Vd, buf.Kpyr, buf.Vpyr, torch.from_numpy(M).cuda(), buf.O, buf.scratch, lse=buf.lse)
+    torch.cuda.synchronize()
+    blocks = [0, op.nq // 2, op.nq - 1]
+    O, lse = orc.psa_attention(Q64, orc.build_pyramid(K64, op), orc.build_pyramid(V64, op), M, op, q_blocks=blocks)
+    rows = np.concatenate([np.arange(i * bq, min((i + 1) * bq, N)) for i in blocks])
+    got = from_dev(buf.O, "bf16")
+    assert not np.isnan(got).any()
+    assert np.abs(got - O)[:, :, rows].max() <= 2e-2 and rel_l2(got[:, :, rows], O[:, :, rows]) <= 1e-2
+    assert np.abs(buf.lse.cpu().numpy() - lse)[:, :, rows].max() <= 2e-2
