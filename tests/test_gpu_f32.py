@@ -67,6 +67,11 @@ def test_attention_and_dense_at_the_edges(shape):
 BWD_SHAPES = [s for s in SHAPES if s[0] == "f32" and s[7] <= 128] + [
     ("f32", 1, 4, 2, 2070, 64, 8, 8, 4, True),            # more column entries than are tested at a time; blocks of one pooled key
     ("bf16", 1, 2, 2, 300, 128, 64, 4, 3, False),         # key blocks smaller than the bfloat16 kernels take
+    ("f32", 1, 32, 8, 1023, 64, 128, 64, 4, False),       # the remaining teams of the dQ kernel: d = 64 in teams of four,
+    ("bf16", 1, 12, 6, 1000, 64, 64, 4, 3, True),         # bfloat16 in teams of two ...
+    ("bf16", 1, 12, 6, 1000, 128, 64, 4, 2, False),
+    ("bf16", 1, 32, 4, 1000, 64, 128, 4, 2, False),       # ... and of four
+    ("bf16", 1, 32, 4, 1000, 128, 128, 4, 3, True),
 ]
 
 

@@ -379,6 +379,38 @@ def test_attention_wide_rows_sparse_masks(nk):
     _attention_case(f"wide_{nk}", {}, mask=M)
 
 
+@pytest.mark.parametrize("nk,d,bk,levels", [(4200, 128, 32, 3), (33000, 64, 8, 1)])
+def test_attention_rows_beyond_the_register_lists(nk, d, bk, levels):
+    """Rows of more than 4096 key blocks in full 128-row workgroups: list and tile descriptors made by one wavefront per
+    row from LDS (33000: more of it than a kernel gets without asking), handed to the attention kernel."""
+    import torch
+    N = nk * bk - 3
+    op = orc.Params(B=1, Hq=1, Hkv=1, N=N, d=d, bq=128, bk=bk, levels=levels, dtype="bf16", sq=8, sk=1)
+    gp = gpu_params(op)
+    host = si.random_qkv(nk, 1, 1, 1, N, d, "bf16")
+    rng = np.random.default_rng(nk)
+    M = np.zeros((1, 1, op.nq, nk), dtype=np.uint8)
+    cols = rng.integers(0, nk, size=(op.nq, 9))
+    M[0, 0, np.arange(op.nq)[:, None], cols] = rng.integers(1, levels + 1, size=cols.shape)
+    M[..., 0] = 1
+    M[0, 0, 1] = 0
+    M[0, 0, 1, nk - 1] = levels                                       # only the last, partial block, coarsest level
+    Qd, Kd, Vd = (to_dev(x, "bf16") for x in host)
+    buf = Buffers(gp)
+    psa.psa_build_pyramid(gp, Kd, Vd, buf.Kpyr, buf.Vpyr)
+    buf.O.fill_(float("nan"))
+    psa.psa_attention_fwd(gp, Qd, Kd, Vd, buf.Kpyr, buf.Vpyr, torch.from_numpy(M).cuda(), buf.O, buf.scratch, lse=buf.lse)
+    torch.cuda.synchronize()
+    Q64, K64, V64 = (si.to_f64(x, "bf16") for x in host)
+    blocks = [0, 1, 2, op.nq // 2, op.nq - 2, op.nq - 1]
+    O, lse = orc.psa_attention(Q64, orc.build_pyramid(K64, op), orc.build_pyramid(V64, op), M, op, q_blocks=blocks)
+    rows = np.concatenate([np.arange(i * 128, min((i + 1) * 128, N)) for i in blocks])
+    got = from_dev(buf.O, "bf16")
+    assert not np.isnan(got).any()
+    assert np.abs(got - O)[:, :, rows].max() <= 2e-2 and rel_l2(got[:, :, rows], O[:, :, rows]) <= 1e-2
+    assert np.abs(buf.lse.cpu().numpy() - lse)[:, :, rows].max() <= 2e-2
+
+
 def test_all_level1_mask_equals_dense_ref():
     """M == 1 reproduces dense attention: PSA kernel vs the independent dense kernel vs the oracle."""
     import torch
