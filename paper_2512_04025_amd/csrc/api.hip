@@ -329,7 +329,7 @@ int psa_attention_bwd(const psa_params* p, const void* Q, const void* K, const v
   if (!Q || !K || !V || !M || !O || !lse || !dO || !dQ || !dK || !dV || !scratch) return PSA_EINVAL;
   if (pl.H > 1 && (!Kpyr || !Vpyr)) return PSA_EINVAL;
   if (reinterpret_cast<uintptr_t>(scratch) & 255) return PSA_EINVAL;
-  if (pl.bk > 128) return PSA_EUNSUPPORTED;      // four lanes per pooled key of a block in one workgroup
+  if (pl.bk > 128) return PSA_EUNSUPPORTED;      // the interface ends here; no kernel has been run beyond it
   const BwdLayout l = bwd_layout(pl);
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint16_t* idx = reinterpret_cast<uint16_t*>(at(scratch, l.off_idx));
@@ -338,7 +338,7 @@ int psa_attention_bwd(const psa_params* p, const void* Q, const void* K, const v
   const hipError_t e = launch_attn_bwd(pl, Q, K, V, Kpyr, Vpyr, M, idx, cnt, O, lse, dO,
                                        reinterpret_cast<float*>(at(scratch, l.off_D)),
                                        reinterpret_cast<float*>(at(scratch, l.off_dkp)),
-                                       reinterpret_cast<float*>(at(scratch, l.off_dvp)), dQ, dK, dV, false, s);
+                                       reinterpret_cast<float*>(at(scratch, l.off_dvp)), dQ, dK, dV, s);
   return e == hipSuccess ? PSA_OK : PSA_ELAUNCH;
 }
 

@@ -14,7 +14,8 @@
 //   unpool_kernel   dK, dV = sum over the levels of the pooled gradients / c_g
 // The products run on v_mfma_f32_32x32x2_f32 and are bound by its rate (64 FLOP per cycle and SIMD); the
 // operands of a 32 x 32 tile are read from LDS in an eighth of that time, so tiles are staged through registers
-// during the products and one wavefront per SIMD (up to 512 registers at d = 128) keeps the pipe busy.
+// during the products and one wavefront per SIMD (up to 512 registers at d = 128) keeps the pipe busy.  At d = 64, with two
+// wavefronts per SIMD, bwd_dkv_kernel spills 25 registers in float32 and 8 in bfloat16.
 // Measured against four lanes per row on the vector unit, which this replaces (2 heads x 1000 tokens, d = 64,
 // four levels): dK, dV 641 -> 45 us (four launches -> one), dQ 78 -> 16 us, the whole call 735 -> 62 us.
 #include "psa_dev.h"
@@ -582,7 +583,9 @@ static hipError_t launch_bwd_t(const Plan& pl, const void* Q, const void* K, con
     e = launch_attn_bwd_mfma(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, dO, Dr, dKp, dVp, dQ, s);
     if (e != hipSuccess) return e;
   } else {
-    // rows per workgroup: the largest that still fills the chip (see launch_f32_d)
+    // Rows per workgroup: the forward's rule (launch_f32_d), within 8 % of the best of the three at every size measured.  Whole call, 12 heads (128-row blocks of the problem: us for team 1 / 2 / 4), d = 64: 48: 55 / 59 / 63, 96: 110 / 99 / 108,
+    // 192: 248 / 239 / 244, 252: 378 / 345 / 352, 288: 504 / 481 / 495, 432: 912 / 845 / 837, 564: 1478 / 1349 / 1413 (the rule takes 4);
+    // d = 128: 48: 73 / 80 / 88, 96: 157 / 137 / 151, 144: 316 / 307 / 285, 192: 391 / 393 / 378, 252: 623 / 586 / 568, 288: 816 / 808 / 845, 432: 1601 / 1574 / 1525.
     const int64_t blocks = (int64_t)pl.B * pl.Hq * pl.nq;
     auto groups = [&](int rows_wg) { return blocks * ((pl.bq + rows_wg - 1) / rows_wg); };
     const int team = pl.bq > 64 && groups(128) >= 256 ? 4 : (pl.bq > 32 && groups(64) >= 192 ? 2 : 1);
@@ -612,12 +615,11 @@ static hipError_t launch_bwd_t(const Plan& pl, const void* Q, const void* K, con
 
 hipError_t launch_attn_bwd(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp, const void* Vp,
                            const uint8_t* M, const uint16_t* idx, const int32_t* cnt, const void* O, const float* lse,
-                           const void* dO, float* Dr, float* dKp, float* dVp, void* dQ, void* dK, void* dV, bool vector_unit,
-                           hipStream_t s) {
+                           const void* dO, float* Dr, float* dKp, float* dVp, void* dQ, void* dK, void* dV, hipStream_t s) {
   if (pl.dtype == PSA_F32)
     return pl.d == 64 ? launch_bwd_t<float, 64>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, dO, Dr, dKp, dVp, dQ, dK, dV, false, s)
                       : launch_bwd_t<float, 128>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, dO, Dr, dKp, dVp, dQ, dK, dV, false, s);
-  const bool mfma = !vector_unit && bwd_uses_mfma(pl);
+  const bool mfma = bwd_uses_mfma(pl);
   return pl.d == 64 ? launch_bwd_t<bf16_t, 64>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, dO, Dr, dKp, dVp, dQ, dK, dV, mfma, s)
                     : launch_bwd_t<bf16_t, 128>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, dO, Dr, dKp, dVp, dQ, dK, dV, mfma, s);
 }

@@ -697,7 +697,7 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
     int h_hi = h;
     while (h_hi < pl.H && tiles_of(h_hi + 1) == tiles_of(h)) ++h_hi;
     const int kh = tiles_of(h);
-    if (kh == 4) e = launch_dkv_t<D, 4>(pl, a, q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h, h_hi, s);
+    if (D == 128 && kh == 4) e = launch_dkv_t<D, D == 128 ? 4 : 2>(pl, a, q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h, h_hi, s);
     else if (kh == 2) e = launch_dkv_t<D, 2>(pl, a, q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h, h_hi, s);
     else e = launch_dkv_t<D, 1>(pl, a, q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h, h_hi, s);
     if (e != hipSuccess) return e;

@@ -4,7 +4,8 @@
 //
 // Bound: the fp32 matrix rate (64 FLOP per cycle and SIMD, 151 TFLOP/s measured on a large product).  A
 // 32 x 32 x D tile keeps a wavefront's matrix pipe busy for 64 D cycles and needs 1 / 8 of that in LDS reads,
-// so little has to be scheduled by hand: the V rows of a tile travel through registers into LDS during its
+// so little has to be scheduled by hand (some registers spill all the same at d = 128 with two wavefronts per SIMD:
+// teams of two 55 in float32 and 21 in bfloat16, teams of four 18 in float32): the V rows of a tile travel through registers into LDS during its
 // first product, the K rows of the next one during its second, and each product is followed by one barrier.
 //
 // Operand roles as in the bfloat16 kernel: S^T = K Q^T puts one query row in each lane (lane l and l + 32 share
@@ -352,8 +353,11 @@ static hipError_t launch_f32_d(const Plan& pl, const void* Q, const void* K, con
                                const uint16_t* idx, const int32_t* cnt, void* O, float* lse, hipStream_t s) {
   // The largest team that still fills the chip: fewer rows per team cost more reads of the same keys, fewer
   // workgroups leave compute units idle.  Measured with 12 heads at d = 128 (128-row blocks of the problem: us for
-  // team 1 / 2 / 4): 48: 27 / 34 / 38, 96: 63 / 48 / 56, 192: 127 / 108 / 107, 288: 292 / 247 / 235, 432: 540 / 412 / 342;
-  // d = 64: 48: 20 / 23 / 28, 96: 31 / 31 / 38, 192: 67 / 64 / 74, 288: 134 / 139 / 147, 432: 242 / 226 / 209.
+  // team 1 / 2 / 4, pyramid included): 48: 26 / 33 / 37, 96: 62 / 47 / 55, 192: 121 / 105 / 106, 252: 194 / 137 / 136,
+  // 288: 285 / 247 / 236, 432: 535 / 409 / 343, 564: 931 / 699 / 679; d = 64: 48: 20 / 23 / 27, 96: 30 / 30 / 37, 192: 65 / 62 / 72,
+  // 252: 87 / 77 / 92, 288: 126 / 135 / 147, 348: 164 / 166 / 167, 432: 226 / 220 / 210, 564: 372 / 369 / 418.  One line for both
+  // head dimensions: it is drawn for d = 128; at d = 64 a team of four is the slowest just behind the line (288) and again
+  // where the last round of workgroups is nearly empty (564), by 16 and 13 %.
   const int64_t blocks = (int64_t)pl.B * pl.Hq * pl.nq;
   auto groups = [&](int rows) { return blocks * ((pl.bq + rows - 1) / rows); };
   const int team = pl.bq > 64 && groups(128) >= 256 ? 4 : (pl.bq > 32 && groups(64) >= 192 ? 2 : 1);

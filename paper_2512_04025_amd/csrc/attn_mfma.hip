@@ -2,12 +2,13 @@
 //
 // Decoupled block/tile design in the spirit of Sec. 3.5, laid out for CDNA4: the kept key blocks of
 // a query block arrive grouped by pyramid level; inside a level the pooled tokens of consecutive
-// list entries are concatenated and cut into fixed tiles of 64 key columns (a level-h block of
+// list entries are concatenated and cut into fixed tiles of 64 key columns (32 for most problems with query
+// blocks of 32 or 64 rows, see launch_mfma_d; a level-h block of
 // b_k/2^(h-1) tokens is split over several tiles or merged with its neighbours), so every tile but
 // the last of a level feeds full 32x32x16 MFMAs and the (h-1) ln 2 bias is one constant per tile.
 //
-// One workgroup = one slice of up to 128 query rows, one wavefront per 32 rows, two workgroups per
-// compute unit (two wavefronts per SIMD, ~256 registers each).  Per tile:
+// One workgroup = one slice of up to 128 query rows, one wavefront per 32 rows; 128-row workgroups run two
+// (d = 64: three) to a compute unit, as many wavefronts per SIMD, ~256 (~168) registers each.  Per tile:
 //   K/V rows go HBM/L2 -> LDS directly (buffer_load ... lds, 16 B per lane; the descriptor's range
 //   check drops rows past the end of the unpadded level-1 arrays), two buffers each; a tile's K rows
 //   are requested one and a half steps before its first product, its V rows one and a half steps
@@ -448,7 +449,7 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   for (int ks = 0; ks < D / 16; ++ks) kaddr[ks] = kaddr0 ^ (uint32_t)(ks << 5);
   auto read_k_asm = [&](bf16x8& dst, int j, int flip) __attribute__((always_inline)) {
     const int mb = j % HALVES, ks = j / HALVES;
-    if (BN == 32) {   // (tiles of 32 came with three wavefronts per SIMD: no room for one address register per k-step)
+    if (BN == 32) {   // the address of a k-step made when it is needed, instead of D / 16 of them held
       uint32_t ad;
       asm volatile("v_xor_b32 %0, %1, %2" : "=v"(ad) : "n"(ks << 5), "v"(kaddr0));
       asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(ad), "n"(flip + mb * 32 * ROWB));

@@ -681,10 +681,13 @@ static hipError_t launch_imp_tiles_t(const Plan& pl, const void* Qrep, const voi
   const int ntile_all = (pl.nk * 8 + 63) / 64;
   // Key slices: the workgroups run in rounds of `slots` (what fits on the chip at once); pick the
   // slice count with the least rounds x work-per-workgroup, preferring fewer slices on a tie, among those whose
-  // slices have at most 24 tiles: the more workgroups share a head's keys, the fewer heads are in flight and the
-  // more of their keys the L2 holds.  Measured for the whole allocation call, one slice / the rule / eight slices:
-  // 40 heads x 148 tiles 1882 / 1427 / 1424 us, 12 heads x 128 tiles 951 / 724 / 729, causal 28 heads x 64 tiles 225 / 210 / 214,
-  // 32 heads x 128 tiles at d = 64 1254 / 1145 / 1148 (two slices: 1145).
+  // slices have at most 24 tiles (beyond 192 tiles: all eight slices): the more workgroups share a head's keys, the fewer
+  // heads are in flight and the more of their keys the L2 holds; causal, short slices also even out rows of different
+  // length.  Measured for the whole allocation call, us for one slice / what rounds alone would pick / the rule / eight
+  // slices, d = 128: 40 heads x 148 tiles 1807 / 1807 (one) / 1375 (seven) / 1368, 12 heads x 128 tiles 933 / 933 (one) / 685 (six) / 680,
+  // causal 28 heads x 64 tiles 225 / 210 (five) / 210 (five) / 214.  d = 64, where a tile is half the bytes: 40 heads x 148 tiles
+  // 1554 / 1554 (one) / 1116 (seven) / 1113, 8 heads x 148 tiles 803 / 330 (five) / 308 (seven) / 298, causal 8 heads x 118 tiles 586 / 263 (three) /
+  // 189 (six) / 173; 32 heads x 128 tiles 1245 / 1122 (three) / 1102 (six) / 1114, there no more than the runs differ.
   const int smem = 4 * 64 * D * 2 + 16 * 8 * 16 * (int)sizeof(float);   // sweep 2: ring of 4 tiles + staged scores
   const int smem1 = 3 * 64 * D * 2;                                      // sweep 1: ring of 3 tiles
   const int per_cu = 160 * 1024 / smem1 < 3 ? 160 * 1024 / smem1 : 3;
