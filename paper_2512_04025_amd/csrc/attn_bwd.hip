@@ -583,9 +583,11 @@ static hipError_t launch_bwd_t(const Plan& pl, const void* Q, const void* K, con
     e = launch_attn_bwd_mfma(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, dO, Dr, dKp, dVp, dQ, s);
     if (e != hipSuccess) return e;
   } else {
-    // Rows per workgroup: the forward's rule (launch_f32_d), within 8 % of the best of the three at every size measured.  Whole call, 12 heads (128-row blocks of the problem: us for team 1 / 2 / 4), d = 64: 48: 55 / 59 / 63, 96: 110 / 99 / 108,
-    // 192: 248 / 239 / 244, 252: 378 / 345 / 352, 288: 504 / 481 / 495, 432: 912 / 845 / 837, 564: 1478 / 1349 / 1413 (the rule takes 4);
-    // d = 128: 48: 73 / 80 / 88, 96: 157 / 137 / 151, 144: 316 / 307 / 285, 192: 391 / 393 / 378, 252: 623 / 586 / 568, 288: 816 / 808 / 845, 432: 1601 / 1574 / 1525.
+    // Rows per workgroup: the forward's rule (launch_f32_d), within 8 % of the best of the three at every size measured.
+    // Whole call, 12 heads (128-row blocks of the problem: us for team 1 / 2 / 4), d = 64: 48: 55 / 59 / 63, 96: 110 / 99 / 108,
+    // 192: 248 / 239 / 244, 252: 378 / 345 / 352, 288: 504 / 481 / 495, 432: 912 / 845 / 837, 564: 1478 / 1349 / 1413 (the rule
+    // takes 4); d = 128: 48: 73 / 80 / 88, 96: 157 / 137 / 151, 144: 316 / 307 / 285, 192: 391 / 393 / 378, 252: 623 / 586 / 568,
+    // 288: 816 / 808 / 845, 432: 1601 / 1574 / 1525.
     const int64_t blocks = (int64_t)pl.B * pl.Hq * pl.nq;
     auto groups = [&](int rows_wg) { return blocks * ((pl.bq + rows_wg - 1) / rows_wg); };
     const int team = pl.bq > 64 && groups(128) >= 256 ? 4 : (pl.bq > 32 && groups(64) >= 192 ? 2 : 1);
