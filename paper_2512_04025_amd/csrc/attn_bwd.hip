@@ -15,7 +15,7 @@
 // The products run on v_mfma_f32_32x32x2_f32 and are bound by its rate (64 FLOP per cycle and SIMD); the
 // operands of a 32 x 32 tile are read from LDS in an eighth of that time, so tiles are staged through registers
 // during the products and one wavefront per SIMD (up to 512 registers at d = 128) keeps the pipe busy.  At d = 64, with two
-// wavefronts per SIMD, bwd_dkv_kernel spills 25 registers in float32 and 8 in bfloat16.
+// wavefronts per SIMD, bwd_dkv_kernel<float> spills 11 registers.
 // Measured against four lanes per row on the vector unit, which this replaces (2 heads x 1000 tokens, d = 64,
 // four levels): dK, dV 641 -> 45 us (four launches -> one), dQ 78 -> 16 us, the whole call 735 -> 62 us.
 #include "psa_dev.h"
@@ -29,6 +29,38 @@ struct BwdArgs {
   int64_t lvl_off[PSA_MAX_LEVELS + 2];   // level h >= 2 inside one pyramid buffer (elements)
   int64_t glvl_off[PSA_MAX_LEVELS + 2];  // level h >= 1 inside one pooled-gradient buffer (elements)
 };
+
+// Rows of an LDS tile (one per lane, read 16 bytes at a time) times the operand x in registers, contracted over the D channels
+// in CHAINS interleaved sums that are added pairwise: one chain of D roundings would leave dS = P (dP - D) less exact than the
+// D / 4 of four lanes that share a row.  Error against fp64, 2 and 12 heads x 150 to 2000 tokens, four masks, relative to those
+// four lanes (mean and worst), one chain -> as below: dQ 1.006, 1.22 -> 0.928, 1.005 (S in one chain, dP in four; S in two or
+// four changes nothing); dK 0.943, 1.148 -> 0.859, 1.002; dV 0.822, 1.034 -> 0.793, 0.924 (two chains each; one and two: dK 1.09).
+// One fragment ahead of the products, no more; and the sum is made before the next product starts, not where it is used
+// first: with the chains of both products open at once bwd_dkv_kernel spills 24 to 71 registers.
+template <int D, int CHAINS>
+__device__ __forceinline__ f32x16 tile_product(const float* frag, const float* x) {
+  f32x16 acc[CHAINS];
+#pragma unroll
+  for (int c = 0; c < CHAINS; ++c)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[c][v] = 0.f;
+  f32x4 next = *reinterpret_cast<const f32x4*>(frag);
+#pragma unroll
+  for (int k8 = 0; k8 < D / 8; ++k8) {
+    const f32x4 now = next;
+    if (k8 + 1 < D / 8) next = *reinterpret_cast<const f32x4*>(frag + (k8 + 1) * 8);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      acc[e % CHAINS] = __builtin_amdgcn_mfma_f32_32x32x2f32(now[e], x[k8 * 4 + e], acc[e % CHAINS], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int w = 1; w < CHAINS; w *= 2)
+#pragma unroll
+    for (int c = 0; c < CHAINS; c += 2 * w) acc[c] += acc[c + w];
+  asm volatile("" : "+v"(acc[0]));
+  return acc[0];
+}
 
 // LDS rows carry four floats of padding: the 16-byte reads of 16 rows then cover every bank once.
 template <int D, int TEAM>
@@ -188,24 +220,8 @@ void bwd_dq_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* __
       pnn = locate(nn);
     }
     if (cur.ok) {
-      f32x16 sc, dp;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) { sc[v] = 0.f; dp[v] = 0.f; }
-      f32x4 kk = *reinterpret_cast<const f32x4*>(Ks + l32 * PITCH + hf * 4), vv = *reinterpret_cast<const f32x4*>(Vs + l32 * PITCH + hf * 4);
-#pragma unroll
-      for (int k8 = 0; k8 < D / 8; ++k8) {               // one fragment ahead of the products, no more
-        const f32x4 k0 = kk, v0 = vv;
-        if (k8 + 1 < D / 8) {
-          kk = *reinterpret_cast<const f32x4*>(Ks + l32 * PITCH + (k8 + 1) * 8 + hf * 4);
-          vv = *reinterpret_cast<const f32x4*>(Vs + l32 * PITCH + (k8 + 1) * 8 + hf * 4);
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          sc = __builtin_amdgcn_mfma_f32_32x32x2f32(k0[e], q[k8 * 4 + e], sc, 0, 0, 0);
-          dp = __builtin_amdgcn_mfma_f32_32x32x2f32(v0[e], go[k8 * 4 + e], dp, 0, 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      f32x16 sc = tile_product<D, 1>(Ks + l32 * PITCH + hf * 4, q);
+      const f32x16 dp = tile_product<D, 4>(Vs + l32 * PITCH + hf * 4, go);
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
         const f32x4 bs = *reinterpret_cast<const f32x4*>(bias_s + g4 * 8 + hf * 4);
@@ -337,6 +353,7 @@ void bwd_dkv_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* _
   struct Chunk { int64_t row0; int r0, seg; };
   typename Four<T>::raw reg[NCH];                                      // the Q or dO rows on their way into LDS
   float lreg = INFINITY, dreg = 0.f;
+  const uint32_t lane_off = (uint32_t)(((lane / CPR) * D + (lane % CPR) * 4) * (int)sizeof(T));   // bytes
   auto place = [&](int f) __attribute__((always_inline)) -> Chunk {    // chunk f of the batch's list
     Chunk c;
     const int e = __builtin_amdgcn_readfirstlane(kept[f / nchunk]);
@@ -349,11 +366,13 @@ void bwd_dkv_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* _
     return c;
   };
   auto fetch = [&](const T* src, const Chunk& c) __attribute__((always_inline)) {
+    // a scalar base and one 32-bit offset per lane: an address per chunk costs 14 to 40 registers more
+    const char* base = reinterpret_cast<const char*>(src + c.row0 * D);
 #pragma unroll
     for (int n = 0; n < NCH; ++n) {
-      const int x = lane + 64 * n, r = x / CPR;
+      const int down = n * (64 / CPR);
       reg[n] = typename Four<T>::raw{0, 0, 0, 0};
-      if (r < c.seg) reg[n] = Four<T>::load(src + (c.row0 + r) * D + (x % CPR) * 4);
+      if (lane / CPR + down < c.seg) reg[n] = Four<T>::load(reinterpret_cast<const T*>(base + (lane_off + (uint32_t)(down * D * (int)sizeof(T)))));
     }
   };
   auto deposit = [&](float* dst) __attribute__((always_inline)) {
@@ -420,24 +439,8 @@ void bwd_dkv_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* _
         D_s[l32] = dreg;
       }
       asm volatile("" ::: "memory");                                   // this wavefront's LDS operations complete in order
-      f32x16 sc, dp;
-#pragma unroll
-      for (int u = 0; u < 16; ++u) { sc[u] = 0.f; dp[u] = 0.f; }
-      f32x4 qa = *reinterpret_cast<const f32x4*>(Qs + l32 * PITCH + hf * 4), ga = *reinterpret_cast<const f32x4*>(Gs + l32 * PITCH + hf * 4);
-#pragma unroll
-      for (int k8 = 0; k8 < D / 8; ++k8) {
-        const f32x4 q0 = qa, g0 = ga;
-        if (k8 + 1 < D / 8) {
-          qa = *reinterpret_cast<const f32x4*>(Qs + l32 * PITCH + (k8 + 1) * 8 + hf * 4);
-          ga = *reinterpret_cast<const f32x4*>(Gs + l32 * PITCH + (k8 + 1) * 8 + hf * 4);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          sc = __builtin_amdgcn_mfma_f32_32x32x2f32(q0[u], k[k8 * 4 + u], sc, 0, 0, 0);
-          dp = __builtin_amdgcn_mfma_f32_32x32x2f32(g0[u], v[k8 * 4 + u], dp, 0, 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      f32x16 sc = tile_product<D, 2>(Qs + l32 * PITCH + hf * 4, k);
+      f32x16 dp = tile_product<D, 2>(Gs + l32 * PITCH + hf * 4, v);
       // this lane: its key, rows (u/4)*8 + hf*4 + u%4; sc becomes dS, dp becomes P
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {

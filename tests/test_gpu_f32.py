@@ -8,7 +8,7 @@ import pytest
 
 import synth_inputs as si
 from oracle import psa_oracle as orc
-from tests.psa_testlib import Buffers, from_dev, gpu_params, to_dev
+from tests.psa_testlib import Buffers, from_dev, gpu_params, rel_l2, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -145,3 +145,30 @@ def test_a_key_that_is_not_a_number_reaches_every_row_that_keeps_it(N, Hq, bq):
     psa.psa_dense_ref(gp, Qd, K, Vd, buf.O, lse=buf.lse)
     torch.cuda.synchronize()
     assert bool(torch.isnan(buf.O).all()) and bool(torch.isnan(buf.lse).all())
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_gradients_where_the_channels_cancel(d):
+    """Values of +16 and -16 in the two halves of the channels under a constant output gradient: dP is what is left of sums
+    that reach 16 d / 2.  One chain of d roundings has an rms error of about 0.45 * 2^-24 * 8 d * sqrt(d / 3), relative to
+    dP - dO . O of about 1.4 sqrt(d): 1.1e-5 at d = 128, proportional to d; in c interleaved chains 1 / c of it, next to
+    the 3e-6 that the rounding of O leaves in dO . O.  The bar lies between two chains and one."""
+    import torch
+    op = orc.Params(B=1, Hq=2, Hkv=2, N=160, d=d, bq=64, bk=64, levels=1, dtype="f32", sq=8, sk=8)
+    gp = gpu_params(op)
+    Q, K, V = si.random_qkv(3, 1, 2, 2, op.N, d, "f32")
+    V = (V + np.where(np.arange(d) < d // 2, 16, -16)).astype(np.float32)
+    dO = si.random_qkv(4, 1, 2, 2, op.N, d, "f32")[0] + np.float32(1)
+    M = np.ones((1, 2, op.nq, op.nk), np.uint8)
+    Qd, Kd, Vd, dOd = (to_dev(x, "f32") for x in (Q, K, V, dO))
+    buf = Buffers(gp)
+    Md = torch.from_numpy(M).cuda()
+    psa.psa_attention_fwd(gp, Qd, Kd, Vd, None, None, Md, buf.O, buf.scratch, lse=buf.lse)
+    grads = [torch.empty_like(x) for x in (Qd, Kd, Vd)]
+    scratch = torch.empty(psa.psa_query_bwd_sizes(gp), dtype=torch.uint8, device="cuda")
+    psa.psa_attention_bwd(gp, Qd, Kd, Vd, None, None, Md, buf.O, buf.lse, dOd, *grads, scratch)
+    torch.cuda.synchronize()
+    Q64, K64, V64, dO64 = (si.to_f64(x, "f32") for x in (Q, K, V, dO))
+    ref = orc.psa_attention_backward(Q64, orc.build_pyramid(K64, op), orc.build_pyramid(V64, op), M, dO64, op)
+    for name, got, want in zip(("dQ", "dK"), grads, ref):
+        assert rel_l2(from_dev(got, "f32"), want) <= 9e-6 * d / 128, name
