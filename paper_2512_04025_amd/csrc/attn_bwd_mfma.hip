@@ -30,6 +30,7 @@ namespace psa {
 
 struct BwdMfmaArgs {
   int B, N, Hq, Hkv, nq, nk, bq, bk, lg_bk, H, causal;
+  int one_head;                          // dK, dV: all XCDs work on one head's neighbouring keys
   float scale, scale_log2;
   int64_t lvl_off[PSA_MAX_LEVELS + 2];   // level h >= 2 inside one pyramid buffer (elements)
   int64_t glvl_off[PSA_MAX_LEVELS + 2];  // level h >= 1 inside one pooled-gradient buffer (elements)
@@ -352,10 +353,10 @@ __global__ __launch_bounds__((DkvShape<D, KH>::NT), 2) void bwd_dkv_mfma_kernel(
   // walk the longest lists, and the finer levels' shorter ones fill the end of the launch.
   // A block of more pooled keys than the workgroup takes (KH * 32) is shared by several workgroups,
   // `pieces` of them, each with its own KH * 32 keys (and its own walk down the same column).
-  // Workgroup ids are dealt round-robin to the 8 XCDs; each XCD takes one contiguous run of a level's
+  // Workgroup ids are dealt round-robin to the 8 XCDs.  Each XCD takes one contiguous run of a level's
   // (head, key block) items, so that what runs on it at one time are columns of one head and level, of
-  // like length, whose query rows meet in its L2.  (All XCDs on one head, a block each in turn: 2 % slower
-  // at 32760 tokens, 12 heads; 13 % slower causal at 16384 tokens, d = 64.)
+  // like length, whose query rows meet in its L2; or all XCDs take the same head, a block each in turn (one_head, see
+  // launch_bwd_mfma_t).
   int h = h_hi, G = 1, pieces = 1, bx = 0, head = 0;
   int slot = (int)(blockIdx.x >> 3);
   for (;; --h) {
@@ -365,7 +366,7 @@ __global__ __launch_bounds__((DkvShape<D, KH>::NT), 2) void bwd_dkv_mfma_kernel(
     pieces = (1 << lg) > KH * 32 ? (1 << lg) / (KH * 32) : 1;
     const int ng = pieces * ((a.nk + G - 1) / G), items = a.B * a.Hq * ng, run = (items + 7) >> 3;
     if (slot < run || h == h_lo) {
-      const int item = (int)(blockIdx.x & 7) * run + slot;
+      const int item = a.one_head ? slot * 8 + (int)(blockIdx.x & 7) : (int)(blockIdx.x & 7) * run + slot;
       if (item >= items) return;
       head = item / ng;
       bx = item % ng;
@@ -664,6 +665,13 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
   a.H = pl.H; a.causal = pl.causal; a.scale = pl.scale; a.scale_log2 = pl.scale * LOG2E;
   a.lg_bk = 0;
   while ((1 << a.lg_bk) < pl.bk) ++a.lg_bk;
+  // With a run of items to each XCD the Q and dO of eight heads are in flight, which the memory-side cache (256 MB) has to
+  // hold; with all XCDs on one head it holds them at any length.  Whole call, ms for runs / one head, not causal, d = 128: 12 heads x
+  // 16000 tokens 2.21 / 2.30, x 32760 8.90 / 8.95, x 40000 13.6 / 13.4, 24 x 60000 60.3 / 58.9, 40 x 75600 160 / 155, 24 x 100000 174 / 162,
+  // single level 16 x 60000 16.7 / 14.9; d = 64: 12 x 40000 6.98 / 7.01, 12 x 75600 26.0 / 25.5, 32 x 131072 183 / 182.  Seven query heads to a
+  // key head, 28 x 16000 4.99 / 5.08, x 24000 11.2 / 11.1, x 32760 20.8 / 20.1 (single level 8.4 / 7.9), x 40000 30.7 / 30.3.  Causal the
+  // columns of a head differ in length, and runs stay better: 16 x 75600 32.3 / 33.7, d = 64 8 x 131072 26.6 / 27.6.
+  a.one_head = !pl.causal && (int64_t)pl.N * pl.d >= (pl.group > 1 ? 4000000 : 5000000);
   int64_t off = 0;
   for (int h = 0; h < PSA_MAX_LEVELS + 2; ++h) { a.lvl_off[h] = pl.lvl_off[h]; a.glvl_off[h] = 0; }
   for (int h = 1; h <= pl.H; ++h) {

@@ -29,6 +29,7 @@ def _off_by_one(x):
     (2, 2, 530, 64, 64, 128, 5, False, 0.6, False),       # d = 64: a 128-key block split over two workgroups
     (3, 1, 333, 64, 96, 32, 3, True, 0.8, False),         # 9 (head, block) runs on 8 XCDs; 96-row blocks: stages of 64 and 32
     (2, 1, 300, 128, 128, 64, 4, False, 0.7, True),
+    (1, 1, 39100, 128, 128, 64, 3, False, 0.02, False),   # long: all XCDs on one head
 ])
 def test_backward_edges(Hq, Hkv, N, d, bq, bk, levels, causal, keep, shifted):
     import torch
