@@ -380,7 +380,9 @@ struct ListArgs {
 // heads x 256 query blocks x 512 key blocks and 3.3 + 3.7 at 12 x 8 x 16, this one 15 and 4.8.  NCH > 0: the row of levels is loaded once into NCH registers per
 // lane (block c*64 + lane in register c), four query blocks per workgroup.  NCH = 0 (rows of more than 4096 blocks):
 // the row is read again for every level, one query block per workgroup.
-template <int NCH>
+// DESC: descriptors are wanted; callers without them run a kernel without that code, as short as the list alone (0.3 us of 20
+// to 40 for pyramid and attention on 64-row blocks x 2000 to 4000 tokens).
+template <int NCH, bool DESC>
 __global__ __launch_bounds__(NCH ? 256 : 64) void lists_kernel(const uint8_t* __restrict__ M, uint16_t* __restrict__ idx,
                                                                int32_t* __restrict__ cnt, uint32_t* __restrict__ desc, ListArgs a) {
   extern __shared__ uint16_t lists[];
@@ -409,7 +411,7 @@ __global__ __launch_bounds__(NCH ? 256 : 64) void lists_kernel(const uint8_t* __
         if (hit) {
           const int at = pos + n + __popcll(mask & below);
           out[at] = (uint16_t)j;
-          if (a.pitch) lst[at] = (uint16_t)j;
+          if constexpr (DESC) lst[at] = (uint16_t)j;
         }
         n += __popcll(mask);
       };
@@ -424,7 +426,7 @@ __global__ __launch_bounds__(NCH ? 256 : 64) void lists_kernel(const uint8_t* __
     nb_h[h - 1] = n;
     pos += n;
   }
-  if (a.pitch == 0) return;
+  if constexpr (!DESC) return;
   // the list passes between lanes of this one wavefront: LDS serves its accesses in order, the fences keep the
   // compiler from moving the reads above the writes
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -467,11 +469,16 @@ __global__ __launch_bounds__(NCH ? 256 : 64) void lists_kernel(const uint8_t* __
 template <int NCH>
 static hipError_t launch_lists_t(const uint8_t* M, uint16_t* idx, int32_t* cnt, uint32_t* desc, const ListArgs& a, hipStream_t s) {
   constexpr int WAVES = NCH ? 4 : 1;
-  const size_t smem = a.pitch ? (size_t)WAVES * ((a.nk + 7) & ~7) * sizeof(uint16_t) : 0;
+  const unsigned grid = (unsigned)((a.rows + WAVES - 1) / WAVES);
+  if (a.pitch == 0) {
+    lists_kernel<NCH, false><<<grid, 64 * WAVES, 0, s>>>(M, idx, cnt, desc, a);
+    return hipGetLastError();
+  }
+  const size_t smem = (size_t)WAVES * ((a.nk + 7) & ~7) * sizeof(uint16_t);
   static LdsOptIn optin;
-  const hipError_t e = allow_max_lds(reinterpret_cast<const void*>(lists_kernel<NCH>), &optin);
+  const hipError_t e = allow_max_lds(reinterpret_cast<const void*>(lists_kernel<NCH, true>), &optin);
   if (e != hipSuccess) return e;
-  lists_kernel<NCH><<<(unsigned)((a.rows + WAVES - 1) / WAVES), 64 * WAVES, smem, s>>>(M, idx, cnt, desc, a);
+  lists_kernel<NCH, true><<<grid, 64 * WAVES, smem, s>>>(M, idx, cnt, desc, a);
   return hipGetLastError();
 }
 
