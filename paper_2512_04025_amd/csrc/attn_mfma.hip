@@ -827,13 +827,14 @@ static hipError_t launch_mfma_d(const Plan& pl, const void* Q, const void* K, co
   // the steps of each, and longer rows take 64 columns too (short ones have few tiles, most of them partly empty).
   // Attention alone, one head, a fifth of the keys, us for 64 / 32 columns, d = 64 and d = 128: 64-row blocks x 3000 tokens 19.1 / 20.0
   // and 23.2 / 23.7, x 8000 31.8 / 38.1 and 41.7 / 46.6, x 15000 55.6 / 65.6 and 72.4 / 79.7; 32-row blocks x 3000 21.9 / 21.3 and 30.3 / 28.3,
-  // x 8000 35.4 / 39.2 and 51.2 / 54.9; more workgroups than fit (three tenths of the keys): d = 64, 12 heads x 6000 tokens in 64-row
+  // x 8000 35.4 / 39.2 and 51.2 / 54.9; three tenths of the keys in 64-row blocks x 2000 17.3 / 19.2 and 21.8 / 22.6 (a tenth 12.8 / 11.4 and
+  // 14.7 / 12.9), but 12 heads x 3000 at d = 128 58 / 42; more workgroups than fit (three tenths of the keys): d = 64, 12 heads x 6000 tokens in 64-row
   // blocks 85 / 70, in 32-row blocks 128 / 95, d = 128 144 / 125 and 277 / 185.  Not with blocks of less than a load at d = 128
   // in one wavefront, whose load plans of 64 rows do not fit its registers (x 8000 119 / 61).
   constexpr bool WIDE = NW == 4 || !(D == 128 && NW == 1);
   const int64_t wgs = (int64_t)pl.B * pl.Hq * pl.nq * ((pl.bq + NW * 32 - 1) / (NW * 32));
   const int64_t resident = 256 * (int64_t)(LDS_LIMIT / attn_mfma_smem_bytes(D, pl.nk, 64));
-  const bool wide = NW == 4 || (wgs <= resident && pl.N >= (NW == 2 ? 4096 : 6144));
+  const bool wide = NW == 4 || (wgs <= resident && pl.N >= (NW == 1 ? 6144 : 2 * wgs <= resident ? 3000 : 4096));
   constexpr int NARROW = NW == 4 ? 64 : 32;
   if (blocks_cover_a_load)
     return wide ? launch_mfma_t<D, NW, true, 64>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s)
