@@ -61,15 +61,17 @@ def test_backward_edges(Hq, Hkv, N, d, bq, bk, levels, causal, keep, shifted):
         assert rel_l2(g, want) <= 1e-2, name
 
 
-@pytest.mark.parametrize("d,bq,bk,levels,causal", [(128, 128, 64, 4, False), (64, 128, 128, 4, True), (128, 32, 32, 4, False), (64, 64, 64, 3, True)])
-def test_tensors_between_two_chunks_give_the_same_bits(d, bq, bk, levels, causal):
-    """Every tensor 2 bytes past a 16-byte boundary: the same kernels, so the same bits as on aligned tensors."""
+@pytest.mark.parametrize("dtype,d,bq,bk,levels,causal", [
+    ("bf16", 128, 128, 64, 4, False), ("bf16", 64, 128, 128, 4, True), ("bf16", 128, 32, 32, 3, False), ("bf16", 64, 64, 64, 3, True),
+    ("f32", 128, 128, 64, 4, False), ("f32", 64, 64, 32, 3, True)])
+def test_tensors_between_two_chunks_give_the_same_bits(dtype, d, bq, bk, levels, causal):
+    """Every tensor one element past a 16-byte boundary: the same kernels, so the same bits as on aligned tensors."""
     import torch
     N, Hq, Hkv = 333, 4, 2
-    op = orc.Params(B=1, Hq=Hq, Hkv=Hkv, N=N, d=d, bq=bq, bk=bk, levels=levels, dtype="bf16", causal=causal, sq=8, sk=8)
+    op = orc.Params(B=1, Hq=Hq, Hkv=Hkv, N=N, d=d, bq=bq, bk=bk, levels=levels, dtype=dtype, causal=causal, sq=8, sk=8)
     gp = gpu_params(op)
-    host = si.random_qkv(5, 1, Hq, Hkv, N, d, "bf16")
-    dO = si.random_qkv(6, 1, Hq, Hq, N, d, "bf16")[0]
+    host = si.random_qkv(5, 1, Hq, Hkv, N, d, dtype)
+    dO = si.random_qkv(6, 1, Hq, Hq, N, d, dtype)[0]
     rng = np.random.default_rng(7)
     vis = orc.block_visibility(op)
     M = rng.integers(1, levels + 1, size=(1, Hq, op.nq, op.nk)) * (rng.random((1, Hq, op.nq, op.nk)) < 0.7)
@@ -77,15 +79,16 @@ def test_tensors_between_two_chunks_give_the_same_bits(d, bq, bk, levels, causal
     Md = torch.from_numpy(np.where(vis[None, None] == 0, 0, np.where(vis[None, None] == 2, 1, M)).astype(np.uint8)).cuda()
     results = []
     for place in (lambda x: x, _off_by_one):
-        Q, K, V, go = (place(to_dev(x, "bf16")) for x in (*host, dO))
+        Q, K, V, go = (place(to_dev(x, dtype)) for x in (*host, dO))
         buf = Buffers(gp)
         Kp, Vp, O = place(buf.Kpyr), place(buf.Vpyr), place(buf.O)
         psa.psa_build_pyramid(gp, K, V, Kp, Vp)
+        psa.psa_allocate_levels(gp, Q, K, Kp, buf.M, buf.scratch, scores_out=buf.S)
         psa.psa_attention_fwd(gp, Q, K, V, Kp, Vp, Md, O, buf.scratch, lse=buf.lse)
         grads = [place(torch.full_like(x, float("nan"))) for x in (Q, K, V)]
         scratch = torch.full((psa.psa_query_bwd_sizes(gp),), 255, dtype=torch.uint8, device="cuda")
         psa.psa_attention_bwd(gp, Q, K, V, Kp, Vp, Md, O, buf.lse, go, *grads, scratch)
         torch.cuda.synchronize()
-        results.append([x.clone() for x in (O, buf.lse, *grads)])
-    for name, a, b in zip(("O", "lse", "dQ", "dK", "dV"), *results):
+        results.append([x.clone() for x in (buf.M, buf.S, O, buf.lse, *grads)])
+    for name, a, b in zip(("M", "S", "O", "lse", "dQ", "dK", "dV"), *results):
         assert torch.equal(a, b), name

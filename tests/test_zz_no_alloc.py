@@ -27,7 +27,7 @@ def test_static_workspace_entry_point_matches_the_workspace_one_twice_in_a_row()
     C = si.CONFIGS
     first = si.small_variant(C["dit1p3b"], 2040, Hq=2, Hkv=2)                 # descriptors + matrix-core kernel
     second = si.small_variant(C["vlm_prefill"], 1000, Hq=4, Hkv=2)            # smaller, causal, grouped-query
-    third = C["tiny"]                                                          # fp32 rows kernel, smaller again
+    third = C["tiny"]                                                          # fp32 kernel, smaller again
     for w, budget in ((first, 0.2), (second, 0.4), (third, 0.25)):
         op, gp, (Qd, Kd, Vd), (Q64, K64, V64), buf = _problem(w, budget)
         psa.psa_build_pyramid(gp, Kd, Vd, buf.Kpyr, buf.Vpyr)
