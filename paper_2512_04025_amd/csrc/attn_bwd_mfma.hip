@@ -2,7 +2,7 @@
 // through Eq. 8 and the mean pooling of Eq. 2-3; see attn_bwd.hip for the formulas and for the fp32
 // version that serves float32 and the shapes this one does not take).
 //
-// Two kernels, both on 32x32x16 MFMAs with fp32 accumulation, P and dS rounded to bfloat16 for the
+// Two kernels with fp32 accumulation, P and dS rounded to bfloat16 for the
 // products that consume them, no atomics, two wavefronts per SIMD (at most 256 registers per lane),
 // double-buffered tiles in LDS (dQ: through registers; dK, dV: loaded directly):
 //   bwd_dq_mfma_kernel   one workgroup per 128 query rows (a wavefront per 32), walking the row's
@@ -11,12 +11,11 @@
 //        D = dO.O are per-lane scalars), dS^T is packed in registers as the B operand of
 //        dQ^T += Kbar^T dS^T, whose A operand is read from the row-major Kbar tile with the transposing
 //        LDS load.
-//   bwd_dkv_mfma_kernel  the same with queries and keys exchanged: one workgroup per (32, 64 or 128
-//        adjacent pooled keys of a level, query head); the pooled keys and values sit in registers as B
-//        operands (one key per lane), the query blocks that use one of the workgroup's key blocks at this
-//        level (a walk down the level map's columns) are staged through LDS 64 rows at a time; S = Q Kbar^T and dP = dO Vbar^T, then dVbar^T += dO^T P and
-//        dKbar^T += Q^T dS with the transposing load on the staged dO and Q.  Half of the wavefronts
-//        accumulate dKbar, the other half dVbar.
+//   bwd_dkv_mfma_kernel  the same with queries and keys exchanged, on 16x16x32 MFMAs: one workgroup per (64 adjacent pooled
+//        keys of a level, query head); the pooled keys and values sit in registers as B operands (one key per lane), the
+//        query blocks that use one of the workgroup's key blocks at this level (a walk down the level map's columns) are
+//        staged through LDS 64 rows at a time; S = Q Kbar^T and dP = dO Vbar^T, then dVbar^T += dO^T P and
+//        dKbar^T += Q^T dS with the transposing load on the staged dO and Q.
 // The dQ kernel's LDS rows carry padding that spreads the rows of an operand read over the banks: 16 bytes serve the
 // row-wise fragments (eight rows x 16 bytes) at either head dimension and, at d = 64, the transposing
 // load too (four rows x 32 bytes); at d = 128 that load wants the rows 8 banks apart and the fragments
@@ -31,6 +30,8 @@ namespace psa {
 struct BwdMfmaArgs {
   int B, N, Hq, Hkv, nq, nk, bq, bk, lg_bk, H, causal;
   int one_head;                          // dK, dV: all XCDs work on one head's neighbouring keys
+  int small_keys;                        // dK, dV: keys of a workgroup where blocks have fewer than 64
+  int lg_cpe;                            // dK, dV: log2 of the 32-row chunks of a query block, or -1
   float scale, scale_log2;
   int64_t lvl_off[PSA_MAX_LEVELS + 2];   // level h >= 2 inside one pyramid buffer (elements)
   int64_t glvl_off[PSA_MAX_LEVELS + 2];  // level h >= 1 inside one pooled-gradient buffer (elements)
@@ -63,6 +64,68 @@ __device__ __forceinline__ bf16x8 frag_transposed(const unsigned char* tile, int
   const bs16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bs16x4*)(p));
   const bs16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bs16x4*)(p + 8 * pitch));
   return __builtin_bit_cast(bf16x8, (bs16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// f(integral_constant 0), f(1) .. f(N - 1)
+template <int N, int I = 0, typename F> __device__ __forceinline__ void each(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    each<N, I + 1>(f);
+  }
+}
+
+// x ^ a constant, made where it is used: an address per constant would otherwise be held in a register over the whole loop
+template <int C> __device__ __forceinline__ uint32_t flip(uint32_t x) {
+  if (C == 0) return x;
+  uint32_t y;
+  asm volatile("v_xor_b32 %0, %1, %2" : "=v"(y) : "n"(C), "v"(x));
+  return y;
+}
+
+// LDS reads with hand-counted waits: lds_wait<N> declares its operands arrived once at most N later LDS operations are outstanding
+template <int OFF, typename T> __device__ __forceinline__ void lds_read(T& dst, uint32_t at) {
+  static_assert(sizeof(T) == 16, "");
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(at), "n"(OFF));
+}
+template <int OFF> __device__ __forceinline__ void lds_read_t(bs16x4& dst, uint32_t at) {
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(at), "n"(OFF));
+}
+template <int N, typename T> __device__ __forceinline__ void lds_wait(T& x, f32x4& y, f32x4& z) {
+  asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(x), "+v"(y), "+v"(z) : "n"(N));
+}
+template <int N, typename T, typename U> __device__ __forceinline__ void lds_wait(T& x, U& y) {
+  asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(x), "+v"(y) : "n"(N));
+}
+
+// the lane's number, made where it is used: what depends on it is worked out again instead of held over the stage loop
+__device__ __forceinline__ int lane_again() {
+  int x;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(x));
+  return x;
+}
+
+typedef __attribute__((ext_vector_type(4))) uint32_t rsrc_words;
+__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(size_t)(lds_byte*)(lds_void*)p; }
+// Loads straight into LDS, at `to` + lane * (16 or 4): source = buffer + v + s.  In assembly, so that the compiler does not track them:
+// next to LDS reads it would make each of those wait for every load in flight, also for those into the other buffer.  They
+// are waited for by hand (vmcnt) before the barrier behind which their bytes are read.
+// (m0 is a reserved register: the compiler keeps nothing in it and warns that it would not restore it.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void load_lds16(const rsrc_words& rsrc, uint32_t to, int v, int s) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(to), "v"(v), "s"(rsrc), "s"(s) : "memory", "m0");
+}
+__device__ __forceinline__ void load_lds4(const rsrc_words& rsrc, uint32_t to, int v, int s) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(to), "v"(v), "s"(rsrc), "s"(s) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+// buffer descriptor: base, bytes, 32-bit data format
+__device__ __forceinline__ rsrc_words make_rsrc(const void* base, uint32_t bytes) {
+  const uint64_t at = (uint64_t)base;
+  rsrc_words r = {(uint32_t)at, (uint32_t)(at >> 32) & 0xffffu, bytes, 0x00020000u};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)r[i]);
+  return r;
 }
 
 // 16 accumulator values of one lane (rows (v/4)*8 + hf*4 + v%4 of a 32-row result) -> the two B
@@ -123,7 +186,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(const bf16_t* __res
 #pragma unroll
     for (int ks = 0; ks < KS; ks += 2 * w) dots[ks] += dots[ks + w];
   float my_D = dots[0] + __shfl_xor(dots[0], 32, 64);
-  if (active && hf == 0) Dr[qhead * a.N + qrow] = my_D;
+  if (active && hf == 0) Dr[qhead * a.N + qrow] = -my_D;
   float lse2 = active ? lse[qhead * a.N + qrow] * LOG2E : INFINITY;   // inactive rows: every weight 0
   // The wait for these loads stands here and not at their first use inside the tile loop, where it would
   // also wait for the rows fetched ahead.
@@ -294,365 +357,453 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(const bf16_t* __res
   }
 }
 
-// One workgroup per (KH * 32 adjacent pooled keys, QUERY head, level): the query heads that share a key
+// One workgroup per (64 adjacent pooled keys, QUERY head, level): the query heads that share a key
 // head each write a partial gradient of their own (added up when the levels are folded back into dK, dV),
 // so that a key block which every query block uses is not one workgroup's walk over the whole group.
-// KH: 32-key tiles of the workgroup (1, 2 or 4).  Blocks of 32 pooled keys or more take KH = keys / 32
-// (one block per workgroup); smaller blocks are packed G = KH * 32 / keys to a workgroup (at most 16),
-// so that a 32-key matrix tile is full and a query block is staged once for all the blocks of the group
-// that it uses at this level.
-// Half of the wavefronts accumulate dKbar (they need S, dP and dS), the other half dVbar (S and P only):
-// that halves the accumulators a wavefront holds, so that two wavefronts fit on each SIMD (two
-// workgroups of four per compute unit, or one of eight for KH = 4) and the matrix pipe works for one
-// while the other is in its exponentials, its LDS reads or a barrier.  Wavefronts of the same half
-// that share a key tile (KH = 1: two of them) split the 32-row chunks of a staged tile.
+// A block of 128 pooled keys is shared by two workgroups; smaller blocks are packed to a workgroup (at most 32).
 //
-// The rows of a stage go straight into LDS (buffer_load ... lds), one stage ahead, with one barrier per stage.  The
-// two buffers are separate objects on purpose: that is what lets the compiler see that reads of one do not depend
-// on the loads in flight into the other, and count its waits instead of draining them.  The 16-byte chunks of a
-// row are stored at chunk ^ row_swizzle(row), which serves both ways a tile is read without padding: the row-wise
-// fragments want 16 consecutive rows at 16 different places, the transposing load wants the four rows of a group
-// in four different 64-byte groups.
+// A wavefront owns two tiles of 16 keys with both of their gradients (128 accumulator registers at d = 128) and every second
+// chunk of 32 query rows: S and dP are computed once, P and dS stay in registers, and where blocks are smaller than the
+// workgroup's keys a chunk costs only the 16-key tiles that it uses.  (Two halves of wavefronts, one a gradient each, computed S
+// twice, on tiles of 32 keys: of four 8-key blocks that were packed to such a tile a query block uses one and a third on average.)
+// The row fragments, transposed fragments and MFMAs of a chunk follow one another in a fixed order (see `chunk`).
 //
-// Measured at 12 heads x 32760 tokens, d = 128 (through registers and padded rows -> directly, swizzled): level 1
-// 2.83 -> 2.73 ms, levels 2-4 3.97 -> 3.65 ms, LDS cycles halved, no bank conflicts; causal, 28 heads x 8000: 1.04 -> 0.86 ms;
-// d = 64, 16 heads x 16384: 8-20 % of the whole call.  With everything but the products switched off the stages of
-// levels 2-4 alone take 2.6 ms (1.5 when every row hits the L2), the products alone 2.3: the two overlap only in
-// part, because one stage is all that fits in flight.
-template <int D, int KH>
-struct DkvShape {
-  static constexpr int NW = KH == 4 ? 8 : 4, NT = NW * 64, RH = (NW / 2) / KH, ROWS = 64;
-  static constexpr int ROWB = D * 2, TILEB = ROWS * ROWB;
-};
-template <int D> __device__ __forceinline__ int row_swizzle(int row) {
-  return D == 128 ? ((row & 3) << 2) | ((row >> 2) & 3) : (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
-}
+// What bounds it, 12 heads x 32760 tokens, d = 128, four levels, a fifth of the keys: the launch takes 4.7-4.8 ms (before: 6.4 in two),
+// the matrix pipe busy in 0.39 of the cycles on level 1 and 0.21 on the coarser ones, LDS in 0.25 without conflicts.  By parts,
+// levels 2-4 / level 1: staging without products 1.93 / 1.29, products without staging 2.04 / 1.50, all 2.8 / 1.9.  128 keys to a workgroup of eight
+// wavefronts stage a quarter less and were slower (3.85 for levels 2-4: one lock-step group on a compute unit).
 constexpr int DKV_LIST = 1024;     // query blocks tested before their rows are walked
+constexpr int DKV_MAXG = 32;       // key blocks of a workgroup: one bit each
+template <int D>
+struct DkvShape {
+  static constexpr int NW = 4, NT = NW * 64, KEYS = 64, ROWS = 64, CHUNKS = ROWS / 32;
+  static constexpr int ROWB = D * 2, TILEB = ROWS * ROWB, WPS = D == 64 ? 3 : 2;
+  static constexpr int LDSB = 4 * TILEB + 16 * ROWS + 6 * DKV_LIST + 4 * NW;
+};
+// Place of a row's 16-byte chunks in LDS: chunk ^ row_swizzle(row).
+template <int D> __host__ __device__ constexpr int row_swizzle(int row) {
+  const int r = D == 128 ? row : row >> 1;                   // rows per 256 bytes of LDS: 1, 2
+  const int fold = ((row >> 2) ^ (row >> 3)) & 1;
+  return D == 128 ? (((r & 3) | (fold << 2)) << 1) | ((row >> 3) & 1) : (((r & 1) | (fold << 1)) << 1) | ((row >> 3) & 1);
+}
+struct DkvPtrs {
+  const bf16_t *Q, *K, *V, *Kp, *Vp, *dO;
+  const uint8_t* M;
+  const float *lse, *Dr;
+  float *dKp, *dVp;
+};
+// What a workgroup does: level, (batch, query head), number among the head's workgroups of this level
+struct DkvItem { int h, head, bx; };
+// pooled keys of a workgroup, key blocks they belong to, workgroups that share a block, workgroups per head
+struct DkvGroup { int keys, G, pieces, ng; };
+__host__ __device__ inline DkvGroup dkv_group(int lg_th, int nk, int small_keys) {
+  const int th = 1 << lg_th;
+  DkvGroup r;
+  r.keys = th >= 64 ? 64 : small_keys;
+  r.G = r.keys / th;
+  r.G = r.G < 1 ? 1 : (r.G > DKV_MAXG ? DKV_MAXG : r.G);
+  r.pieces = th > r.keys ? th / r.keys : 1;
+  r.ng = r.pieces * ((nk + r.G - 1) / r.G);
+  return r;
+}
 
-template <int D, int KH, bool CAUSAL>
-__global__ __launch_bounds__((DkvShape<D, KH>::NT), 2) void bwd_dkv_mfma_kernel(
-    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V, const bf16_t* __restrict__ Kp,
-    const bf16_t* __restrict__ Vp, const uint8_t* __restrict__ M, const float* __restrict__ lse, const float* __restrict__ Dr,
-    const bf16_t* __restrict__ dO, float* __restrict__ dKp, float* __restrict__ dVp, int h_lo, int h_hi, BwdMfmaArgs a) {
-  using S = DkvShape<D, KH>;
-  constexpr int NW = S::NW, NT = S::NT, RH = S::RH, ROWS = S::ROWS, ROWB = S::ROWB, TILEB = S::TILEB;
-  constexpr int CPR = D / 8, KS = D / 16, MD = D / 32, RPI = 64 / CPR, NI = ROWS / RPI / NW;   // NI: load instructions per wavefront, stage and tensor
-  // Q rows [ROWS][ROWB] | dO rows [ROWS][ROWB]
-  __shared__ __attribute__((aligned(1024))) unsigned char buf0[2 * TILEB];
-  __shared__ __attribute__((aligned(1024))) unsigned char buf1[2 * TILEB];
-  __shared__ __attribute__((aligned(16))) float stat0[2 * ROWS], stat1[2 * ROWS];   // lse [ROWS] | D [ROWS]
-  __shared__ uint32_t kept[DKV_LIST];              // query block | used blocks << 16
-  __shared__ int wcount[8];
-  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // 0: this wavefront accumulates dKbar, 1: dVbar.  The halves change places from one workgroup to the
-  // next, so that two workgroups on a compute unit do not put both heavier halves on the same SIMDs.
-  const int role = (wave / (NW / 2)) ^ (int)((blockIdx.x >> 3) & 1);
-  const int w2 = wave % (NW / 2), kh = w2 % KH, rh = w2 / KH;
-  // One launch covers the levels h_lo .. h_hi that share this KH, the coarsest first: its workgroups
-  // walk the longest lists, and the finer levels' shorter ones fill the end of the launch.
-  // A block of more pooled keys than the workgroup takes (KH * 32) is shared by several workgroups,
-  // `pieces` of them, each with its own KH * 32 keys (and its own walk down the same column).
-  // Workgroup ids are dealt round-robin to the 8 XCDs.  Each XCD takes one contiguous run of a level's
-  // (head, key block) items, so that what runs on it at one time are columns of one head and level, of
-  // like length, whose query rows meet in its L2; or all XCDs take the same head, a block each in turn (one_head, see
-  // launch_bwd_mfma_t).
-  int h = h_hi, G = 1, pieces = 1, bx = 0, head = 0;
-  int slot = (int)(blockIdx.x >> 3);
-  for (;; --h) {
-    const int lg = a.lg_bk - (h - 1);
-    G = (KH * 32) >> lg;
-    G = G < 1 ? 1 : (G > 16 ? 16 : G);
-    pieces = (1 << lg) > KH * 32 ? (1 << lg) / (KH * 32) : 1;
-    const int ng = pieces * ((a.nk + G - 1) / G), items = a.B * a.Hq * ng, run = (items + 7) >> 3;
-    if (slot < run || h == h_lo) {
-      const int item = a.one_head ? slot * 8 + (int)(blockIdx.x & 7) : (int)(blockIdx.x & 7) * run + slot;
-      if (item >= items) return;
-      head = item / ng;
-      bx = item % ng;
-      break;
-    }
-    slot -= run;
-  }
+template <int D, bool FULL, bool CAUSAL>
+__device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr, const BwdMfmaArgs& a, const DkvItem it) {
+  using S = DkvShape<D>;
+  constexpr int NW = S::NW, NT = S::NT, KEYS = S::KEYS, ROWS = S::ROWS, ROWB = S::ROWB, TILEB = S::TILEB, CHUNKS = S::CHUNKS;
+  constexpr int CPR = D / 8, KS = D / 32, MD = D / 16, RPI = 64 / CPR, WROWS = ROWS / NW, NI = WROWS / RPI;   // rows and load instructions per wavefront, stage and tensor
+  static_assert(WROWS == 16, "a wavefront's rows are of one chunk and start where the swizzle does");
+  // two stage buffers (Q rows [ROWS][ROWB] | dO rows [ROWS][ROWB]), two of statistics (lse [ROWS] | -D [ROWS]), the list of query
+  // blocks (the group's blocks that each uses, its number), counts per wavefront
+  constexpr int BUFB = 2 * TILEB, STATB = 8 * ROWS, OFF_STAT = 2 * BUFB, OFF_BITS = OFF_STAT + 2 * STATB, OFF_ROW = OFF_BITS + 4 * DKV_LIST,
+                OFF_COUNT = OFF_ROW + 2 * DKV_LIST;
+  static_assert((BUFB & (BUFB - 1)) == 0 && OFF_STAT % (2 * STATB) == 0, "the buffers alternate by one address bit");
+  static_assert(OFF_COUNT + 4 * NW <= S::LDSB, "LDS");
+  uint32_t* kept_bits = reinterpret_cast<uint32_t*>(smem + OFF_BITS);
+  uint16_t* kept_row = reinterpret_cast<uint16_t*>(smem + OFF_ROW);
+  int* wcount = reinterpret_cast<int*>(smem + OFF_COUNT);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int lane = lane_again(), l16 = lane & 15, g = lane >> 4;
+  const int rh = wave >> 1, pair = wave & 1;         // which 32 rows of a stage; which 16-key tiles: pair, pair + 2
+  const bf16_t *Q = ptr.Q, *K = ptr.K, *V = ptr.V, *Kp = ptr.Kp, *Vp = ptr.Vp, *dO = ptr.dO;
+  const uint8_t* M = ptr.M;
+  const float *lse = ptr.lse, *Dr = ptr.Dr;
+  const int h = it.h, head = it.head, bx = it.bx;
+  const DkvGroup grp = dkv_group(a.lg_bk - (h - 1), a.nk, a.small_keys);
+  const int G = grp.G, pieces = grp.pieces, keys = FULL ? KEYS : grp.keys;
   const int hq = head % a.Hq, b = head / a.Hq;
   const int hk = hq / (a.Hq / a.Hkv);
   const int lg_th = a.lg_bk - (h - 1), span = 1 << (h - 1);
-  const int j0 = (bx / pieces) * G, koff = (bx % pieces) * KH * 32;   // first block; first key inside it
+  const int j0 = (bx / pieces) * G, koff = (bx % pieces) * keys;       // first block; first key inside it
   const int64_t qhead = (int64_t)b * a.Hq + hq, khead = (int64_t)b * a.Hkv + hk;
   const bf16_t* kbase = h == 1 ? K + khead * (int64_t)a.N * D : Kp + a.lvl_off[h] + khead * ((int64_t)a.nk << lg_th) * D;
   const bf16_t* vbase = h == 1 ? V + khead * (int64_t)a.N * D : Vp + a.lvl_off[h] + khead * ((int64_t)a.nk << lg_th) * D;
 
-  // this lane's pooled key (B operands of both first products): key koff + kh*32 + l32 of the group
-  const int key = koff + kh * 32 + l32;
-  const int kblk = key >> lg_th;                  // its block within the group
-  const int prow = (j0 << lg_th) + key;
-  const int first = prow * span;
-  int ctok = a.N - first;
-  ctok = ctok < 0 ? 0 : (ctok > span ? span : ctok);
-  const bool valid = kblk < G && j0 + kblk < a.nk && ctok > 0;
-  const float bias2 = valid ? __log2f((float)ctok) : -INFINITY;
-  const int last = first + (ctok > 0 ? ctok : 1) - 1;
-  // the blocks this wavefront's 32 keys belong to, as bits of a stage's block mask
-  const int wb0 = (koff + kh * 32) >> lg_th, wb1 = (koff + kh * 32 + 31) >> lg_th;
-  const uint32_t wave_bits = wb0 < G ? (((2u << (wb1 < G ? wb1 : G - 1)) - 1u) & ~((1u << wb0) - 1u)) : 0u;
-  bf16x8 kf[KS], vf[KS];                          // vf: only the dKbar half multiplies by it
+  // This lane's two pooled keys (B operands of the first products, 16 keys each): key l16 of tile `pair` + u * 2
+  bf16x8 kf[2][KS], vf[2][KS];
+  [[maybe_unused]] int seen_from[2], kblk[2];      // causal: the key's last token - 4 g (rows from there on see it)
+  uint32_t tile_bits[2];                           // the blocks that the tile's keys belong to
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    u32x4 x = {0u, 0u, 0u, 0u}, y = {0u, 0u, 0u, 0u};
-    if (valid) {
-      x = *reinterpret_cast<const u32x4*>(kbase + (int64_t)prow * D + ks * 16 + hf * 8);
-      if (role == 0) y = *reinterpret_cast<const u32x4*>(vbase + (int64_t)prow * D + ks * 16 + hf * 8);
+  for (int u = 0; u < 2; ++u) {
+    const int t0 = koff + (pair + u * 2) * 16, key = t0 + l16;
+    kblk[u] = key >> lg_th;                        // the key's block within the group
+    const int prow = (j0 << lg_th) + key, first = prow * span;
+    int ctok = a.N - first;
+    ctok = ctok < 0 ? 0 : (ctok > span ? span : ctok);
+    const bool valid = kblk[u] < G && j0 + kblk[u] < a.nk && ctok > 0 && (FULL || (pair + u * 2) * 16 < keys);
+    seen_from[u] = first + (ctok > 0 ? ctok : 1) - 1 - g * 4;
+    const int wb0 = t0 >> lg_th, wb1 = (t0 + 15) >> lg_th;
+    tile_bits[u] = wb0 < G && (FULL || (pair + u * 2) * 16 < keys) ? ((2u << (wb1 < G ? wb1 : G - 1)) - 1u) & ~((1u << wb0) - 1u) : 0u;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      u32x4 x = {0u, 0u, 0u, 0u}, y = {0u, 0u, 0u, 0u};
+      if (valid) {
+        x = *reinterpret_cast<const u32x4*>(kbase + (int64_t)prow * D + ks * 32 + g * 8);
+        y = *reinterpret_cast<const u32x4*>(vbase + (int64_t)prow * D + ks * 32 + g * 8);
+      }
+      kf[u][ks] = __builtin_bit_cast(bf16x8, x);
+      vf[u][ks] = __builtin_bit_cast(bf16x8, y);
     }
-    kf[ks] = __builtin_bit_cast(bf16x8, x);
-    vf[ks] = __builtin_bit_cast(bf16x8, y);
   }
   // The operands are declared used here, so that the wait for their loads stands here and not at their
   // first use inside the stage loop, where it would also wait for the rows fetched ahead.
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) asm volatile("" ::"v"(kf[ks]), "v"(vf[ks]));
-  f32x16 acc[MD];                                 // dKbar^T or dVbar^T of this lane's key
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
-  for (int md = 0; md < MD; ++md)
+    for (int ks = 0; ks < KS; ++ks) asm volatile("" ::"v"(kf[u][ks]), "v"(vf[u][ks]));
+  f32x4 dk[2][MD], dv[2][MD];                      // dKbar^T, dVbar^T: channels md * 16 + g * 4 .. +3 of this lane's keys
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[md][v] = 0.f;
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int md = 0; md < MD; ++md) dk[u][md] = dv[u][md] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // ---- loads: instruction n = wave * NI + k covers 1024 bytes of LDS, RPI rows
-  const __amdgpu_buffer_rsrc_t qrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(Q + qhead * a.N * D), 0, (int)((uint32_t)a.N * (uint32_t)ROWB), 0x00020000);
-  const __amdgpu_buffer_rsrc_t grsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(dO + qhead * a.N * D), 0, (int)((uint32_t)a.N * (uint32_t)ROWB), 0x00020000);
-  const int lrow = lane / CPR;
-  int lane_chunk[NI];                              // byte offset inside its source row that this lane reads
+  // ---- loads: a wavefront fetches rows wave * WROWS .. of a stage, RPI rows per instruction
+  const rsrc_words qrsrc = make_rsrc(Q + qhead * a.N * D, (uint32_t)a.N * (uint32_t)ROWB), grsrc = make_rsrc(dO + qhead * a.N * D, (uint32_t)a.N * (uint32_t)ROWB);
+  // chunk number c of the walk: 32 rows of the query block kept[c / cpe]
+  const int cpe = (a.bq + 31) >> 5;
+  auto entry_of = [&](int c) __attribute__((always_inline)) { return a.lg_cpe >= 0 ? c >> a.lg_cpe : c / cpe; };
+  const rsrc_words lrsrc = make_rsrc(lse + qhead * a.N, (uint32_t)a.N * 4u), drsrc = make_rsrc(Dr + qhead * a.N, (uint32_t)a.N * 4u);
+  struct Part { int row, valid; };                 // WROWS rows of a query block: the first one, and how many there are
+  auto part_of = [&](int c) __attribute__((always_inline)) -> Part {
+    const int e = entry_of(c);
+    const int blk = __builtin_amdgcn_readfirstlane((int)kept_row[e]), sub = (c - e * cpe) * 32 + wave * WROWS % 32;
+    int end = a.N - blk * a.bq;
+    end = end < a.bq ? end : a.bq;
+    return Part{blk * a.bq + sub, end - sub};
+  };
+  auto fire = [&](int c0, int total, int to) __attribute__((always_inline)) {
+    const int c = c0 + wave * WROWS / 32;
+    if (c >= total) return;
+    const Part p = part_of(c);
+    const int ln = lane_again(), lrow = ln / CPR;
+    // byte offset that this lane reads with load 0; with load k, RPI rows further down: ^ row_swizzle(k * RPI) << 4
+    const uint32_t lane_off = lrow * ROWB + (((ln % CPR) ^ row_swizzle<D>(lrow)) << 4);
+    const uint32_t dst = to * BUFB + wave * NI * 1024, st = OFF_STAT + to * STATB + wave * WROWS * 4;
+    if (p.valid >= WROWS) {
+      each<NI>([&](auto tag) __attribute__((always_inline)) {
+        constexpr int k = decltype(tag)::value;
+        const int v = (int)flip<(row_swizzle<D>(k * RPI) << 4)>(lane_off), at = (p.row + k * RPI) * ROWB;
+        load_lds16(qrsrc, dst + k * 1024, v, at);
+        load_lds16(grsrc, dst + k * 1024 + TILEB, v, at);
+      });
+    } else {
+      // past its end a block repeats its last row: the weights of the rows past it are 0, and what they multiply has to be a
+      // row that takes part anyway
+      each<NI>([&](auto tag) __attribute__((always_inline)) {
+        constexpr int k = decltype(tag)::value;
+        const int v = (int)flip<(row_swizzle<D>(k * RPI) << 4)>(lane_off);
+        const int r = k * RPI + lrow, at = (p.row + (r < p.valid ? r : p.valid - 1) - lrow) * ROWB + v;
+        load_lds16(qrsrc, dst + k * 1024, at, 0);
+        load_lds16(grsrc, dst + k * 1024 + TILEB, at, 0);
+      });
+    }
+    if (ln < WROWS) {                              // lse and -D of the rows
+      load_lds4(lrsrc, st, ln * 4, p.row * 4);
+      load_lds4(drsrc, st + 4 * ROWS, ln * 4, p.row * 4);
+    }
+  };
+  // ---- LDS addresses in buffer 0 of this wavefront's 32-row chunk: row fragments (k-step ks: ^ ks * 64), transposed ones
+  // (channels md * 16: ^ md * 32), statistics
+  int total = 0, at = 0;                           // chunks of the walk; buffer of the next stage
+  uint32_t rowaddr = (rh * 32 + l16) * ROWB + ((g ^ row_swizzle<D>(l16)) << 4);
+  uint32_t traddr = (rh * 32 + g * 4 + (l16 >> 2)) * ROWB + ((((l16 & 3) >> 1) ^ row_swizzle<D>(g * 4 + (l16 >> 2))) << 4) + (l16 & 1) * 8;
+
+  // One chunk of 32 rows (two row tiles of 16) against the tiles LO .. HI of this wavefront: 4 KS + 2 MD operand fragments,
+  // each requested PF fragments ahead of the MFMAs that read it, in the order
+  //   both tiles: S of row tile 0, dP of row tile 0, S of row tile 1, dP of row tile 1, dV, dK (two MFMAs a fragment)
+  //   one tile:   S of the row tiles in turn, dP of the row tiles in turn, dV, dK (one MFMA a fragment)
+  // Behind every fragment's MFMAs stands a slice of the vector work.  The reads are assembly with counted waits: left to the
+  // compiler every fragment was waited for right after its read (LDS latency: two thirds of the time).
+  auto chunk = [&](auto lo_tag, auto hi_tag, uint32_t bits, int row0) __attribute__((always_inline)) {
+    constexpr int LO = decltype(lo_tag)::value, HI = decltype(hi_tag)::value;
+    constexpr bool BOTH = LO != HI;
+    constexpr int NR = 4 * KS, NF = NR + 2 * MD, PF = BOTH ? 2 : 2, RING = PF + 1;
+    bf16x8 fr[RING], pf[2], df[2];
+    bs16x4 lo[RING], hi[RING];
+    f32x4 sc[2][2], dp[2][2], ls[2];                // [row tile][tile]
+    // a key counts only if its block is used.  (A pooled key's token count multiplies its gradients at the end; keys that do not exist
+    // get gradients that are dropped there.)
+    float off[2];
 #pragma unroll
-  for (int k = 0; k < NI; ++k) lane_chunk[k] = ((lane % CPR) ^ row_swizzle<D>((wave * NI + k) * RPI + lrow)) << 4;
-  struct Stage { int k, i, r0, seg; uint32_t bits; bool ok; };
-  float lreg = INFINITY, dreg = 0.f;
-  auto fire = [&](const Stage& st, unsigned char* dst) __attribute__((always_inline)) {
-    lds_void* q0 = (lds_void*)(dst);
-    lds_void* g0 = (lds_void*)(dst + TILEB);
-    auto load = [&](auto tag) __attribute__((always_inline)) {
-      constexpr int k = decltype(tag)::value;
-      if constexpr (k < NI) {
-        const int n = wave * NI + k;
-        int r = n * RPI + lrow;
-        // a short stage repeats its last row: the weights of the rows past it are 0, and what they multiply has to be a
-        // row that takes part anyway
-        if (st.seg < ROWS) r = r < st.seg ? r : st.seg - 1;
-        const int at = (st.r0 + r) * ROWB + lane_chunk[k];
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(qrsrc, (lds_void*)((lds_byte*)q0 + n * 1024), 16, at, 0, 0, 0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(grsrc, (lds_void*)((lds_byte*)g0 + n * 1024), 16, at, 0, 0, 0);
+    for (int u = LO; u <= HI; ++u) off[u] = FULL || ((bits >> kblk[u]) & 1u) != 0u ? 0.f : -INFINITY;
+    // row fragment j: product (0: S, 1: dP), row tile, k-step
+    constexpr auto prod = [](int j) { return BOTH ? (j / KS) & 1 : j / (2 * KS); };
+    constexpr auto rtile = [](int j) { return BOTH ? j / (2 * KS) : j & 1; };
+    constexpr auto kstep = [](int j) { return BOTH ? j % KS : (j % (2 * KS)) >> 1; };
+    // slot in which the statistics of row tile 1 are requested, ahead of that slot's fragment
+    constexpr int SR = BOTH ? 3 * KS - PF : -1;
+    constexpr auto later = [](int j) {               // LDS reads issued behind those of fragment j when it is waited for
+      int n = 0;
+      for (int i = j + 1; i <= j + PF && i < NF; ++i) n += i < NR ? 1 : 2;
+      if (BOTH && SR + PF - 1 >= j && SR <= j) n += 3;   // (they stand between the fragments SR + PF - 1 and SR + PF)
+      return n;
+    };
+    auto request = [&](auto tag) __attribute__((always_inline)) {
+      constexpr int j = decltype(tag)::value;
+      if constexpr (j < NR) {
+        lds_read<prod(j) * TILEB + rtile(j) * 16 * ROWB>(fr[j % RING], flip<kstep(j) * 64>(rowaddr));
+      } else if constexpr (j < NF) {
+        constexpr int md = (j - NR) % MD, off = j - NR < MD ? TILEB : 0;
+        const uint32_t x = flip<md * 32>(traddr);
+        lds_read_t<off>(lo[j % RING], x);
+        lds_read_t<off + 16 * ROWB>(hi[j % RING], x);
       }
     };
-    static_assert(NI <= 4, "loads below");
-    load(std::integral_constant<int, 0>{});
-    load(std::integral_constant<int, 1>{});
-    load(std::integral_constant<int, 2>{});
-    load(std::integral_constant<int, 3>{});
-    if (tid < ROWS) {
-      const int64_t row = qhead * a.N + st.r0 + tid;
-      lreg = tid < st.seg ? lse[row] * LOG2E : INFINITY;
-      dreg = tid < st.seg ? Dr[row] : 0.f;
-    }
-  };
-  // ---- LDS addresses inside a tile: this wavefront's first 32-row chunk
-  int rowaddr[KS], traddr[MD];
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) rowaddr[ks] = (rh * 32 + l32) * ROWB + (((2 * ks + hf) ^ row_swizzle<D>(l32)) << 4);
-  {
-    const int grp = lane >> 4, s16 = lane & 15, row = hf * 4 + (s16 >> 2);
-#pragma unroll
-    for (int md = 0; md < MD; ++md)
-      traddr[md] = (rh * 32 + row) * ROWB + (((md * 4 + (grp & 1) * 2 + ((s16 & 3) >> 1)) ^ row_swizzle<D>(row)) << 4) + (s16 & 1) * 8;
-  }
-  // channels md*32 .. +31 of rows r0 .. r0+15, transposed: the order in which pack_b lays the rows out.  Eight rows
-  // further down the swizzle differs in one bit.
-  auto frag_t = [&](const unsigned char* tile, int r0, int md) __attribute__((always_inline)) -> bf16x8 {
-    const bs16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bs16x4*)(tile + traddr[md] + r0 * ROWB));
-    const bs16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bs16x4*)(tile + (traddr[md] ^ 32) + (r0 + 8) * ROWB));
-    return __builtin_bit_cast(bf16x8, (bs16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-  };
-  // one stage: cur has been requested into `now`, the stage after it goes into `later`
-  int nkept = 0;
-  auto settle = [&](Stage st) __attribute__((always_inline)) -> Stage {   // first existing stage at or after (k, r0)
-    for (; st.k < nkept; ++st.k, st.r0 = -1) {
-      const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)kept[st.k]);   // the same for every lane: scalar from here on
-      st.i = (int)(w & 0xffffu);
-      st.bits = w >> 16;
-      int row_end = (st.i + 1) * a.bq;
-      row_end = row_end < a.N ? row_end : a.N;
-      if (st.r0 < 0) st.r0 = st.i * a.bq;
-      if (st.r0 < row_end) {
-        st.seg = row_end - st.r0 < ROWS ? row_end - st.r0 : ROWS;
-        st.ok = true;
-        return st;
+    // lse of a row tile's rows, and -D straight into the accumulators of dP
+    auto request_stat = [&](auto rt_tag) __attribute__((always_inline)) {
+      constexpr int rt = decltype(rt_tag)::value;
+      const uint32_t staddr = OFF_STAT + at * STATB + rh * 128 + (lane_again() & 0x30);
+      lds_read<rt * 64>(ls[rt], staddr);
+      lds_read<4 * ROWS + rt * 64>(dp[rt][LO], staddr);
+      if constexpr (BOTH) lds_read<4 * ROWS + rt * 64>(dp[rt][HI], staddr);
+    };
+    // weight number e of a row tile: tile LO + e / 4, row g * 4 + e % 4
+    auto weight = [&](auto rt_tag, auto e_tag) __attribute__((always_inline)) {
+      constexpr int rt = decltype(rt_tag)::value, e = decltype(e_tag)::value, u = LO + e / 4, v = e % 4;
+      if constexpr (u == LO) ls[rt][v] *= -LOG2E;
+      float x = fmaf(sc[rt][u][v], a.scale_log2, FULL ? ls[rt][v] : ls[rt][v] + off[u]);
+      if (CAUSAL) x = seen_from[u] > row0 + (rt * 16 + v) ? -INFINITY : x;
+      sc[rt][u][v] = __builtin_amdgcn_exp2f(x);
+      if constexpr (v & 1) {
+        pf[u][rt * 4 + v - 1] = (__bf16)sc[rt][u][v - 1];
+        pf[u][rt * 4 + v] = (__bf16)sc[rt][u][v];
       }
-    }
-    st.ok = false;
-    return st;
+    };
+    auto dscore = [&](auto rt_tag, auto e_tag) __attribute__((always_inline)) {
+      constexpr int rt = decltype(rt_tag)::value, e = decltype(e_tag)::value, u = LO + e / 4, v = e % 4;
+      sc[rt][u][v] *= dp[rt][u][v];
+      if constexpr (v & 1) {
+        df[u][rt * 4 + v - 1] = (__bf16)sc[rt][u][v - 1];
+        df[u][rt * 4 + v] = (__bf16)sc[rt][u][v];
+      }
+    };
+    // f(0) .. f(7) spread over the slots FROM .. TO - 1
+    auto spread = [&](auto slot_tag, auto from_tag, auto to_tag, auto&& f) __attribute__((always_inline)) {
+      constexpr int J = decltype(slot_tag)::value, FROM = decltype(from_tag)::value, TO = decltype(to_tag)::value;
+      if constexpr (J >= FROM && J < TO)
+        each<8>([&](auto e_tag) __attribute__((always_inline)) {
+          constexpr int e = decltype(e_tag)::value;
+          if constexpr (e >= 8 * (J - FROM) / (TO - FROM) && e < 8 * (J + 1 - FROM) / (TO - FROM)) f(e_tag);
+        });
+    };
+    const std::integral_constant<int, 0> c0;
+    const std::integral_constant<int, 1> c1;
+    __builtin_amdgcn_sched_barrier(0);
+    request_stat(c0);
+    if constexpr (!BOTH) request_stat(c1);
+    each<PF>([&](auto tag) __attribute__((always_inline)) { request(tag); });
+    each<NF>([&](auto tag) __attribute__((always_inline)) {
+      constexpr int j = decltype(tag)::value;
+      if constexpr (j == SR) request_stat(c1);
+      request(std::integral_constant<int, j + PF>{});
+      if constexpr (j < NR) {
+        constexpr int rt = rtile(j), ks = kstep(j);
+        // (the statistics read before this fragment have arrived with it)
+        if constexpr (prod(j) == 0) lds_wait<later(j)>(fr[j % RING], ls[rt]);
+        else lds_wait<later(j)>(fr[j % RING], dp[rt][LO], dp[rt][HI]);
+#pragma unroll
+        for (int u = LO; u <= HI; ++u) {
+          if (prod(j) == 0) sc[rt][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[j % RING], kf[u][ks], ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sc[rt][u], 0, 0, 0);
+          else dp[rt][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[j % RING], vf[u][ks], dp[rt][u], 0, 0, 0);
+        }
+      } else {
+        constexpr int md = (j - NR) % MD;
+        lds_wait<later(j)>(lo[j % RING], hi[j % RING]);
+        const bf16x8 f = __builtin_bit_cast(bf16x8, (bs16x8)__builtin_shufflevector(lo[j % RING], hi[j % RING], 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+        for (int u = LO; u <= HI; ++u) {
+          if (j - NR < MD) dv[u][md] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, pf[u], dv[u][md], 0, 0, 0);
+          else dk[u][md] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, df[u], dk[u][md], 0, 0, 0);
+        }
+      }
+      auto range = [&](auto from, auto to, auto&& f) __attribute__((always_inline)) { spread(tag, from, to, f); };
+      using std::integral_constant;
+      if constexpr (BOTH) {
+        range(integral_constant<int, KS + 1>{}, integral_constant<int, 2 * KS>{}, [&](auto e) __attribute__((always_inline)) { weight(c0, e); });
+        range(integral_constant<int, 2 * KS>{}, integral_constant<int, 3 * KS - KS / 2>{}, [&](auto e) __attribute__((always_inline)) { dscore(c0, e); });
+        range(integral_constant<int, 3 * KS + 1>{}, integral_constant<int, 4 * KS>{}, [&](auto e) __attribute__((always_inline)) { weight(c1, e); });
+        range(integral_constant<int, 4 * KS + 1>{}, integral_constant<int, 4 * KS + MD>{}, [&](auto e) __attribute__((always_inline)) { dscore(c1, e); });
+      } else {                                       // (four weights a row tile)
+        range(integral_constant<int, 2 * KS + 1>{}, integral_constant<int, 4 * KS>{}, [&](auto e) __attribute__((always_inline)) {
+          weight(integral_constant<int, decltype(e)::value / 4>{}, integral_constant<int, decltype(e)::value % 4>{});
+        });
+        range(integral_constant<int, 4 * KS + 1>{}, integral_constant<int, 4 * KS + MD>{}, [&](auto e) __attribute__((always_inline)) {
+          dscore(integral_constant<int, decltype(e)::value / 4>{}, integral_constant<int, decltype(e)::value % 4>{});
+        });
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
   };
-  Stage cur;
-  auto step = [&](const unsigned char* now, float* stat, unsigned char* later) __attribute__((always_inline)) {
-    Stage nxt = cur;
-    nxt.r0 += ROWS;
-    nxt = settle(nxt);
+  // one stage: its chunks have been requested into buffer `at`, those of the stage after it go into the other one
+  auto step = [&](int c0) __attribute__((always_inline)) {
     // this wavefront's part of the stage has landed; behind the barrier everyone's has, and the other buffer is
     // no longer being read
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (tid < ROWS) {
-      stat[tid] = lreg;
-      stat[ROWS + tid] = dreg;
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    if (nxt.ok) fire(nxt, later);
-    const unsigned char* Qs = now;
-    const unsigned char* Gs = now + TILEB;
-    const float* lse_s = stat;                                             // log2 domain, +inf for rows that do not exist
-    const float* D_s = stat + ROWS;
-    const unsigned char* Ts = role == 0 ? Qs : Gs;                         // dKbar^T += Q^T dS, dVbar^T += dO^T P
-    // this lane's key counts only if its block is used by this query block
-    const float bias_on = ((cur.bits >> kblk) & 1u) != 0u ? bias2 : -INFINITY;
-    if ((cur.bits & wave_bits) != 0u) {                                    // ... and so is one of this wavefront's
-#pragma unroll
-      for (int cc = 0; cc < 2 / RH; ++cc) {                                 // this wavefront's 32-row chunks
-        const int c = rh + cc * RH;
-        if (c * 32 >= cur.seg) break;
-        f32x16 sc;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) sc[v] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(Qs + rowaddr[ks] + cc * RH * 32 * ROWB), kf[ks], sc, 0, 0, 0);
-        // this lane: key `key`, rows c*32 + (v/4)*8 + hf*4 + v%4
-        float w[16];                               // P, or dS for the dKbar half
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-          const int r = c * 32 + g4 * 8 + hf * 4;
-          const f32x4 ls = *reinterpret_cast<const f32x4*>(lse_s + r);
-#pragma unroll
-          for (int e4 = 0; e4 < 4; ++e4) {
-            float x = fmaf(sc[g4 * 4 + e4], a.scale_log2, bias_on) - ls[e4];
-            if (CAUSAL) x = last > cur.r0 + r + e4 ? -INFINITY : x;
-            w[g4 * 4 + e4] = __builtin_amdgcn_exp2f(x);
-          }
+    if (c0 + wave * WROWS / 32 < total) {
+      const Part p = part_of(c0 + wave * WROWS / 32);
+      if (p.valid < WROWS) {                       // rows past the end of the query block: weight 0
+        const int ln = lane_again();
+        float* stat = reinterpret_cast<float*>(smem + OFF_STAT + at * STATB);
+        if (ln < WROWS && ln >= p.valid) {
+          stat[wave * WROWS + ln] = INFINITY;
+          stat[ROWS + wave * WROWS + ln] = 0.f;
         }
-        if (role == 0) {
-          f32x16 dp;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) dp[v] = 0.f;
-#pragma unroll
-          for (int ks = 0; ks < KS; ++ks)
-            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(Gs + rowaddr[ks] + cc * RH * 32 * ROWB), vf[ks], dp, 0, 0, 0);
-#pragma unroll
-          for (int g4 = 0; g4 < 4; ++g4) {
-            const f32x4 dd = *reinterpret_cast<const f32x4*>(D_s + c * 32 + g4 * 8 + hf * 4);
-#pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4) w[g4 * 4 + e4] *= dp[g4 * 4 + e4] - dd[e4];
-          }
-        }
-        bf16x8 wf[2];
-        pack_b(w, wf[0], wf[1]);
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-          for (int md = 0; md < MD; ++md)
-            acc[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_t(Ts, cc * RH * 32 + ks * 16, md), wf[ks], acc[md], 0, 0, 0);
       }
     }
-    cur = nxt;
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    fire(c0 + CHUNKS, total, at ^ 1);
+    const int c = c0 + rh;
+    if (c < total) {
+      const int e = entry_of(c);
+      const uint32_t bits = (uint32_t)__builtin_amdgcn_readfirstlane((int)kept_bits[e]);
+      int row0 = 0;
+      if (CAUSAL) row0 = __builtin_amdgcn_readfirstlane((int)kept_row[e]) * a.bq + (c - e * cpe) * 32;
+      const std::integral_constant<int, 0> t0;
+      const std::integral_constant<int, 1> t1;
+      if constexpr (FULL) {
+        chunk(t0, t1, bits, row0);
+      } else {
+        if ((bits & tile_bits[0]) != 0u) chunk(t0, t0, bits, row0);
+        if ((bits & tile_bits[1]) != 0u) chunk(t1, t1, bits, row0);
+      }
+    }
+    rowaddr ^= BUFB;
+    traddr ^= BUFB;
+    at ^= 1;
   };
 
   for (int e_lo = 0; e_lo < a.nq; e_lo += DKV_LIST) {
+    const int tid = wave * 64 + lane_again(), lane = tid & 63;
     // The columns of the level map: which of the next query blocks of this query head use any of the group's key blocks
     // at this level, as an ordered list in LDS with the blocks used as a bit mask (one round of independent
     // loads per NT entries; a walk that tests one entry after the other spends a memory latency on each of them).
-    nkept = 0;
+    int nkept = 0;
     const int e_hi = e_lo + DKV_LIST < a.nq ? e_lo + DKV_LIST : a.nq;
     for (int e0 = e_lo; e0 < e_hi; e0 += NT) {
       const int e = e0 + tid;
       uint32_t bits = 0u;
       if (e < e_hi) {
         const uint8_t* mrow = M + (qhead * a.nq + e) * a.nk + j0;
-        for (int g = 0; g < G && j0 + g < a.nk; ++g) bits |= ((int)mrow[g] == h ? 1u : 0u) << g;
+        const int n = j0 + G < a.nk ? G : a.nk - j0;
+        if constexpr (FULL) {
+          bits = (int)mrow[0] == h ? 1u : 0u;
+        } else {
+          for (int x0 = 0; x0 < n; x0 += 8) {      // eight loads in flight
+            int m[8];
+#pragma unroll
+            for (int x = 0; x < 8; ++x) m[x] = mrow[x0 + x < n ? x0 + x : n - 1];
+#pragma unroll
+            for (int x = 0; x < 8; ++x) bits |= (x0 + x < n && m[x] == h ? 1u : 0u) << (x0 + x);
+          }
+        }
       }
       const uint64_t mask = __ballot(bits != 0u);
       if (lane == 0) wcount[wave] = __popcll(mask);
       __syncthreads();                             // (and the list before is done with)
-      int base = nkept, total = 0;
+      int base = nkept, found = 0;
 #pragma unroll
       for (int w = 0; w < NW; ++w) {
         base += w < wave ? wcount[w] : 0;
-        total += wcount[w];
+        found += wcount[w];
       }
-      if (bits) kept[base + __popcll(mask & ((1ull << lane) - 1ull))] = (uint32_t)e | (bits << 16);
-      nkept += total;
+      if (bits) {
+        const int at = base + __popcll(mask & ((1ull << lane) - 1ull));
+        kept_bits[at] = bits;
+        kept_row[at] = (uint16_t)e;
+      }
+      nkept += found;
       __syncthreads();
     }
-    cur = settle(Stage{0, 0, -1, 0, 0u, false});
-    if (cur.ok) fire(cur, buf0);
-    while (cur.ok) {
-      step(buf0, stat0, buf1);
-      if (!cur.ok) break;
-      step(buf1, stat1, buf0);
-    }
-    __syncthreads();                               // everyone has read the last stage: buf0 may be filled again
+    total = __builtin_amdgcn_readfirstlane(nkept) * cpe;
+    fire(0, total, at);
+    for (int c0 = 0; c0 < total; c0 += CHUNKS) step(c0);
+    __syncthreads();                               // everyone has read the last stage: the buffers may be filled again
   }
-  // partial sums of the wavefronts that share a key tile -> LDS [wavefront of the half][key][channel],
-  // added in a fixed order, first dKbar, then dVbar; lane (key, hf) holds channels
-  // md*32 + (v/4)*8 + hf*4 + v%4.  Every pooled key of the group is written (zeros where no query block
-  // used it).
-  auto red = [&](int w) __attribute__((always_inline)) {                    // 32 x D floats of wavefront w of a half: two fit a buffer
-    return reinterpret_cast<float*>((w < 2 ? buf0 : buf1) + (w & 1) * 32 * D * 4);
+  // The two row halves' partial sums -> LDS [half][pair][tile][key][channel], added in a fixed order, first dKbar, then
+  // dVbar.  Every pooled key of the group is written (zeros where no query block used it).
+  const int tid = wave * 64 + lane_again(), l16e = tid & 15, ge = (tid & 63) >> 4;
+  auto red = [&](int half, int p, int u) __attribute__((always_inline)) {   // 16 x D floats
+    return reinterpret_cast<float*>(smem + ((half * 2 + p) * 2 + u) * 16 * D * 4);
   };
+  static_assert(2 * 2 * 2 * 16 * D * 4 <= OFF_STAT, "the partial sums fit the buffers");
+#pragma unroll
   for (int which = 0; which < 2; ++which) {
     __syncthreads();
-    if (role == which) {
 #pragma unroll
-      for (int md = 0; md < MD; ++md)
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          f32x4 x;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) x[e] = acc[md][4 * g + e];
-          *reinterpret_cast<f32x4*>(red(w2) + (l32 * D + ((md * 32 + g * 8 + hf * 4) ^ ((l32 & 7) << 2)))) = x;   // (rows spread over the banks)
-        }
-    }
+      for (int md = 0; md < MD; ++md)              // (rows spread over the banks)
+        *reinterpret_cast<f32x4*>(red(rh, pair, u) + (l16e * D + ((md * 16 + ge * 4) ^ (l16e << 2)))) = which ? dv[u][md] : dk[u][md];
     __syncthreads();
-    float* dst = (which ? dVp : dKp) + a.glvl_off[h] + (qhead * ((int64_t)a.nk << lg_th) + ((int64_t)j0 << lg_th)) * D;
-    const float mul = which ? 1.f : a.scale;
-    for (int x = tid; x < KH * 32 * (D / 4); x += NT) {
+    float* dst = (which ? ptr.dVp : ptr.dKp) + a.glvl_off[h] + (qhead * ((int64_t)a.nk << lg_th) + ((int64_t)j0 << lg_th)) * D;
+    for (int x = tid; x < keys * (D / 4); x += NT) {
       const int kk = x / (D / 4), c4 = x % (D / 4);     // key of the workgroup, group of four channels
       const int blk = (koff + kk) >> lg_th;
       if (blk >= G || j0 + blk >= a.nk) continue;
-      const int g2 = kk / 32, k32 = kk % 32;
-      f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int r = 0; r < RH; ++r) sum += *reinterpret_cast<const f32x4*>(red(r * KH + g2) + (k32 * D + ((c4 * 4) ^ ((k32 & 7) << 2))));
-      *reinterpret_cast<f32x4*>(dst + (int64_t)(koff + kk) * D + c4 * 4) = sum * mul;
+      const int t = kk >> 4, k16 = kk & 15, at = k16 * D + ((c4 * 4) ^ (k16 << 2));
+      const f32x4 sum = *reinterpret_cast<const f32x4*>(red(0, t & 1, t >> 1) + at) + *reinterpret_cast<const f32x4*>(red(1, t & 1, t >> 1) + at);
+      int ctok = a.N - ((j0 << lg_th) + koff + kk) * span;      // tokens under the key
+      ctok = ctok < 0 ? 0 : (ctok > span ? span : ctok);
+      const f32x4 none = {0.f, 0.f, 0.f, 0.f};
+      *reinterpret_cast<f32x4*>(dst + (int64_t)(koff + kk) * D + c4 * 4) = ctok > 0 ? sum * ((float)ctok * (which ? 1.f : a.scale)) : none;
     }
   }
+}
+
+// One launch covers all levels.  Workgroup ids are dealt round-robin to the 8 XCDs.  Each XCD takes one contiguous run of a
+// level's (head, key block) items, so that what runs on it at one time are columns of one head and level, of
+// like length, whose query rows meet in its L2; or all XCDs take the same head, a block each in turn (one_head, see
+// launch_bwd_mfma_t).  An XCD's items, level after level from the coarsest down, are its slots.
+__device__ __forceinline__ bool dkv_item(const BwdMfmaArgs& a, int xcd, int slot, DkvItem& it) {
+  for (int h = a.H; h >= 1; --h) {
+    const int ng = dkv_group(a.lg_bk - (h - 1), a.nk, a.small_keys).ng, items = a.B * a.Hq * ng, run = (items + 7) >> 3;
+    if (slot >= run) {
+      slot -= run;
+      continue;
+    }
+    const int item = a.one_head ? slot * 8 + xcd : xcd * run + slot;
+    it = {h, item / ng, item % ng};
+    return item < items;
+  }
+  return false;
+}
+
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__((DkvShape<D>::NT), (DkvShape<D>::WPS)) void bwd_dkv_mfma_kernel(DkvPtrs ptr, BwdMfmaArgs a) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[DkvShape<D>::LDSB];
+  const int xcd = (int)(blockIdx.x & 7);
+  const int slot = (int)(blockIdx.x >> 3);
+  DkvItem it;
+  if (!dkv_item(a, xcd, slot, it)) return;
+  if (a.lg_bk - (it.h - 1) >= 6) dkv_body<D, true, CAUSAL>(smem, ptr, a, it);
+  else dkv_body<D, false, CAUSAL>(smem, ptr, a, it);
 }
 
 // (32-bit byte offsets reach every row of a head: at most 65535 key blocks of 128 keys of 256 bytes are less than 2^31.
 // Addresses need no more than element alignment, in the direct-to-LDS loads as in all others.)
 bool bwd_uses_mfma(const Plan& pl) {
   return pl.dtype == PSA_BF16 && pl.bk >= 8 && pl.bk <= 128 && (pl.d == 64 || pl.d == 128) &&
-         pl.nq <= 8192;                            // a query block's number and its 16 block bits share a list entry
-}
-
-// levels h_lo .. h_hi in one launch (they share KH)
-template <int D, int KH>
-static hipError_t launch_dkv_t(const Plan& pl, const BwdMfmaArgs& a, const bf16_t* q, const bf16_t* k, const bf16_t* v,
-                               const bf16_t* kp, const bf16_t* vp, const uint8_t* M, const float* lse, const float* Dr,
-                               const bf16_t* go, float* dKp, float* dVp, int h_lo, int h_hi, hipStream_t s) {
-  int groups = 0;                                // as the kernel counts them
-  for (int h = h_lo; h <= h_hi; ++h) {
-    const int th = pl.bk >> (h - 1);
-    int G = KH * 32 / th;                        // key blocks per workgroup
-    G = G < 1 ? 1 : (G > 16 ? 16 : G);
-    const int pieces = th > KH * 32 ? th / (KH * 32) : 1;
-    groups += (pl.B * pl.Hq * pieces * ((pl.nk + G - 1) / G) + 7) / 8;
-  }
-  if (pl.causal) bwd_dkv_mfma_kernel<D, KH, true><<<8 * groups, DkvShape<D, KH>::NT, 0, s>>>(q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h_lo, h_hi, a);
-  else bwd_dkv_mfma_kernel<D, KH, false><<<8 * groups, DkvShape<D, KH>::NT, 0, s>>>(q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h_lo, h_hi, a);
-  return hipGetLastError();
+         pl.nq <= 8192;                            // (the bound that the header states)
 }
 
 template <int D>
@@ -665,6 +816,10 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
   a.H = pl.H; a.causal = pl.causal; a.scale = pl.scale; a.scale_log2 = pl.scale * LOG2E;
   a.lg_bk = 0;
   while ((1 << a.lg_bk) < pl.bk) ++a.lg_bk;
+  const int cpe = (pl.bq + 31) / 32;
+  a.lg_cpe = 0;
+  while ((1 << a.lg_cpe) < cpe) ++a.lg_cpe;
+  if ((1 << a.lg_cpe) != cpe) a.lg_cpe = -1;
   // With a run of items to each XCD the Q and dO of eight heads are in flight, which the memory-side cache (256 MB) has to
   // hold; with all XCDs on one head it holds them at any length.  Whole call, ms for runs / one head, not causal, d = 128: 12 heads x
   // 16000 tokens 2.21 / 2.30, x 32760 8.90 / 8.95, x 40000 13.6 / 13.4, 24 x 60000 60.3 / 58.9, 40 x 75600 160 / 155, 24 x 100000 174 / 162,
@@ -693,25 +848,22 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
                                                                                  static_cast<bf16_t*>(dQ), a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // KH of level h.  d = 64: a 128-key block goes to two workgroups of 64 keys (four wavefronts, three of
-  // them per SIMD) rather than one of eight wavefronts that would have a compute unit to itself: 83 -> 55 ms
-  // at the 131072-token shape, although both then stage the block's query rows.
-  auto tiles_of = [&](int h) {
-    const int th = pl.bk >> (h - 1);
-    if (D == 64 && th > 64) return 2;
-    return th > 64 ? 4 : (th > 32 ? 2 : 1);
+  auto groups = [&](int small_keys) {            // workgroups of an XCD, as the kernel counts them
+    int64_t n = 0;
+    for (int h = 1; h <= pl.H; ++h) n += ((int64_t)pl.B * pl.Hq * dkv_group(a.lg_bk - (h - 1), pl.nk, small_keys).ng + 7) / 8;
+    return n;
   };
-  for (int h = 1; h <= pl.H;) {
-    int h_hi = h;
-    while (h_hi < pl.H && tiles_of(h_hi + 1) == tiles_of(h)) ++h_hi;
-    const int kh = tiles_of(h);
-    if (D == 128 && kh == 4) e = launch_dkv_t<D, D == 128 ? 4 : 2>(pl, a, q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h, h_hi, s);
-    else if (kh == 2) e = launch_dkv_t<D, 2>(pl, a, q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h, h_hi, s);
-    else e = launch_dkv_t<D, 1>(pl, a, q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, h, h_hi, s);
-    if (e != hipSuccess) return e;
-    h = h_hi + 1;
-  }
-  return hipSuccess;
+  // Where blocks have fewer than 64 pooled keys a workgroup takes 64 keys, or 32 (half of its tiles) while the longest walk (half of
+  // the query blocks, say) would end after the work that there is for every resident workgroup (walks of a fifth of the query blocks,
+  // a tenth if causal; what a workgroup costs besides is worth four).  Whole call, us for 64 / 32, d = 128, four levels: 2 heads x 3000 tokens 130 / 109,
+  // x 8000 291 / 235, x 20000 740 / 650; 12 x 3000 169 / 179, x 8000 648 / 688, 28 grouped causal x 8000 982 / 1029; d = 64 2 x 8000 201 / 163, 12 x 8000 342 / 349.
+  const int64_t resident = 256 * DkvShape<D>::WPS, walk = pl.nq / (pl.causal ? 10 : 5) + 4;
+  a.small_keys = groups(64) * 8 * walk < resident * (pl.nq / 2 + 4) ? 32 : 64;
+  const DkvPtrs ptr = {q, k, v, kp, vp, go, M, lse, Dr, dKp, dVp};
+  const int pitch = (int)groups(a.small_keys);
+  if (pl.causal) bwd_dkv_mfma_kernel<D, true><<<8 * pitch, DkvShape<D>::NT, 0, s>>>(ptr, a);
+  else bwd_dkv_mfma_kernel<D, false><<<8 * pitch, DkvShape<D>::NT, 0, s>>>(ptr, a);
+  return hipGetLastError();
 }
 
 // dQ, D = dO.O per row and the pooled gradients dKp, dVp of every level (bfloat16 inputs)
