@@ -789,14 +789,100 @@ __device__ __forceinline__ bool dkv_item(const BwdMfmaArgs& a, int xcd, int slot
 }
 
 template <int D, bool CAUSAL>
-__global__ __launch_bounds__((DkvShape<D>::NT), (DkvShape<D>::WPS)) void bwd_dkv_mfma_kernel(DkvPtrs ptr, BwdMfmaArgs a) {
+__global__ __launch_bounds__((DkvShape<D>::NT), (DkvShape<D>::WPS)) void bwd_dkv_mfma_kernel(DkvPtrs ptr, const uint32_t* __restrict__ order, BwdMfmaArgs a) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[DkvShape<D>::LDSB];
   const int xcd = (int)(blockIdx.x & 7);
-  const int slot = (int)(blockIdx.x >> 3);
+  int slot = (int)(blockIdx.x >> 3);
+  if (order) slot = (int)order[xcd * (int)(gridDim.x >> 3) + slot];
   DkvItem it;
   if (!dkv_item(a, xcd, slot, it)) return;
   if (a.lg_bk - (it.h - 1) >= 6) dkv_body<D, true, CAUSAL>(smem, ptr, a, it);
   else dkv_body<D, false, CAUSAL>(smem, ptr, a, it);
+}
+
+// The walks of an XCD differ in length (12 heads x 32760 tokens: 7 to 171 query blocks on level 1, 205 to 242 on level 4), so the long ones are
+// started first: in the order of the slots the last walks ended 1.2 to 1.4 times the mean later, 1.8 to 2.3 times in causal problems.
+// bwd_dkv_length_kernel counts the query blocks of every item (64 columns of the level map a workgroup, the rows dealt to its
+// wavefronts), bwd_dkv_order_kernel sorts each XCD's slots into classes of length, half an octave each (within a class as they
+// come: neighbours in the key sequence stay close).  Both are latency: 4 us each.
+constexpr int LEN_WAVES = 8;
+__global__ __launch_bounds__(LEN_WAVES * 64) void bwd_dkv_length_kernel(const uint8_t* __restrict__ M, uint32_t* __restrict__ len, int pitch, BwdMfmaArgs a) {
+  __shared__ int part[LEN_WAVES][PSA_MAX_LEVELS][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, head = blockIdx.z * a.Hq + blockIdx.y, j = blockIdx.x * 64 + lane;
+  const uint8_t* col = M + (int64_t)head * a.nq * a.nk + (j < a.nk ? j : a.nk - 1);
+  int n[PSA_MAX_LEVELS];
+  uint64_t mates[PSA_MAX_LEVELS];                  // the lanes whose blocks share a workgroup with this lane's
+#pragma unroll
+  for (int h = 1; h <= PSA_MAX_LEVELS; ++h) {
+    const int G = h <= a.H ? dkv_group(a.lg_bk - (h - 1), a.nk, a.small_keys).G : 1;
+    n[h - 1] = 0;
+    mates[h - 1] = ((1ull << G) - 1ull) << (lane / G * G);     // (G is a power of two, at most 32)
+  }
+  for (int e0 = wave; e0 < a.nq; e0 += LEN_WAVES * 8) {
+    int m[8];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      const int e = e0 + x * LEN_WAVES;
+      m[x] = e < a.nq && j < a.nk ? (int)col[(int64_t)e * a.nk] : 0;
+    }
+#pragma unroll
+    for (int h = 1; h <= PSA_MAX_LEVELS; ++h) {
+      if (h > a.H) break;
+#pragma unroll
+      for (int x = 0; x < 8; ++x) n[h - 1] += (__ballot(m[x] == h) & mates[h - 1]) != 0ull;
+    }
+  }
+#pragma unroll
+  for (int h = 1; h <= PSA_MAX_LEVELS; ++h) part[wave][h - 1][lane] = n[h - 1];
+  __syncthreads();
+  int base = 0;                                    // slots of the coarser levels
+  for (int h = a.H; h >= 1; --h) {
+    const DkvGroup g = dkv_group(a.lg_bk - (h - 1), a.nk, a.small_keys);
+    const int items = a.B * a.Hq * g.ng, run = (items + 7) >> 3;
+    if (wave == h % LEN_WAVES && j < a.nk && lane % g.G == 0) {
+      int sum = 0;
+      for (int w = 0; w < LEN_WAVES; ++w) sum += part[w][h - 1][lane];
+      // in fifths of a query block of a small block's walk; what a workgroup costs besides its walk is worth about three
+      const uint32_t cost = (uint32_t)(sum * (a.lg_bk - (h - 1) >= 6 ? 7 : 5) + 15);
+      for (int p = 0; p < g.pieces; ++p) {
+        const int item = head * g.ng + j / g.G * g.pieces + p;
+        const int xcd = a.one_head ? item & 7 : item / run, slot = a.one_head ? item >> 3 : item % run;
+        len[xcd * pitch + base + slot] = cost;
+      }
+    }
+    base += run;
+  }
+}
+
+constexpr int ORDER_CLASSES = 40;
+__global__ __launch_bounds__(1024) void bwd_dkv_order_kernel(const uint32_t* __restrict__ len, uint32_t* __restrict__ order, int pitch, BwdMfmaArgs a) {
+  __shared__ int count[ORDER_CLASSES];
+  const int xcd = blockIdx.x, tid = threadIdx.x;
+  auto class_of = [&](int slot) __attribute__((always_inline)) -> int {      // the longest walks: class 0
+    DkvItem it;
+    if (!dkv_item(a, xcd, slot, it)) return ORDER_CLASSES - 1;               // a slot without an item
+    const uint32_t c = len[xcd * pitch + slot];                              // 15 .. 7 * 8192 + 15
+    const int top = 31 - __clz((int)c), half = 2 * top + (int)((c >> (top - 1)) & 1u);
+    return ORDER_CLASSES - 2 - half;
+  };
+  if (tid < ORDER_CLASSES) count[tid] = 0;
+  __syncthreads();
+  for (int s = tid; s < pitch; s += 1024) atomicAdd(&count[class_of(s)], 1);
+  __syncthreads();
+  if (tid == 0) {
+    int at = 0;
+    for (int c = 0; c < ORDER_CLASSES; ++c) {
+      const int n = count[c];
+      count[c] = at;
+      at += n;
+    }
+  }
+  __syncthreads();
+  for (int s0 = 0; s0 < pitch; s0 += 1024) {
+    const int s = s0 + tid;
+    if (s < pitch) order[xcd * pitch + atomicAdd(&count[class_of(s)], 1)] = (uint32_t)s;
+    __syncthreads();
+  }
 }
 
 // (32-bit byte offsets reach every row of a head: at most 65535 key blocks of 128 keys of 256 bytes are less than 2^31.
@@ -861,8 +947,20 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
   a.small_keys = groups(64) * 8 * walk < resident * (pl.nq / 2 + 4) ? 32 : 64;
   const DkvPtrs ptr = {q, k, v, kp, vp, go, M, lse, Dr, dKp, dVp};
   const int pitch = (int)groups(a.small_keys);
-  if (pl.causal) bwd_dkv_mfma_kernel<D, true><<<8 * pitch, DkvShape<D>::NT, 0, s>>>(ptr, a);
-  else bwd_dkv_mfma_kernel<D, false><<<8 * pitch, DkvShape<D>::NT, 0, s>>>(ptr, a);
+  // Started in the order of their lengths once they are more than fit at a time and the launch is long enough to gain more than the two
+  // small kernels take (13 to 20 us; about 36 query blocks for every resident workgroup).  The dQ kernel was the last to read the block
+  // lists: their place takes the lengths and the order.
+  uint32_t* order = nullptr;
+  if (8 * pitch > resident && 8 * pitch * walk > 36 * resident && (size_t)pitch * 8 * 2 * sizeof(uint32_t) <= (size_t)pl.B * pl.Hq * pl.nq * pl.nk * sizeof(uint16_t)) {
+    uint32_t* len = const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(idx));
+    order = len + 8 * pitch;
+    bwd_dkv_length_kernel<<<dim3((pl.nk + 63) / 64, pl.Hq, pl.B), LEN_WAVES * 64, 0, s>>>(M, len, pitch, a);
+    bwd_dkv_order_kernel<<<8, 1024, 0, s>>>(len, order, pitch, a);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  if (pl.causal) bwd_dkv_mfma_kernel<D, true><<<8 * pitch, DkvShape<D>::NT, 0, s>>>(ptr, order, a);
+  else bwd_dkv_mfma_kernel<D, false><<<8 * pitch, DkvShape<D>::NT, 0, s>>>(ptr, order, a);
   return hipGetLastError();
 }
 

@@ -16,6 +16,9 @@ pytestmark = pytest.mark.gpu
     (48, 48, 520, 128, 128, 64, 4, False, 0.5),   # 64 keys a workgroup
     (48, 6, 461, 64, 96, 32, 4, True, 0.7),       # ... three chunks a query block, grouped heads
     (1, 1, 9000, 64, 8, 32, 3, False, 0.03),      # packed blocks over two lists of query blocks
+    (24, 24, 2100, 128, 32, 32, 3, False, 0.2),   # workgroups started by length
+    (28, 4, 4200, 64, 32, 64, 4, True, 0.2),
+    (3, 1, 22000, 128, 128, 128, 4, False, 0.04),  # 128-key blocks in two parts
 ])
 def test_backward_tile_edges(Hq, Hkv, N, d, bq, bk, levels, causal, keep):
     edges.test_backward_edges(Hq, Hkv, N, d, bq, bk, levels, causal, keep, False)
