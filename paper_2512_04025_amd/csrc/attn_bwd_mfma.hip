@@ -39,32 +39,12 @@ struct BwdMfmaArgs {
 
 typedef __attribute__((ext_vector_type(4))) short bs16x4;
 typedef __attribute__((ext_vector_type(8))) short bs16x8;
+typedef __attribute__((ext_vector_type(4))) int i32x4;
 typedef __attribute__((address_space(3))) bs16x4 lds_bs16x4;
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
 
 constexpr float LOG2E = 1.44269504088896340736f;
-
-// A operand [32 x 16] whose rows are the lanes' own rows of a row-major LDS tile: row `row`, the 16
-// bytes at channel k0 + hf * 8
-__device__ __forceinline__ bf16x8 frag_rows(const unsigned char* tile, int pitch, int row, int k0, int hf) {
-  return *reinterpret_cast<const bf16x8*>(tile + row * pitch + (k0 + hf * 8) * 2);
-}
-
-// A operand [32 channels x 16 rows] = the transpose of rows r0 .. r0+15, channels c0 .. c0+31 of a
-// row-major LDS tile, through the transposing load: the 16 lanes of a group address 4 rows x 32 bytes
-// and lane s of the group receives channel s of those rows; lane (l32, hf) ends up with channel
-// c0 + l32 of rows r0 + hf*4 + {0..3} and r0 + 8 + hf*4 + {0..3}: the order in which pack_b lays the
-// contraction index out.
-__device__ __forceinline__ bf16x8 frag_transposed(const unsigned char* tile, int pitch, int r0, int c0, int lane) {
-  const int grp = lane >> 4, s16 = lane & 15;
-  const int row = r0 + (lane >> 5) * 4 + (s16 >> 2);
-  const int byte = (c0 + (grp & 1) * 16 + (s16 & 3) * 4) * 2;
-  const unsigned char* p = tile + row * pitch + byte;
-  const bs16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bs16x4*)(p));
-  const bs16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bs16x4*)(p + 8 * pitch));
-  return __builtin_bit_cast(bf16x8, (bs16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
 
 // f(integral_constant 0), f(1) .. f(N - 1)
 template <int N, int I = 0, typename F> __device__ __forceinline__ void each(F&& f) {
@@ -90,6 +70,7 @@ template <int OFF, typename T> __device__ __forceinline__ void lds_read(T& dst, 
 template <int OFF> __device__ __forceinline__ void lds_read_t(bs16x4& dst, uint32_t at) {
   asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(at), "n"(OFF));
 }
+template <int N> __device__ __forceinline__ void lds_wait(bf16x8& x) { asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(x) : "n"(N)); }
 template <int N, typename T> __device__ __forceinline__ void lds_wait(T& x, f32x4& y, f32x4& z) {
   asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(x), "+v"(y), "+v"(z) : "n"(N));
 }
@@ -128,42 +109,67 @@ __device__ __forceinline__ rsrc_words make_rsrc(const void* base, uint32_t bytes
   return r;
 }
 
-// 16 accumulator values of one lane (rows (v/4)*8 + hf*4 + v%4 of a 32-row result) -> the two B
-// operands of the next product, whose contraction index runs over those 32 rows
-__device__ __forceinline__ void pack_b(const float (&x)[16], bf16x8& f0, bf16x8& f1) {
-#pragma unroll
-  for (int v = 0; v < 8; ++v) {
-    f0[v] = (__bf16)x[v];
-    f1[v] = (__bf16)x[8 + v];
-  }
+// Place of a row's 16-byte chunks in LDS: chunk ^ swizzle(row).  row_swizzle32 serves operands of 32 rows (two lanes a row): 16 consecutive
+// rows at 16 different places, and the four rows of a transposing group in four different 64-byte groups.  row_swizzle serves
+// operands of 16 rows (four lanes a row, 16 rows x 32 bytes transposed): no two of the rows that the LDS serves together meet either way.
+template <int D> __host__ __device__ constexpr int row_swizzle32(int row) {
+  return D == 128 ? ((row & 3) << 2) | ((row >> 2) & 3) : (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
+}
+template <int D> __host__ __device__ constexpr int row_swizzle(int row) {
+  const int r = D == 128 ? row : row >> 1;                   // rows per 256 bytes of LDS: 1, 2
+  const int fold = ((row >> 2) ^ (row >> 3)) & 1;
+  return D == 128 ? (((r & 3) | (fold << 2)) << 1) | ((row >> 3) & 1) : (((r & 1) | (fold << 1)) << 1) | ((row >> 3) & 1);
 }
 
+// dQ, and D = dO.O for the kernel after it.  One workgroup per 128 query rows, a wavefront per 32 with its Q and dO fragments and
+// the accumulators of dQ^T in registers.  The row's level-sorted block list is walked in tiles of 64 pooled keys; the
+// rows of a tile go straight into LDS, one tile ahead, with one barrier per tile, and the block ids that say where the
+// rows of the tile after that lie are on their way at the same time.
+//
+// As in the forward kernel the order of a tile is fixed by hand: every operand fragment is requested two fragments ahead of its MFMA, a
+// slice of the vector work stands behind each MFMA (S and dP of the second 32 keys take turns while the weights of the first are made),
+// tiles whose keys all count the same take one constant, and the rare others have their scores rewritten first.  Workgroups are dealt
+// to the XCDs as in the forward kernel.
 template <int D>
-__global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
+__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                                              const bf16_t* __restrict__ V, const bf16_t* __restrict__ Kp,
                                                              const bf16_t* __restrict__ Vp, const uint16_t* __restrict__ idx,
                                                              const int32_t* __restrict__ cnt, const bf16_t* __restrict__ O,
                                                              const float* __restrict__ lse, float* __restrict__ Dr,
                                                              const bf16_t* __restrict__ dO, bf16_t* __restrict__ dQ, BwdMfmaArgs a) {
-  constexpr int PITCH = D * 2 + (D == 128 ? 48 : 16), CPR = D / 8, KS = D / 16, MD = D / 32;
-  constexpr int TILEB = 64 * PITCH, BUFB = 2 * TILEB + 2 * 64 * 4;
-  // two buffers, each: Kbar rows [64][PITCH] | Vbar rows [64][PITCH] | bias term [64] | last token [64]
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, hf = lane >> 5;
-  const int slices = (a.bq + 127) / 128;
-  // causal rows get longer towards the end of the sequence: the longest are started first
-  const int i = a.causal ? a.nq - 1 - (int)(blockIdx.x / slices) : (int)(blockIdx.x / slices), slice = blockIdx.x % slices;
-  const int hq = blockIdx.y, b = blockIdx.z;
+  constexpr int ROWB = D * 2, TILEB = 64 * ROWB, BUFB = 2 * TILEB, CPR = D / 8, RPI = 64 / CPR, NI = 16 / RPI, KS = D / 16, MD = D / 32;
+  // two buffers (Kbar rows [64][ROWB] | Vbar rows [64][ROWB]), a table per wavefront for irregular tiles (term [64] | last token [64])
+  constexpr int OFF_FIX = 2 * BUFB, OFF_CNT = OFF_FIX + 4 * 512;   // and the row's blocks per level
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[OFF_CNT + 4 * PSA_MAX_LEVELS];
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int slices = (a.bq + 127) / 128, per_head = a.nq * slices;
+  // not causal: all XCDs on one head at a time, a contiguous run of query blocks each; causal: a contiguous run of (head, query
+  // block) items to each XCD, the longest rows first
+  int head, item;
+  if (a.causal) {
+    const int items = per_head * a.Hq * a.B, run = (items + 7) >> 3, at = (int)(blockIdx.x & 7) * run + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= run || at >= items) return;
+    head = at / per_head;
+    item = at % per_head;
+  } else {
+    const int run = (per_head + 7) >> 3, slot = (int)(blockIdx.x >> 3);
+    head = slot / run;
+    item = (int)(blockIdx.x & 7) * run + slot % run;
+    if (item >= per_head) return;
+  }
+  const int slice = item % slices, i = a.causal ? a.nq - 1 - item / slices : item / slices;
+  const int hq = head % a.Hq, b = head / a.Hq;
   const int hk = hq / (a.Hq / a.Hkv);
   const int64_t qhead = (int64_t)b * a.Hq + hq, khead = (int64_t)b * a.Hkv + hk;
   int row_end = (i + 1) * a.bq;
   row_end = row_end < a.N ? row_end : a.N;
-  const int qrow = i * a.bq + slice * 128 + wave * 32 + l32;
+  const int row0 = i * a.bq + slice * 128, qrow = row0 + wave * 32 + l32;
   const bool active = qrow < row_end;
 
   bf16x8 qf[KS], gf[KS];
   // D = dO . O of the row: eight channels at a time, the sums of eight added pairwise.  The dKbar, dVbar kernel, which
-  // runs after this one, reads it from memory.  (A kernel of its own read dO once more and cost
+  // runs after this one, reads -D from memory.  (A kernel of its own read dO once more and cost
   // a launch: 1 % of a call on 2 heads x 1000 tokens, 0.4 % on 28 x 8000.)
   float dots[KS];
 #pragma unroll
@@ -201,17 +207,17 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(const bf16_t* __res
 
   const int64_t srow = qhead * a.nq + i;
   const uint16_t* my_idx = idx + srow * a.nk;
-  const int32_t* my_cnt = cnt + srow * CNT_STRIDE;
+  // (in LDS: read from memory at a change of level it would wait for the rows that are under way)
+  int* my_cnt = reinterpret_cast<int*>(smem + OFF_CNT);
+  if (tid < a.H) my_cnt[tid] = cnt[srow * CNT_STRIDE + tid];
+  __syncthreads();
 
-  // The tiles of 64 pooled keys, level after level down the row's level-sorted block list.  Three are in
-  // flight: one is multiplied from LDS, the rows of the next are on their way from memory into
-  // registers (they go into the other LDS buffer afterwards), and the block ids that say where the rows
-  // of the one after that lie are being read.
-  struct Tile { int h, tl, ntl, nblk, start; bool ok; };
+  // ---- the tiles of 64 pooled keys, level after level down the row's list
+  struct Tile { int h, tl, ntl, nblk, start, ok; };   // (no padding: its bytes were copied through LDS)
   auto settle = [&](Tile t) __attribute__((always_inline)) -> Tile {   // first existing tile at or after (h, tl)
     for (; t.h <= a.H; ++t.h, t.tl = 0, t.start += t.nblk, t.ntl = -1) {
       if (t.ntl < 0) {
-        t.nblk = my_cnt[t.h - 1];
+        t.nblk = __builtin_amdgcn_readfirstlane(my_cnt[t.h - 1]);
         t.ntl = ((t.nblk << (a.lg_bk - (t.h - 1))) + 63) >> 6;
       }
       if (t.tl < t.ntl) {
@@ -222,126 +228,183 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_mfma_kernel(const bf16_t* __res
     t.ok = false;
     return t;
   };
-  constexpr int NCH = 64 * CPR / 256;              // 16-byte chunks per thread, tile and tensor
-  struct Where { int prow[NCH], mine; };            // pooled rows of this thread's chunks and of tile row `tid`; -1: none
-  auto locate = [&](const Tile& t) __attribute__((always_inline)) -> Where {
-    Where w;
-    const int lg_th = a.lg_bk - (t.h - 1), th = 1 << lg_th;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int r = (tid + 256 * c) / CPR, g = (t.tl << 6) + r, e = g >> lg_th;
-      w.prow[c] = e < t.nblk ? ((int)my_idx[t.start + e] << lg_th) | (g & (th - 1)) : -1;
-    }
-    w.mine = -1;
-    if (tid < 64) {
-      const int g = (t.tl << 6) + tid, e = g >> lg_th;
-      if (e < t.nblk) w.mine = ((int)my_idx[t.start + e] << lg_th) | (g & (th - 1));
-    }
-    return w;
+  auto next = [&](Tile t) __attribute__((always_inline)) -> Tile {
+    t.tl += 1;
+    return settle(t);
   };
-  u32x4 kreg[NCH], vreg[NCH];
-  float treg = -INFINITY;
-  int lastreg = 0;
-  auto fetch = [&](const Tile& t, const Where& w) __attribute__((always_inline)) {
-    const int lg_th = a.lg_bk - (t.h - 1), span = 1 << (t.h - 1);
-    const bf16_t* kbase = t.h == 1 ? K + khead * (int64_t)a.N * D : Kp + a.lvl_off[t.h] + khead * ((int64_t)a.nk << lg_th) * D;
-    const bf16_t* vbase = t.h == 1 ? V + khead * (int64_t)a.N * D : Vp + a.lvl_off[t.h] + khead * ((int64_t)a.nk << lg_th) * D;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int ch = (tid + 256 * c) % CPR;
-      const u32x4 z = {0u, 0u, 0u, 0u};
-      kreg[c] = z;
-      vreg[c] = z;
-      if (w.prow[c] >= 0 && w.prow[c] * span < a.N) {
-        kreg[c] = *reinterpret_cast<const u32x4*>(kbase + (int64_t)w.prow[c] * D + ch * 8);
-        vreg[c] = *reinterpret_cast<const u32x4*>(vbase + (int64_t)w.prow[c] * D + ch * 8);
-      }
-    }
-    treg = -INFINITY;
-    lastreg = 0;
-    if (w.mine >= 0) {
-      const int first = w.mine * span;
-      int c = a.N - first;
-      c = c < 0 ? 0 : (c > span ? span : c);
-      if (c > 0) treg = __log2f((float)c);
-      lastreg = first + (c > 0 ? c : 1) - 1;
-    }
+  // the block that tile row `lane` is of (rows past the level's last block: that block)
+  auto block_of = [&](const Tile& t) __attribute__((always_inline)) -> int {
+    const int e = ((t.tl << 6) + lane) >> (a.lg_bk - (t.h - 1));
+    return (int)my_idx[t.start + (e < t.nblk ? e : t.nblk - 1)];
   };
-  auto deposit = [&](int buf) __attribute__((always_inline)) {
-    unsigned char* base = smem + buf * BUFB;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int x = tid + 256 * c, r = x / CPR, ch = x % CPR;
-      *reinterpret_cast<u32x4*>(base + r * PITCH + ch * 16) = kreg[c];
-      *reinterpret_cast<u32x4*>(base + TILEB + r * PITCH + ch * 16) = vreg[c];
-    }
-    if (tid < 64) {
-      reinterpret_cast<float*>(base + 2 * TILEB)[tid] = treg;
-      reinterpret_cast<int*>(base + 2 * TILEB)[64 + tid] = lastreg;
-    }
+  // its row in the level's array, from the block's id
+  auto row_of = [&](const Tile& t, int block) __attribute__((always_inline)) -> int {
+    const int lg_th = a.lg_bk - (t.h - 1);
+    return (block << lg_th) | (((t.tl << 6) + lane) & ((1 << lg_th) - 1));
   };
-  Tile cur = settle(Tile{1, 0, -1, 0, 0, false});
-  Tile nxt = cur, nn = cur;
-  Where wn = {}, wnn = {};
+  // whether some row of the tile is past the kept blocks, covers fewer tokens than others of its level or is not visible to every row
+  auto irregular = [&](const Tile& t, int prow) __attribute__((always_inline)) -> bool {
+    const int lg_th = a.lg_bk - (t.h - 1);
+    int lim = a.N >> (t.h - 1);
+    if (a.causal) {
+      const int vis = (row0 + 1) >> (t.h - 1);
+      lim = vis < lim ? vis : lim;
+    }
+    return ((t.tl + 1) << 6) > (t.nblk << lg_th) || __any(prow >= lim);
+  };
+  // this wavefront's 16 rows of a tile, RPI to an instruction -> buffer `to`
+  auto fire = [&](const Tile& t, int prow, int to) __attribute__((always_inline)) {
+    const int lg_th = a.lg_bk - (t.h - 1);
+    const int64_t rows = (int64_t)a.nk << lg_th;
+    const int n = t.h == 1 ? a.N : (int)rows;       // rows of this head's level array: level 1 is not padded to whole blocks
+    const bf16_t* kbase = t.h == 1 ? K + khead * (int64_t)a.N * D : Kp + a.lvl_off[t.h] + khead * rows * D;
+    const bf16_t* vbase = t.h == 1 ? V + khead * (int64_t)a.N * D : Vp + a.lvl_off[t.h] + khead * rows * D;
+    const rsrc_words krsrc = make_rsrc(kbase, (uint32_t)n * (uint32_t)ROWB), vrsrc = make_rsrc(vbase, (uint32_t)n * (uint32_t)ROWB);
+    // (a row past the end: the last one, whose weight is 0 there and which takes part elsewhere)
+    const int off = (prow < n ? prow : n - 1) * ROWB;
+    const int ln = lane_again(), lrow = ln / CPR;
+    const uint32_t dst = to * BUFB + wave * NI * 1024;
+    each<NI>([&](auto tag) __attribute__((always_inline)) {
+      constexpr int k = decltype(tag)::value;
+      const int r = wave * 16 + k * RPI + lrow;
+      const int v = __shfl(off, r, 64) + (((ln % CPR) ^ row_swizzle32<D>(r)) << 4);
+      load_lds16(krsrc, dst + k * 1024, v, 0);
+      load_lds16(vrsrc, dst + k * 1024 + TILEB, v, 0);
+    });
+  };
+
+  uint32_t rowaddr = l32 * ROWB + ((hf ^ row_swizzle32<D>(l32)) << 4);                                       // k-step ks: ^ ks * 32
+  const int trow = hf * 4 + ((lane & 15) >> 2);
+  uint32_t traddr = trow * ROWB + (((((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) ^ row_swizzle32<D>(trow)) << 4) + (lane & 1) * 8;   // channels md * 32: ^ md * 64
+
+  Tile cur = settle(Tile{1, 0, -1, 0, 0, 0}), nxt = cur;
+  int prow = 0, id = 0;                            // rows of the current tile; block ids of the next one
+  bool irr = false;
   if (cur.ok) {
-    fetch(cur, locate(cur));
-    deposit(0);
-    nxt.tl += 1;
-    nxt = settle(nxt);
-    if (nxt.ok) wn = locate(nxt);
+    prow = row_of(cur, block_of(cur));
+    irr = irregular(cur, prow);
+    fire(cur, prow, 0);
+    nxt = next(cur);
+    if (nxt.ok) id = block_of(nxt);
   }
   for (int buf = 0; cur.ok; buf ^= 1) {
-    if (nxt.ok) {
-      nn = nxt;
-      nn.tl += 1;
-      nn = settle(nn);
-      if (nn.ok) wnn = locate(nn);
-      fetch(nxt, wn);
-    } else {
-      nn.ok = false;
-    }
-    // this tile's rows are in LDS; the other buffer is no longer being read.  A bare barrier after the
-    // LDS counter alone: __syncthreads() would also wait for the loads just issued for the next tiles.
+    // this wavefront's rows of the tile and the ids of the next have landed; behind the barrier everyone's rows have, and the
+    // other buffer is no longer being read
+    asm volatile("s_waitcnt vmcnt(0)" : "+v"(id)::"memory");
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    const unsigned char* Ks = smem + buf * BUFB;
-    const unsigned char* Vs = Ks + TILEB;
-    const float* term_s = reinterpret_cast<const float*>(Ks + 2 * TILEB);
-    const int* last_s = reinterpret_cast<const int*>(Ks + 2 * TILEB) + 64;
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb) {
-      f32x16 sc, dp;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) { sc[v] = 0.f; dp[v] = 0.f; }
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows(Ks, PITCH, mb * 32 + l32, ks * 16, hf), qf[ks], sc, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows(Vs, PITCH, mb * 32 + l32, ks * 16, hf), gf[ks], dp, 0, 0, 0);
+    int prow_next = 0;
+    bool irr_next = false;
+    Tile nn = nxt;
+    if (nxt.ok) {
+      prow_next = row_of(nxt, id);
+      irr_next = irregular(nxt, prow_next);
+      fire(nxt, prow_next, buf ^ 1);
+      nn = next(nxt);
+      if (nn.ok) id = block_of(nn);
+    }
+    // S and dP of the tile's first 32 keys in turn, of its second 32, then dQ for the first and the second: 6 KS fragments
+    constexpr int PF = 2, RING = 3, NR = 4 * KS, NF = 6 * KS;
+    bf16x8 fr[RING], ds[2][2];
+    bs16x4 lo[RING], hi[RING];
+    f32x16 sc[2], dp[2];
+    const float shift = (float)(cur.h - 1) - lse2;
+    constexpr auto later = [](int j) {              // LDS reads issued behind those of fragment j when it is waited for
+      int n = 0;
+      for (int x = j + 1; x <= j + PF && x < NF; ++x) n += x < NR ? 1 : 2;
+      return n;
+    };
+    auto request = [&](auto tag) __attribute__((always_inline)) {
+      constexpr int j = decltype(tag)::value;
+      if constexpr (j < NR) {
+        constexpr int mb = j / (2 * KS), ks = (j % (2 * KS)) >> 1;
+        lds_read<(j & 1) * TILEB + mb * 32 * ROWB>(fr[j % RING], flip<ks * 32>(rowaddr));
+      } else if constexpr (j < NF) {
+        constexpr int x = j - NR, md = x % MD, r0 = x / MD * 16;                  // 16 keys, 32 channels; eight rows further down the swizzle differs in one bit
+        lds_read_t<r0 * ROWB>(lo[j % RING], flip<md * 64>(traddr));
+        lds_read_t<(r0 + 8) * ROWB>(hi[j % RING], flip<(md * 64) ^ 32>(traddr));
       }
-      float ds[16];
+    };
+    auto weight = [&](auto mb_tag, auto e_tag) __attribute__((always_inline)) {
+      constexpr int mb = decltype(mb_tag)::value, e = decltype(e_tag)::value;
+      sc[mb][e] = __builtin_amdgcn_exp2f(fmaf(sc[mb][e], a.scale_log2, shift));
+      sc[mb][e] *= dp[mb][e] - my_D;
+      if constexpr (e & 1) {
+        ds[mb][e >> 3][(e & 7) - 1] = (__bf16)sc[mb][e - 1];
+        ds[mb][e >> 3][e & 7] = (__bf16)sc[mb][e];
+      }
+    };
+    // Scores of an irregular tile: rewritten so that the constant of the regular path gives log2 of the tokens under the key, -inf for
+    // a key that must not be seen.  Each lane works out one key of the tile.
+    auto fixup = [&](auto mb_tag) __attribute__((always_inline)) {
+      constexpr int mb = decltype(mb_tag)::value;
+      float* term = reinterpret_cast<float*>(smem + OFF_FIX + wave * 512);
+      int* last = reinterpret_cast<int*>(smem + OFF_FIX + wave * 512 + 256);
+      {
+        const int ln = lane_again(), span = 1 << (cur.h - 1), first = prow * span;
+        int c = a.N - first;
+        c = c < 0 ? 0 : (c > span ? span : c);
+        if (((cur.tl << 6) + ln) >> (a.lg_bk - (cur.h - 1)) >= cur.nblk) c = 0;
+        term[ln] = c == 0 ? -INFINITY : (__log2f((float)c) - (float)(cur.h - 1)) / a.scale_log2;
+        last[ln] = first + c - 1;
+      }
+      const int qlim = a.causal ? qrow : 0x7fffffff;
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
         const int col = mb * 32 + g4 * 8 + hf * 4;
-        const f32x4 tm = *reinterpret_cast<const f32x4*>(term_s + col);
+        const f32x4 tm = *reinterpret_cast<const f32x4*>(term + col);
+        const i32x4 la = *reinterpret_cast<const i32x4*>(last + col);
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
-          float x = fmaf(sc[g4 * 4 + e4], a.scale_log2, tm[e4]) - lse2;
-          if (a.causal) x = last_s[col + e4] > qrow ? -INFINITY : x;
-          const float p = __builtin_amdgcn_exp2f(x);
-          ds[g4 * 4 + e4] = p * (dp[g4 * 4 + e4] - my_D);
+          const float x = sc[mb][g4 * 4 + e4] + tm[e4];
+          sc[mb][g4 * 4 + e4] = la[e4] > qlim ? -INFINITY : x;
         }
       }
-      bf16x8 dsf[2];
-      pack_b(ds, dsf[0], dsf[1]);
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-        for (int md = 0; md < MD; ++md)
-          dq[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_transposed(Ks, PITCH, mb * 32 + ks * 16, md * 32, lane), dsf[ks], dq[md], 0, 0, 0);
-    }
-    if (nxt.ok) deposit(buf ^ 1);
+    };
+    using std::integral_constant;
+    const integral_constant<int, 0> c0;
+    const integral_constant<int, 1> c1;
+    __builtin_amdgcn_sched_barrier(0);
+    each<PF>([&](auto tag) __attribute__((always_inline)) { request(tag); });
+    each<NF>([&](auto tag) __attribute__((always_inline)) {
+      constexpr int j = decltype(tag)::value;
+      request(integral_constant<int, j + PF>{});
+      if constexpr (j < NR) {
+        constexpr int mb = j / (2 * KS), ks = (j % (2 * KS)) >> 1;
+        lds_wait<later(j)>(fr[j % RING]);
+        const f32x16 z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if constexpr ((j & 1) == 0) sc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[j % RING], qf[ks], ks == 0 ? z : sc[mb], 0, 0, 0);
+        else dp[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[j % RING], gf[ks], ks == 0 ? z : dp[mb], 0, 0, 0);
+      } else {
+        constexpr int x = j - NR, md = x % MD, kq = x / MD;
+        lds_wait<later(j)>(lo[j % RING], hi[j % RING]);
+        const bf16x8 f = __builtin_bit_cast(bf16x8, (bs16x8)__builtin_shufflevector(lo[j % RING], hi[j % RING], 0, 1, 2, 3, 4, 5, 6, 7));
+        dq[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, ds[kq >> 1][kq & 1], dq[md], 0, 0, 0);
+      }
+      // weights of the first 32 keys beside S and dP of the second, of the second beside dQ of the first
+      if constexpr (j == 2 * KS) {
+        if (irr) fixup(c0);
+      }
+      if constexpr (j == NR) {
+        if (irr) fixup(c1);
+      }
+      if constexpr (j > 2 * KS && j < NR)
+        each<16>([&](auto e) __attribute__((always_inline)) {
+          constexpr int at = decltype(e)::value * (2 * KS - 1) / 16;
+          if constexpr (at == j - 2 * KS - 1) weight(c0, e);
+        });
+      if constexpr (j >= NR && j < NR + KS)
+        each<16>([&](auto e) __attribute__((always_inline)) {
+          constexpr int at = decltype(e)::value * KS / 16;
+          if constexpr (at == j - NR) weight(c1, e);
+        });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    rowaddr ^= BUFB;
+    traddr ^= BUFB;
     cur = nxt;
     nxt = nn;
-    wn = wnn;
+    prow = prow_next;
+    irr = irr_next;
   }
   if (active) {
     bf16_t* op = dQ + (qhead * a.N + qrow) * D;
@@ -380,12 +443,6 @@ struct DkvShape {
   static constexpr int ROWB = D * 2, TILEB = ROWS * ROWB, WPS = D == 64 ? 3 : 2;
   static constexpr int LDSB = 4 * TILEB + 16 * ROWS + 6 * DKV_LIST + 4 * NW;
 };
-// Place of a row's 16-byte chunks in LDS: chunk ^ row_swizzle(row).
-template <int D> __host__ __device__ constexpr int row_swizzle(int row) {
-  const int r = D == 128 ? row : row >> 1;                   // rows per 256 bytes of LDS: 1, 2
-  const int fold = ((row >> 2) ^ (row >> 3)) & 1;
-  return D == 128 ? (((r & 3) | (fold << 2)) << 1) | ((row >> 3) & 1) : (((r & 1) | (fold << 1)) << 1) | ((row >> 3) & 1);
-}
 struct DkvPtrs {
   const bf16_t *Q, *K, *V, *Kp, *Vp, *dO;
   const uint8_t* M;
@@ -926,13 +983,9 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
   const bf16_t* vp = static_cast<const bf16_t*>(Vp);
   const bf16_t* go = static_cast<const bf16_t*>(dO);
   const int slices = (pl.bq + 127) / 128;
-  static LdsOptIn dq_optin;
-  hipError_t e = allow_max_lds(reinterpret_cast<const void*>(bwd_dq_mfma_kernel<D>), &dq_optin);
-  if (e != hipSuccess) return e;
-  constexpr size_t dq_smem = 2 * (2 * (size_t)64 * (D * 2 + (D == 128 ? 48 : 16)) + 2 * 64 * 4);   // two buffers of the kernel's layout
-  bwd_dq_mfma_kernel<D><<<dim3(pl.nq * slices, pl.Hq, pl.B), 256, dq_smem, s>>>(q, k, v, kp, vp, idx, cnt, static_cast<const bf16_t*>(O), lse, Dr, go,
-                                                                                 static_cast<bf16_t*>(dQ), a);
-  e = hipGetLastError();
+  const unsigned dq_grid = pl.causal ? 8u * (unsigned)((pl.nq * slices * pl.Hq * pl.B + 7) / 8) : 8u * (unsigned)(pl.B * pl.Hq) * (unsigned)((pl.nq * slices + 7) / 8);
+  bwd_dq_mfma_kernel<D><<<dq_grid, 256, 0, s>>>(q, k, v, kp, vp, idx, cnt, static_cast<const bf16_t*>(O), lse, Dr, go, static_cast<bf16_t*>(dQ), a);
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   auto groups = [&](int small_keys) {            // workgroups of an XCD, as the kernel counts them
     int64_t n = 0;
