@@ -4,7 +4,7 @@
 //
 // Two kernels with fp32 accumulation, P and dS rounded to bfloat16 for the
 // products that consume them, no atomics, two wavefronts per SIMD (at most 256 registers per lane),
-// double-buffered tiles in LDS (dQ: through registers; dK, dV: loaded directly):
+// double-buffered tiles that are loaded straight into LDS:
 //   bwd_dq_mfma_kernel   one workgroup per 128 query rows (a wavefront per 32), walking the row's
 //        level-sorted block list in tiles of 64 pooled keys gathered into LDS.  Same operand roles as the
 //        forward kernel: S^T = Kbar Q^T and dP^T = Vbar dO^T put one query row in each lane (lse and
@@ -14,12 +14,8 @@
 //   bwd_dkv_mfma_kernel  the same with queries and keys exchanged, on 16x16x32 MFMAs: one workgroup per (64 adjacent pooled
 //        keys of a level, query head); the pooled keys and values sit in registers as B operands (one key per lane), the
 //        query blocks that use one of the workgroup's key blocks at this level (a walk down the level map's columns) are
-//        staged through LDS 64 rows at a time; S = Q Kbar^T and dP = dO Vbar^T, then dVbar^T += dO^T P and
+//        staged through LDS 32 or 64 rows at a time; S = Q Kbar^T and dP = dO Vbar^T, then dVbar^T += dO^T P and
 //        dKbar^T += Q^T dS with the transposing load on the staged dO and Q.
-// The dQ kernel's LDS rows carry padding that spreads the rows of an operand read over the banks: 16 bytes serve the
-// row-wise fragments (eight rows x 16 bytes) at either head dimension and, at d = 64, the transposing
-// load too (four rows x 32 bytes); at d = 128 that load wants the rows 8 banks apart and the fragments
-// an odd multiple of 4, which 48 bytes give.
 #include <type_traits>
 
 #include "psa_dev.h"
@@ -437,9 +433,12 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_mfma_kernel(const
 // wavefronts stage a quarter less and were slower (3.85 for levels 2-4: one lock-step group on a compute unit).
 constexpr int DKV_LIST = 1024;     // query blocks tested before their rows are walked
 constexpr int DKV_MAXG = 32;       // key blocks of a workgroup: one bit each
-template <int D>
+// RH: 32-row chunks of a stage, one for every two wavefronts.  With one the workgroups are of two wavefronts: four of them on a compute
+// unit (d = 64: six) wait for each other less at their barriers than two of four wavefronts (12 heads x 32760 tokens 6.57 -> 6.32 ms for
+// the call, causal 28 x 8000 0.849 -> 0.780), but a walk takes twice as long (the rule stands at the launch).
+template <int D, int RH>
 struct DkvShape {
-  static constexpr int NW = 4, NT = NW * 64, KEYS = 64, ROWS = 64, CHUNKS = ROWS / 32;
+  static constexpr int NW = 2 * RH, NT = NW * 64, KEYS = 64, ROWS = 32 * RH, CHUNKS = RH;
   static constexpr int ROWB = D * 2, TILEB = ROWS * ROWB, WPS = D == 64 ? 3 : 2;
   static constexpr int LDSB = 4 * TILEB + 16 * ROWS + 6 * DKV_LIST + 4 * NW;
 };
@@ -464,9 +463,9 @@ __host__ __device__ inline DkvGroup dkv_group(int lg_th, int nk, int small_keys)
   return r;
 }
 
-template <int D, bool FULL, bool CAUSAL>
+template <int D, int RH, bool FULL, bool CAUSAL>
 __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr, const BwdMfmaArgs& a, const DkvItem it) {
-  using S = DkvShape<D>;
+  using S = DkvShape<D, RH>;
   constexpr int NW = S::NW, NT = S::NT, KEYS = S::KEYS, ROWS = S::ROWS, ROWB = S::ROWB, TILEB = S::TILEB, CHUNKS = S::CHUNKS;
   constexpr int CPR = D / 8, KS = D / 32, MD = D / 16, RPI = 64 / CPR, WROWS = ROWS / NW, NI = WROWS / RPI;   // rows and load instructions per wavefront, stage and tensor
   static_assert(WROWS == 16, "a wavefront's rows are of one chunk and start where the swizzle does");
@@ -802,7 +801,7 @@ __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr
   auto red = [&](int half, int p, int u) __attribute__((always_inline)) {   // 16 x D floats
     return reinterpret_cast<float*>(smem + ((half * 2 + p) * 2 + u) * 16 * D * 4);
   };
-  static_assert(2 * 2 * 2 * 16 * D * 4 <= OFF_STAT, "the partial sums fit the buffers");
+  static_assert(RH * 2 * 2 * 16 * D * 4 <= OFF_STAT, "the partial sums fit the buffers");
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
     __syncthreads();
@@ -818,7 +817,8 @@ __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr
       const int blk = (koff + kk) >> lg_th;
       if (blk >= G || j0 + blk >= a.nk) continue;
       const int t = kk >> 4, k16 = kk & 15, at = k16 * D + ((c4 * 4) ^ (k16 << 2));
-      const f32x4 sum = *reinterpret_cast<const f32x4*>(red(0, t & 1, t >> 1) + at) + *reinterpret_cast<const f32x4*>(red(1, t & 1, t >> 1) + at);
+      f32x4 sum = *reinterpret_cast<const f32x4*>(red(0, t & 1, t >> 1) + at);
+      if constexpr (RH == 2) sum += *reinterpret_cast<const f32x4*>(red(1, t & 1, t >> 1) + at);
       int ctok = a.N - ((j0 << lg_th) + koff + kk) * span;      // tokens under the key
       ctok = ctok < 0 ? 0 : (ctok > span ? span : ctok);
       const f32x4 none = {0.f, 0.f, 0.f, 0.f};
@@ -845,23 +845,23 @@ __device__ __forceinline__ bool dkv_item(const BwdMfmaArgs& a, int xcd, int slot
   return false;
 }
 
-template <int D, bool CAUSAL>
-__global__ __launch_bounds__((DkvShape<D>::NT), (DkvShape<D>::WPS)) void bwd_dkv_mfma_kernel(DkvPtrs ptr, const uint32_t* __restrict__ order, BwdMfmaArgs a) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[DkvShape<D>::LDSB];
+template <int D, int RH, bool CAUSAL>
+__global__ __launch_bounds__((DkvShape<D, RH>::NT), (DkvShape<D, RH>::WPS)) void bwd_dkv_mfma_kernel(DkvPtrs ptr, const uint32_t* __restrict__ order, BwdMfmaArgs a) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[DkvShape<D, RH>::LDSB];
   const int xcd = (int)(blockIdx.x & 7);
   int slot = (int)(blockIdx.x >> 3);
   if (order) slot = (int)order[xcd * (int)(gridDim.x >> 3) + slot];
   DkvItem it;
   if (!dkv_item(a, xcd, slot, it)) return;
-  if (a.lg_bk - (it.h - 1) >= 6) dkv_body<D, true, CAUSAL>(smem, ptr, a, it);
-  else dkv_body<D, false, CAUSAL>(smem, ptr, a, it);
+  if (a.lg_bk - (it.h - 1) >= 6) dkv_body<D, RH, true, CAUSAL>(smem, ptr, a, it);
+  else dkv_body<D, RH, false, CAUSAL>(smem, ptr, a, it);
 }
 
 // The walks of an XCD differ in length (12 heads x 32760 tokens: 7 to 171 query blocks on level 1, 205 to 242 on level 4), so the long ones are
 // started first: in the order of the slots the last walks ended 1.2 to 1.4 times the mean later, 1.8 to 2.3 times in causal problems.
 // bwd_dkv_length_kernel counts the query blocks of every item (64 columns of the level map a workgroup, the rows dealt to its
-// wavefronts), bwd_dkv_order_kernel sorts each XCD's slots into classes of length, half an octave each (within a class as they
-// come: neighbours in the key sequence stay close).  Both are latency: 4 us each.
+// wavefronts), bwd_dkv_order_kernel sorts each XCD's slots into classes of length, an eighth of an octave each (within a class as they
+// come: neighbours in the key sequence stay close; in half octaves the calls took up to 1.5 % longer).  Both are latency: 4 us each.
 constexpr int LEN_WAVES = 8;
 __global__ __launch_bounds__(LEN_WAVES * 64) void bwd_dkv_length_kernel(const uint8_t* __restrict__ M, uint32_t* __restrict__ len, int pitch, BwdMfmaArgs a) {
   __shared__ int part[LEN_WAVES][PSA_MAX_LEVELS][64];
@@ -911,7 +911,7 @@ __global__ __launch_bounds__(LEN_WAVES * 64) void bwd_dkv_length_kernel(const ui
   }
 }
 
-constexpr int ORDER_CLASSES = 40;
+constexpr int ORDER_CLASSES = 160;
 __global__ __launch_bounds__(1024) void bwd_dkv_order_kernel(const uint32_t* __restrict__ len, uint32_t* __restrict__ order, int pitch, BwdMfmaArgs a) {
   __shared__ int count[ORDER_CLASSES];
   const int xcd = blockIdx.x, tid = threadIdx.x;
@@ -919,8 +919,8 @@ __global__ __launch_bounds__(1024) void bwd_dkv_order_kernel(const uint32_t* __r
     DkvItem it;
     if (!dkv_item(a, xcd, slot, it)) return ORDER_CLASSES - 1;               // a slot without an item
     const uint32_t c = len[xcd * pitch + slot];                              // 15 .. 7 * 8192 + 15
-    const int top = 31 - __clz((int)c), half = 2 * top + (int)((c >> (top - 1)) & 1u);
-    return ORDER_CLASSES - 2 - half;
+    const int top = 31 - __clz((int)c), eighth = 8 * top + (int)((c >> (top - 3)) & 7u);
+    return ORDER_CLASSES - 2 - eighth;
   };
   if (tid < ORDER_CLASSES) count[tid] = 0;
   __syncthreads();
@@ -996,7 +996,12 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
   // the query blocks, say) would end after the work that there is for every resident workgroup (walks of a fifth of the query blocks,
   // a tenth if causal; what a workgroup costs besides is worth four).  Whole call, us for 64 / 32, d = 128, four levels: 2 heads x 3000 tokens 130 / 109,
   // x 8000 291 / 235, x 20000 740 / 650; 12 x 3000 169 / 179, x 8000 648 / 688, 28 grouped causal x 8000 982 / 1029; d = 64 2 x 8000 201 / 163, 12 x 8000 342 / 349.
-  const int64_t resident = 256 * DkvShape<D>::WPS, walk = pl.nq / (pl.causal ? 10 : 5) + 4;
+  const int64_t walk = pl.nq / (pl.causal ? 10 : 5) + 4;
+  // Workgroups of two wavefronts (twice as many resident, each walk twice as long) where the work for every resident one is at least the
+  // longest walk that there can be.  Whole call, time in four wavefronts over time in two, 70 shapes, by that work over that walk: up to
+  // 0.2 0.60-0.91, 0.2-0.5 0.63-0.97 (32-row blocks up to 1.07), 0.5-0.95 0.71-1.08, from 1.0 on 1.01-1.06.
+  const bool pairs = groups(64) * 8 * walk >= 256 * DkvShape<D, 1>::WPS * 2 * (int64_t)pl.nq;
+  const int64_t resident = 256 * DkvShape<D, 2>::WPS * (pairs ? 2 : 1);
   a.small_keys = groups(64) * 8 * walk < resident * (pl.nq / 2 + 4) ? 32 : 64;
   const DkvPtrs ptr = {q, k, v, kp, vp, go, M, lse, Dr, dKp, dVp};
   const int pitch = (int)groups(a.small_keys);
@@ -1012,8 +1017,9 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if (pl.causal) bwd_dkv_mfma_kernel<D, true><<<8 * pitch, DkvShape<D>::NT, 0, s>>>(ptr, order, a);
-  else bwd_dkv_mfma_kernel<D, false><<<8 * pitch, DkvShape<D>::NT, 0, s>>>(ptr, order, a);
+  auto launch = [&](auto kernel, int threads) { kernel<<<8 * pitch, threads, 0, s>>>(ptr, order, a); };
+  if (pairs) launch(pl.causal ? bwd_dkv_mfma_kernel<D, 1, true> : bwd_dkv_mfma_kernel<D, 1, false>, DkvShape<D, 1>::NT);
+  else launch(pl.causal ? bwd_dkv_mfma_kernel<D, 2, true> : bwd_dkv_mfma_kernel<D, 2, false>, DkvShape<D, 2>::NT);
   return hipGetLastError();
 }
 

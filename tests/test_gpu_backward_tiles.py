@@ -18,6 +18,10 @@ pytestmark = pytest.mark.gpu
     (1, 1, 9000, 64, 8, 32, 3, False, 0.03),      # packed blocks over two lists of query blocks
     (24, 24, 2100, 128, 32, 32, 3, False, 0.2),   # workgroups started by length
     (28, 4, 4200, 64, 32, 64, 4, True, 0.2),
+    (192, 192, 264, 128, 32, 16, 3, False, 0.4),  # workgroups of two wavefronts: packed blocks only, a ragged last query block
+    (140, 14, 461, 64, 96, 32, 4, True, 0.7),     # ... three chunks a query block, grouped heads
+    (128, 128, 900, 128, 24, 64, 4, False, 0.2),  # ... chunks of 24 rows
+    (96, 12, 524, 128, 128, 128, 2, True, 0.6),    # ... 128-key blocks in two parts
     (3, 1, 22000, 128, 128, 128, 4, False, 0.04),  # 128-key blocks in two parts
 ])
 def test_backward_tile_edges(Hq, Hkv, N, d, bq, bk, levels, causal, keep):
