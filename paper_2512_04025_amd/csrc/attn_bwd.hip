@@ -498,36 +498,56 @@ void bwd_dkv_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* _
   }
 }
 
-// dK[t] = sum_h dKbar^h[t >> (h-1)] / c  (Eq. 2-3 backwards); same for V.  One thread per 4 channels.
+// dK[t] = sum_h dKbar^h[t >> (h-1)] / c  (Eq. 2-3 backwards); same for V.  One thread per 4 channels of TOK consecutive
+// tokens: a pooled gradient is read once for all of them, and the rows of a level are independent loads.
 // The pooled gradients of a key head come in `parts` consecutive partial tensors (one per query head of
 // its group when the matrix-core kernel wrote them), added here in a fixed order.
-template <typename T>
+template <typename T, int TOK>
 __global__ __launch_bounds__(256) void unpool_kernel(const float* __restrict__ dKp, const float* __restrict__ dVp,
                                                      T* __restrict__ dK, T* __restrict__ dV, int heads, int parts, int d,
                                                      BwdArgs a) {
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int q4 = d / 4;
-  if (gid >= (int64_t)heads * a.N * q4) return;
+  const int q4 = d / 4, groups = (a.N + TOK - 1) / TOK;
+  if (gid >= (int64_t)heads * groups * q4) return;
   const int c4 = (int)(gid % q4);
-  const int t = (int)((gid / q4) % a.N);
-  const int64_t bh = gid / ((int64_t)q4 * a.N);
+  const int t0 = (int)((gid / q4) % groups) * TOK;
+  const int64_t bh = gid / ((int64_t)q4 * groups);
   const float* src = blockIdx.y ? dVp : dKp;
   T* dst = blockIdx.y ? dV : dK;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int h = 1; h <= a.H; ++h) {
-    const int span = 1 << (h - 1), th = a.bk >> (h - 1);
-    const int prow = t >> (h - 1);
-    int c = a.N - prow * span;
-    c = c > span ? span : c;                       // >= 1: token t is under this pooled token
-    f32x4 g = {0.f, 0.f, 0.f, 0.f};
-    for (int part = 0; part < parts; ++part)
-      g += *reinterpret_cast<const f32x4*>(src + a.glvl_off[h] + ((bh * parts + part) * (int64_t)a.nk * th + prow) * d + c4 * 4);
-    const float inv = 1.f / (float)c;
-    acc += g * inv;
-  }
-  T* o = dst + (bh * a.N + t) * d + c4 * 4;
+  f32x4 acc[TOK];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) o[u] = Elem<T>::from_f32(acc[u]);
+  for (int u = 0; u < TOK; ++u) acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int h = 1; h <= PSA_MAX_LEVELS; ++h) {
+    if (h > a.H) break;
+    const int span = 1 << (h - 1), n = TOK >> (h - 1) > 1 ? TOK >> (h - 1) : 1;     // tokens under a row, rows
+    const int row0 = t0 >> (h - 1), rows = a.nk * (a.bk >> (h - 1));                // (TOK divides the tokens of a block)
+    const float* at = src + a.glvl_off[h] + (bh * parts * (int64_t)rows + row0) * d + c4 * 4;
+    f32x4 g[TOK];
+#pragma unroll
+    for (int x = 0; x < n; ++x) g[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+    for (int part = 0; part < parts; ++part, at += (int64_t)rows * d) {
+#pragma unroll
+      for (int x = 0; x < n; ++x) g[x] += *reinterpret_cast<const f32x4*>(at + x * d);
+    }
+#pragma unroll
+    for (int x = 0; x < n; ++x) {
+      int c = a.N - (row0 + x) * span;
+      c = c > span ? span : c;                     // < 1: no token of this thread is under this row
+      const float inv = 1.f / (float)c;
+      g[x] *= inv;
+    }
+#pragma unroll
+    for (int u = 0; u < TOK; ++u) acc[u] += g[u >> (h - 1)];
+  }
+#pragma unroll
+  for (int u = 0; u < TOK; ++u) {
+    if (t0 + u >= a.N) break;
+    T* o = dst + (bh * a.N + t0 + u) * d + c4 * 4;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) o[v] = Elem<T>::from_f32(acc[u][v]);
+  }
 }
 
 bool bwd_uses_mfma(const Plan& pl);
@@ -612,9 +632,15 @@ static hipError_t launch_bwd_t(const Plan& pl, const void* Q, const void* K, con
     if (e != hipSuccess) return e;
   }
   const int heads = pl.B * pl.Hkv;
-  const int64_t n = (int64_t)heads * pl.N * (pl.d / 4);
-  unpool_kernel<T><<<dim3((unsigned)((n + 255) / 256), 2), 256, 0, s>>>(dKp, dVp, static_cast<T*>(dK), static_cast<T*>(dV),
-                                                                         heads, parts, pl.d, a);
+  auto unpool = [&](auto kernel, int tokens) {
+    const int64_t n = (int64_t)heads * ((pl.N + tokens - 1) / tokens) * (pl.d / 4);
+    kernel<<<dim3((unsigned)((n + 255) / 256), 2), 256, 0, s>>>(dKp, dVp, static_cast<T*>(dK), static_cast<T*>(dV), heads, parts, pl.d, a);
+  };
+  // Four tokens a thread where that still fills the chip.  Whole call, us for one / four, d = 128, four levels: 12 heads x 32760 tokens
+  // 6268 / 6225, x 8000 509 / 493, x 2000 91.7 / 91.3, x 1000 56.2 / 55.4, 40 x 4000 512 / 494, 28 in groups of seven x 8000 768 / 764,
+  // x 3000 202 / 200, but x 1000 69.1 / 73.1 and 2 heads x 1000 at d = 64 36.5 / 37.5 (eight tokens: 6220, 494, 91.1, 56.1, 492, 765, 207, 85.1, 38.7).
+  if ((int64_t)heads * pl.N * (pl.d / 4) >= 300000 && pl.bk >= 4) unpool(unpool_kernel<T, 4>, 4);
+  else unpool(unpool_kernel<T, 1>, 1);
   return hipGetLastError();
 }
 
