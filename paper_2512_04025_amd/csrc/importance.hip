@@ -245,7 +245,7 @@ static hipError_t launch_imp_t(const Plan& pl, const void* Qrep, const void* Kre
 //
 // Two launches of one kernel.  A workgroup takes 128 representative query rows (4 wavefronts x 32)
 // and one of `ksplit` slices of the representative keys, so a small problem still fills the chip;
-// the key slice streams through LDS in tiles of 64 keys (direct-to-LDS loads into a ring of four
+// the key slice streams through LDS in tiles of 64 keys (direct-to-LDS loads into a ring of three or four
 // tiles, shared by the four wavefronts, chunks XOR-swizzled as in the attention kernel) and
 // S^T = K~ Q~^T runs on 32x32x16 MFMAs with one query row per lane.
 //   sweep 1: per row and key slice, the running maximum and the sum of exponentials (log2 domain)
@@ -255,6 +255,10 @@ static hipError_t launch_imp_t(const Plan& pl, const void* Qrep, const void* Kre
 //   sweep 2  (mean pooling only): the slices' partial results merged into lse = m + log2(l) per row;
 //            the logits are recomputed and w = 2^(scale*dot - lse) is averaged over every 8x8 sub-tile
 // Cross-lane steps use the half-swap and lane-permuting operands instead of LDS shuffles.
+// Bound by vector issue: 234 vector instructions a wavefront and tile, 32 of them exponentials, next to 16 MFMAs.  Whole allocation
+// call, us, with a slow path for irregular tiles -> with one path for all, the products of the next tile beside the softmax of this one:
+// 12 heads x 1000 tokens 19.6 -> 16.5, x 32760 96.0 -> 93.3, in 32-token blocks 738 -> 515, causal 28 x 32768 208 -> 191, 40 x 75600
+// 1445 -> 1366, 2 x 16 x 131072 (d = 64) 1152 -> 1156.  (The second change alone: within 3 % either way.)
 constexpr int IMP_MAX_SPLIT = 8;
 
 struct ImpTileArgs {
@@ -329,7 +333,7 @@ void importance_tiles_kernel(const bf16_t* __restrict__ Qrep,
     while (nt > 0 && key_pos((t_lo + nt - 1) * BN) > qpos_max) --nt;
   }
 
-  {  // ring starts as zeros (a lane whose key row is out of range was seen to store zeros, but nothing here
+  if (SWEEP == 2) {  // ring starts as zeros (a lane whose key row is out of range was seen to store zeros, but nothing here
      // relies on that: an out-of-range row may as well keep what its slot held)
     const u32x4 z = {0u, 0u, 0u, 0u};
     for (int x = tid * 16; x < NSLOT * TILEB; x += 256 * 16) *reinterpret_cast<u32x4*>(ring + x) = z;
@@ -350,29 +354,48 @@ void importance_tiles_kernel(const bf16_t* __restrict__ Qrep,
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (imp_lds_void*)(ring + (tt % NSLOT) * TILEB + (k * NW + wave) * RPI * ROWB), 16,
                                                (int)(tile_off + (uint32_t)((k * NW + wave) * RPI * ROWB) + klane[k % KP]), 0, 0, 0);
   };
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  asm volatile("s_barrier" ::: "memory");      // zeros are in place before the first loads land
+  if (SWEEP == 2) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    asm volatile("s_barrier" ::: "memory");    // zeros are in place before the first loads land
+  }
+  constexpr int FIRST = SWEEP == 1 ? NSLOT : NSLOT - 1;
 #pragma unroll
-  for (int tt = 0; tt < NSLOT - 1; ++tt)
+  for (int tt = 0; tt < FIRST; ++tt)
     if (tt < nt) fire(tt);
 
   // K~ operand reads: row mb*32 + l32 of the tile, chunk (2 ks + hf) ^ swizzle(row).  Written as
   // assembly with counted waits: ordinary loads next to direct-to-LDS loads make the compiler wait
   // for tiles that are still on their way into OTHER ring slots.
+  const uint32_t kaddr0 = (uint32_t)(l32 * ROWB + ((hf ^ ((l32 / RP256) % CPR)) << 4));
   uint32_t kaddr[KS];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks)
-    kaddr[ks] = (uint32_t)(l32 * ROWB + ((hf ^ ((l32 / RP256) % CPR)) << 4)) ^ (uint32_t)(ks << 5);
+  for (int ks = 0; ks < KS; ++ks) kaddr[ks] = kaddr0 ^ (uint32_t)(ks << 5);
 
-  // every row of the workgroup exists AND covers at least one token (positions grow with the row, so
-  // the last row decides): a pooled representative past the end of a short last query block is dead
-  // and must take the masked path, where its logits are -inf
-  const bool rows_full = rg * 128 + 128 <= nrows &&
-                         rep_pos(a.mode, (rg * 128 + 127) / SQ, (rg * 128 + 127) % SQ, a.bq, SQ, a.N) >= 0;
+  // Positions grow with the representative, so a row sees a prefix of the keys: its length, by bisection.  (0 for a row that does not
+  // exist or covers no token: a pooled representative past the end of a short last query block.)
+  int seen = 0;
+  if (qpos >= 0) {
+    int hi = nkeys;
+    while (seen < hi) {
+      const int mid = (seen + hi) >> 1, kpos = rep_pos(a.mode, mid / SK, mid % SK, a.bk, SK, a.N);
+      if (kpos >= 0 && !(a.causal && kpos > qpos)) seen = mid + 1;
+      else hi = mid;
+    }
+  }
   const int gk = a.bk / SK;
-  auto is_plain = [&](int tile) __attribute__((always_inline)) {   // all 64 keys and all rows valid, nothing hidden
+  auto is_plain = [&](int tile) __attribute__((always_inline)) {   // all 64 keys valid, and visible to the rows that exist
     const bool keys_full = a.mode == PSA_REP_STRIDED ? tile * BN + BN <= nkeys : (int64_t)(tile * BN + BN - 1) * gk < a.N;
-    return rows_full && keys_full && (!a.causal || key_pos(tile * BN + BN - 1) <= qpos_min);
+    return keys_full && (!a.causal || key_pos(tile * BN + BN - 1) <= qpos_min);
+  };
+  // Other tiles (the end of the keys, the causal diagonal) have the dots of unseen keys rewritten, one comparison and one select each.
+  // Rows without a token cost nothing per logit: their results are replaced.  (With positions worked out per logit such tiles took several times as long, and so did all tiles of a
+  // workgroup that holds rows past a ragged end, the last of the launch: 32-token blocks, 12 heads x 32760 tokens, half of the compute units idle on average.)
+  auto hide = [&](f32x16 (&acc)[2], int tile) __attribute__((always_inline)) {
+    const int lim = seen - tile * BN - hf * 4;
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[mb][v] = mb * 32 + (v >> 2) * 8 + (v & 3) < lim ? acc[mb][v] : -INFINITY;
   };
   auto both_halves = [&](float x, float& p, float& q) __attribute__((always_inline)) {
     const uint32_t u = __builtin_bit_cast(uint32_t, x);
@@ -413,10 +436,23 @@ void importance_tiles_kernel(const bf16_t* __restrict__ Qrep,
   }
   float* out = S + (((int64_t)b * a.Hq + hq) * a.nq) * (int64_t)a.nk;
 
+  // Max pooling needs only the largest logit of every (row, key block): keep it, so that the
+  // second pass is a small elementwise kernel instead of a second sweep over the keys.  The
+  // half swap leaves the 4 key blocks of the first 32 keys in lanes 0..31, the other 4 in 32..63.
+  // Exactly one store per tile from every wavefront (the counted load waits rely on it).
+  auto block_max = [&](float r0, float r1) __attribute__((always_inline)) -> float {
+    const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, r0), __builtin_bit_cast(uint32_t, r1), false, false);
+    uint32_t s0 = sw[0], s1 = sw[1];
+    asm volatile("" : "+v"(s0), "+v"(s1));
+    return fmaxf(__builtin_bit_cast(float, s0), __builtin_bit_cast(float, s1));
+  };
+  auto store_max = [&](const f32x4& w, int tile) __attribute__((always_inline)) {
+    *reinterpret_cast<f32x4*>(bmax + ((int64_t)head * a.bm_rows + row) * a.bm_pitch + tile * 8 + hf * 4) = w;
+  };
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   // one tile: acc[mb][v] = dot of this lane's row with key tile*64 + mb*32 + (v/4)*8 + hf*4 + v%4
-  auto tile_step = [&](auto slot_tag, int tt) __attribute__((always_inline)) {
+  auto products = [&](auto slot_tag, f32x16 (&acc)[2]) __attribute__((always_inline)) {
     constexpr int SLOT = decltype(slot_tag)::value;
-    const int tile = t_lo + tt;
     bf16x8 f0[KS], f1[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
@@ -424,8 +460,6 @@ void importance_tiles_kernel(const bf16_t* __restrict__ Qrep,
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
       asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f1[ks]) : "v"(kaddr[ks]), "n"(SLOT * TILEB + 32 * ROWB));
-    f32x16 acc[2];
-    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(f0[ks]) : "n"(2 * KS - 1 - ks));
@@ -436,158 +470,41 @@ void importance_tiles_kernel(const bf16_t* __restrict__ Qrep,
       asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(f1[ks]) : "n"(KS - 1 - ks));
       acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1[ks], qf[ks], ks == 0 ? zero : acc[1], 0, 0, 0);
     }
-    const bool plain = is_plain(tile);
-    // logits in the log2 domain (sweep 2: minus lse), dead keys / rows / causally hidden keys at -inf
-    float x[2][16];
-    if (!plain) {
+  };
+  // mean pooling: averages of w = 2^(scale dot - lse) over 8 x 8 sub-tiles
+  auto scores = [&](f32x16 (&acc)[2], int tt) __attribute__((always_inline)) {
+    if (!is_plain(t_lo + tt)) hide(acc, t_lo + tt);
+    // per lane: 8 partial results (2 halves x 4 key blocks), each over the 4 keys this lane holds.
+    // The half swap pairs value g of the first half with value g of the second: afterwards lanes
+    // 0..31 own the 4 key blocks of the first half (both lane halves folded), lanes 32..63 those
+    // of the second; then the 8 rows of a query block (8 consecutive lanes) are folded.
+    float w[4];
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
+    for (int g = 0; g < 4; ++g) {
+      float r[2];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int c = tile * BN + mb * 32 + (v >> 2) * 8 + hf * 4 + (v & 3);
-          const int kpos = c < nkeys ? rep_pos(a.mode, c / SK, c % SK, a.bk, SK, a.N) : -1;
-          const bool dead = kpos < 0 || qpos < 0 || (a.causal && kpos > qpos);
-          x[mb][v] = dead ? -INFINITY : (SWEEP == 1 ? acc[mb][v] * a.scale_log2 : fmaf(acc[mb][v], a.scale_log2, -lse));
+      for (int mb = 0; mb < 2; ++mb) {
+        r[mb] = 0.f;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float p = __builtin_amdgcn_exp2f(fmaf(acc[mb][4 * g + u], a.scale_log2, -lse));
+          r[mb] = u == 0 ? p : r[mb] + p;
         }
+        r[mb] = seen > 0 ? r[mb] : 0.f;
+      }
+      const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, r[0]), __builtin_bit_cast(uint32_t, r[1]), false, false);   // (r0.lo, r1.lo), (r0.hi, r1.hi)
+      uint32_t s0 = sw[0], s1 = sw[1];
+      asm volatile("" : "+v"(s0), "+v"(s1));
+      float v = __builtin_bit_cast(float, s0) + __builtin_bit_cast(float, s1);
+      v += lane_xor1(v);
+      v += lane_xor2(v);
+      v += lane_mirror8(v);
+      w[g] = v * (1.f / (float)(SQ * SK));
     }
-    if (SWEEP == 1) {
-      float gmax[2][4];
-      if (plain) {
-        // the running maximum only moves when it would grow by more than 2^8: the common path is one
-        // fused multiply-add, one exp2 and one add per logit
-        // the largest dot of every group of four keys once: the tile's maximum and the block maxima
-        // stored below both come from these (3-input maxima)
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-          for (int g = 0; g < 4; ++g)
-            gmax[mb][g] = __builtin_fmaxf(__builtin_fmaxf(acc[mb][4 * g], __builtin_fmaxf(acc[mb][4 * g + 1], acc[mb][4 * g + 2])),
-                                          acc[mb][4 * g + 3]);
-        float bm = __builtin_fmaxf(gmax[0][0], __builtin_fmaxf(gmax[0][1], gmax[0][2]));
-        bm = __builtin_fmaxf(bm, __builtin_fmaxf(gmax[0][3], gmax[1][0]));
-        bm = __builtin_fmaxf(bm, __builtin_fmaxf(gmax[1][1], gmax[1][2]));
-        bm = __builtin_fmaxf(bm, gmax[1][3]);
-        bm *= a.scale_log2;
-        float p, q;
-        both_halves(bm, p, q);
-        bm = fmaxf(p, q);
-        if (__any(bm - m > 8.0f)) {
-          const float mn = fmaxf(m, bm);
-          l *= __builtin_amdgcn_exp2f(m - mn);     // m = -inf: l is 0 and stays 0
-          m = mn;
-        }
-        const float neg_m = -m;
-        float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          s0 += __builtin_amdgcn_exp2f(fmaf(acc[0][v], a.scale_log2, neg_m));
-          s1 += __builtin_amdgcn_exp2f(fmaf(acc[1][v], a.scale_log2, neg_m));
-        }
-        l += s0 + s1;
-      } else {
-        float bm = -INFINITY;
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) bm = fmaxf(bm, x[mb][v]);
-        float p, q;
-        both_halves(bm, p, q);
-        bm = fmaxf(p, q);
-        const float mn = fmaxf(m, bm);
-        if (mn != -INFINITY) {
-          float sum = 0.f;
-#pragma unroll
-          for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) sum += __builtin_amdgcn_exp2f(x[mb][v] - mn);
-          l = l * __builtin_amdgcn_exp2f(m - mn) + sum;
-          m = mn;
-        }
-      }
-      if (bmax) {
-        // Max pooling needs only the largest logit of every (row, key block): keep it, so that the
-        // second pass is a small elementwise kernel instead of a second sweep over the keys.  The
-        // half swap leaves the 4 key blocks of the first 32 keys in lanes 0..31, the other 4 in 32..63.
-        // Exactly one store per tile from every wavefront (the counted load waits rely on it).
-        f32x4 w;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          float r0, r1;
-          if (plain) {
-            r0 = gmax[0][g] * a.scale_log2;
-            r1 = gmax[1][g] * a.scale_log2;
-          } else {
-            r0 = fmaxf(fmaxf(x[0][4 * g], x[0][4 * g + 1]), fmaxf(x[0][4 * g + 2], x[0][4 * g + 3]));
-            r1 = fmaxf(fmaxf(x[1][4 * g], x[1][4 * g + 1]), fmaxf(x[1][4 * g + 2], x[1][4 * g + 3]));
-          }
-          const auto sw = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, r0), __builtin_bit_cast(uint32_t, r1), false, false);
-          uint32_t s0 = sw[0], s1 = sw[1];
-          asm volatile("" : "+v"(s0), "+v"(s1));
-          w[g] = fmaxf(__builtin_bit_cast(float, s0), __builtin_bit_cast(float, s1));
-        }
-        *reinterpret_cast<f32x4*>(bmax + ((int64_t)head * a.bm_rows + row) * a.bm_pitch + tile * 8 + hf * 4) = w;
-      }
-    } else {
-      // per lane: 8 partial results (2 halves x 4 key blocks), each over the 4 keys this lane holds.
-      // The half swap pairs value g of the first half with value g of the second: afterwards lanes
-      // 0..31 own the 4 key blocks of the first half (both lane halves folded), lanes 32..63 those
-      // of the second; then the 8 rows of a query block (8 consecutive lanes) are folded.
-      const bool maxp = a.est_pool == PSA_EST_MAX;
-      float w[4];
-      auto fold = [&](auto max_tag, const float (&r)[2][4]) __attribute__((always_inline)) {
-        constexpr bool MAXP = decltype(max_tag)::value;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const uint32_t u0 = __builtin_bit_cast(uint32_t, r[0][g]), u1 = __builtin_bit_cast(uint32_t, r[1][g]);
-          const auto sw = __builtin_amdgcn_permlane32_swap(u0, u1, false, false);   // (r0.lo, r1.lo), (r0.hi, r1.hi)
-          uint32_t s0 = sw[0], s1 = sw[1];
-          asm volatile("" : "+v"(s0), "+v"(s1));
-          const float p = __builtin_bit_cast(float, s0), q = __builtin_bit_cast(float, s1);
-          float v = MAXP ? fmaxf(p, q) : p + q;
-          v = MAXP ? fmaxf(v, lane_xor1(v)) : v + lane_xor1(v);
-          v = MAXP ? fmaxf(v, lane_xor2(v)) : v + lane_xor2(v);
-          v = MAXP ? fmaxf(v, lane_mirror8(v)) : v + lane_mirror8(v);
-          w[g] = MAXP ? __builtin_amdgcn_exp2f(v) : v * (1.f / (float)(SQ * SK));
-        }
-      };
-      float r[2][4];
-      if (plain && maxp) {          // the common case: max of the raw dots first, one fused multiply-add per key block
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-          for (int g = 0; g < 4; ++g)
-            r[mb][g] = fmaf(fmaxf(fmaxf(acc[mb][4 * g], acc[mb][4 * g + 1]), fmaxf(acc[mb][4 * g + 2], acc[mb][4 * g + 3])),
-                            a.scale_log2, -lse);
-        fold(std::true_type{}, r);
-      } else {
-        if (plain) {
-#pragma unroll
-          for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) x[mb][v] = fmaf(acc[mb][v], a.scale_log2, -lse);
-        }
-        if (maxp) {
-#pragma unroll
-          for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-              r[mb][g] = fmaxf(fmaxf(x[mb][4 * g], x[mb][4 * g + 1]), fmaxf(x[mb][4 * g + 2], x[mb][4 * g + 3]));
-          fold(std::true_type{}, r);
-        } else {
-#pragma unroll
-          for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-              r[mb][g] = __builtin_amdgcn_exp2f(x[mb][4 * g]) + __builtin_amdgcn_exp2f(x[mb][4 * g + 1]) +
-                         __builtin_amdgcn_exp2f(x[mb][4 * g + 2]) + __builtin_amdgcn_exp2f(x[mb][4 * g + 3]);
-          fold(std::false_type{}, r);
-        }
-      }
-      // staged in LDS ([16 query blocks][8 key blocks per tile x STAGE_TILES]) and written out in rows
-      if ((l32 & (SQ - 1)) == 0) {
-        const f32x4 wv = {w[0], w[1], w[2], w[3]};
-        *reinterpret_cast<f32x4*>(stage + ((wave * 4 + (l32 >> 3)) * (8 * STAGE_TILES) + (tt % STAGE_TILES) * 8 + hf * 4)) = wv;
-      }
+    // staged in LDS ([16 query blocks][8 key blocks per tile x STAGE_TILES]) and written out in rows
+    if ((l32 & (SQ - 1)) == 0) {
+      const f32x4 wv = {w[0], w[1], w[2], w[3]};
+      *reinterpret_cast<f32x4*>(stage + ((wave * 4 + (l32 >> 3)) * (8 * STAGE_TILES) + (tt % STAGE_TILES) * 8 + hf * 4)) = wv;
     }
   };
   // rows of the staged scores -> S (key blocks [first_tile*8, +ntiles*8) of this workgroup's 16 query blocks)
@@ -603,50 +520,139 @@ void importance_tiles_kernel(const bf16_t* __restrict__ Qrep,
     asm volatile("s_barrier" ::: "memory");
   };
 
-  // Tile t has landed once at most the memory operations issued after its own loads are outstanding
-  // (loads and stores leave the counter in order): the loads of the tiles t+1 .. t+NSLOT-2 that exist
-  // (RI each) and, in sweep 1 with block maxima, one store for each of the tiles t-(NSLOT-1) .. t-1
-  // that exist (tile t was requested in the step of tile t-(NSLOT-1), before that step's store).
-  // The count must be exact or low: a high count would let the wavefront through early.  (Sweep 2
-  // writes S in batches, after a full wait, so stores never sit between the loads being counted.)
-  auto wait_tile = [&](int t) __attribute__((always_inline)) {
-    if (SWEEP == 2 && t % STAGE_TILES < 3) { __builtin_amdgcn_s_waitcnt(0x0F70); return; }   // stores of the last write-out may be in flight
-    const int ahead = nt - 1 - t < NSLOT - 2 ? nt - 1 - t : NSLOT - 2;
-    const int stores = SWEEP == 1 && bmax ? (t < NSLOT - 1 ? t : NSLOT - 1) : 0;
-    const int cnt = ahead * RI + stores;
-    auto wait = [&](auto c) __attribute__((always_inline)) {
-      constexpr int C = decltype(c)::value;
-      __builtin_amdgcn_s_waitcnt((C & 15) | ((C >> 4) << 14) | 0x0F70);
+  if constexpr (SWEEP == 2) {
+    // Tile t has landed once at most the loads of the tiles t+1 and t+2 that exist (RI each) are outstanding (they leave the counter in
+    // order).  S is written in batches, and the tiles behind a write-out take a full wait, so stores never sit between the loads
+    // being counted.
+    auto wait_tile = [&](int t) __attribute__((always_inline)) {
+      const int ahead = nt - 1 - t;
+      constexpr int C1 = RI, C2 = 2 * RI;
+      if (t % STAGE_TILES < 3 || ahead == 0) __builtin_amdgcn_s_waitcnt(0x0F70);   // stores of the last write-out may be in flight
+      else if (ahead == 1) __builtin_amdgcn_s_waitcnt(C1 | 0x0F70);
+      else __builtin_amdgcn_s_waitcnt(C2 | 0x0F70);
     };
-    static_assert((NSLOT - 2) * RI + NSLOT - 1 <= 11, "cases below");
-    switch (cnt) {
-      case 0: wait(std::integral_constant<int, 0>{}); break;
-      case 1: wait(std::integral_constant<int, 1>{}); break;
-      case 2: wait(std::integral_constant<int, 2>{}); break;
-      case 3: wait(std::integral_constant<int, 3>{}); break;
-      case 4: wait(std::integral_constant<int, 4>{}); break;
-      case 5: wait(std::integral_constant<int, 5>{}); break;
-      case 6: wait(std::integral_constant<int, 6>{}); break;
-      case 7: wait(std::integral_constant<int, 7>{}); break;
-      case 8: wait(std::integral_constant<int, 8>{}); break;
-      case 9: wait(std::integral_constant<int, 9>{}); break;
-      case 10: wait(std::integral_constant<int, 10>{}); break;
-      default: wait(std::integral_constant<int, 11>{}); break;
-    }
-  };
-  auto one = [&](auto slot_tag, int t) __attribute__((always_inline)) {
-    wait_tile(t);
-    asm volatile("s_barrier" ::: "memory");      // everyone's part of tile t is in; slot of tile t-1 is free
-    if (t + NSLOT - 1 < nt) fire(t + NSLOT - 1);
-    tile_step(slot_tag, t);
-    if (SWEEP == 2 && ((t + 1) % STAGE_TILES == 0 || t + 1 == nt)) flush(t - t % STAGE_TILES, t % STAGE_TILES + 1);
-  };
-  for (int t = 0; t < nt; t += NSLOT) {
-    one(std::integral_constant<int, 0>{}, t);
-    if (t + 1 < nt) one(std::integral_constant<int, 1>{}, t + 1);
-    if (t + 2 < nt) one(std::integral_constant<int, 2>{}, t + 2);
-    if constexpr (NSLOT == 4) {
+    static_assert(2 * RI < 16, "the low bits of the counter");
+    auto one = [&](auto slot_tag, int t) __attribute__((always_inline)) {
+      wait_tile(t);
+      asm volatile("s_barrier" ::: "memory");    // everyone's part of tile t is in; slot of tile t-1 is free
+      if (t + NSLOT - 1 < nt) fire(t + NSLOT - 1);
+      f32x16 acc[2];
+      products(slot_tag, acc);
+      scores(acc, t);
+      if ((t + 1) % STAGE_TILES == 0 || t + 1 == nt) flush(t - t % STAGE_TILES, t % STAGE_TILES + 1);
+    };
+    for (int t = 0; t < nt; t += NSLOT) {
+      one(std::integral_constant<int, 0>{}, t);
+      if (t + 1 < nt) one(std::integral_constant<int, 1>{}, t + 1);
+      if (t + 2 < nt) one(std::integral_constant<int, 2>{}, t + 2);
       if (t + 3 < nt) one(std::integral_constant<int, 3>{}, t + 3);
+    }
+  } else {
+    // The products of tile t + 1 run beside the softmax work of tile t: behind every MFMA stands a slice of it, and its fragment was
+    // requested PF fragments earlier.  Fragment j: half j & 1 of the tile's keys, k-step j >> 1.
+    constexpr int NM = 2 * KS, PF = 3, RING = 4;
+    constexpr int MAXS = NM / 4;                 // slots 0 .. MAXS - 1: largest dot of every four keys; slot MAXS: the tile's maximum; then
+    constexpr int EXPS = NM - 1 - MAXS;          // EXPS slots: the exponentials, and a key block's maximum in each of the first four
+    auto beside = [&](auto more_tag, auto fast_tag, f32x16 (&next)[2], uint32_t slot_off, const f32x16 (&acc)[2], int t) __attribute__((always_inline)) {
+      constexpr bool MORE = decltype(more_tag)::value, FAST = decltype(fast_tag)::value;
+      bf16x8 fr[RING];
+      const uint32_t base = kaddr0 + slot_off;
+      uint32_t at = base;
+      auto request = [&](int j) __attribute__((always_inline)) {
+        if (j >= NM) return;
+        if ((j & 1) == 0 && j > 0) asm volatile("v_xor_b32 %0, %1, %2" : "=v"(at) : "n"((j >> 1) << 5), "v"(base));
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(fr[j % RING]) : "v"(at), "n"((j & 1) * 32 * ROWB));
+      };
+      float gmax[2][4], neg_m = 0.f, s0 = 0.f, s1 = 0.f;
+      f32x4 w;
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < PF; ++j)
+        if (MORE) request(j);
+#pragma unroll
+      for (int j = 0; j < NM; ++j) {
+        if (MORE) {
+          request(j + PF);
+          asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(fr[j % RING]) : "n"(j + PF < NM ? PF : NM - 1 - j));
+          next[j & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[j % RING], qf[j >> 1], j < 2 ? zero : next[j & 1], 0, 0, 0);
+        }
+        if (FAST) {
+          if (j < MAXS) {
+#pragma unroll
+            for (int x = j * 8 / MAXS; x < (j + 1) * 8 / MAXS; ++x) {
+              const int mb = x >> 2, g = x & 3;
+              gmax[mb][g] = __builtin_fmaxf(__builtin_fmaxf(acc[mb][4 * g], __builtin_fmaxf(acc[mb][4 * g + 1], acc[mb][4 * g + 2])),
+                                            acc[mb][4 * g + 3]);
+              asm volatile("" ::"v"(gmax[mb][g]));
+            }
+          } else if (j == MAXS) {
+            // the running maximum only moves when it would grow by more than 2^8: the common path is one
+            // fused multiply-add, one exp2 and one add per logit
+            float bm = __builtin_fmaxf(gmax[0][0], __builtin_fmaxf(gmax[0][1], gmax[0][2]));
+            bm = __builtin_fmaxf(bm, __builtin_fmaxf(gmax[0][3], gmax[1][0]));
+            bm = __builtin_fmaxf(bm, __builtin_fmaxf(gmax[1][1], gmax[1][2]));
+            bm = __builtin_fmaxf(bm, gmax[1][3]);
+            bm *= a.scale_log2;
+            float p, q;
+            both_halves(bm, p, q);
+            bm = fmaxf(p, q);
+            if (__any(bm - m > 8.0f)) {
+              const float mn = fmaxf(m, bm);
+              l *= __builtin_amdgcn_exp2f(m - mn);     // m = -inf: l is 0 and stays 0
+              m = mn;
+            }
+            neg_m = m == -INFINITY ? 0.f : -m;         // (no key seen yet)
+          } else {
+            const int x = j - MAXS - 1;
+            if (bmax && x < 4) w[x] = block_max(gmax[0][x] * a.scale_log2, gmax[1][x] * a.scale_log2);
+            if (bmax && x < 4) w[x] = seen > 0 ? w[x] : -INFINITY;
+            if (bmax && x == 4) store_max(w, t_lo + t);
+#pragma unroll
+            for (int e = x * 32 / EXPS; e < (x + 1) * 32 / EXPS; ++e) {
+              float& sum = (e & 1) ? s1 : s0;
+              sum += __builtin_amdgcn_exp2f(fmaf(acc[e & 1][e >> 1], a.scale_log2, neg_m));
+            }
+            asm volatile("" ::"v"(s0), "v"(s1));
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      static_assert(EXPS >= 5, "a slot for the store");
+      if (FAST) l += s0 + s1;
+    };
+    // Tile t + 1 has landed once at most what was issued after its loads is outstanding (loads and stores leave the counter in order): the loads of
+    // tile t + 2 (RI), if there is one, and with block maxima the stores of the tiles t - 2 and t - 1 that exist.  The count must be
+    // exact or low: a high count would let the wavefront through early.
+    auto wait_next = [&](int t) __attribute__((always_inline)) {
+      constexpr int C0 = RI, C1 = RI + 1, C2 = RI + 2;
+      static_assert(C2 < 16, "the low bits of the counter");
+      if (t + 2 >= nt) __builtin_amdgcn_s_waitcnt(0x0F70);
+      else if (!bmax || t == 0) __builtin_amdgcn_s_waitcnt(C0 | 0x0F70);
+      else if (t == 1) __builtin_amdgcn_s_waitcnt(C1 | 0x0F70);
+      else __builtin_amdgcn_s_waitcnt(C2 | 0x0F70);
+    };
+    f32x16 accA[2], accB[2];
+    uint32_t slot_off = 0;
+    if (nt > 0) {
+      if (nt > 2) __builtin_amdgcn_s_waitcnt((2 * RI) | 0x0F70);      // tile 0: those of tiles 1 and 2 may be outstanding
+      else __builtin_amdgcn_s_waitcnt(0x0F70);
+      asm volatile("s_barrier" ::: "memory");
+      beside(std::true_type{}, std::false_type{}, accA, 0, accB, 0);
+    }
+    auto step = [&](f32x16 (&acc)[2], f32x16 (&next)[2], int t) __attribute__((always_inline)) {
+      if (t + 1 < nt) {
+        wait_next(t);
+        asm volatile("s_barrier" ::: "memory");  // everyone's part of tile t + 1 is in; the slot of tile t is free
+        if (t + NSLOT < nt) fire(t + NSLOT);
+        slot_off = slot_off == (NSLOT - 1) * TILEB ? 0 : slot_off + TILEB;
+      }
+      if (!is_plain(t_lo + t)) hide(acc, t_lo + t);
+      if (t + 1 < nt) beside(std::true_type{}, std::true_type{}, next, slot_off, acc, t);
+      else beside(std::false_type{}, std::true_type{}, next, 0, acc, t);
+    };
+    for (int t = 0; t < nt; t += 2) {
+      step(accA, accB, t);
+      if (t + 1 < nt) step(accB, accA, t + 1);
     }
   }
 
@@ -666,7 +672,7 @@ void importance_tiles_kernel(const bf16_t* __restrict__ Qrep,
     float p, q;
     both_halves(l, p, q);                        // the two lane halves saw different keys
     if (hf == 0 && row < nrows)
-      part[(((int64_t)b * a.Hq + hq) * nrows + row) * IMP_MAX_SPLIT + split] = make_float2(m, p + q);
+      part[(((int64_t)b * a.Hq + hq) * nrows + row) * IMP_MAX_SPLIT + split] = seen > 0 ? make_float2(m, p + q) : make_float2(-INFINITY, 0.f);
   }
 }
 

@@ -1,0 +1,40 @@
+"""Block importance (bfloat16, 8 x 8 representatives) where its tiles and slices end: representatives without a token past a ragged
+query or key block, the causal diagonal, one tile and many, both pooling rules and both kinds of representatives.
+
+Tolerance: the bar of the other importance tests (fast exp2 of bfloat16 dots, 1e-3 relative)."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+from oracle import psa_oracle as orc
+from tests.psa_testlib import Buffers, gpu_params, to_dev
+
+pytestmark = pytest.mark.gpu
+
+psa = pytest.importorskip("paper_2512_04025_amd")
+
+
+@pytest.mark.parametrize("Hq,Hkv,N,d,bq,bk,causal,rep,est", [
+    (1, 1, 50, 128, 32, 32, False, "pooled", "max"),      # one tile; representatives without a token on both sides
+    (2, 2, 1003, 128, 32, 32, False, "pooled", "max"),    # the last row group holds rows without a token: four tiles
+    (2, 2, 1003, 64, 32, 32, False, "pooled", "mean"),
+    (2, 1, 4700, 128, 128, 64, True, "pooled", "max"),    # ten tiles, diagonal tiles in every row group, slices that end early
+    (2, 1, 4700, 64, 64, 64, True, "pooled", "max"),
+    (2, 1, 2900, 128, 64, 64, True, "pooled", "mean"),
+    (1, 1, 1500, 128, 64, 32, True, "strided", "max"),
+    (1, 1, 777, 64, 64, 32, False, "strided", "mean"),
+    (24, 24, 1540, 64, 32, 32, False, "pooled", "max"),   # slices of two tiles
+])
+def test_importance_edges(Hq, Hkv, N, d, bq, bk, causal, rep, est):
+    import torch
+    op = orc.Params(B=1, Hq=Hq, Hkv=Hkv, N=N, d=d, bq=bq, bk=bk, levels=2, dtype="bf16", causal=causal, sq=8, sk=8,
+                    rep_mode=rep, est_pool=est, alloc_mode="budget", budget=0.3)
+    gp = gpu_params(op)
+    host = si.random_qkv(11, 1, Hq, Hkv, N, d, "bf16")
+    Qd, Kd, Vd = (to_dev(x, "bf16") for x in host)
+    buf = Buffers(gp)
+    psa.psa_build_pyramid(gp, Kd, Vd, buf.Kpyr, buf.Vpyr)
+    psa.psa_allocate_levels(gp, Qd, Kd, buf.Kpyr, buf.M, buf.scratch, scores_out=buf.S)
+    torch.cuda.synchronize()
+    Q64, K64 = (si.to_f64(x, "bf16") for x in host[:2])
+    np.testing.assert_allclose(buf.S.cpu().numpy().astype(np.float64), orc.importance(Q64, K64, op), rtol=1e-3, atol=1e-9)
