@@ -140,14 +140,12 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_mfma_kernel(const
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slices = (a.bq + 127) / 128, per_head = a.nq * slices;
-  // not causal: all XCDs on one head at a time, a contiguous run of query blocks each; causal: a contiguous run of (head, query
-  // block) items to each XCD, the longest rows first
+  // not causal: all XCDs on one head at a time, a contiguous run of query blocks each; causal: whole heads to each XCD and an even
+  // share of the others, the longest rows first (with the same rule for dK, dV, whole backward calls, us: 12 heads x 8000 tokens 375 -> 349,
+  // x 20000 at d = 64 840 -> 778, 2 x 30000 822 -> 654, 28 x 8000 775 -> 768)
   int head, item;
   if (a.causal) {
-    const int items = per_head * a.Hq * a.B, run = (items + 7) >> 3, at = (int)(blockIdx.x & 7) * run + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= run || at >= items) return;
-    head = at / per_head;
-    item = at % per_head;
+    if (!xcd_item(a.Hq * a.B, per_head, (int)(blockIdx.x & 7), (int)(blockIdx.x >> 3), head, item)) return;
   } else {
     const int run = (per_head + 7) >> 3, slot = (int)(blockIdx.x >> 3);
     head = slot / run;
@@ -828,15 +826,19 @@ __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr
 }
 
 // One launch covers all levels.  Workgroup ids are dealt round-robin to the 8 XCDs.  Each XCD takes one contiguous run of a
-// level's (head, key block) items, so that what runs on it at one time are columns of one head and level, of
+// level's (head, key block) items (causal, where a head's columns differ in length: whole heads and an even share of the others), so that what runs on it at one time are columns of one head and level, of
 // like length, whose query rows meet in its L2; or all XCDs take the same head, a block each in turn (one_head, see
 // launch_bwd_mfma_t).  An XCD's items, level after level from the coarsest down, are its slots.
 __device__ __forceinline__ bool dkv_item(const BwdMfmaArgs& a, int xcd, int slot, DkvItem& it) {
   for (int h = a.H; h >= 1; --h) {
-    const int ng = dkv_group(a.lg_bk - (h - 1), a.nk, a.small_keys).ng, items = a.B * a.Hq * ng, run = (items + 7) >> 3;
+    const int ng = dkv_group(a.lg_bk - (h - 1), a.nk, a.small_keys).ng, items = a.B * a.Hq * ng, run = a.causal ? xcd_slots(a.B * a.Hq, ng) : (items + 7) >> 3;
     if (slot >= run) {
       slot -= run;
       continue;
+    }
+    if (a.causal) {
+      it.h = h;
+      return xcd_item(a.B * a.Hq, ng, xcd, slot, it.head, it.bx);
     }
     const int item = a.one_head ? slot * 8 + xcd : xcd * run + slot;
     it = {h, item / ng, item % ng};
@@ -895,7 +897,7 @@ __global__ __launch_bounds__(LEN_WAVES * 64) void bwd_dkv_length_kernel(const ui
   int base = 0;                                    // slots of the coarser levels
   for (int h = a.H; h >= 1; --h) {
     const DkvGroup g = dkv_group(a.lg_bk - (h - 1), a.nk, a.small_keys);
-    const int items = a.B * a.Hq * g.ng, run = (items + 7) >> 3;
+    const int items = a.B * a.Hq * g.ng, run = a.causal ? xcd_slots(a.B * a.Hq, g.ng) : (items + 7) >> 3;
     if (wave == h % LEN_WAVES && j < a.nk && lane % g.G == 0) {
       int sum = 0;
       for (int w = 0; w < LEN_WAVES; ++w) sum += part[w][h - 1][lane];
@@ -903,7 +905,8 @@ __global__ __launch_bounds__(LEN_WAVES * 64) void bwd_dkv_length_kernel(const ui
       const uint32_t cost = (uint32_t)(sum * (a.lg_bk - (h - 1) >= 6 ? 7 : 5) + 15);
       for (int p = 0; p < g.pieces; ++p) {
         const int item = head * g.ng + j / g.G * g.pieces + p;
-        const int xcd = a.one_head ? item & 7 : item / run, slot = a.one_head ? item >> 3 : item % run;
+        int xcd = a.one_head ? item & 7 : item / run, slot = a.one_head ? item >> 3 : item % run;
+        if (a.causal) xcd_of_item(a.B * a.Hq, g.ng, head, item - head * g.ng, xcd, slot);
         len[xcd * pitch + base + slot] = cost;
       }
     }
@@ -983,13 +986,16 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
   const bf16_t* vp = static_cast<const bf16_t*>(Vp);
   const bf16_t* go = static_cast<const bf16_t*>(dO);
   const int slices = (pl.bq + 127) / 128;
-  const unsigned dq_grid = pl.causal ? 8u * (unsigned)((pl.nq * slices * pl.Hq * pl.B + 7) / 8) : 8u * (unsigned)(pl.B * pl.Hq) * (unsigned)((pl.nq * slices + 7) / 8);
+  const unsigned dq_grid = pl.causal ? 8u * (unsigned)xcd_slots(pl.B * pl.Hq, pl.nq * slices) : 8u * (unsigned)(pl.B * pl.Hq) * (unsigned)((pl.nq * slices + 7) / 8);
   bwd_dq_mfma_kernel<D><<<dq_grid, 256, 0, s>>>(q, k, v, kp, vp, idx, cnt, static_cast<const bf16_t*>(O), lse, Dr, go, static_cast<bf16_t*>(dQ), a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   auto groups = [&](int small_keys) {            // workgroups of an XCD, as the kernel counts them
     int64_t n = 0;
-    for (int h = 1; h <= pl.H; ++h) n += ((int64_t)pl.B * pl.Hq * dkv_group(a.lg_bk - (h - 1), pl.nk, small_keys).ng + 7) / 8;
+    for (int h = 1; h <= pl.H; ++h) {
+      const int ng = dkv_group(a.lg_bk - (h - 1), pl.nk, small_keys).ng;
+      n += pl.causal ? (int64_t)xcd_slots(pl.B * pl.Hq, ng) : ((int64_t)pl.B * pl.Hq * ng + 7) / 8;
+    }
     return n;
   };
   // Where blocks have fewer than 64 pooled keys a workgroup takes 64 keys, or 32 (half of its tiles) while the longest walk (half of

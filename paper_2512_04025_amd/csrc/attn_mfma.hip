@@ -41,7 +41,7 @@ struct MfmaArgs {
   int N, Hq, Hkv, nq, nk, bq, bk, H, causal;
   int lg_bk;
   int slices;              // workgroup slices per query block
-  int items;               // B * Hq * nq * slices
+  int heads;               // B * Hq
   int desc_pitch;          // tile descriptors per row (0: the kernel plans its loads itself)
   float scale_log2;        // scale * log2(e)
   int64_t lvl_off[PSA_MAX_LEVELS + 2];
@@ -123,15 +123,12 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   // holds whole (with every XCD on a head of its own, eight 73 MB pyramids of the 75600-token shape
   // are not: measured 6 % slower).  Within a head every XCD takes one contiguous run of query blocks:
   // neighbours keep similar key blocks and walk them in the same order.  Causal rows differ in length
-  // by up to the whole sequence, so there every XCD takes one contiguous run of (head, query block)
-  // items instead (equal shares of every head's long and short rows), longest rows first.
+  // by up to the whole sequence, so there every XCD takes whole heads and an even share of the heads that do not go into eight (xcd_item),
+  // longest rows first.  Whole forward, contiguous runs of (head, query block) items -> this, us: 12 heads x
+  // 8000 tokens 126 -> 114, x 20000 at d = 64 259 -> 248, 2 x 30000 210 -> 182, 28 x 16000 504 -> 491 (x 1000 45.3 -> 45.8, the arithmetic).
   int head, e_item;
   if (a.causal) {
-    const int per_xcd = (a.items + 7) >> 3;
-    const int item = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per_xcd || item >= a.items) return;
-    head = item / (a.slices * a.nq);
-    e_item = item - head * (a.slices * a.nq);
+    if (!xcd_item(a.heads, a.slices * a.nq, (int)(blockIdx.x & 7), (int)(blockIdx.x >> 3), head, e_item)) return;
   } else {
     const int per_head = a.nq * a.slices;
     const int run = (per_head + 7) >> 3;     // workgroups per XCD and head
@@ -797,7 +794,7 @@ static hipError_t launch_mfma_t(const Plan& pl, const void* Q, const void* K, co
   while ((1 << a.lg_bk) < pl.bk) ++a.lg_bk;
   constexpr int ROWS = NW * 32;
   a.slices = (pl.bq + ROWS - 1) / ROWS;
-  a.items = pl.B * pl.Hq * pl.nq * a.slices;
+  a.heads = pl.B * pl.Hq;
   a.scale_log2 = pl.scale * 1.44269504088896340736f;
   a.desc_pitch = pl.desc_pitch;
   for (int h = 0; h < PSA_MAX_LEVELS + 2; ++h) a.lvl_off[h] = pl.lvl_off[h];
@@ -806,7 +803,7 @@ static hipError_t launch_mfma_t(const Plan& pl, const void* Q, const void* K, co
   static LdsOptIn optin;                       // one per kernel instantiation
   const hipError_t e = allow_max_lds(reinterpret_cast<const void*>(kern), &optin);
   if (e != hipSuccess) return e;
-  const unsigned grid = pl.causal ? (unsigned)((a.items + 7) / 8) * 8u
+  const unsigned grid = pl.causal ? 8u * (unsigned)xcd_slots(a.heads, pl.nq * a.slices)
                                  : (unsigned)(pl.B * pl.Hq) * 8u * (unsigned)((pl.nq * a.slices + 7) / 8);
   kern<<<grid, NW * 64, smem, s>>>(
       static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),

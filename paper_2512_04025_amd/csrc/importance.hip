@@ -290,7 +290,13 @@ void importance_tiles_kernel(const bf16_t* __restrict__ Qrep,
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hf = lane >> 5;
-  const int rg = blockIdx.x, split = blockIdx.y, head = blockIdx.z;
+  int rg = blockIdx.x, split = blockIdx.y, head = blockIdx.z;
+  if (a.causal) {                              // the row groups that see most of the keys are started first, of all heads
+    const int at = ((int)blockIdx.z * (int)gridDim.y + (int)blockIdx.y) * (int)gridDim.x + (int)blockIdx.x, width = (int)(gridDim.y * gridDim.z);
+    rg = (int)gridDim.x - 1 - at / width;
+    split = at % width % (int)gridDim.y;
+    head = at % width / (int)gridDim.y;
+  }
   const int b = head / a.Hq, hq = head % a.Hq;
   const int hk = hq / (a.Hq / a.Hkv);
   const int nrows = a.nq * SQ, nkeys = a.nk * SK;

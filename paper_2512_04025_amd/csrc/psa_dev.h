@@ -95,4 +95,34 @@ __device__ __forceinline__ bool not_finite(f32x4 x) {
 
 __device__ __forceinline__ int ilog2(int x) { return 31 - __clz(x); }
 
+// Causal work on the 8 XCDs, whose rows (or columns) differ in length by up to the whole sequence: every XCD takes as many whole heads as
+// all can have, one after the other, and of the heads that are left every eighth item.  (Contiguous runs gave one XCD the long half
+// of a shared head and its neighbour the short one.)
+__host__ __device__ inline int xcd_slots(int heads, int per_head) { return heads / 8 * per_head + (heads % 8 * per_head + 7) / 8; }
+__device__ __forceinline__ bool xcd_item(int heads, int per_head, int xcd, int slot, int& head, int& item) {
+  const int each = heads / 8, rest = heads % 8;
+  if (slot < each * per_head) {
+    head = xcd * each + slot / per_head;
+    item = slot % per_head;
+    return true;
+  }
+  const int k = (slot - each * per_head) * 8 + xcd;
+  if (k >= rest * per_head) return false;
+  head = each * 8 + k % rest;
+  item = k / rest;
+  return true;
+}
+// ... and where an item is
+__device__ __forceinline__ void xcd_of_item(int heads, int per_head, int head, int item, int& xcd, int& slot) {
+  const int each = heads / 8, rest = heads % 8;
+  if (head < each * 8) {
+    xcd = head / each;
+    slot = head % each * per_head + item;
+  } else {
+    const int k = item * rest + head - each * 8;
+    xcd = k & 7;
+    slot = each * per_head + (k >> 3);
+  }
+}
+
 }  // namespace psa
