@@ -18,6 +18,7 @@
 //        dKbar^T += Q^T dS with the transposing load on the staged dO and Q.
 #include <type_traits>
 
+#include "bwd_walk.h"
 #include "psa_dev.h"
 #include "psa_internal.h"
 
@@ -466,7 +467,7 @@ __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr
   using S = DkvShape<D, RH>;
   constexpr int NW = S::NW, NT = S::NT, KEYS = S::KEYS, ROWS = S::ROWS, ROWB = S::ROWB, TILEB = S::TILEB, CHUNKS = S::CHUNKS;
   constexpr int CPR = D / 8, KS = D / 32, MD = D / 16, RPI = 64 / CPR, WROWS = ROWS / NW, NI = WROWS / RPI;   // rows and load instructions per wavefront, stage and tensor
-  static_assert(WROWS == 16, "a wavefront's rows are of one chunk and start where the swizzle does");
+  static_assert(WROWS == DKV_PART && WROWS == 16, "a wavefront's rows are of one chunk and start where the swizzle does");
   // two stage buffers (Q rows [ROWS][ROWB] | dO rows [ROWS][ROWB]), two of statistics (lse [ROWS] | -D [ROWS]), the list of query
   // blocks (the group's blocks that each uses, its number), counts per wavefront
   constexpr int BUFB = 2 * TILEB, STATB = 8 * ROWS, OFF_STAT = 2 * BUFB, OFF_BITS = OFF_STAT + 2 * STATB, OFF_ROW = OFF_BITS + 4 * DKV_LIST,
@@ -537,18 +538,15 @@ __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr
   const int cpe = (a.bq + 31) >> 5;
   auto entry_of = [&](int c) __attribute__((always_inline)) { return a.lg_cpe >= 0 ? c >> a.lg_cpe : c / cpe; };
   const rsrc_words lrsrc = make_rsrc(lse + qhead * a.N, (uint32_t)a.N * 4u), drsrc = make_rsrc(Dr + qhead * a.N, (uint32_t)a.N * 4u);
-  struct Part { int row, valid; };                 // WROWS rows of a query block: the first one, and how many there are
-  auto part_of = [&](int c) __attribute__((always_inline)) -> Part {
+  auto part_of = [&](int c) __attribute__((always_inline)) -> DkvPart {     // this wavefront's rows of the chunk
     const int e = entry_of(c);
-    const int blk = __builtin_amdgcn_readfirstlane((int)kept_row[e]), sub = (c - e * cpe) * 32 + wave * WROWS % 32;
-    int end = a.N - blk * a.bq;
-    end = end < a.bq ? end : a.bq;
-    return Part{blk * a.bq + sub, end - sub};
+    const int blk = __builtin_amdgcn_readfirstlane((int)kept_row[e]);
+    return dkv_part(a.N, a.bq, blk, (c - e * cpe) * 32 + wave * WROWS % 32);
   };
   auto fire = [&](int c0, int total, int to) __attribute__((always_inline)) {
     const int c = c0 + wave * WROWS / 32;
     if (c >= total) return;
-    const Part p = part_of(c);
+    const DkvPart p = part_of(c);
     const int ln = lane_again(), lrow = ln / CPR;
     // byte offset that this lane reads with load 0; with load k, RPI rows further down: ^ row_swizzle(k * RPI) << 4
     const uint32_t lane_off = lrow * ROWB + (((ln % CPR) ^ row_swizzle<D>(lrow)) << 4);
@@ -566,12 +564,12 @@ __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr
       each<NI>([&](auto tag) __attribute__((always_inline)) {
         constexpr int k = decltype(tag)::value;
         const int v = (int)flip<(row_swizzle<D>(k * RPI) << 4)>(lane_off);
-        const int r = k * RPI + lrow, at = (p.row + (r < p.valid ? r : p.valid - 1) - lrow) * ROWB + v;
+        const int r = k * RPI + lrow, at = (dkv_source_row(p, r) - lrow) * ROWB + v;
         load_lds16(qrsrc, dst + k * 1024, at, 0);
         load_lds16(grsrc, dst + k * 1024 + TILEB, at, 0);
       });
     }
-    if (ln < WROWS) {                              // lse and -D of the rows
+    if (dkv_reads_stat(p, ln)) {                   // lse and -D of the rows that there are (step() makes up the others')
       load_lds4(lrsrc, st, ln * 4, p.row * 4);
       load_lds4(drsrc, st + 4 * ROWS, ln * 4, p.row * 4);
     }
@@ -714,7 +712,7 @@ __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr
     // no longer being read
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (c0 + wave * WROWS / 32 < total) {
-      const Part p = part_of(c0 + wave * WROWS / 32);
+      const DkvPart p = part_of(c0 + wave * WROWS / 32);
       if (p.valid < WROWS) {                       // rows past the end of the query block: weight 0
         const int ln = lane_again();
         float* stat = reinterpret_cast<float*>(smem + OFF_STAT + at * STATB);

@@ -1,0 +1,50 @@
+"""The rows that the dK, dV walk touches, worked out by the kernel's own arithmetic (csrc/bwd_walk.h) compiled for the host:
+every row of a query block once, and nothing outside it, also where the last block is short."""
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_04025_amd", "csrc")
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "bwd_walk.h"
+using namespace psa;
+int main(int, char** argv) {
+  const int N = atoi(argv[1]), bq = atoi(argv[2]), nq = (N + bq - 1) / bq, cpe = (bq + 31) / 32;
+  for (int blk = 0; blk < nq; ++blk)
+    for (int sub = 0; sub < cpe * 32; sub += DKV_PART) {
+      const DkvPart p = dkv_part(N, bq, blk, sub);
+      for (int r = 0; r < 64; ++r)
+        if (dkv_reads_stat(p, r)) printf("stat %d %d\n", blk, p.row + r);
+      for (int r = 0; r < DKV_PART; ++r) printf("row %d %d\n", blk, dkv_source_row(p, r));
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def walk(tmp_path_factory):
+    folder = tmp_path_factory.mktemp("walk")
+    (folder / "walk.cpp").write_text(PROGRAM)
+    exe = str(folder / "walk")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(folder / "walk.cpp"), "-o", exe], check=True)
+
+    def run(N, bq):
+        lines = subprocess.run([exe, str(N), str(bq)], check=True, capture_output=True, text=True).stdout.split("\n")
+        out = {"stat": [], "row": []}
+        for line in filter(None, lines):
+            kind, blk, row = line.split()
+            out[kind].append((int(blk), int(row)))
+        return out
+    return run
+
+
+@pytest.mark.parametrize("N,bq", [(1, 128), (8, 8), (200, 128), (256, 128), (257, 128), (283, 24), (300, 32), (461, 96), (523, 40), (1000, 128)])
+def test_walk_stays_inside_the_query_blocks(walk, N, bq):
+    got = walk(N, bq)
+    assert got["stat"] == [(row // bq, row) for row in range(N)]       # lse and D: every row once, none past the end
+    assert all(0 <= row < N and row // bq == blk for blk, row in got["row"])
+    assert set(got["row"]) == set(got["stat"])
