@@ -786,7 +786,8 @@ __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr
       nkept += found;
       __syncthreads();
     }
-    total = __builtin_amdgcn_readfirstlane(nkept) * cpe;
+    total = __builtin_amdgcn_readfirstlane(nkept);
+    total = dkv_chunks(a.N, a.bq, a.nq, total, total > 0 ? __builtin_amdgcn_readfirstlane((int)kept_row[total - 1]) : 0);
     fire(0, total, at);
     for (int c0 = 0; c0 < total; c0 += CHUNKS) step(c0);
     __syncthreads();                               // everyone has read the last stage: the buffers may be filled again

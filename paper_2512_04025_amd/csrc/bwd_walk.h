@@ -7,8 +7,8 @@ namespace psa {
 
 constexpr int DKV_PART = 16;       // rows of a stage that one wavefront fetches
 
-// Rows row .. row + DKV_PART - 1 of the sequence, of which the first `valid` are of the query block (none if <= 0: the last block's 32-row
-// chunks go past its end).
+// Rows row .. row + DKV_PART - 1 of the sequence, of which the first `valid` are of the query block (none if <= 0: a 32-row chunk
+// is two parts).
 struct DkvPart { int row, valid; };
 constexpr DkvPart dkv_part(int N, int bq, int blk, int sub) {
   const int left = N - blk * bq, rows = left < bq ? left : bq;
@@ -18,6 +18,13 @@ constexpr DkvPart dkv_part(int N, int bq, int blk, int sub) {
 constexpr int dkv_source_row(DkvPart p, int r) { return p.row + (r < p.valid ? r : p.valid - 1); }
 // Whether lse and D are read for row r of the part.  They are arrays of exactly N entries a head, so nothing past the end may be.
 constexpr bool dkv_reads_stat(DkvPart p, int r) { return r < DKV_PART && r < p.valid; }
+
+// 32-row chunks in the walk over `kept` query blocks, given in order, of which the last one is `last`: the short block at the sequence's end has
+// no more of them than it has rows for.
+constexpr int dkv_chunks(int N, int bq, int nq, int kept, int last) {
+  const int cpe = (bq + 31) / 32, rows = N - (nq - 1) * bq;
+  return kept * cpe - (kept > 0 && last == nq - 1 ? cpe - (rows + 31) / 32 : 0);
+}
 
 }  // namespace psa
 #endif

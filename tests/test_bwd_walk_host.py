@@ -1,5 +1,5 @@
 """The rows that the dK, dV walk touches, worked out by the kernel's own arithmetic (csrc/bwd_walk.h) compiled for the host:
-every row of a query block once, and nothing outside it, also where the last block is short."""
+every row of a query block once, nothing outside it and no chunk without a row, also where the last block is short."""
 import os
 import subprocess
 
@@ -14,8 +14,12 @@ PROGRAM = r"""
 using namespace psa;
 int main(int, char** argv) {
   const int N = atoi(argv[1]), bq = atoi(argv[2]), nq = (N + bq - 1) / bq, cpe = (bq + 31) / 32;
+  const int total = dkv_chunks(N, bq, nq, nq, nq - 1), first = dkv_chunks(N, bq, nq, nq / 2, nq / 2 - 1);
+  printf("first 0 %d\n", first);
   for (int blk = 0; blk < nq; ++blk)
     for (int sub = 0; sub < cpe * 32; sub += DKV_PART) {
+      if (blk * cpe + sub / 32 >= total) continue;
+      if (sub % 32 == 0) printf("chunk %d %d\n", blk, sub);
       const DkvPart p = dkv_part(N, bq, blk, sub);
       for (int r = 0; r < 64; ++r)
         if (dkv_reads_stat(p, r)) printf("stat %d %d\n", blk, p.row + r);
@@ -34,7 +38,7 @@ def walk(tmp_path_factory):
 
     def run(N, bq):
         lines = subprocess.run([exe, str(N), str(bq)], check=True, capture_output=True, text=True).stdout.split("\n")
-        out = {"stat": [], "row": []}
+        out = {"stat": [], "row": [], "chunk": [], "first": []}
         for line in filter(None, lines):
             kind, blk, row = line.split()
             out[kind].append((int(blk), int(row)))
@@ -48,3 +52,5 @@ def test_walk_stays_inside_the_query_blocks(walk, N, bq):
     assert got["stat"] == [(row // bq, row) for row in range(N)]       # lse and D: every row once, none past the end
     assert all(0 <= row < N and row // bq == blk for blk, row in got["row"])
     assert set(got["row"]) == set(got["stat"])
+    assert all(blk * bq + sub < N for blk, sub in got["chunk"])        # every chunk has a row
+    assert got["first"] == [(0, -(-N // bq) // 2 * -(-bq // 32))]      # (blocks before the last one have all of theirs)
