@@ -604,7 +604,9 @@ void importance_tiles_kernel(const bf16_t* __restrict__ Qrep,
             bm = fmaxf(p, q);
             if (__any(bm - m > 8.0f)) {
               const float mn = fmaxf(m, bm);
-              l *= __builtin_amdgcn_exp2f(m - mn);     // m = -inf: l is 0 and stays 0
+              // m = -inf: l is 0 and stays 0, also in a row whose logits have all been -inf (unseen keys, or dots below the range of
+              // float32) when another row of the wavefront moves its maximum
+              l *= __builtin_amdgcn_exp2f(m - (mn == -INFINITY ? 0.f : mn));
               m = mn;
             }
             neg_m = m == -INFINITY ? 0.f : -m;         // (no key seen yet)

@@ -38,3 +38,31 @@ def test_importance_edges(Hq, Hkv, N, d, bq, bk, causal, rep, est):
     torch.cuda.synchronize()
     Q64, K64 = (si.to_f64(x, "bf16") for x in host[:2])
     np.testing.assert_allclose(buf.S.cpu().numpy().astype(np.float64), orc.importance(Q64, K64, op), rtol=1e-3, atol=1e-9)
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("est", ["max", "mean"])
+def test_logits_below_the_range_of_float32(est, causal):
+    """Every second tile of 64 representative keys gives some rows logits that overflow to -inf, next to rows of the same wavefront
+    for which they are finite: such a key has weight 0, and what the row sees later (or has seen) counts as ever.  Two tiles a slice."""
+    import torch
+    N, d, bq, bk = 8192, 64, 128, 64
+    op = orc.Params(B=1, Hq=1, Hkv=1, N=N, d=d, bq=bq, bk=bk, levels=2, dtype="bf16", causal=causal, sq=8, sk=8, est_pool=est,
+                    rep_mode="pooled", alloc_mode="budget", budget=0.3)
+    gp = gpu_params(op)
+    rng = np.random.default_rng(3)
+    token = np.arange(N)
+    q = rng.uniform(0.5, 1.5, (N, d)) * np.where(token // bq % 4 == 0, 1e30, 1e-10)[:, None]
+    k = np.where((token // (8 * bk) % 2 == 0)[:, None], -1e10, 1e-30 * rng.standard_normal((N, d)))
+    if causal:
+        k[:bk] = 1e-30                             # (every row sees a key with a finite logit)
+    def bits(x):
+        return torch.from_numpy(x.astype(np.float32)).to(torch.bfloat16).view(torch.int16).numpy().view(np.uint16)[None, None]
+    host = bits(q), bits(k)
+    Qd, Kd = (to_dev(x, "bf16") for x in host)
+    buf = Buffers(gp)
+    psa.psa_build_pyramid(gp, Kd, Kd, buf.Kpyr, buf.Vpyr)
+    psa.psa_allocate_levels(gp, Qd, Kd, buf.Kpyr, buf.M, buf.scratch, scores_out=buf.S)
+    torch.cuda.synchronize()
+    Q64, K64 = (si.to_f64(x, "bf16") for x in host)
+    np.testing.assert_allclose(buf.S.cpu().numpy().astype(np.float64), orc.importance(Q64, K64, op), rtol=1e-3, atol=1e-9)
