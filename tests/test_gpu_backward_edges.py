@@ -92,3 +92,42 @@ def test_tensors_between_two_chunks_give_the_same_bits(dtype, d, bq, bk, levels,
         results.append([x.clone() for x in (buf.M, buf.S, O, buf.lse, *grads)])
     for name, a, b in zip(("M", "S", "O", "lse", "dQ", "dK", "dV"), *results):
         assert torch.equal(a, b), name
+
+
+def _before_nan(x):
+    """The same tensor with 64 KB of NaN right behind it."""
+    import torch
+    flat = torch.full((x.numel() + 65536 // x.element_size(),), float("nan"), dtype=x.dtype, device=x.device)
+    y = flat[:x.numel()].view(x.shape)
+    y.copy_(x)
+    return y
+
+
+@pytest.mark.parametrize("N,d,bq,bk,levels,causal", [
+    (321, 128, 128, 64, 4, False), (450, 64, 128, 128, 4, True), (449, 128, 128, 128, 1, False), (290, 128, 32, 32, 3, True), (1000, 64, 128, 64, 2, False)])
+def test_what_lies_behind_the_tensors_does_not_count(N, d, bq, bk, levels, causal):
+    """Ragged lengths whose last tiles, stages and chunks reach far past the last row: the same bits with NaN behind every input."""
+    import torch
+    Hq, Hkv = 2, 1
+    op = orc.Params(B=1, Hq=Hq, Hkv=Hkv, N=N, d=d, bq=bq, bk=bk, levels=levels, dtype="bf16", causal=causal, sq=8, sk=8)
+    gp = gpu_params(op)
+    host = si.random_qkv(5, 1, Hq, Hkv, N, d, "bf16")
+    dO = si.random_qkv(6, 1, Hq, Hq, N, d, "bf16")[0]
+    vis = orc.block_visibility(op)
+    M = np.broadcast_to(np.arange(op.nk) % levels + 1, (1, Hq, op.nq, op.nk))
+    Md = torch.from_numpy(np.where(vis[None, None] == 0, 0, np.where(vis[None, None] == 2, 1, M)).astype(np.uint8)).cuda()
+    results = []
+    for place in (lambda x: x, _before_nan):
+        Q, K, V, go = (place(to_dev(x, "bf16")) for x in (*host, dO))
+        buf = Buffers(gp)
+        psa.psa_build_pyramid(gp, K, V, buf.Kpyr, buf.Vpyr)
+        psa.psa_attention_fwd(gp, Q, K, V, buf.Kpyr, buf.Vpyr, Md, buf.O, buf.scratch, lse=buf.lse)
+        O, lse = place(buf.O), place(buf.lse)
+        grads = [torch.full_like(x, float("nan")) for x in (Q, K, V)]
+        scratch = torch.full((psa.psa_query_bwd_sizes(gp),), 255, dtype=torch.uint8, device="cuda")
+        psa.psa_attention_bwd(gp, Q, K, V, buf.Kpyr, buf.Vpyr, Md, O, lse, go, *grads, scratch)
+        torch.cuda.synchronize()
+        results.append([x.clone() for x in (buf.O, buf.lse, *grads)])
+    for name, a, b in zip(("O", "lse", "dQ", "dK", "dV"), *results):
+        assert torch.equal(a, b), name
+        assert not torch.isnan(a).any(), name
