@@ -27,6 +27,7 @@ namespace psa {
 struct BwdMfmaArgs {
   int B, N, Hq, Hkv, nq, nk, bq, bk, lg_bk, H, causal;
   int one_head;                          // dK, dV: all XCDs work on one head's neighbouring keys
+  int dq_runs;                           // dQ: each XCD takes a contiguous run of all heads' query blocks
   int small_keys;                        // dK, dV: keys of a workgroup where blocks have fewer than 64
   int lg_cpe;                            // dK, dV: log2 of the 32-row chunks of a query block, or -1
   float scale, scale_log2;
@@ -141,16 +142,23 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_mfma_kernel(const
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slices = (a.bq + 127) / 128, per_head = a.nq * slices;
-  // not causal: all XCDs on one head at a time, a contiguous run of query blocks each; causal: whole heads to each XCD and an even
-  // share of the others, the longest rows first (with the same rule for dK, dV, whole backward calls, us: 12 heads x 8000 tokens 375 -> 349,
-  // x 20000 at d = 64 840 -> 778, 2 x 30000 822 -> 654, 28 x 8000 775 -> 768)
+  // not causal: all XCDs on one head at a time, a contiguous run of query blocks each, or a contiguous run of all heads' blocks to each XCD
+  // (dq_runs, see launch_bwd_mfma_t); causal: whole heads to each XCD and an even share of the others, the longest rows first (with
+  // the same rule for dK, dV, whole backward calls, us: 12 heads x 8000 tokens 375 -> 349, x 20000 at d = 64 840 -> 778, 2 x 30000 822 -> 654,
+  // 28 x 8000 775 -> 768)
+  const int xcd = (int)(blockIdx.x & 7), slot = (int)(blockIdx.x >> 3);
   int head, item;
   if (a.causal) {
-    if (!xcd_item(a.Hq * a.B, per_head, (int)(blockIdx.x & 7), (int)(blockIdx.x >> 3), head, item)) return;
+    if (!xcd_item(a.Hq * a.B, per_head, xcd, slot, head, item)) return;
+  } else if (a.dq_runs) {
+    const int items = a.Hq * a.B * per_head, at = xcd * ((items + 7) >> 3) + slot;
+    if (at >= items) return;
+    head = at / per_head;
+    item = at % per_head;
   } else {
-    const int run = (per_head + 7) >> 3, slot = (int)(blockIdx.x >> 3);
+    const int run = (per_head + 7) >> 3;
     head = slot / run;
-    item = (int)(blockIdx.x & 7) * run + slot % run;
+    item = xcd * run + slot % run;
     if (item >= per_head) return;
   }
   const int slice = item % slices, i = a.causal ? a.nq - 1 - item / slices : item / slices;
@@ -985,7 +993,14 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
   const bf16_t* vp = static_cast<const bf16_t*>(Vp);
   const bf16_t* go = static_cast<const bf16_t*>(dO);
   const int slices = (pl.bq + 127) / 128;
-  const unsigned dq_grid = pl.causal ? 8u * (unsigned)xcd_slots(pl.B * pl.Hq, pl.nq * slices) : 8u * (unsigned)(pl.B * pl.Hq) * (unsigned)((pl.nq * slices + 7) / 8);
+  // A head of few query blocks does not reach all XCDs (2 blocks: two of the eight; 9: five, two blocks each but the last): there each XCD
+  // takes an eighth of all heads' blocks.  Whole call, us for a head's runs / this, 40 heads, one level: x 130 tokens 37.0 / 31.1, x 350
+  // 44.0 / 38.4, x 1100 92.7 / 80.5, d = 64 x 161 24.9 / 22.4, x 1100 55.3 / 50.4; four levels 12 x 2000 92.0 / 91.6.  From 32 blocks on the two are
+  // within 1 % of each other (12 x 4000 197.0 / 198.3, x 32760 6199 / 6254, 40 x 20000 8399 / 8391, 24 x 60000 46488 / 46609).
+  const int dq_items = pl.nq * slices, heads = pl.B * pl.Hq;
+  a.dq_runs = !pl.causal && dq_items < 32;
+  const int dq_slots = pl.causal ? xcd_slots(heads, dq_items) : (a.dq_runs ? (heads * dq_items + 7) / 8 : heads * ((dq_items + 7) / 8));
+  const unsigned dq_grid = 8u * (unsigned)dq_slots;
   bwd_dq_mfma_kernel<D><<<dq_grid, 256, 0, s>>>(q, k, v, kp, vp, idx, cnt, static_cast<const bf16_t*>(O), lse, Dr, go, static_cast<bf16_t*>(dQ), a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
