@@ -25,7 +25,7 @@
 namespace psa {
 
 struct BwdMfmaArgs {
-  int B, N, Hq, Hkv, nq, nk, bq, bk, lg_bk, H, causal;
+  int B, N, Hq, Hkv, group, nq, nk, bq, bk, lg_bk, H, causal;
   int one_head;                          // dK, dV: all XCDs work on one head's neighbouring keys
   int dq_runs;                           // dQ: each XCD takes a contiguous run of all heads' query blocks
   int small_keys;                        // dK, dV: keys of a workgroup where blocks have fewer than 64
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_mfma_kernel(const
   }
   const int slice = item % slices, i = a.causal ? a.nq - 1 - item / slices : item / slices;
   const int hq = head % a.Hq, b = head / a.Hq;
-  const int hk = hq / (a.Hq / a.Hkv);
+  const int hk = hq / a.group;
   const int64_t qhead = (int64_t)b * a.Hq + hq, khead = (int64_t)b * a.Hkv + hk;
   int row_end = (i + 1) * a.bq;
   row_end = row_end < a.N ? row_end : a.N;
@@ -439,7 +439,6 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_mfma_kernel(const
 // levels 2-4 / level 1: staging without products 1.93 / 1.29, products without staging 2.04 / 1.50, all 2.8 / 1.9.  128 keys to a workgroup of eight
 // wavefronts stage a quarter less and were slower (3.85 for levels 2-4: one lock-step group on a compute unit).
 constexpr int DKV_LIST = 1024;     // query blocks tested before their rows are walked
-constexpr int DKV_MAXG = 32;       // key blocks of a workgroup: one bit each
 // RH: 32-row chunks of a stage, one for every two wavefronts.  With one the workgroups are of two wavefronts: four of them on a compute
 // unit (d = 64: six) wait for each other less at their barriers than two of four wavefronts (12 heads x 32760 tokens 6.57 -> 6.32 ms for
 // the call, causal 28 x 8000 0.849 -> 0.780), but a walk takes twice as long (the rule stands at the launch).
@@ -457,18 +456,6 @@ struct DkvPtrs {
 };
 // What a workgroup does: level, (batch, query head), number among the head's workgroups of this level
 struct DkvItem { int h, head, bx; };
-// pooled keys of a workgroup, key blocks they belong to, workgroups that share a block, workgroups per head
-struct DkvGroup { int keys, G, pieces, ng; };
-__host__ __device__ inline DkvGroup dkv_group(int lg_th, int nk, int small_keys) {
-  const int th = 1 << lg_th;
-  DkvGroup r;
-  r.keys = th >= 64 ? 64 : small_keys;
-  r.G = r.keys / th;
-  r.G = r.G < 1 ? 1 : (r.G > DKV_MAXG ? DKV_MAXG : r.G);
-  r.pieces = th > r.keys ? th / r.keys : 1;
-  r.ng = r.pieces * ((nk + r.G - 1) / r.G);
-  return r;
-}
 
 template <int D, int RH, bool FULL, bool CAUSAL>
 __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr, const BwdMfmaArgs& a, const DkvItem it) {
@@ -493,11 +480,11 @@ __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr
   const float *lse = ptr.lse, *Dr = ptr.Dr;
   const int h = it.h, head = it.head, bx = it.bx;
   const DkvGroup grp = dkv_group(a.lg_bk - (h - 1), a.nk, a.small_keys);
-  const int G = grp.G, pieces = grp.pieces, keys = FULL ? KEYS : grp.keys;
+  const int G = 1 << grp.lg_G, keys = FULL ? KEYS : grp.keys;
   const int hq = head % a.Hq, b = head / a.Hq;
-  const int hk = hq / (a.Hq / a.Hkv);
+  const int hk = hq / a.group;
   const int lg_th = a.lg_bk - (h - 1), span = 1 << (h - 1);
-  const int j0 = (bx / pieces) * G, koff = (bx % pieces) * keys;       // first block; first key inside it
+  const int j0 = (bx >> grp.lg_pieces) << grp.lg_G, koff = (bx & ((1 << grp.lg_pieces) - 1)) * keys;       // first block; first key inside it
   const int64_t qhead = (int64_t)b * a.Hq + hq, khead = (int64_t)b * a.Hkv + hk;
   const bf16_t* kbase = h == 1 ? K + khead * (int64_t)a.N * D : Kp + a.lvl_off[h] + khead * ((int64_t)a.nk << lg_th) * D;
   const bf16_t* vbase = h == 1 ? V + khead * (int64_t)a.N * D : Vp + a.lvl_off[h] + khead * ((int64_t)a.nk << lg_th) * D;
@@ -880,9 +867,9 @@ __global__ __launch_bounds__(LEN_WAVES * 64) void bwd_dkv_length_kernel(const ui
   uint64_t mates[PSA_MAX_LEVELS];                  // the lanes whose blocks share a workgroup with this lane's
 #pragma unroll
   for (int h = 1; h <= PSA_MAX_LEVELS; ++h) {
-    const int G = h <= a.H ? dkv_group(a.lg_bk - (h - 1), a.nk, a.small_keys).G : 1;
+    const int lg_G = h <= a.H ? dkv_group(a.lg_bk - (h - 1), a.nk, a.small_keys).lg_G : 0, G = 1 << lg_G;
     n[h - 1] = 0;
-    mates[h - 1] = ((1ull << G) - 1ull) << (lane / G * G);     // (G is a power of two, at most 32)
+    mates[h - 1] = ((1ull << G) - 1ull) << (lane >> lg_G << lg_G);     // (G is at most 32)
   }
   for (int e0 = wave; e0 < a.nq; e0 += LEN_WAVES * 8) {
     int m[8];
@@ -905,13 +892,13 @@ __global__ __launch_bounds__(LEN_WAVES * 64) void bwd_dkv_length_kernel(const ui
   for (int h = a.H; h >= 1; --h) {
     const DkvGroup g = dkv_group(a.lg_bk - (h - 1), a.nk, a.small_keys);
     const int items = a.B * a.Hq * g.ng, run = a.causal ? xcd_slots(a.B * a.Hq, g.ng) : (items + 7) >> 3;
-    if (wave == h % LEN_WAVES && j < a.nk && lane % g.G == 0) {
+    if (wave == h % LEN_WAVES && j < a.nk && (lane & ((1 << g.lg_G) - 1)) == 0) {
       int sum = 0;
       for (int w = 0; w < LEN_WAVES; ++w) sum += part[w][h - 1][lane];
       // in fifths of a query block of a small block's walk; what a workgroup costs besides its walk is worth about three
       const uint32_t cost = (uint32_t)(sum * (a.lg_bk - (h - 1) >= 6 ? 7 : 5) + 15);
-      for (int p = 0; p < g.pieces; ++p) {
-        const int item = head * g.ng + j / g.G * g.pieces + p;
+      for (int p = 0; p < 1 << g.lg_pieces; ++p) {
+        const int item = head * g.ng + (j >> g.lg_G << g.lg_pieces) + p;
         int xcd = a.one_head ? item & 7 : item / run, slot = a.one_head ? item >> 3 : item % run;
         if (a.causal) xcd_of_item(a.B * a.Hq, g.ng, head, item - head * g.ng, xcd, slot);
         len[xcd * pitch + base + slot] = cost;
@@ -965,7 +952,7 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
                                     const void* O, const float* lse, const void* dO, float* Dr, float* dKp, float* dVp, void* dQ,
                                     hipStream_t s) {
   BwdMfmaArgs a;
-  a.B = pl.B; a.N = pl.N; a.Hq = pl.Hq; a.Hkv = pl.Hkv; a.nq = pl.nq; a.nk = pl.nk; a.bq = pl.bq; a.bk = pl.bk;
+  a.B = pl.B; a.N = pl.N; a.Hq = pl.Hq; a.Hkv = pl.Hkv; a.group = pl.group; a.nq = pl.nq; a.nk = pl.nk; a.bq = pl.bq; a.bk = pl.bk;
   a.H = pl.H; a.causal = pl.causal; a.scale = pl.scale; a.scale_log2 = pl.scale * LOG2E;
   a.lg_bk = 0;
   while ((1 << a.lg_bk) < pl.bk) ++a.lg_bk;

@@ -1,4 +1,4 @@
-// Which rows the dK, dV walk over the query blocks touches (attn_bwd_mfma.hip).  Plain arithmetic, the same on host and device, so
+// Which keys a workgroup of the dK, dV kernel takes and which rows its walk over the query blocks touches (attn_bwd_mfma.hip).  Plain arithmetic, the same on host and device, so
 // that its bounds can be checked without a GPU (tests/test_bwd_walk_host.py).
 #ifndef PSA_BWD_WALK_H
 #define PSA_BWD_WALK_H
@@ -24,6 +24,22 @@ constexpr bool dkv_reads_stat(DkvPart p, int r) { return r < DKV_PART && r < p.v
 constexpr int dkv_chunks(int N, int bq, int nq, int kept, int last) {
   const int cpe = (bq + 31) / 32, rows = N - (nq - 1) * bq;
   return kept * cpe - (kept > 0 && last == nq - 1 ? cpe - (rows + 31) / 32 : 0);
+}
+
+// log2 of the most key blocks of a workgroup: one bit each
+constexpr int DKV_LG_MAXG = 5;
+// pooled keys of a workgroup, log2 of the key blocks they belong to and of the workgroups that share a block, workgroups per head.
+// (All but the last are powers of two, and shifts: 19 integer divisions stood before a workgroup's first load, which short calls wait for.
+// Whole call, us, one level: 2 heads x 161 tokens 25.7 -> 25.1, in 32-token key blocks 24.8 -> 24.2, 12 x 300 30.8 -> 30.3, 40 x 161 31.5 -> 30.8.)
+struct DkvGroup { int keys, lg_G, lg_pieces, ng; };
+constexpr DkvGroup dkv_group(int lg_th, int nk, int small_keys) {
+  const int lg_keys = lg_th >= 6 || small_keys == 64 ? 6 : 5, packed = lg_keys - lg_th;
+  DkvGroup r{};
+  r.keys = 1 << lg_keys;
+  r.lg_G = packed < 0 ? 0 : (packed > DKV_LG_MAXG ? DKV_LG_MAXG : packed);
+  r.lg_pieces = packed < 0 ? -packed : 0;
+  r.ng = ((nk + (1 << r.lg_G) - 1) >> r.lg_G) << r.lg_pieces;
+  return r;
 }
 
 }  // namespace psa

@@ -1,4 +1,4 @@
-"""The rows that the dK, dV walk touches, worked out by the kernel's own arithmetic (csrc/bwd_walk.h) compiled for the host:
+"""The keys and rows that the dK, dV kernel's workgroups touch, worked out by the kernel's own arithmetic (csrc/bwd_walk.h) compiled for the host:
 every row of a query block once, nothing outside it and no chunk without a row, also where the last block is short."""
 import os
 import subprocess
@@ -12,7 +12,12 @@ PROGRAM = r"""
 #include <cstdlib>
 #include "bwd_walk.h"
 using namespace psa;
-int main(int, char** argv) {
+int main(int argc, char** argv) {
+  if (argc == 4) {
+    const DkvGroup g = dkv_group(atoi(argv[1]), atoi(argv[2]), atoi(argv[3]));
+    printf("group %d %d\ngroup %d %d\n", g.keys, g.lg_G, g.lg_pieces, g.ng);
+    return 0;
+  }
   const int N = atoi(argv[1]), bq = atoi(argv[2]), nq = (N + bq - 1) / bq, cpe = (bq + 31) / 32;
   const int total = dkv_chunks(N, bq, nq, nq, nq - 1), first = dkv_chunks(N, bq, nq, nq / 2, nq / 2 - 1);
   printf("first 0 %d\n", first);
@@ -36,9 +41,9 @@ def walk(tmp_path_factory):
     exe = str(folder / "walk")
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(folder / "walk.cpp"), "-o", exe], check=True)
 
-    def run(N, bq):
-        lines = subprocess.run([exe, str(N), str(bq)], check=True, capture_output=True, text=True).stdout.split("\n")
-        out = {"stat": [], "row": [], "chunk": [], "first": []}
+    def run(*args):
+        lines = subprocess.run([exe, *map(str, args)], check=True, capture_output=True, text=True).stdout.split("\n")
+        out = {"stat": [], "row": [], "chunk": [], "first": [], "group": []}
         for line in filter(None, lines):
             kind, blk, row = line.split()
             out[kind].append((int(blk), int(row)))
@@ -54,3 +59,16 @@ def test_walk_stays_inside_the_query_blocks(walk, N, bq):
     assert set(got["row"]) == set(got["stat"])
     assert all(blk * bq + sub < N for blk, sub in got["chunk"])        # every chunk has a row
     assert got["first"] == [(0, -(-N // bq) // 2 * -(-bq // 32))]      # (blocks before the last one have all of theirs)
+
+
+@pytest.mark.parametrize("small_keys", [32, 64])
+@pytest.mark.parametrize("nk", [1, 2, 31, 32, 33, 500])
+@pytest.mark.parametrize("lg_th", range(8))
+def test_groups_take_every_key_once(walk, lg_th, nk, small_keys):
+    (keys, lg_G), (lg_pieces, ng) = walk(lg_th, nk, small_keys)["group"]
+    th, taken = 1 << lg_th, []
+    assert keys == (64 if th >= 64 else small_keys) and 1 << lg_G <= 32
+    for bx in range(ng):                                              # as the kernel reads it
+        j0, koff = (bx >> lg_pieces) << lg_G, (bx & ((1 << lg_pieces) - 1)) * keys
+        taken += [j0 * th + koff + k for k in range(min(keys, (th << lg_G) - koff)) if j0 + (koff + k) // th < nk]
+    assert taken == list(range(nk * th))
