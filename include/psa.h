@@ -210,7 +210,7 @@ int psa_attention_fwd(const psa_params* p, const void* Q, const void* K, const v
  * bfloat16: the products run on MFMA with fp32 accumulation, P and dS rounded to bfloat16 for the products
  * that consume them (dQ per query block; the pooled dK, dV per key block and level, walking the level
  * map's column).  float32, and bfloat16 shapes the matrix-core kernels do not take (b_k < 8, more than
- * 8192 query blocks): fp32 products and sums throughout.  No atomics either way: the
+ * 8192 query blocks): fp32 products and sums throughout.  No atomics on results either way: the
  * result is bit-reproducible.
  * Errors: PSA_EINVAL (null pointer, misaligned scratch), PSA_EUNSUPPORTED (b_k > 128), PSA_ELAUNCH.
  */

@@ -3,7 +3,7 @@
 // version that serves float32 and the shapes this one does not take).
 //
 // Two kernels with fp32 accumulation, P and dS rounded to bfloat16 for the
-// products that consume them, no atomics, two wavefronts per SIMD (at most 256 registers per lane),
+// products that consume them, no atomics on results, two wavefronts per SIMD (at most 256 registers per lane),
 // double-buffered tiles that are loaded straight into LDS:
 //   bwd_dq_mfma_kernel   one workgroup per 128 query rows (a wavefront per 32), walking the row's
 //        level-sorted block list in tiles of 64 pooled keys gathered into LDS.  Same operand roles as the
@@ -38,9 +38,6 @@ struct BwdMfmaArgs {
 typedef __attribute__((ext_vector_type(4))) short bs16x4;
 typedef __attribute__((ext_vector_type(8))) short bs16x8;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
-typedef __attribute__((address_space(3))) bs16x4 lds_bs16x4;
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(3))) unsigned char lds_byte;
 
 constexpr float LOG2E = 1.44269504088896340736f;
 
@@ -84,7 +81,6 @@ __device__ __forceinline__ int lane_again() {
 }
 
 typedef __attribute__((ext_vector_type(4))) uint32_t rsrc_words;
-__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(size_t)(lds_byte*)(lds_void*)p; }
 // Loads straight into LDS, at `to` + lane * (16 or 4): source = buffer + v + s.  In assembly, so that the compiler does not track them:
 // next to LDS reads it would make each of those wait for every load in flight, also for those into the other buffer.  They
 // are waited for by hand (vmcnt) before the barrier behind which their bytes are read.
@@ -138,6 +134,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_mfma_kernel(const
   constexpr int ROWB = D * 2, TILEB = 64 * ROWB, BUFB = 2 * TILEB, CPR = D / 8, RPI = 64 / CPR, NI = 16 / RPI, KS = D / 16, MD = D / 32;
   // two buffers (Kbar rows [64][ROWB] | Vbar rows [64][ROWB]), a table per wavefront for irregular tiles (term [64] | last token [64])
   constexpr int OFF_FIX = 2 * BUFB, OFF_CNT = OFF_FIX + 4 * 512;   // and the row's blocks per level
+  // The kernel's only LDS object: the addresses in the assembly are offsets into it, so it has to start at LDS address 0.
   __shared__ __attribute__((aligned(1024))) unsigned char smem[OFF_CNT + 4 * PSA_MAX_LEVELS];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -434,10 +431,11 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_mfma_kernel(const
 // twice, on tiles of 32 keys: of four 8-key blocks that were packed to such a tile a query block uses one and a third on average.)
 // The row fragments, transposed fragments and MFMAs of a chunk follow one another in a fixed order (see `chunk`).
 //
-// What bounds it, 12 heads x 32760 tokens, d = 128, four levels, a fifth of the keys: the launch takes 4.7-4.8 ms (before: 6.4 in two),
-// the matrix pipe busy in 0.39 of the cycles on level 1 and 0.21 on the coarser ones, LDS in 0.25 without conflicts.  By parts,
-// levels 2-4 / level 1: staging without products 1.93 / 1.29, products without staging 2.04 / 1.50, all 2.8 / 1.9.  128 keys to a workgroup of eight
-// wavefronts stage a quarter less and were slower (3.85 for levels 2-4: one lock-step group on a compute unit).
+// What bounds it, 12 heads x 32760 tokens, d = 128, four levels, a fifth of the keys: the launch takes 4.1-4.4 ms (before the 16-key tiles 6.4 in two),
+// the matrix pipe busy in 0.34 of the cycles, LDS in 0.30 without conflicts, the wavefronts waiting in 0.42 of theirs.  40 GB of
+// rows are requested from the L2, 65 % of them miss it.  By parts, measured when four wavefronts were a workgroup and the launch took
+// 4.7-4.8 ms, levels 2-4 / level 1: staging without products 1.93 / 1.29, products without staging 2.04 / 1.50, all 2.8 / 1.9.  128 keys to a
+// workgroup of eight wavefronts stage a quarter less and were slower (3.85 for levels 2-4: one lock-step group on a compute unit).
 constexpr int DKV_LIST = 1024;     // query blocks tested before their rows are walked
 // RH: 32-row chunks of a stage, one for every two wavefronts.  With one the workgroups are of two wavefronts: four of them on a compute
 // unit (d = 64: six) wait for each other less at their barriers than two of four wavefronts (12 heads x 32760 tokens 6.57 -> 6.32 ms for
@@ -584,7 +582,7 @@ __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr
   auto chunk = [&](auto lo_tag, auto hi_tag, uint32_t bits, int row0) __attribute__((always_inline)) {
     constexpr int LO = decltype(lo_tag)::value, HI = decltype(hi_tag)::value;
     constexpr bool BOTH = LO != HI;
-    constexpr int NR = 4 * KS, NF = NR + 2 * MD, PF = BOTH ? 2 : 2, RING = PF + 1;
+    constexpr int NR = 4 * KS, NF = NR + 2 * MD, PF = 2, RING = PF + 1;
     bf16x8 fr[RING], pf[2], df[2];
     bs16x4 lo[RING], hi[RING];
     f32x4 sc[2][2], dp[2][2], ls[2];                // [row tile][tile]
@@ -843,6 +841,7 @@ __device__ __forceinline__ bool dkv_item(const BwdMfmaArgs& a, int xcd, int slot
 
 template <int D, int RH, bool CAUSAL>
 __global__ __launch_bounds__((DkvShape<D, RH>::NT), (DkvShape<D, RH>::WPS)) void bwd_dkv_mfma_kernel(DkvPtrs ptr, const uint32_t* __restrict__ order, BwdMfmaArgs a) {
+  // The kernel's only LDS object: the addresses in the assembly are offsets into it, so it has to start at LDS address 0.
   __shared__ __attribute__((aligned(1024))) unsigned char smem[DkvShape<D, RH>::LDSB];
   const int xcd = (int)(blockIdx.x & 7);
   int slot = (int)(blockIdx.x >> 3);
@@ -857,7 +856,8 @@ __global__ __launch_bounds__((DkvShape<D, RH>::NT), (DkvShape<D, RH>::WPS)) void
 // started first: in the order of the slots the last walks ended 1.2 to 1.4 times the mean later, 1.8 to 2.3 times in causal problems.
 // bwd_dkv_length_kernel counts the query blocks of every item (64 columns of the level map a workgroup, the rows dealt to its
 // wavefronts), bwd_dkv_order_kernel sorts each XCD's slots into classes of length, an eighth of an octave each (within a class as they
-// come: neighbours in the key sequence stay close; in half octaves the calls took up to 1.5 % longer).  Both are latency: 4 us each.
+// come: neighbours in the key sequence stay close; in half octaves the calls took up to 1.5 % longer).  Both are latency: with the rocprofv3 trace's idle GPU
+// before each, 9.6 and 9.2 us there, 9.8 and 17 at 28 x 32768.
 constexpr int LEN_WAVES = 8;
 __global__ __launch_bounds__(LEN_WAVES * 64) void bwd_dkv_length_kernel(const uint8_t* __restrict__ M, uint32_t* __restrict__ len, int pitch, BwdMfmaArgs a) {
   __shared__ int part[LEN_WAVES][PSA_MAX_LEVELS][64];
@@ -961,11 +961,12 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
   while ((1 << a.lg_cpe) < cpe) ++a.lg_cpe;
   if ((1 << a.lg_cpe) != cpe) a.lg_cpe = -1;
   // With a run of items to each XCD the Q and dO of eight heads are in flight, which the memory-side cache (256 MB) has to
-  // hold; with all XCDs on one head it holds them at any length.  Whole call, ms for runs / one head, not causal, d = 128: 12 heads x
-  // 16000 tokens 2.21 / 2.30, x 32760 8.90 / 8.95, x 40000 13.6 / 13.4, 24 x 60000 60.3 / 58.9, 40 x 75600 160 / 155, 24 x 100000 174 / 162,
-  // single level 16 x 60000 16.7 / 14.9; d = 64: 12 x 40000 6.98 / 7.01, 12 x 75600 26.0 / 25.5, 32 x 131072 183 / 182.  Seven query heads to a
-  // key head, 28 x 16000 4.99 / 5.08, x 24000 11.2 / 11.1, x 32760 20.8 / 20.1 (single level 8.4 / 7.9), x 40000 30.7 / 30.3.  Causal the
-  // columns of a head differ in length, and runs stay better: 16 x 75600 32.3 / 33.7, d = 64 8 x 131072 26.6 / 27.6.
+  // hold; with all XCDs on one head it holds them at any length.  The line was drawn for the kernels before the 16-key tiles, for which
+  // one head was up to 12 % better behind it.  With these runs are better on most of both sides.  Whole call, ms for runs / one head, not causal,
+  // d = 128: 12 heads x 16000 tokens 1.53 / 1.80, x 32760 6.25 / 6.94, x 40000 9.40 / 10.48, 24 x 60000 43.1 / 46.8, 40 x 75600 116 / 125,
+  // 24 x 100000 123 / 131, single level 16 x 60000 21.1 / 21.7; d = 64: 12 x 40000 4.81 / 5.22, x 75600 17.3 / 18.4, 32 x 131072 127 / 135.  Seven query
+  // heads to a key head, 28 x 16000 3.70 / 4.25, x 32760 15.3 / 16.5 (single level 11.0 / 11.7), x 40000 23.1 / 24.5.  One head is better for few
+  // heads: 1 x 40000 0.929 / 0.924, 2 x 100000 in a single level 8.04 / 7.55, d = 64 4 x 120000 11.4 / 11.0 (2 x 40000 1.61 / 1.63).  The line has yet to be moved.
   a.one_head = !pl.causal && (int64_t)pl.N * pl.d >= (pl.group > 1 ? 4000000 : 5000000);
   int64_t off = 0;
   for (int h = 0; h < PSA_MAX_LEVELS + 2; ++h) { a.lvl_off[h] = pl.lvl_off[h]; a.glvl_off[h] = 0; }
@@ -1001,8 +1002,8 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
   };
   // Where blocks have fewer than 64 pooled keys a workgroup takes 64 keys, or 32 (half of its tiles) while the longest walk (half of
   // the query blocks, say) would end after the work that there is for every resident workgroup (walks of a fifth of the query blocks,
-  // a tenth if causal; what a workgroup costs besides is worth four).  Whole call, us for 64 / 32, d = 128, four levels: 2 heads x 3000 tokens 130 / 109,
-  // x 8000 291 / 235, x 20000 740 / 650; 12 x 3000 169 / 179, x 8000 648 / 688, 28 grouped causal x 8000 982 / 1029; d = 64 2 x 8000 201 / 163, 12 x 8000 342 / 349.
+  // a tenth if causal; what a workgroup costs besides is worth four).  Whole call, us for 64 / 32, d = 128, four levels: 2 heads x 3000 tokens 112 / 90,
+  // x 8000 241 / 193, x 20000 644 / 505; 12 x 3000 148 / 147, x 8000 489 / 512, 28 grouped causal x 8000 674 / 709; d = 64 2 x 8000 164 / 129, 12 x 8000 256 / 266.
   const int64_t walk = pl.nq / (pl.causal ? 10 : 5) + 4;
   // Workgroups of two wavefronts (twice as many resident, each walk twice as long) where the work for every resident one is at least the
   // longest walk that there can be.  Whole call, time in four wavefronts over time in two, 70 shapes, by that work over that walk: up to
@@ -1013,7 +1014,9 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
   const DkvPtrs ptr = {q, k, v, kp, vp, go, M, lse, Dr, dKp, dVp};
   const int pitch = (int)groups(a.small_keys);
   // Started in the order of their lengths once they are more than fit at a time and the launch is long enough to gain more than the two
-  // small kernels take (13 to 20 us; about 36 query blocks for every resident workgroup).  The dQ kernel was the last to read the block
+  // small kernels take (about 36 query blocks for every resident workgroup).  Whole call, us in the order of the keys / of their lengths: 12 heads x
+  // 3000 tokens 148 / 159, x 4000 198 / 193, x 5000 255 / 235, x 32760 6659 / 6170, 2 x 8000 193 / 205, x 20000 555 / 502, causal 28 x 3000 192 / 197, x 4000
+  // 281 / 274, x 8000 690 / 674; 40 x 3000 392 / 342, which the line leaves in the order of the keys.  The dQ kernel was the last to read the block
   // lists: their place takes the lengths and the order.
   uint32_t* order = nullptr;
   if (8 * pitch > resident && 8 * pitch * walk > 36 * resident && (size_t)pitch * 8 * 2 * sizeof(uint32_t) <= (size_t)pl.B * pl.Hq * pl.nq * pl.nk * sizeof(uint16_t)) {
