@@ -25,7 +25,7 @@ def _off_by_one(x):
 
 @pytest.mark.parametrize("Hq,Hkv,N,d,bq,bk,levels,causal,keep,shifted", [
     (1, 1, 8300, 128, 8, 64, 3, False, 0.04, False),      # 1038 query blocks: two lists; stages of 8 rows
-    (2, 1, 1050, 128, 128, 128, 4, True, 0.6, False),     # 128-key blocks: eight wavefronts
+    (2, 1, 1050, 128, 128, 128, 4, True, 0.6, False),     # 128-key blocks: two workgroups each
     (2, 2, 530, 64, 64, 128, 5, False, 0.6, False),       # d = 64: a 128-key block split over two workgroups
     (3, 1, 333, 64, 96, 32, 3, True, 0.8, False),         # 9 (head, block) runs on 8 XCDs; 96-row blocks: stages of 64 and 32
     (2, 1, 300, 128, 128, 64, 4, False, 0.7, True),
