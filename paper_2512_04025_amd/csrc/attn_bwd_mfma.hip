@@ -147,16 +147,8 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_mfma_kernel(const
   int head, item;
   if (a.causal) {
     if (!xcd_item(a.Hq * a.B, per_head, xcd, slot, head, item)) return;
-  } else if (a.dq_runs) {
-    const int items = a.Hq * a.B * per_head, at = xcd * ((items + 7) >> 3) + slot;
-    if (at >= items) return;
-    head = at / per_head;
-    item = at % per_head;
-  } else {
-    const int run = (per_head + 7) >> 3;
-    head = slot / run;
-    item = xcd * run + slot % run;
-    if (item >= per_head) return;
+  } else if (!dq_item(a.Hq * a.B, per_head, a.dq_runs, xcd, slot, head, item)) {
+    return;
   }
   const int slice = item % slices, i = a.causal ? a.nq - 1 - item / slices : item / slices;
   const int hq = head % a.Hq, b = head / a.Hq;
@@ -986,9 +978,9 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
   // 44.0 / 38.4, x 1100 92.7 / 80.5, d = 64 x 161 24.9 / 22.4, x 1100 55.3 / 50.4; four levels 12 x 2000 92.0 / 91.6.  From 32 blocks on the two are
   // within 1 % of each other (12 x 4000 197.0 / 198.3, x 32760 6199 / 6254, 40 x 20000 8399 / 8391, 24 x 60000 46488 / 46609).
   const int dq_items = pl.nq * slices, heads = pl.B * pl.Hq;
-  a.dq_runs = !pl.causal && dq_items < 32;
-  const int dq_slots = pl.causal ? xcd_slots(heads, dq_items) : (a.dq_runs ? (heads * dq_items + 7) / 8 : heads * ((dq_items + 7) / 8));
-  const unsigned dq_grid = 8u * (unsigned)dq_slots;
+  a.dq_runs = dq_runs(dq_items);
+  const int dq_slot_count = pl.causal ? xcd_slots(heads, dq_items) : dq_slots(heads, dq_items);
+  const unsigned dq_grid = 8u * (unsigned)dq_slot_count;
   bwd_dq_mfma_kernel<D><<<dq_grid, 256, 0, s>>>(q, k, v, kp, vp, idx, cnt, static_cast<const bf16_t*>(O), lse, Dr, go, static_cast<bf16_t*>(dQ), a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -1,4 +1,4 @@
-// Which keys a workgroup of the dK, dV kernel takes and which rows its walk over the query blocks touches (attn_bwd_mfma.hip).  Plain arithmetic, the same on host and device, so
+// Which work a workgroup of the backward kernels takes and which rows the dK, dV walk over the query blocks touches (attn_bwd_mfma.hip).  Plain arithmetic, the same on host and device, so
 // that its bounds can be checked without a GPU (tests/test_bwd_walk_host.py).
 #ifndef PSA_BWD_WALK_H
 #define PSA_BWD_WALK_H
@@ -24,6 +24,23 @@ constexpr bool dkv_reads_stat(DkvPart p, int r) { return r < DKV_PART && r < p.v
 constexpr int dkv_chunks(int N, int bq, int nq, int kept, int last) {
   const int cpe = (bq + 31) / 32, rows = N - (nq - 1) * bq;
   return kept * cpe - (kept > 0 && last == nq - 1 ? cpe - (rows + 31) / 32 : 0);
+}
+
+// Work order of dQ, not causal: workgroup `slot` of XCD `xcd` takes query block `item` of head `head`, or nothing.  All XCDs are on one head at a time, a
+// contiguous run of its blocks each; with `runs` each XCD takes a contiguous run of all heads' blocks (see launch_bwd_mfma_t).
+constexpr bool dq_runs(int per_head) { return per_head < 32; }
+constexpr int dq_slots(int heads, int per_head) { return dq_runs(per_head) ? (heads * per_head + 7) / 8 : heads * ((per_head + 7) / 8); }
+constexpr bool dq_item(int heads, int per_head, bool runs, int xcd, int slot, int& head, int& item) {
+  if (runs) {
+    const int at = xcd * ((heads * per_head + 7) >> 3) + slot;
+    head = at / per_head;
+    item = at % per_head;
+    return at < heads * per_head;
+  }
+  const int run = (per_head + 7) >> 3;
+  head = slot / run;
+  item = xcd * run + slot % run;
+  return item < per_head;
 }
 
 // log2 of the most key blocks of a workgroup: one bit each

@@ -1,4 +1,4 @@
-"""The keys and rows that the dK, dV kernel's workgroups touch, worked out by the kernel's own arithmetic (csrc/bwd_walk.h) compiled for the host:
+"""The work that the backward kernels' workgroups take, worked out by the kernel's own arithmetic (csrc/bwd_walk.h) compiled for the host:
 every row of a query block once, nothing outside it and no chunk without a row, also where the last block is short."""
 import os
 import subprocess
@@ -16,6 +16,15 @@ int main(int argc, char** argv) {
   if (argc == 4) {
     const DkvGroup g = dkv_group(atoi(argv[1]), atoi(argv[2]), atoi(argv[3]));
     printf("group %d %d\ngroup %d %d\n", g.keys, g.lg_G, g.lg_pieces, g.ng);
+    return 0;
+  }
+  if (argc == 3 && atoi(argv[1]) < 0) {
+    const int heads = -atoi(argv[1]), per_head = atoi(argv[2]);
+    for (int xcd = 0; xcd < 8; ++xcd)
+      for (int slot = 0; slot < dq_slots(heads, per_head); ++slot) {
+        int head = 0, item = 0;
+        if (dq_item(heads, per_head, dq_runs(per_head), xcd, slot, head, item)) printf("x%d %d %d\n", xcd, head, item);
+      }
     return 0;
   }
   const int N = atoi(argv[1]), bq = atoi(argv[2]), nq = (N + bq - 1) / bq, cpe = (bq + 31) / 32;
@@ -43,7 +52,7 @@ def walk(tmp_path_factory):
 
     def run(*args):
         lines = subprocess.run([exe, *map(str, args)], check=True, capture_output=True, text=True).stdout.split("\n")
-        out = {"stat": [], "row": [], "chunk": [], "first": [], "group": []}
+        out = {f"x{x}": [] for x in range(8)} | {"stat": [], "row": [], "chunk": [], "first": [], "group": []}
         for line in filter(None, lines):
             kind, blk, row = line.split()
             out[kind].append((int(blk), int(row)))
@@ -72,3 +81,12 @@ def test_groups_take_every_key_once(walk, lg_th, nk, small_keys):
         j0, koff = (bx >> lg_pieces) << lg_G, (bx & ((1 << lg_pieces) - 1)) * keys
         taken += [j0 * th + koff + k for k in range(min(keys, (th << lg_G) - koff)) if j0 + (koff + k) // th < nk]
     assert taken == list(range(nk * th))
+
+
+@pytest.mark.parametrize("heads,per_head", [(1, 1), (40, 2), (12, 9), (3, 4), (16, 31), (2, 32), (5, 33), (12, 256), (7, 257)])
+def test_query_blocks_are_dealt_once_and_evenly(walk, heads, per_head):
+    got = walk(-heads, per_head)
+    shares = [got[f"x{x}"] for x in range(8)]
+    assert sorted(sum(shares, [])) == [(h, i) for h in range(heads) for i in range(per_head)]
+    most = -(-heads * per_head // 8) if per_head < 32 else heads * -(-per_head // 8)
+    assert max(map(len, shares)) <= most                              # from 32 blocks on: at most a quarter more than an even share
