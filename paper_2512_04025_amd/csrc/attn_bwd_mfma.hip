@@ -505,12 +505,6 @@ __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr
       vf[u][ks] = __builtin_bit_cast(bf16x8, y);
     }
   }
-  // The operands are declared used here, so that the wait for their loads stands here and not at their
-  // first use inside the stage loop, where it would also wait for the rows fetched ahead.
-#pragma unroll
-  for (int u = 0; u < 2; ++u)
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) asm volatile("" ::"v"(kf[u][ks]), "v"(vf[u][ks]));
   f32x4 dk[2][MD], dv[2][MD];                      // dKbar^T, dVbar^T: channels md * 16 + g * 4 .. +3 of this lane's keys
 #pragma unroll
   for (int u = 0; u < 2; ++u)
@@ -773,6 +767,12 @@ __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr
     }
     total = __builtin_amdgcn_readfirstlane(nkept);
     total = dkv_chunks(a.N, a.bq, a.nq, total, total > 0 ? __builtin_amdgcn_readfirstlane((int)kept_row[total - 1]) : 0);
+    // The operands are declared used here, so that the wait for their loads stands here, where those of the level map have been waited for
+    // too, and not at their first use inside the stage loop, where it would also wait for the rows fetched ahead.
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) asm volatile("" ::"v"(kf[u][ks]), "v"(vf[u][ks]));
     fire(0, total, at);
     for (int c0 = 0; c0 < total; c0 += CHUNKS) step(c0);
     __syncthreads();                               // everyone has read the last stage: the buffers may be filled again
