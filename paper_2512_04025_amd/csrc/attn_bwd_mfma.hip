@@ -16,8 +16,6 @@
 //        query blocks that use one of the workgroup's key blocks at this level (a walk down the level map's columns) are
 //        staged through LDS 32 or 64 rows at a time; S = Q Kbar^T and dP = dO Vbar^T, then dVbar^T += dO^T P and
 //        dKbar^T += Q^T dS with the transposing load on the staged dO and Q.
-#include <type_traits>
-
 #include "bwd_walk.h"
 #include "psa_dev.h"
 #include "psa_internal.h"
@@ -41,22 +39,6 @@ typedef __attribute__((ext_vector_type(4))) int i32x4;
 
 constexpr float LOG2E = 1.44269504088896340736f;
 
-// f(integral_constant 0), f(1) .. f(N - 1)
-template <int N, int I = 0, typename F> __device__ __forceinline__ void each(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    each<N, I + 1>(f);
-  }
-}
-
-// x ^ a constant, made where it is used: an address per constant would otherwise be held in a register over the whole loop
-template <int C> __device__ __forceinline__ uint32_t flip(uint32_t x) {
-  if (C == 0) return x;
-  uint32_t y;
-  asm volatile("v_xor_b32 %0, %1, %2" : "=v"(y) : "n"(C), "v"(x));
-  return y;
-}
-
 // LDS reads with hand-counted waits: lds_wait<N> declares its operands arrived once at most N later LDS operations are outstanding
 template <int OFF, typename T> __device__ __forceinline__ void lds_read(T& dst, uint32_t at) {
   static_assert(sizeof(T) == 16, "");
@@ -71,13 +53,6 @@ template <int N, typename T> __device__ __forceinline__ void lds_wait(T& x, f32x
 }
 template <int N, typename T, typename U> __device__ __forceinline__ void lds_wait(T& x, U& y) {
   asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(x), "+v"(y) : "n"(N));
-}
-
-// the lane's number, made where it is used: what depends on it is worked out again instead of held over the stage loop
-__device__ __forceinline__ int lane_again() {
-  int x;
-  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(x));
-  return x;
 }
 
 typedef __attribute__((ext_vector_type(4))) uint32_t rsrc_words;
@@ -103,12 +78,8 @@ __device__ __forceinline__ rsrc_words make_rsrc(const void* base, uint32_t bytes
   return r;
 }
 
-// Place of a row's 16-byte chunks in LDS: chunk ^ swizzle(row).  row_swizzle32 serves operands of 32 rows (two lanes a row): 16 consecutive
-// rows at 16 different places, and the four rows of a transposing group in four different 64-byte groups.  row_swizzle serves
+// Place of a row's 16-byte chunks in LDS: chunk ^ row_swizzle32(row) (psa_dev.h) for operands of 32 rows; row_swizzle serves
 // operands of 16 rows (four lanes a row, 16 rows x 32 bytes transposed): no two of the rows that the LDS serves together meet either way.
-template <int D> __host__ __device__ constexpr int row_swizzle32(int row) {
-  return D == 128 ? ((row & 3) << 2) | ((row >> 2) & 3) : (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
-}
 template <int D> __host__ __device__ constexpr int row_swizzle(int row) {
   const int r = D == 128 ? row : row >> 1;                   // rows per 256 bytes of LDS: 1, 2
   const int fold = ((row >> 2) ^ (row >> 3)) & 1;

@@ -1,26 +1,30 @@
 // Attention in fp32 arithmetic on the gfx950 matrix cores: psa_attention_fwd in float32 (Alg. 1 with accurate
 // exp, the 1e-5 mode), psa_dense_ref (Eq. 1) for both element types, and the bfloat16 block sizes that
-// attn_mfma_kernel does not take.  Products and sums are fp32 throughout (v_mfma_f32_32x32x2_f32).
+// attn_mfma_kernel does not take.  Sums are fp32 throughout; a float32 operand is the exact sum of three bfloat16 planes
+// (psa_dev.h), and a product of two is six products of planes on v_mfma_f32_32x32x16_bf16: 192 cycles of the matrix pipe for
+// 16 channels where v_mfma_f32_32x32x2_f32 needs 512.  A bfloat16 operand is one plane, the weights are three either way.
+// In S the products of the leading planes and all others are two sums that are added at the end; error against 64 bits
+// of 12 heads x 4680 tokens 3.9e-7 (float32 instructions) -> 3.3e-7, of 2 x 1024 at d = 64 1.4e-7 -> 1.1e-7.
 //
-// Bound: the fp32 matrix rate (64 FLOP per cycle and SIMD, 151 TFLOP/s measured on a large product).  A
-// 32 x 32 x D tile keeps a wavefront's matrix pipe busy for 64 D cycles and needs 1 / 8 of that in LDS reads,
-// so little has to be scheduled by hand (some registers spill all the same at d = 128 with two wavefronts per SIMD:
-// teams of two 55 in float32 and 21 in bfloat16, teams of four 18 in float32): the V rows of a tile travel through registers into LDS during its
-// first product, the K rows of the next one during its second, and each product is followed by one barrier.
+// What bounds it: 12 heads x 4680 tokens, d = 128, a fifth of the keys: a wavefront issues about 830 vector instructions a
+// tile (72 conversions and what belongs to them, addresses, softmax) next to 96 MFMAs, two wavefronts on a SIMD: the vector port is
+// busy as long as the matrix pipe, and 444 workgroups take one and a half rounds of the chip.  The V rows of a tile travel through registers into LDS during its
+// first product, the K rows of the next one during its second, and each product is followed by one barrier; the block ids that say
+// where rows lie are requested a step ahead.
 //
 // Operand roles as in the bfloat16 kernel: S^T = K Q^T puts one query row in each lane (lane l and l + 32 share
-// row l: keys (v/4)*8 + (l/32)*4 + v%4 in register v), and register v of P^T is then directly the B operand of
-// O^T += V^T P^T for the pair of keys that the two halves hold.  The contraction over channels runs in the
-// order in which a 16-byte read delivers them, for both operands alike.
+// row l: keys (v/4)*8 + (l/32)*4 + v%4 in register v), and the planes of P^T are directly the B operands of
+// O^T += V^T P^T, whose A operands the transposing LDS load makes from the row-major V planes.
 //
 // What decides the speed of small problems is how many wavefronts there are, so the four wavefronts of a
 // workgroup are dealt out in two ways: TEAM of them own 32 query rows each and share the tiles of one
 // stream of keys, and there are 4 / TEAM such teams over the SAME 32 * TEAM rows, each taking every
 // (4 / TEAM)-th tile of the row's list; their (maximum, sum, output) are merged through LDS at the end.
 //
-// Measured (pyramid and block lists included) against one thread per query row on the vector unit, which this
-// replaces: 12 heads x 4680 tokens, d = 128, a fifth of the keys: 2250 -> 350 us (27 GFLOP: 77 TFLOP/s, half of
-// the rate of a large product); 2 heads x 1024 tokens, d = 64, the attention alone: 217 -> 20 us.
+// Measured (pyramid and block lists included), products on v_mfma_f32_32x32x2_f32 -> here: 12 heads x 4680 tokens, d = 128, a fifth of the
+// keys 353 -> 205 us, x 1000 49 -> 38, x 6000 at d = 64 430 -> 227; causal 2 x 2435 154 -> 97; 4 x 3433 at d = 64 81 -> 53.
+#include <math.h>
+
 #include "psa_dev.h"
 #include "psa_internal.h"
 
@@ -29,36 +33,66 @@ namespace psa {
 struct F32Args {
   int N, Hq, Hkv, nq, nk, bq, bk, lg_bk, H, causal;
   int slices;              // workgroups per query block
-  float scale;
+  float scale_hi, scale_lo;  // scale * log2(e) as a sum of two
   int64_t lvl_off[PSA_MAX_LEVELS + 2];
 };
 
-// LDS rows: K + 4 floats (a 16-byte read of 16 rows covers every bank once), V + 8 (the two halves of a
-// 4-byte read sit four rows, half the banks, apart).
-template <int D, int TEAM>
+// bfloat16 planes of an element type: what a value is the exact sum of
+template <typename T> struct Planes { static constexpr int N = 1; };
+template <> struct Planes<float> { static constexpr int N = 3; };
+
+// A tile: its planes one after the other, rows of D bfloat16, 16-byte chunks at chunk ^ row_swizzle32(row).  A team of one wavefront puts V
+// where K was (it has nobody to wait for), so that four such teams fit the LDS at d = 128.
+template <typename T, int D, int TEAM>
 struct F32Shape {
-  static constexpr int KS = 4 / TEAM, ROWS = 32 * TEAM, KPITCH = D + 4, VPITCH = D + 8;
-  static constexpr int TILEF = 32 * KPITCH + 32 * VPITCH + 128 + 4;    // K | V | (bias [32] | last token [32]) x 2 | flags
-  static constexpr int MERGEF = 2 * KS * ROWS + KS * ROWS * KPITCH;     // m, l | O of every team
-  static constexpr size_t BYTES = sizeof(float) * (KS * TILEF > MERGEF ? KS * TILEF : MERGEF);
+  static constexpr int KS = 4 / TEAM, ROWS = 32 * TEAM, PITCH = D + 4, NPL = Planes<T>::N;
+  static constexpr int ROWB = 2 * D, PLANEB = 32 * ROWB, TENSORB = NPL * PLANEB;
+  static constexpr int OFF_V = TEAM == 1 ? 0 : TENSORB, OFF_TAB = OFF_V + TENSORB;
+  static constexpr int TILEB = OFF_TAB + TEAM * 256;                   // K | V | (term [32] | last token [32]) per wavefront
+  static constexpr int MERGEB = 4 * (2 * KS * ROWS + KS * ROWS * PITCH);   // m, l | O of every team
+  static constexpr int OFF_FLAG = KS * TILEB;                          // behind the teams' tiles: one flag per wavefront
+  static constexpr size_t BYTES = OFF_FLAG + 16 > MERGEB ? OFF_FLAG + 16 : MERGEB;
 };
 
+// Four consecutive elements as their planes: put(plane, its four bfloat16).  NaN comes back if one is not finite (0 times its remainder otherwise).
+template <typename F> __device__ __forceinline__ float to_planes(f32x4 x, F&& put) {
+  float rest = 0.f;
+  const Split2 a = split2(x[0], x[1], rest), b = split2(x[2], x[3], rest);
+  put(0, u32x2{a.h, b.h});
+  put(1, u32x2{a.m, b.m});
+  put(2, u32x2{a.l, b.l});
+  return rest;
+}
+template <typename F> __device__ __forceinline__ float to_planes(Four<bf16_t>::raw x, F&& put) {
+  const u32x2 w = __builtin_bit_cast(u32x2, x);
+  put(0, w);
+  bool bad = false;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) bad |= (x[e] & 0x7f80u) == 0x7f80u;
+  return bad ? __builtin_nanf("") : 0.f;
+}
+
+typedef short f32_s16x4 __attribute__((ext_vector_type(4)));
+typedef short f32_s16x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) f32_s16x4 f32_lds_s16x4;
+
 template <typename T, int D, int TEAM>
-__global__ __launch_bounds__(256, (F32Shape<D, TEAM>::BYTES <= 80 * 1024 ? 2 : 1))
+__global__ __launch_bounds__(256, (F32Shape<T, D, TEAM>::BYTES <= 80 * 1024 ? 2 : 1))
 void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ Kp,
                      const T* __restrict__ Vp, const uint16_t* __restrict__ idx, const int32_t* __restrict__ cnt,
                      T* __restrict__ O, float* __restrict__ lse, F32Args a) {
-  using S = F32Shape<D, TEAM>;
-  constexpr int KS = S::KS, ROWS = S::ROWS, KPITCH = S::KPITCH, VPITCH = S::VPITCH, CPR = D / 4, MD = D / 32;
+  using S = F32Shape<T, D, TEAM>;
+  constexpr int KS = S::KS, ROWS = S::ROWS, PITCH = S::PITCH, NPL = S::NPL, ROWB = S::ROWB, PLANEB = S::PLANEB, CPR = D / 4, MD = D / 32, KSTEPS = D / 16;
   constexpr int TT = 64 * TEAM, NCH = 32 * CPR / TT;     // threads of a team; 4-element chunks per thread, tile and tensor
-  extern __shared__ __attribute__((aligned(16))) float fsm[];
+  extern __shared__ __attribute__((aligned(16))) unsigned char fsm[];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int team = wave / TEAM, wr = wave % TEAM, tt = tid & (TT - 1);
-  float* Ks = fsm + team * S::TILEF;
-  float* Vs = Ks + 32 * KPITCH;
-  float* table_s = Vs + 32 * VPITCH;                     // of tile t in half t & 1: additive term and last covered token per key
-  int* flag_s = reinterpret_cast<int*>(table_s + 128);   // per wavefront of the team: did it stage a value of V that is not finite
+  const int team = wave / TEAM, wr = wave % TEAM;
+  unsigned char* Ks = fsm + team * S::TILEB;
+  unsigned char* Vs = Ks + S::OFF_V;
+  float* term_s = reinterpret_cast<float*>(Ks + S::OFF_TAB + wr * 256);   // irregular tiles: additive term per key, its last token
+  int* last_s = reinterpret_cast<int*>(term_s + 32);
+  int* flag_s = reinterpret_cast<int*>(fsm + S::OFF_FLAG);               // did the wavefront meet a value that is not finite
 
   const bool dense = idx == nullptr;
   const int slice = blockIdx.x % a.slices;
@@ -73,20 +107,28 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
   const int row = row0 + wr * 32 + l32;
   const bool active = row < row_end;
 
-  float q[D / 2];                                        // channels k8*8 + hf*4 + e of this lane's row
+  bf16x8 q[NPL][KSTEPS];                                 // planes of channels ks * 16 + hf * 8 .. +7 of this lane's row
 #pragma unroll
-  for (int k8 = 0; k8 < D / 8; ++k8) {
-    f32x4 x = {0.f, 0.f, 0.f, 0.f};
-    if (active) x = Four<T>::widen(Four<T>::load(Q + (qhead * a.N + row) * D + k8 * 8 + hf * 4));
+  for (int ks = 0; ks < KSTEPS; ++ks) {
+    u32x4 w[NPL];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) q[k8 * 4 + e] = x[e];
+    for (int u = 0; u < 2; ++u) {
+      typename Four<T>::raw x = {0, 0, 0, 0};
+      if (active) x = Four<T>::load(Q + (qhead * a.N + row) * D + ks * 16 + hf * 8 + u * 4);
+      to_planes(x, [&](int plane, u32x2 v) __attribute__((always_inline)) {
+        w[plane][2 * u] = v[0];
+        w[plane][2 * u + 1] = v[1];
+      });
+    }
+#pragma unroll
+    for (int pl = 0; pl < NPL; ++pl) q[pl][ks] = __builtin_bit_cast(bf16x8, w[pl]);
   }
   f32x16 o[MD];
 #pragma unroll
   for (int md = 0; md < MD; ++md)
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[md][v] = 0.f;
-  float m = -INFINITY, l = 0.f;
+  float m = -INFINITY, l = 0.f;                          // reference of the weights (log2, a whole number), sum of the weights
 
   const int64_t srow = qhead * a.nq + i;
   const uint16_t* my_idx = dense ? nullptr : idx + srow * a.nk;
@@ -96,63 +138,124 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
   if (a.causal) dense_blocks = (row_end - 1) / a.bk + 1;
 
   // The pooled tokens of a level's kept blocks, in list order, are one stream that is cut into tiles of 32.
-  struct Tile { int h, tl, ntl, nblk, start; bool ok; };
+  struct Tile { int h, tl, ntl, nblk, start, ok; };      // (no padding: its bytes were copied through memory)
   auto enter = [&](Tile& t) __attribute__((always_inline)) {
     t.nblk = dense ? dense_blocks : my_cnt[t.h - 1];
     t.ntl = (int)((((int64_t)t.nblk << (a.lg_bk - (t.h - 1))) + 31) >> 5);
   };
   auto settle = [&](Tile& t) __attribute__((always_inline)) {   // carry tl over to the level that holds it
     for (;;) {
-      if (t.tl < t.ntl) { t.ok = true; return; }
+      if (t.tl < t.ntl) { t.ok = 1; return; }
       t.tl -= t.ntl;
       t.start += t.nblk;
-      if (++t.h > H) { t.h = H; t.ok = false; t.ntl = 0; t.nblk = 0; return; }
+      if (++t.h > H) { t.h = H; t.ok = 0; t.ntl = 0; t.nblk = 0; return; }
       enter(t);
     }
   };
-  auto locate = [&](const Tile& t) __attribute__((always_inline)) -> int {   // pooled row of tile row l32; -1: none
-    if (!t.ok) return -1;
-    const int lg_th = a.lg_bk - (t.h - 1), g = (t.tl << 5) + l32, e = g >> lg_th;
-    if (e >= t.nblk) return -1;
-    return ((dense ? e : (int)my_idx[t.start + e]) << lg_th) | (g & ((1 << lg_th) - 1));
+  // The block of tile row l32 (past the level's last block: that block) is requested a step before its row is worked out.
+  auto block_of = [&](const Tile& t) __attribute__((always_inline)) -> int {
+    const int e = ((t.tl << 5) + l32) >> (a.lg_bk - (t.h - 1)), f = e < t.nblk ? e : t.nblk - 1;
+    return dense ? f : (int)my_idx[t.start + f];
   };
+  auto row_of = [&](const Tile& t, int block) __attribute__((always_inline)) -> int {   // pooled row of tile row l32; -1: none
+    const int lg_th = a.lg_bk - (t.h - 1), g = (t.tl << 5) + l32, pr = (block << lg_th) | (g & ((1 << lg_th) - 1));
+    return t.ok && g >> lg_th < t.nblk && ((int64_t)pr << (t.h - 1)) < a.N ? pr : -1;
+  };
+  auto base_of = [&](const T* level1, const T* pooled, const Tile& t) __attribute__((always_inline)) -> const T* {
+    return t.h == 1 ? level1 + khead * (int64_t)a.N * D : pooled + a.lvl_off[t.h] + khead * ((int64_t)a.nk << (a.lg_bk - (t.h - 1))) * D;
+  };
+  // this thread's number in its team; where registers are short what depends on it is worked out again at every use
+  auto place = [&]() __attribute__((always_inline)) -> int { return wr * 64 + (D == 128 && TEAM == 4 && NPL == 3 ? lane_again() : lane); };
   typename Four<T>::raw reg[NCH];                        // this thread's part of the K or V rows on their way into LDS
+  // (a row that does not exist: row 0, which is replaced by zeros on its way into LDS)
   auto fetch = [&](const T* level1, const T* pooled, const Tile& t, int prow) __attribute__((always_inline)) {
-    const int lg_th = a.lg_bk - (t.h - 1), hm1 = t.h - 1;
-    const T* base = hm1 == 0 ? level1 + khead * (int64_t)a.N * D : pooled + a.lvl_off[t.h] + khead * ((int64_t)a.nk << lg_th) * D;
+    const T* base = base_of(level1, pooled, t);
+    const int at = prow < 0 ? 0 : prow, x0 = place();
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      const int x = tt + TT * c, pr = __shfl(prow, x / CPR, 64);
-      reg[c] = typename Four<T>::raw{0, 0, 0, 0};
-      if (pr >= 0 && ((int64_t)pr << hm1) < a.N) reg[c] = Four<T>::load(base + (int64_t)pr * D + (x % CPR) * 4);
+      const int x = x0 + TT * c;
+      reg[c] = Four<T>::load(base + (int64_t)__shfl(at, x / CPR, 64) * D + (x % CPR) * 4);
     }
   };
-  auto deposit_k = [&](const Tile& t, int prow, int half) __attribute__((always_inline)) {
+  auto deposit = [&](unsigned char* tensor, int prow) __attribute__((always_inline)) -> bool {   // whether a value is not finite
+    const int x0 = place();
+    if (__any(prow < 0)) {
+#pragma unroll
+      for (int c = 0; c < NCH; ++c)
+        if (__shfl(prow, (x0 + TT * c) / CPR, 64) < 0) reg[c] = typename Four<T>::raw{0, 0, 0, 0};
+    }
+    float rest = 0.f;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      const int x = tt + TT * c;
-      *reinterpret_cast<f32x4*>(Ks + (x / CPR) * KPITCH + (x % CPR) * 4) = Four<T>::widen(reg[c]);
+      const int x = x0 + TT * c, r = x / CPR, ch = x % CPR;
+      unsigned char* at = tensor + r * ROWB + (((ch >> 1) ^ row_swizzle32<D>(r)) << 4) + (ch & 1) * 8;
+      rest += to_planes(reg[c], [&](int plane, u32x2 v) __attribute__((always_inline)) { *reinterpret_cast<u32x2*>(at + plane * PLANEB) = v; });
     }
-    if (tt < 32) {
-      const int span = 1 << (t.h - 1);
-      const int64_t first = (int64_t)prow * span;
+    return !(rest == rest);
+  };
+  // scores of tile t -> weights of its keys for this lane's row; reference, sum and output follow
+  auto weights = [&](const Tile& t, int prow, f32x16& sc) __attribute__((always_inline)) {
+    // log2 of the tokens under a key: one constant, unless the tile holds keys that do not exist, cover fewer tokens than others of the level
+    // or (causal) are hidden from a row of this wavefront
+    const int hm1 = t.h - 1;
+    int lim = a.N >> hm1;
+    if (a.causal) {
+      const int vis = (row0 + wr * 32 + 1) >> hm1;
+      lim = vis < lim ? vis : lim;
+    }
+    const bool irregular = __any(prow < 0 || prow >= lim);
+    float tmax = -INFINITY;
+    if (irregular) {
+      const int span = 1 << hm1;
+      const int64_t first = (int64_t)prow << hm1;
       int64_t c = a.N - first;
-      c = prow < 0 || c < 0 ? 0 : (c > span ? span : c);
-      table_s[half * 64 + tt] = c > 0 ? logf((float)c) : -INFINITY;   // (h-1) ln 2 for a full pooled key
-      reinterpret_cast<int*>(table_s)[half * 64 + 32 + tt] = (int)(first + (c > 0 ? c : 1) - 1);
-    }
-  };
-  auto deposit_v = [&]() __attribute__((always_inline)) {
-    bool bad = false;
+      c = prow < 0 ? 0 : (c > span ? span : c);
+      if (hf == 0) {
+        term_s[l32] = c > 0 ? (c == span ? (float)hm1 : log2f((float)c)) : -INFINITY;
+        last_s[l32] = (int)(first + (c > 0 ? c : 1) - 1);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");          // (LDS serves one wavefront in order)
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int x = tt + TT * c;
-      const f32x4 vv = Four<T>::widen(reg[c]);
-      *reinterpret_cast<f32x4*>(Vs + (x / CPR) * VPITCH + (x % CPR) * 4) = vv;
-      if (a.causal) bad |= not_finite(vv);
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const f32x4 ts = *reinterpret_cast<const f32x4*>(term_s + g4 * 8 + hf * 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float s = ts[e] == -INFINITY ? -INFINITY : fmaf(sc[g4 * 4 + e], a.scale_lo, fmaf(sc[g4 * 4 + e], a.scale_hi, ts[e]));
+          if (a.causal && last_s[g4 * 8 + hf * 4 + e] > row) s = -INFINITY;
+          sc[g4 * 4 + e] = s;
+          tmax = fmaxf(tmax, s);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) tmax = fmaxf(tmax, sc[v]);
+      tmax = fmaf(tmax, a.scale_hi, (float)hm1);
     }
-    const bool any_bad = a.causal && __any(bad);
-    if (lane == 0) flag_s[wr] = any_bad ? 1 : 0;
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+    // The reference is a whole number, so that changing it rounds nothing, and is raised when a weight would pass 2^8.
+    if (__any(tmax - m > 8.f)) {
+      const float mn = fmaxf(m, ceilf(tmax));
+      const float alpha = mn == -INFINITY ? 1.f : exp2f(m - mn);      // m = -inf: 0
+      l *= alpha;
+#pragma unroll
+      for (int md = 0; md < MD; ++md)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[md][v] *= alpha;
+      m = mn;
+    }
+    const float ref = m == -INFINITY ? 0.f : m;
+    if (irregular) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sc[v] = __builtin_amdgcn_exp2f(sc[v] - ref);
+    } else {
+      const float shift = (float)hm1 - ref;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sc[v] = __builtin_amdgcn_exp2f(fmaf(sc[v], a.scale_lo, fmaf(sc[v], a.scale_hi, shift)));
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) l += sc[v];
   };
   // a team of one wavefront owns its buffer: its LDS operations complete in order, nothing to wait for
   auto barrier = [&]() __attribute__((always_inline)) {
@@ -167,130 +270,188 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
     enter(t);
     total += t.ntl;
   }
-  Tile cur = {1, team, 0, 0, 0, false};
+  Tile cur = {1, team, 0, 0, 0, 0};
   enter(cur);
   settle(cur);
-  int pc = locate(cur);
-  fetch(K, Kp, cur, pc);
-  deposit_k(cur, pc, 0);
   Tile nxt = cur;
-  nxt.tl += KS;
-  if (nxt.ok) settle(nxt);
-  int pn = locate(nxt);
+  int pc = -1, id = 0;                                   // rows of this tile; blocks of the next one
+  if (cur.ok) {
+    pc = row_of(cur, block_of(cur));
+    fetch(K, Kp, cur, pc);
+    nxt.tl += KS;
+    settle(nxt);
+    if (nxt.ok) id = block_of(nxt);
+    deposit(Ks, pc);
+  }
   barrier();
-  for (int step = 0, half = 0; step < total; step += KS, half ^= 1) {
-    const float* bias_s = table_s + half * 64;
-    const int* last_s = reinterpret_cast<const int*>(bias_s + 32);
+  bool finite = true;
+  for (int step = 0; step < total; step += KS) {
+    const int pn = row_of(nxt, id);
     Tile nn = nxt;
-    int pnn = -1;
-    if (cur.ok) fetch(V, Vp, cur, pc);
     if (nxt.ok) {
       nn.tl += KS;
       settle(nn);
-      pnn = locate(nn);
+      if (nn.ok) id = block_of(nn);
     }
+    if (cur.ok) fetch(V, Vp, cur, pc);
     f32x16 sc;
-    float ref = 0.f;
+    bool bad = false;
     if (cur.ok) {
+      // S: the large terms in one sum, the others in another that is added at the end (fewer roundings than one chain of D products).  One k-step's
+      // fragments ahead of the products, no more.
+      f32x16 low;
+      const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      const uint32_t kaddr = (uint32_t)(l32 * ROWB + ((hf ^ row_swizzle32<D>(l32)) << 4));
+      bf16x8 fr[2][NPL];
+      auto read_k = [&](bf16x8 (&dst)[NPL], auto tag) __attribute__((always_inline)) {
+        const unsigned char* at = Ks + flip<decltype(tag)::value * 32>(kaddr);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) sc[v] = 0.f;
-      // one fragment ahead of the products (256 cycles of matrix work each), no more: left alone the compiler
-      // requests all of them first and spills
-      f32x4 kk = *reinterpret_cast<const f32x4*>(Ks + l32 * KPITCH + hf * 4);
-#pragma unroll
-      for (int k8 = 0; k8 < D / 8; ++k8) {
-        f32x4 kn = kk;
-        if (k8 + 1 < D / 8) kn = *reinterpret_cast<const f32x4*>(Ks + l32 * KPITCH + (k8 + 1) * 8 + hf * 4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kk[e], q[k8 * 4 + e], sc, 0, 0, 0);
-        kk = kn;
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      float tmax = -INFINITY;
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const f32x4 bs = *reinterpret_cast<const f32x4*>(bias_s + g4 * 8 + hf * 4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          float s = bs[e] == -INFINITY ? -INFINITY : fmaf(sc[g4 * 4 + e], a.scale, bs[e]);
-          if (a.causal && last_s[g4 * 8 + hf * 4 + e] > row) s = -INFINITY;
-          sc[g4 * 4 + e] = s;
-          tmax = fmaxf(tmax, s);
+        for (int pl = 0; pl < NPL; ++pl) dst[pl] = *reinterpret_cast<const bf16x8*>(at + pl * PLANEB);
+      };
+      read_k(fr[0], std::integral_constant<int, 0>{});
+      each<KSTEPS>([&](auto tag) __attribute__((always_inline)) {
+        constexpr int ks = decltype(tag)::value;
+        if constexpr (ks + 1 < KSTEPS) read_k(fr[(ks + 1) & 1], std::integral_constant<int, ks + 1>{});
+        const bf16x8(&kk)[NPL] = fr[ks & 1];
+        if constexpr (NPL == 3) {
+          low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk[2], q[0][ks], ks == 0 ? zero : low, 0, 0, 0);
+          low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk[0], q[2][ks], low, 0, 0, 0);
+          low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk[1], q[1][ks], low, 0, 0, 0);
+          low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk[1], q[0][ks], low, 0, 0, 0);
+          low = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk[0], q[1][ks], low, 0, 0, 0);
         }
-      }
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-      const float mn = fmaxf(m, tmax);
-      ref = mn == -INFINITY ? 0.f : mn;
-      if (__any(mn > m)) {
-        const float alpha = expf(m - ref);               // m = -inf: 0
-        l *= alpha;
-#pragma unroll
-        for (int md = 0; md < MD; ++md)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) o[md][v] *= alpha;
-        m = mn;
-      }
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        sc[v] = expf(sc[v] - ref);
-        l += sc[v];
-      }
-      deposit_v();
-    }
-    barrier();                                           // V rows in LDS; everyone is done with the K rows
-    if (nxt.ok) fetch(K, Kp, nxt, pn);
-    if (cur.ok) {
-      int bad = 0;
-      if (a.causal) {
-#pragma unroll
-        for (int w = 0; w < TEAM; ++w) bad |= flag_s[w];
-      }
-      if (__builtin_amdgcn_readfirstlane(bad) == 0) {
-        float va[MD], vn[MD];
-#pragma unroll
-        for (int md = 0; md < MD; ++md) va[md] = Vs[hf * 4 * VPITCH + md * 32 + l32];
+        sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk[0], q[0][ks], ks == 0 ? zero : sc, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      if constexpr (NPL == 3) {
+        float any = 0.f;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          if (v + 1 < 16) {
-#pragma unroll
-            for (int md = 0; md < MD; ++md) vn[md] = Vs[(((v + 1) >> 2) * 8 + hf * 4 + ((v + 1) & 3)) * VPITCH + md * 32 + l32];
-          }
-#pragma unroll
-          for (int md = 0; md < MD; ++md) {
-            o[md] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[md], sc[v], o[md], 0, 0, 0);
-            va[md] = vn[md];
-          }
-          __builtin_amdgcn_sched_barrier(0);
+          sc[v] += low[v];
+          any += sc[v];
         }
-      } else {
-        // Causal, and the tile holds a value that is not finite: a row must not see 0 * inf of a key that is
-        // hidden from it, so hidden keys are left out one by one (rare: on the vector unit).
-        for (int kk = 0; kk < 32; ++kk) {
-          const int vi = (kk >> 3) * 4 + (kk & 3), from = l32 + ((kk >> 2) & 1) * 32;
-          float pv = 0.f;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) pv = v == vi ? sc[v] : pv;
-          pv = __shfl(pv, from, 64);
-          if (bias_s[kk] == -INFINITY || last_s[kk] > row) continue;
-#pragma unroll
-          for (int md = 0; md < MD; ++md)
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-              o[md][v] = fmaf(pv, Vs[kk * VPITCH + md * 32 + (v >> 2) * 8 + hf * 4 + (v & 3)], o[md][v]);
-        }
+        bad = __any(!(fabsf(any) < INFINITY));           // a row or key that is not finite, or a product that overflows
       }
+      weights(cur, pc, sc);
+      bad |= (bool)__any(deposit(Vs, pc));
     }
-    if (nxt.ok) deposit_k(nxt, pn, half ^ 1);
+    if (lane == 0) flag_s[wave] = bad ? 1 : 0;
+    barrier();                                           // V rows in LDS; everyone is done with the K rows
+    int stop = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) stop |= TEAM == 1 && w != wave ? 0 : flag_s[w];
+    finite = __builtin_amdgcn_readfirstlane(stop) == 0;
+    if (!finite) break;
+    if (nxt.ok) fetch(K, Kp, nxt, pn);
+    if (cur.ok) {
+      bf16x8 p[3][2];                                    // planes of the weights: keys f * 16 .. as they stand in the registers
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        u32x4 w[3];
+        float rest = 0.f;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          const Split2 t = split2(sc[8 * f + 2 * x], sc[8 * f + 2 * x + 1], rest);
+          w[0][x] = t.h;
+          w[1][x] = t.m;
+          w[2][x] = t.l;
+        }
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) p[pl][f] = __builtin_bit_cast(bf16x8, w[pl]);
+      }
+      const int trow = hf * 4 + ((lane & 15) >> 2);
+      const uint32_t taddr = (uint32_t)(trow * ROWB + (((((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) ^ row_swizzle32<D>(trow)) << 4) + (lane & 1) * 8);
+      auto read_v = [&](bf16x8 (&dst)[NPL], auto tag) __attribute__((always_inline)) {   // 16 keys j / MD, channels (j % MD) * 32 ..
+        constexpr int j = decltype(tag)::value, down = (j / MD) * 16 * ROWB, md = j % MD;
+        unsigned char *at = Vs + flip<md * 64>(taddr), *at8 = Vs + flip<(md * 64) ^ 32>(taddr);   // (eight rows further down the swizzle differs in one bit)
+#pragma unroll
+        for (int pl = 0; pl < NPL; ++pl) {
+          const f32_s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((f32_lds_s16x4*)(at + pl * PLANEB + down));
+          const f32_s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((f32_lds_s16x4*)(at8 + pl * PLANEB + down + 8 * ROWB));
+          dst[pl] = __builtin_bit_cast(bf16x8, (f32_s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        }
+      };
+      bf16x8 fr[2][NPL];
+      read_v(fr[0], std::integral_constant<int, 0>{});
+      each<2 * MD>([&](auto tag) __attribute__((always_inline)) {
+        constexpr int j = decltype(tag)::value, f = j / MD, md = j % MD;
+        if constexpr (j + 1 < 2 * MD) read_v(fr[(j + 1) & 1], std::integral_constant<int, j + 1>{});
+        const bf16x8(&va)[NPL] = fr[j & 1];
+        if constexpr (NPL == 3) o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[2], p[0][f], o[md], 0, 0, 0);
+        o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[0], p[2][f], o[md], 0, 0, 0);
+        if constexpr (NPL == 3) {
+          o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[1], p[1][f], o[md], 0, 0, 0);
+          o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[1], p[0][f], o[md], 0, 0, 0);
+        }
+        o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[0], p[1][f], o[md], 0, 0, 0);
+        o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[0], p[0][f], o[md], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0x7);             // (arithmetic may pass: the next weights' planes, addresses; 237 -> 228 us at 12 heads x 4680 tokens)
+      });
+    }
+    if (nxt.ok) deposit(Ks, pn);
     barrier();                                           // the next K rows in LDS; everyone is done with the V rows
     cur = nxt;
     pc = pn;
     nxt = nn;
-    pn = pnn;
+  }
+  if (!finite) {
+    // A value that is not finite was met: the planes of an infinity give NaN where the product has a sign, and (causal) a row must not see 0 * inf of
+    // a key that is hidden from it.  The row's list is walked again from memory, S in float32, the outputs key by key on the vector unit (rare).
+    // (Of the workgroup or, where a team is a wavefront that waits for nobody, of the team.)
+    m = -INFINITY;
+    l = 0.f;
+#pragma unroll
+    for (int md = 0; md < MD; ++md)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) o[md][v] = 0.f;
+    Tile t = {1, team, 0, 0, 0, 0};
+    enter(t);
+    settle(t);
+#pragma unroll 1
+    while (t.ok) {
+      const int prow = row_of(t, block_of(t));
+      f32x16 sc;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sc[v] = 0.f;
+      const T* krow = base_of(K, Kp, t) + (int64_t)(prow < 0 ? 0 : prow) * D + hf * 4;
+      const T* qrow = Q + (qhead * a.N + (active ? row : row0)) * D + hf * 4;
+#pragma unroll 1
+      for (int c = 0; c < D; c += 8) {
+        f32x4 x = Four<T>::widen(Four<T>::load(krow + c)), y = Four<T>::widen(Four<T>::load(qrow + c));
+        if (prow < 0) x = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (!active) y = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], sc, 0, 0, 0);
+      }
+      weights(t, prow, sc);
+      const T* vbase = base_of(V, Vp, t) + hf * 4;
+#pragma unroll 1
+      for (int kk = 0; kk < 32; ++kk) {
+        const int vi = (kk >> 3) * 4 + (kk & 3), from = l32 + ((kk >> 2) & 1) * 32, pr = __shfl(prow, kk, 64);
+        if (pr < 0) continue;                            // no such key
+        float pv = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) pv = v == vi ? sc[v] : pv;
+        pv = __shfl(pv, from, 64);
+        const int64_t end = ((int64_t)pr + 1) << (t.h - 1);
+        const bool hidden = a.causal && (end < a.N ? end : a.N) - 1 > row;
+#pragma unroll
+        for (int md = 0; md < MD; ++md)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const f32x4 x = Four<T>::widen(Four<T>::load(vbase + (int64_t)pr * D + md * 32 + g * 8));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[md][g * 4 + e] = hidden ? o[md][g * 4 + e] : fmaf(pv, x[e], o[md][g * 4 + e]);
+          }
+      }
+      t.tl += KS;
+      settle(t);
+    }
   }
 
   // merge the teams through LDS (fixed order) and write whole rows
-  float* ms = fsm;                                       // [KS][ROWS] maxima | [KS][ROWS] sums | [KS][ROWS][KPITCH] outputs
-  float* os = fsm + 2 * KS * ROWS;
+  float* ms = reinterpret_cast<float*>(fsm);             // [KS][ROWS] maxima | [KS][ROWS] sums | [KS][ROWS][PITCH] outputs
+  float* os = ms + 2 * KS * ROWS;
   l += __shfl_xor(l, 32, 64);
   __syncthreads();
   const int slot = team * ROWS + wr * 32 + l32;
@@ -302,7 +463,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
   for (int md = 0; md < MD; ++md)
 #pragma unroll
     for (int g = 0; g < 4; ++g)
-      *reinterpret_cast<f32x4*>(os + slot * KPITCH + md * 32 + g * 8 + hf * 4) =
+      *reinterpret_cast<f32x4*>(os + slot * PITCH + md * 32 + g * 8 + hf * 4) =
           f32x4{o[md][4 * g], o[md][4 * g + 1], o[md][4 * g + 2], o[md][4 * g + 3]};
   __syncthreads();
   for (int x = tid; x < ROWS * CPR; x += 256) {
@@ -317,23 +478,27 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
     for (int k = 0; k < KS; ++k) {
       // A team that saw no key of the row adds 0 * 0.  None is left out for a maximum of -inf alone: fmaxf drops NaN, so
       // a team all of whose scores are NaN has that maximum too, with a sum and outputs that are NaN and have to stay.
-      const float w = KS == 1 ? 1.f : expf(ms[k * ROWS + r] - (mm == -INFINITY ? 0.f : mm));
+      const float w = KS == 1 ? 1.f : exp2f(ms[k * ROWS + r] - (mm == -INFINITY ? 0.f : mm));
       ll += w * ms[KS * ROWS + k * ROWS + r];
-      acc += w * *reinterpret_cast<const f32x4*>(os + (k * ROWS + r) * KPITCH + c);
+      acc += w * *reinterpret_cast<const f32x4*>(os + (k * ROWS + r) * PITCH + c);
     }
     const float inv = 1.f / ll;                          // no visible key at all: NaN
     Four<T>::store(O + (qhead * a.N + row0 + r) * D + c, acc * inv);
-    if (lse && c == 0) lse[qhead * a.N + row0 + r] = mm + logf(ll);
+    if (lse && c == 0) lse[qhead * a.N + row0 + r] = fmaf(mm, 0.69314718055994531f, logf(ll));
   }
 }
 
 template <typename T, int D, int TEAM>
 static hipError_t launch_f32_t(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp, const void* Vp,
                                const uint16_t* idx, const int32_t* cnt, void* O, float* lse, hipStream_t s) {
-  using S = F32Shape<D, TEAM>;
+  using S = F32Shape<T, D, TEAM>;
   F32Args a;
   a.N = pl.N; a.Hq = pl.Hq; a.Hkv = pl.Hkv; a.nq = pl.nq; a.nk = pl.nk; a.bq = pl.bq; a.bk = pl.bk;
-  a.H = pl.H; a.causal = pl.causal; a.scale = pl.scale;
+  a.H = pl.H; a.causal = pl.causal;
+  const double scale2 = (double)pl.scale * 1.4426950408889634074;
+  a.scale_hi = (float)scale2;
+  if ((double)a.scale_hi >= scale2) a.scale_hi = nextafterf(a.scale_hi, 0.f);   // both parts positive: times -inf they must not meet as NaN
+  a.scale_lo = (float)(scale2 - (double)a.scale_hi);
   a.lg_bk = 0;
   while ((1 << a.lg_bk) < pl.bk) ++a.lg_bk;
   a.slices = (pl.bq + S::ROWS - 1) / S::ROWS;
@@ -351,16 +516,14 @@ static hipError_t launch_f32_t(const Plan& pl, const void* Q, const void* K, con
 template <typename T, int D>
 static hipError_t launch_f32_d(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp, const void* Vp,
                                const uint16_t* idx, const int32_t* cnt, void* O, float* lse, hipStream_t s) {
-  // The largest team that still fills the chip: fewer rows per team cost more reads of the same keys, fewer
-  // workgroups leave compute units idle.  Measured with 12 heads at d = 128 (128-row blocks of the problem: us for
-  // team 1 / 2 / 4, pyramid included): 48: 26 / 33 / 37, 96: 62 / 47 / 55, 192: 121 / 105 / 106, 252: 194 / 137 / 136,
-  // 288: 285 / 247 / 236, 432: 535 / 409 / 343, 564: 931 / 699 / 679; d = 64: 48: 20 / 23 / 27, 96: 30 / 30 / 37, 192: 65 / 62 / 72,
-  // 252: 87 / 77 / 92, 288: 126 / 135 / 147, 348: 164 / 166 / 167, 432: 226 / 220 / 210, 564: 372 / 369 / 418.  One line for both
-  // head dimensions: it is drawn for d = 128; at d = 64 a team of four is the slowest just behind the line (288) and again
-  // where the last round of workgroups is nearly empty (564), by 16 and 13 %.
+  // The largest team that still fills the chip: fewer rows per team cost more reads (and conversions) of the same keys, fewer
+  // workgroups leave compute units idle.  Measured with 12 heads at d = 128 (128-row blocks of the problem: us for team 1 / 2 / 4, pyramid and
+  // block lists included): 48: 25 / 31 / 33, 96: 55 / 38 / 45, 192: 106 / 93 / 80, 252: 183 / 127 / 107, 288: 225 / 190 / 151, 432: 415 / 328 / 240,
+  // 564: 673 / 515 / 417; d = 64: 48: 20 / 28 / 29, 96: 28 / 31 / 32, 192: 52 / 47 / 53, 252: 77 / 61 / 66, 288: 97 / 94 / 87, 432: 177 / 151 / 129,
+  // 564: 284 / 242 / 232.  So teams of four from 150 such blocks on at d = 128 and from 256 on at d = 64, where a row of keys is converted in half the time.
   const int64_t blocks = (int64_t)pl.B * pl.Hq * pl.nq;
   auto groups = [&](int rows) { return blocks * ((pl.bq + rows - 1) / rows); };
-  const int team = pl.bq > 64 && groups(128) >= 256 ? 4 : (pl.bq > 32 && groups(64) >= 192 ? 2 : 1);
+  const int team = pl.bq > 64 && groups(128) >= (D == 128 ? 150 : 256) ? 4 : (pl.bq > 32 && groups(64) >= 192 ? 2 : 1);
   if (team == 4) return launch_f32_t<T, D, 4>(pl, Q, K, V, Kp, Vp, idx, cnt, O, lse, s);
   if (team == 2) return launch_f32_t<T, D, 2>(pl, Q, K, V, Kp, Vp, idx, cnt, O, lse, s);
   return launch_f32_t<T, D, 1>(pl, Q, K, V, Kp, Vp, idx, cnt, O, lse, s);

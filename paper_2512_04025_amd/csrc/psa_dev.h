@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace psa {
 
 typedef uint16_t bf16_t;  // raw bfloat16 bits
@@ -91,6 +93,56 @@ __device__ __forceinline__ bool not_finite(f32x4 x) {
 #pragma unroll
   for (int u = 0; u < 4; ++u) bad |= (__float_as_uint(x[u]) & 0x7f800000u) == 0x7f800000u;
   return bad;
+}
+
+// f(integral_constant 0), f(1) .. f(N - 1)
+template <int N, int I = 0, typename F> __device__ __forceinline__ void each(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    each<N, I + 1>(f);
+  }
+}
+
+// x ^ a constant, made where it is used: an address per constant would otherwise be held in a register over the whole loop
+template <int C> __device__ __forceinline__ uint32_t flip(uint32_t x) {
+  if (C == 0) return x;
+  uint32_t y;
+  asm volatile("v_xor_b32 %0, %1, %2" : "=v"(y) : "n"(C), "v"(x));
+  return y;
+}
+
+// the lane's number, made where it is used: what depends on it is worked out again instead of held over the stage loop
+__device__ __forceinline__ int lane_again() {
+  int x;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(x));
+  return x;
+}
+
+// Place of a bfloat16 row's 16-byte chunks in LDS for operands of 32 rows (two lanes a row): chunk ^ row_swizzle32(row).  16 consecutive
+// rows are at 16 different places, and the four rows of a transposing group in four different 64-byte groups.
+template <int D> __host__ __device__ constexpr int row_swizzle32(int row) {
+  return D == 128 ? ((row & 3) << 2) | ((row >> 2) & 3) : (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
+}
+
+// float32 on the bfloat16 matrix cores: x = h + m + l exactly, three bfloat16 (8 bits each, the remainders rounded to nearest and signed), so that
+// a product is the six terms down to 2^-16 of it (h h, h m, m h, m m, h l, l h); the three that are left out are of the order of 2^-25 of it.
+// Not for values that are not finite (or round to infinity): their m and l are NaN.
+struct Split2 { uint32_t h, m, l; };                 // of two neighbours: the first in the low halves
+__device__ __forceinline__ Split2 split2(float a, float b, float& rest) {
+  typedef __attribute__((ext_vector_type(2))) float f32x2;
+  auto pack = [](float x, float y) __attribute__((always_inline)) {   // (as a vector: one conversion for the pair)
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x, y}), bf16x2));
+  };
+  Split2 s;
+  s.h = pack(a, b);
+  a -= __uint_as_float(s.h << 16);
+  b -= __uint_as_float(s.h & 0xffff0000u);
+  s.m = pack(a, b);
+  a -= __uint_as_float(s.m << 16);
+  b -= __uint_as_float(s.m & 0xffff0000u);
+  s.l = pack(a, b);
+  rest += a + b;                                     // NaN if either was not finite
+  return s;
 }
 
 __device__ __forceinline__ int ilog2(int x) { return 31 - __clz(x); }

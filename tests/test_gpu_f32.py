@@ -172,3 +172,36 @@ def test_gradients_where_the_channels_cancel(d):
     ref = orc.psa_attention_backward(Q64, orc.build_pyramid(K64, op), orc.build_pyramid(V64, op), M, dO64, op)
     for name, got, want in zip(("dQ", "dK"), grads, ref):
         assert rel_l2(from_dev(got, "f32"), want) <= 9e-6 * d / 128, name
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("N,Hq,bq", [(97, 2, 64), (993, 12, 64), (993, 32, 128)])
+def test_infinite_keys_and_values_act_as_in_float32(N, Hq, bq, d):
+    """Products of the bfloat16 planes of an infinity would be NaN; teams of one, two and four.  The last key has an infinite
+    channel: rows whose query is negative there do not see it, the others are NaN.  One value is infinite, one is finite but
+    rounds to infinity in bfloat16.  Bars: the fp32 bar of the parity tests, relative where values are of the order of 1e36."""
+    import torch
+    op = orc.Params(B=1, Hq=Hq, Hkv=1, N=N, d=d, bq=bq, bk=32, levels=1, dtype="f32", sq=8, sk=1)
+    gp = gpu_params(op)
+    Q, K, V = si.random_qkv(6, 1, Hq, 1, N, d, "f32")
+    K[:, :, -1, 0] = np.inf
+    V[:, :, 3, 5] = -np.inf
+    V[:, :, 4, 6] = 3.4e38
+    buf = Buffers(gp)
+    buf.M.fill_(1)
+    psa.psa_attention_fwd(gp, *(to_dev(x, "f32") for x in (Q, K, V)), None, None, buf.M, buf.O, buf.scratch, lse=buf.lse)
+    torch.cuda.synchronize()
+    got, lse = from_dev(buf.O, "f32"), buf.lse.cpu().numpy()
+    sees = Q[..., 0] < 0
+    assert np.all(np.isnan(got[~sees]))
+    x = Q.astype(np.float64) @ K[:, :, :-1].astype(np.float64).swapaxes(2, 3) / np.sqrt(d)
+    top = x.max(-1, keepdims=True)
+    P = np.exp(x - top)
+    total = P.sum(-1, keepdims=True)
+    with np.errstate(invalid="ignore"):
+        want = (P / total) @ V[:, :, :-1].astype(np.float64)
+    assert np.all(got[sees][:, 5] == -np.inf)
+    assert np.allclose(got[sees][:, 6], want[sees][:, 6], rtol=1e-5, atol=0)
+    rest = [c for c in range(d) if c not in (5, 6)]
+    assert np.abs(got[sees][:, rest] - want[sees][:, rest]).max() <= 1e-5
+    assert np.abs(lse[sees] - (top + np.log(total))[..., 0][sees]).max() <= 1e-4
