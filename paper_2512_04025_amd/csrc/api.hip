@@ -24,7 +24,7 @@ hipError_t allow_max_lds(const void* kernel, LdsOptIn* state) {
   return e;
 }
 
-size_t attn_mfma_smem_bytes(int d, int nk, int bn);
+size_t attn_mfma_smem_bytes(int d, int nk, int bn, int bufs, int nw);
 
 int make_plan(const psa_params* p, Plan* o) {
   if (!p || !o) return PSA_EINVAL;
@@ -273,7 +273,7 @@ int psa_attention_fwd(const psa_params* p, const void* Q, const void* K, const v
   if (pl.H > 1 && (!Kpyr || !Vpyr)) return PSA_EINVAL;
   if (reinterpret_cast<uintptr_t>(scratch) & 255) return PSA_EINVAL;
   // the matrix-core kernel keeps a row's block list in LDS next to its four tiles
-  if (pl.use_mfma && attn_mfma_smem_bytes(pl.d, pl.nk, 64) > LDS_LIMIT) return PSA_EUNSUPPORTED;
+  if (pl.use_mfma && attn_mfma_smem_bytes(pl.d, pl.nk, 64, 2, 4) > LDS_LIMIT) return PSA_EUNSUPPORTED;
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint16_t* idx = reinterpret_cast<uint16_t*>(at(scratch, pl.off_idx));
   int32_t* cnt = reinterpret_cast<int32_t*>(at(scratch, pl.off_cnt));
@@ -367,7 +367,7 @@ int psa_attention_fwd_static(const psa_params* p, const void* Q, const void* K, 
   if (rc != PSA_OK) return rc;
   if (!Q || !K || !V || !M || !O) return PSA_EINVAL;
   if (pl.H > 1 && (!Kpyr || !Vpyr)) return PSA_EINVAL;
-  if (pl.use_mfma && attn_mfma_smem_bytes(pl.d, pl.nk, 64) > LDS_LIMIT) return PSA_EUNSUPPORTED;
+  if (pl.use_mfma && attn_mfma_smem_bytes(pl.d, pl.nk, 64, 2, 4) > LDS_LIMIT) return PSA_EUNSUPPORTED;
   // only the attention call's part of the workspace: block lists, level counts, tile descriptors
   const size_t rows_q = (size_t)pl.B * pl.Hq * pl.nq;
   const size_t off_idx = 0;

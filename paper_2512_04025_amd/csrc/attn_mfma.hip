@@ -30,8 +30,7 @@
 // where it happens: waits for LDS reads next to direct-to-LDS loads (tile reads are assembly with
 // counted waits), the fence of __syncthreads (plain s_barrier plus counted vmcnt waits), and pure
 // arithmetic drifting out of its slice (empty asm pins).
-#include <type_traits>
-
+#include "bwd_walk.h"
 #include "psa_dev.h"
 #include "psa_internal.h"
 
@@ -42,6 +41,7 @@ struct MfmaArgs {
   int lg_bk;
   int slices;              // workgroup slices per query block
   int heads;               // B * Hq
+  int runs;                // not causal: each XCD takes a contiguous run of all heads' query blocks
   int desc_pitch;          // tile descriptors per row (0: the kernel plans its loads itself)
   float scale_log2;        // scale * log2(e)
   int64_t lvl_off[PSA_MAX_LEVELS + 2];
@@ -80,10 +80,17 @@ struct LevelState {
 // tokens (pyramid included), tiles of 64 and two wavefronts per SIMD allowed -> tiles of 32, no tight limit -> this:
 // 32-row blocks d = 128 4104 -> 3915 -> 2360 us, d = 64 1752 -> 1685 -> 1180; 64-row blocks d = 128 2142 -> 1777 -> 1765,
 // d = 64 1160 -> 1118 -> 1040.
-constexpr int most_waves(int d, int nw, int bn) { return bn == 64 ? (d == 64 ? 3 : 2) : (d == 64 ? nw + 1 : nw); }
-constexpr int least_waves(int d, int nw, int bn) { return bn == 64 ? 2 : most_waves(d, nw, bn); }
-template <int D, int NW, bool SC, int BN>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((least_waves(D, NW, BN)), most_waves(D, NW, BN))))
+// BUFS: K and V buffers of a tile.  With one each (K(t+2) is requested when the first product of a step has read K(t+1), V(t+1) when the second has read
+// V(t)) a load has half a step to arrive instead of one and a half, but a workgroup's LDS is half as large and one more wavefront
+// fits on every SIMD: a lone wavefront issues for 1400 of the 2100 cycles that a 32-column tile took and waits for the rest.  Pyramid and attention, 12 heads,
+// a fifth of the keys, us for two buffers / one (both with the work order below): 32-row blocks d = 128 x 4000 tokens 78 / 59, x 9000 266 / 203, x 18000 799 / 651,
+// x 32760 (back and forth, see the list) 2290 / 2250; d = 64 x 6000 81 / 69, x 24000 658 / 612; 64-row blocks d = 128 x 6000 105 / 91, x 13000 357 / 312, x 24000 998 / 916.
+constexpr int most_waves(int d, int nw, bool sc, int bn, int bufs) {
+  return bn == 64 ? (d == 64 ? 3 : 2) : bufs == 2 ? (d == 64 ? nw + 1 : nw) : d == 64 ? nw + 2 : sc ? nw + 1 : 2;
+}
+constexpr int least_waves(int d, int nw, bool sc, int bn, int bufs) { return bn == 64 ? 2 : most_waves(d, nw, sc, bn, bufs); }
+template <int D, int NW, bool SC, int BN, int BUFS>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((least_waves(D, NW, SC, BN, BUFS)), most_waves(D, NW, SC, BN, BUFS))))
 void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
                       const bf16_t* __restrict__ Kp, const bf16_t* __restrict__ Vp,
                       const uint16_t* __restrict__ idx, const int32_t* __restrict__ cnt,
@@ -106,16 +113,18 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   // Full-size workgroups on shapes whose load instructions never straddle a pooled block read their
   // load plan from per-tile descriptors made by lists_kernel instead of deriving it per tile.
   constexpr bool DESC = SC && NW == 4;
+  constexpr bool BACK = BUFS == 1 && NW == 1 && D == 128;
+  constexpr int GENERATION = 32 * 4 * most_waves(D, NW, SC, BN, BUFS) / NW;   // workgroups of an XCD that run at one time
   static_assert(BN == 64 || (BN == 32 && NW < 4), "tile width");
   static_assert(NINST % NW == 0, "tile rows must split evenly over the wavefronts");
   static_assert(MPC * NB == NPAIR, "chunking of the softmax work");
   // LDS map: K[2] | V[2] | per-wavefront table for irregular tiles | block list
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  constexpr int OFF_K = 0, OFF_V = 2 * TILEB, OFF_FIX = 4 * TILEB, OFF_LIST = OFF_FIX + NW * 512;
+  constexpr int OFF_K = 0, OFF_V = BUFS * TILEB, OFF_FIX = 2 * BUFS * TILEB, OFF_LIST = OFF_FIX + NW * 512;
   uint16_t* list = reinterpret_cast<uint16_t*>(smem + OFF_LIST);    // kept block ids, level-major
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hf = lane >> 5;
   // Workgroup ids are dealt round-robin to the 8 XCDs (each with its own L2; the memory-side cache is
   // shared by all).  Non-causal: all XCDs walk the SAME head at a time, heads outermost, so the
@@ -126,16 +135,15 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   // by up to the whole sequence, so there every XCD takes whole heads and an even share of the heads that do not go into eight (xcd_item),
   // longest rows first.  Whole forward, contiguous runs of (head, query block) items -> this, us: 12 heads x
   // 8000 tokens 126 -> 114, x 20000 at d = 64 259 -> 248, 2 x 30000 210 -> 182, 28 x 16000 504 -> 491 (x 1000 45.3 -> 45.8, the arithmetic).
+  // Workgroups of one or two wavefronts, and heads of fewer than 32 query blocks: each XCD takes a contiguous run of ALL heads' query blocks, so that more
+  // of the rows that an L2 serves at one time are of one head, and none idles where a head's blocks do not go into eight.  Pyramid and attention, us for one
+  // head at a time / runs, 32-row blocks, d = 128: 12 heads x 13000 tokens 430 / 381, 4 x 20000 404 / 306, 40 x 3000 141 / 107; 64-row blocks 12 x 9000
+  // 215 / 180, 40 x 3000 110 / 92; 128-row blocks 40 x 3000 88.2 / 85.8.  (Two or four XCDs to a head at a time: 12 x 24000 1380 and 1407, runs 1245.)
   int head, e_item;
   if (a.causal) {
     if (!xcd_item(a.heads, a.slices * a.nq, (int)(blockIdx.x & 7), (int)(blockIdx.x >> 3), head, e_item)) return;
   } else {
-    const int per_head = a.nq * a.slices;
-    const int run = (per_head + 7) >> 3;     // workgroups per XCD and head
-    const int slot = (int)(blockIdx.x >> 3);
-    head = slot / run;
-    e_item = (int)(blockIdx.x & 7) * run + (slot - head * run);
-    if (e_item >= per_head) return;
+    if (!dq_item(a.heads, a.nq * a.slices, a.runs, (int)(blockIdx.x & 7), (int)(blockIdx.x >> 3), head, e_item)) return;
   }
   const int slice = e_item % a.slices;
   int i = e_item / a.slices;
@@ -161,11 +169,23 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
     total_blocks += nb;
     total_tiles += ((nb << lg_th) + BN - 1) >> LG_BN;
   }
-  for (int x = tid; x < total_blocks; x += NT) list[x] = my_idx[x];
+  // Where the rows in flight on an XCD outgrow its L2 (d = 128, 32-row blocks, not causal) every second generation of workgroups walks its lists backwards:
+  // a workgroup that follows one which has just reached the end of the sequence begins where that one's neighbours still are.  12 heads x 24000 tokens
+  // 1260 -> 1215 us, x 32760 2430 -> 2260, 4 x 30000 730 -> 638; no change at 18000, none at d = 64 or with 64-row blocks.
+  if (BACK && !a.causal && (((int)(blockIdx.x >> 3) / GENERATION) & 1)) {
+    int first = 0;
+    for (int h = 1; h <= a.H; ++h) {
+      const int nb = my_cnt[h - 1];
+      for (int x = tid; x < nb; x += NT) list[first + x] = my_idx[first + nb - 1 - x];
+      first += nb;
+    }
+  } else {
+    for (int x = tid; x < total_blocks; x += NT) list[x] = my_idx[x];
+  }
   {  // tile buffers start as zeros (a lane whose source row is out of range was seen to store zeros, but
      // nothing here relies on that: an out-of-range row may as well keep what its slot held)
     const u32x4 z = {0u, 0u, 0u, 0u};
-    for (int x = tid * 16; x < 4 * TILEB; x += NT * 16) *reinterpret_cast<u32x4*>(smem + x) = z;
+    for (int x = tid * 16; x < 2 * BUFS * TILEB; x += NT * 16) *reinterpret_cast<u32x4*>(smem + x) = z;
   }
 
   LevelState ls;
@@ -282,21 +302,23 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
       do { enter_level(ls.h + 1, ls.lvl_start + ls.nblk); } while (ls.h <= a.H && ls.ntl == 0);
     }
   };
+  // a wave-uniform row offset is the instruction's scalar offset (which takes part in the range check): no vector add
+  auto load_rows = [&](__amdgpu_buffer_rsrc_t rsrc, unsigned char* to, uint32_t row_off, uint32_t lane_off) __attribute__((always_inline)) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)to, 16, (int)(SC ? lane_off : row_off + lane_off), (int)(SC ? row_off : 0u), 0, 0);
+  };
   auto fire_k = [&](int t) __attribute__((always_inline)) {      // K rows of tile t -> K buffer t & 1
     // rows past the end of the unpadded level-1 array are out of the descriptor's range: such lanes
     // read nothing (the scores of those columns are masked, see fixup_special)
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)planK_kbase, 0, (int)planK_nrec, RSRC_FLAGS);
 #pragma unroll
     for (int k = 0; k < RI; ++k)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(smem + OFF_K + (t & 1) * TILEB + (k * NW + wave) * RPI * ROWB),
-                                               16, (int)(planK[k] + klane[k % KP]), 0, 0, 0);
+      load_rows(rsrc, smem + OFF_K + (t & (BUFS - 1)) * TILEB + (k * NW + wave) * RPI * ROWB, planK[k], klane[k % KP]);
   };
   auto fire_v = [&](int t) __attribute__((always_inline)) {      // V rows of tile t -> V buffer t & 1
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)planV1_vbase, 0, (int)planV1_nrec, RSRC_FLAGS);
 #pragma unroll
     for (int k = 0; k < RI; ++k)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(smem + OFF_V + (t & 1) * TILEB + (k * NW + wave) * RPI * ROWB),
-                                               16, (int)(planV1[k] + vlane[k % KP]), 0, 0, 0);
+      load_rows(rsrc, smem + OFF_V + (t & (BUFS - 1)) * TILEB + (k * NW + wave) * RPI * ROWB, planV1[k], vlane[k % KP]);
   };
   auto rotate_plans = [&]() __attribute__((always_inline)) {     // after the K rows of planK have gone out
 #pragma unroll
@@ -311,7 +333,7 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   auto wg_barrier = [&]() __attribute__((always_inline)) { asm volatile("s_barrier" ::: "memory"); };
   // wait until at most `groups` of this wavefront's tile-load groups (RI loads each) are still in flight
   auto wait_loads = [&](bool two_behind) __attribute__((always_inline)) {
-    constexpr int N2 = 2 * RI;
+    constexpr int N2 = BUFS * RI;
     if (two_behind) __builtin_amdgcn_s_waitcnt((N2 & 15) | ((N2 >> 4) << 14) | 0x0F70);
     else __builtin_amdgcn_s_waitcnt(0x0F70);
   };
@@ -598,18 +620,20 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
     constexpr int PAR = decltype(parity_tag)::value;      // t & 1, known at each call site
     constexpr bool MORE = true, k3 = true, k4 = true;
     const bool has_next = t + 1 < total_tiles;
-    wait_loads(true);                         // K(t+1): only V(t) and K(t+2) were requested after it
+    wait_loads(BUFS == 2 || NW == 1);         // K(t+1): only V(t) and (two buffers) K(t+2) were requested after it
     wg_barrier();                             // ... everyone's part of it; the buffer of V(t-1) is free
     if constexpr (DESC) {                     // (both descriptors were waited for in the middle of the last step)
       meta_next = dV[0] & 31u;
       fire_desc(dV, vst, false, t + 1);
       desc_load(dK, t + 3);                   // cache hits: their line was touched at least a step ago
       desc_load(dV, t + 2);
-    } else {
+    } else if constexpr (BUFS == 2) {
       fire_v(t + 1);
+    } else if constexpr (NW > 1) {
+      fire_v(t);
     }
-    constexpr uint32_t flip_n = PAR ? 0u : (uint32_t)TILEB;
-    constexpr uint32_t flip_c = PAR ? (uint32_t)TILEB : 0u;
+    constexpr uint32_t flip_n = PAR || BUFS == 1 ? 0u : (uint32_t)TILEB;
+    constexpr uint32_t flip_c = PAR && BUFS == 2 ? (uint32_t)TILEB : 0u;
     bf16x8 pf[BN / 16];
     bf16x8 fr[4];                             // rolling operand fragments, requested PF MFMAs ahead
     constexpr int PF = 2;
@@ -632,16 +656,26 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
       __builtin_amdgcn_sched_barrier(0);
     }
     if (!DESC && k4) plan_resolve();
-    wait_loads(true);                         // V(t): only K(t+2) and V(t+1) were requested after it
+    if constexpr (BUFS == 1 && NW == 1) {     // (the one wavefront has read K(t+1))
+      fire_k(t + 2);
+      rotate_plans();
+    }
+    wait_loads(BUFS == 2 || NW == 1);         // V(t): only K(t+2) and (two buffers) V(t+1) were requested after it
     wg_barrier();                             // ... everyone's part of it; the buffer of K(t+1) is free
+    if constexpr (BUFS == 1 && NW > 1) {
+      fire_k(t + 2);
+      rotate_plans();
+    }
     if constexpr (DESC) {
       desc_wait(dK, dV);                      // the only drain of scalar loads in a step
       fire_desc(dK, kst, true, t + 3);
       desc_touch(t + 3);                      // has a whole step to arrive before the next drain
       if (has_next && (meta_next & 16u)) fixup_special(sn, t + 1);
     } else {
-      if (k3) fire_k(t + 3);
-      rotate_plans();
+      if constexpr (BUFS == 2) {
+        if (k3) fire_k(t + 3);
+        rotate_plans();
+      }
       if (has_next && ((spec_ring >> ((t + 1) & 7)) & 1u)) fixup_special(sn, t + 1);
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -670,7 +704,8 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (!DESC && k4) plan_end(t + 4);
+    if (!DESC && k4) plan_end(t + 2 + BUFS);
+    if constexpr (BUFS == 1 && NW == 1) fire_v(t + 1);
     if (has_next) shift_cur = advance_max(rawmax, DESC ? (float)(meta_next & 15u) : (float)((lvl_ring >> (4 * ((t + 1) & 7))) & 15u));
   };
 
@@ -701,6 +736,10 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
       fire_desc(d1, kst, true, 1);
       meta_next = d0[0] & 31u;
       dV = d1;                               // step 0 sends the V rows of tile 1
+    } else if constexpr (BUFS == 1) {
+      plan_whole(0);
+      fire_k(0);
+      rotate_plans();                          // V2 = plan 0
     } else {
       plan_whole(0);
       fire_k(0);
@@ -737,6 +776,12 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
     wg_barrier();                            // every wavefront has read K(0): its buffer takes K(2)
     if constexpr (DESC) {
       fire_desc(d2, kst, true, 2);
+    } else if constexpr (BUFS == 1) {
+      plan_whole(1);
+      fire_k(1);
+      rotate_plans();                          // V1 = plan 0, V2 = plan 1
+      if (NW == 1) fire_v(0);
+      plan_whole(2);
     } else {
       fire_k(2);
       plan_whole(3);
@@ -779,11 +824,11 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   }
 }
 
-size_t attn_mfma_smem_bytes(int d, int nk, int bn) {
-  return 4 * (size_t)bn * d * sizeof(bf16_t) + 4 * 512 + (((size_t)nk * 2 + 15) & ~(size_t)15);
+size_t attn_mfma_smem_bytes(int d, int nk, int bn, int bufs, int nw) {
+  return 2 * bufs * (size_t)bn * d * sizeof(bf16_t) + nw * 512 + (((size_t)nk * 2 + 15) & ~(size_t)15);
 }
 
-template <int D, int NW, bool SC, int BN>
+template <int D, int NW, bool SC, int BN, int BUFS>
 static hipError_t launch_mfma_t(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp,
                                 const void* Vp, const uint16_t* idx, const int32_t* cnt, const uint32_t* desc, void* O,
                                 float* lse, hipStream_t s) {
@@ -798,13 +843,14 @@ static hipError_t launch_mfma_t(const Plan& pl, const void* Q, const void* K, co
   a.scale_log2 = pl.scale * 1.44269504088896340736f;
   a.desc_pitch = pl.desc_pitch;
   for (int h = 0; h < PSA_MAX_LEVELS + 2; ++h) a.lvl_off[h] = pl.lvl_off[h];
-  const size_t smem = attn_mfma_smem_bytes(D, pl.nk, BN);
-  auto kern = attn_mfma_kernel<D, NW, SC, BN>;
+  const size_t smem = attn_mfma_smem_bytes(D, pl.nk, BN, BUFS, NW);
+  auto kern = attn_mfma_kernel<D, NW, SC, BN, BUFS>;
   static LdsOptIn optin;                       // one per kernel instantiation
   const hipError_t e = allow_max_lds(reinterpret_cast<const void*>(kern), &optin);
   if (e != hipSuccess) return e;
-  const unsigned grid = pl.causal ? 8u * (unsigned)xcd_slots(a.heads, pl.nq * a.slices)
-                                 : (unsigned)(pl.B * pl.Hq) * 8u * (unsigned)((pl.nq * a.slices + 7) / 8);
+  const int per_head = pl.nq * a.slices;
+  a.runs = NW < 4 || dq_runs(per_head);
+  const unsigned grid = 8u * (unsigned)(pl.causal ? xcd_slots(a.heads, per_head) : a.runs ? (a.heads * per_head + 7) / 8 : a.heads * ((per_head + 7) / 8));
   kern<<<grid, NW * 64, smem, s>>>(
       static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),
       static_cast<const bf16_t*>(Kp), static_cast<const bf16_t*>(Vp), idx, cnt, desc, static_cast<bf16_t*>(O), lse, a);
@@ -830,14 +876,35 @@ static hipError_t launch_mfma_d(const Plan& pl, const void* Q, const void* K, co
   // in one wavefront, whose load plans of 64 rows do not fit its registers (x 8000 119 / 61).
   constexpr bool WIDE = NW == 4 || !(D == 128 && NW == 1);
   const int64_t wgs = (int64_t)pl.B * pl.Hq * pl.nq * ((pl.bq + NW * 32 - 1) / (NW * 32));
-  const int64_t resident = 256 * (int64_t)(LDS_LIMIT / attn_mfma_smem_bytes(D, pl.nk, 64));
+  const int64_t resident = 256 * (int64_t)(LDS_LIMIT / attn_mfma_smem_bytes(D, pl.nk, 64, 2, NW));
   const bool wide = NW == 4 || (wgs <= resident && pl.N >= (NW == 1 ? 6144 : 2 * wgs <= resident ? 3000 : 4096));
-  constexpr int NARROW = NW == 4 ? 64 : 32;
-  if (blocks_cover_a_load)
-    return wide ? launch_mfma_t<D, NW, true, 64>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s)
-                : launch_mfma_t<D, NW, true, NARROW>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s);
-  return wide && WIDE ? launch_mfma_t<D, NW, false, WIDE ? 64 : NARROW>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s)
-                      : launch_mfma_t<D, NW, false, NARROW>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s);
+  // Buffers of a narrow tile (see the kernel): two only for d = 64 in 64-row blocks, where three wavefronts fit a SIMD with two buffers and four with one,
+  // if the rounds of the chip then hold fewer wavefronts.  12 heads, us for two / one: x 6000 68.5 / 69.5, x 9000 124 / 113, x 13000 210 / 218, x 18000
+  // 376 / 366, x 32760 1035 / 1011, pooled blocks of four keys x 8000 89 / 102.
+  const int64_t in_one = 256 * 2 * most_waves(D, 2, true, 32, 1), in_two = 256 * 2 * most_waves(D, 2, true, 32, 2);
+  const bool one_buffer = (wgs + in_one - 1) / in_one * in_one <= (wgs + in_two - 1) / in_two * in_two;
+  auto launch = [&](auto sc, auto bn, auto bufs) {
+    return launch_mfma_t<D, NW, decltype(sc)::value, decltype(bn)::value, decltype(bufs)::value>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s);
+  };
+  const std::integral_constant<int, 64> c64;
+  const std::integral_constant<int, 32> c32;
+  const std::integral_constant<int, 1> c1;
+  const std::integral_constant<int, 2> c2;
+  if constexpr (NW == 4) {
+    return blocks_cover_a_load ? launch(std::true_type{}, c64, c2) : launch(std::false_type{}, c64, c2);
+  } else {
+    auto narrow = [&](auto sc) {
+      if constexpr (D == 64 && NW == 2) {
+        if (!one_buffer) return launch(sc, c32, c2);
+      }
+      return launch(sc, c32, c1);
+    };
+    if (blocks_cover_a_load) return wide ? launch(std::true_type{}, c64, c2) : narrow(std::true_type{});
+    if constexpr (WIDE) {
+      if (wide) return launch(std::false_type{}, c64, c2);
+    }
+    return narrow(std::false_type{});
+  }
 }
 
 hipError_t launch_attn_mfma(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp,

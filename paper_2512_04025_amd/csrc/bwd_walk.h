@@ -26,7 +26,7 @@ constexpr int dkv_chunks(int N, int bq, int nq, int kept, int last) {
   return kept * cpe - (kept > 0 && last == nq - 1 ? cpe - (rows + 31) / 32 : 0);
 }
 
-// Work order of dQ, not causal: workgroup `slot` of XCD `xcd` takes query block `item` of head `head`, or nothing.  All XCDs are on one head at a time, a
+// Work order of dQ (and of the forward, which takes runs for other problems too), not causal: workgroup `slot` of XCD `xcd` takes query block `item` of head `head`, or nothing.  All XCDs are on one head at a time, a
 // contiguous run of its blocks each; with `runs` each XCD takes a contiguous run of all heads' blocks (see launch_bwd_mfma_t).
 constexpr bool dq_runs(int per_head) { return per_head < 32; }
 constexpr int dq_slots(int heads, int per_head) { return dq_runs(per_head) ? (heads * per_head + 7) / 8 : heads * ((per_head + 7) / 8); }
