@@ -244,15 +244,9 @@ int psa_allocate_levels(const psa_params* p, const void* Q, const void* K, const
   if (pl.krep_is_pyramid ? !Kpyr : !K) return PSA_EINVAL;
   if (!importance_uses_mfma(pl) && importance_smem_bytes(pl.sq, pl.nk, pl.d) > LDS_LIMIT) return PSA_EUNSUPPORTED;
   void* qrep = at(scratch, pl.off_qrep);
-  const void* krep;
-  if (launch_representatives(pl, Q, qrep, true, s) != hipSuccess) return PSA_ELAUNCH;
-  if (pl.krep_is_pyramid) {
-    krep = static_cast<const char*>(Kpyr) + (size_t)pl.lvl_off[pl.H] * pl.esize;
-  } else {
-    void* kr = at(scratch, pl.off_krep);
-    if (launch_representatives(pl, K, kr, false, s) != hipSuccess) return PSA_ELAUNCH;
-    krep = kr;
-  }
+  void* kr = pl.krep_is_pyramid ? nullptr : at(scratch, pl.off_krep);
+  if (launch_representatives(pl, Q, qrep, K, kr, s) != hipSuccess) return PSA_ELAUNCH;
+  const void* krep = kr ? kr : static_cast<const char*>(Kpyr) + (size_t)pl.lvl_off[pl.H] * pl.esize;
   float* sdst = scores_out ? scores_out : reinterpret_cast<float*>(at(scratch, pl.off_scores));
   FactoredScores fs;
   fs.bmax = nullptr;

@@ -506,12 +506,12 @@ template <typename T, int TOK>
 __global__ __launch_bounds__(256) void unpool_kernel(const float* __restrict__ dKp, const float* __restrict__ dVp,
                                                      T* __restrict__ dK, T* __restrict__ dV, int heads, int parts, int d,
                                                      BwdArgs a) {
-  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int q4 = d / 4, groups = (a.N + TOK - 1) / TOK;
-  if (gid >= (int64_t)heads * groups * q4) return;
-  const int c4 = (int)(gid % q4);
-  const int t0 = (int)((gid / q4) % groups) * TOK;
-  const int64_t bh = gid / ((int64_t)q4 * groups);
+  // (32-bit arithmetic: a grid has fewer than 2^32 threads)
+  const uint32_t gid = blockIdx.x * 256u + threadIdx.x, q4 = (uint32_t)d / 4u, groups = ((uint32_t)a.N + TOK - 1) / TOK, rest = gid / q4;
+  const int c4 = (int)(gid - rest * q4);
+  const int64_t bh = rest / groups;
+  if (bh >= heads) return;
+  const int t0 = (int)(rest - (uint32_t)bh * groups) * TOK;
   const float* src = blockIdx.y ? dVp : dKp;
   T* dst = blockIdx.y ? dV : dK;
   f32x4 acc[TOK];

@@ -60,7 +60,8 @@ hipError_t launch_level_cap(const Plan& pl, const float* sims, const float* tau_
 // Hilbert-curve token order of a T x Hg x W grid (host) and the row gather / scatter that applies it
 int hilbert_order_host(int T, int Hg, int W, int32_t* perm);
 hipError_t launch_permute(const Plan& pl, int heads, const void* X, const int32_t* perm, bool inverse, void* Y, hipStream_t s);
-hipError_t launch_representatives(const Plan& pl, const void* X, void* R, bool is_query, hipStream_t s);
+// Rk (nullable): also the keys'
+hipError_t launch_representatives(const Plan& pl, const void* Q, void* Rq, const void* K, void* Rk, hipStream_t s);
 // part: per (row, key slice) partial softmax statistics of the matrix-core path (Plan::off_part)
 // bmax: per (representative row, key block) largest logit, kept for max pooling (Plan::off_bmax)
 // factored (nullable out): when the scores can stay in factored form it is filled in, S is NOT written
