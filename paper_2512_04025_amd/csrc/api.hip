@@ -3,6 +3,7 @@
 #include <math.h>
 #include <string.h>
 
+#include "psa_dev.h"
 #include "psa_internal.h"
 
 namespace psa {
@@ -132,6 +133,9 @@ static int plan_allocation(const psa_params* p, Plan* o) {
   }
   return PSA_OK;
 }
+
+static bool few_pairs(const Plan& pl) { return (int64_t)pl.B * pl.Hq * pl.nq * pl.nk <= 40000; }
+bool lists_in_kernel(const Plan& pl, bool descriptors) { return pl.nk <= ROW_LISTS_NK && (!descriptors || pl.desc_pitch == 0 || few_pairs(pl)); }
 
 static inline char* at(void* base, size_t off) { return static_cast<char*>(base) + off; }
 
@@ -272,9 +276,10 @@ int psa_attention_fwd(const psa_params* p, const void* Q, const void* K, const v
   uint16_t* idx = reinterpret_cast<uint16_t*>(at(scratch, pl.off_idx));
   int32_t* cnt = reinterpret_cast<int32_t*>(at(scratch, pl.off_cnt));
   uint32_t* desc = reinterpret_cast<uint32_t*>(at(scratch, pl.off_desc));
-  if (launch_lists(pl, M, idx, cnt, desc, s) != hipSuccess) return PSA_ELAUNCH;
-  const hipError_t e = pl.use_mfma ? launch_attn_mfma(pl, Q, K, V, Kpyr, Vpyr, idx, cnt, desc, O, lse, s)
-                                   : launch_attn_f32(pl, Q, K, V, Kpyr, Vpyr, idx, cnt, O, lse, s);
+  const uint8_t* own = lists_in_kernel(pl, true) ? M : nullptr;
+  if (!own && launch_lists(pl, M, idx, cnt, desc, s) != hipSuccess) return PSA_ELAUNCH;
+  const hipError_t e = pl.use_mfma ? launch_attn_mfma(pl, Q, K, V, Kpyr, Vpyr, own, idx, cnt, desc, O, lse, s)
+                                   : launch_attn_f32(pl, Q, K, V, Kpyr, Vpyr, own, idx, cnt, O, lse, s);
   return e == hipSuccess ? PSA_OK : PSA_ELAUNCH;
 }
 
@@ -284,7 +289,7 @@ int psa_dense_ref(const psa_params* p, const void* Q, const void* K, const void*
   const int rc = make_plan(p, &pl);
   if (rc != PSA_OK) return rc;
   if (!Q || !K || !V || !O) return PSA_EINVAL;
-  const hipError_t e = launch_attn_f32(pl, Q, K, V, nullptr, nullptr, nullptr, nullptr, O, lse,
+  const hipError_t e = launch_attn_f32(pl, Q, K, V, nullptr, nullptr, nullptr, nullptr, nullptr, O, lse,
                                         static_cast<hipStream_t>(stream));
   return e == hipSuccess ? PSA_OK : PSA_ELAUNCH;
 }
@@ -328,7 +333,7 @@ int psa_attention_bwd(const psa_params* p, const void* Q, const void* K, const v
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint16_t* idx = reinterpret_cast<uint16_t*>(at(scratch, l.off_idx));
   int32_t* cnt = reinterpret_cast<int32_t*>(at(scratch, l.off_cnt));
-  if (launch_lists(pl, M, idx, cnt, nullptr, s) != hipSuccess) return PSA_ELAUNCH;
+  if (!lists_in_kernel(pl, false) && launch_lists(pl, M, idx, cnt, nullptr, s) != hipSuccess) return PSA_ELAUNCH;
   const hipError_t e = launch_attn_bwd(pl, Q, K, V, Kpyr, Vpyr, M, idx, cnt, O, lse, dO,
                                        reinterpret_cast<float*>(at(scratch, l.off_D)),
                                        reinterpret_cast<float*>(at(scratch, l.off_dkp)),
@@ -378,9 +383,10 @@ int psa_attention_fwd_static(const psa_params* p, const void* Q, const void* K, 
   uint32_t* desc = reinterpret_cast<uint32_t*>(at(base, off_desc));
   // every word the attention kernel reads is rewritten by the kernel below, so nothing needs
   // clearing between calls (what an earlier, larger call left behind is never read)
-  if (launch_lists(pl, M, idx, cnt, desc, s) != hipSuccess) return PSA_ELAUNCH;
-  const hipError_t e = pl.use_mfma ? launch_attn_mfma(pl, Q, K, V, Kpyr, Vpyr, idx, cnt, desc, O, lse, s)
-                                   : launch_attn_f32(pl, Q, K, V, Kpyr, Vpyr, idx, cnt, O, lse, s);
+  const uint8_t* own = lists_in_kernel(pl, true) ? M : nullptr;
+  if (!own && launch_lists(pl, M, idx, cnt, desc, s) != hipSuccess) return PSA_ELAUNCH;
+  const hipError_t e = pl.use_mfma ? launch_attn_mfma(pl, Q, K, V, Kpyr, Vpyr, own, idx, cnt, desc, O, lse, s)
+                                   : launch_attn_f32(pl, Q, K, V, Kpyr, Vpyr, own, idx, cnt, O, lse, s);
   return e == hipSuccess ? PSA_OK : PSA_ELAUNCH;
 }
 

@@ -68,7 +68,9 @@ struct BwdDqShape {
   static constexpr int KS = 4 / TEAM, ROWS = 32 * TEAM, PITCH = D + 4;
   static constexpr int TILEF = 2 * 32 * PITCH + 64;                    // K | V | bias [32] | last token [32]
   static constexpr int MERGEF = KS * ROWS * PITCH;
-  static constexpr size_t BYTES = sizeof(float) * (KS * TILEF > MERGEF ? KS * TILEF : MERGEF);
+  static constexpr int OFF_LIST = 4 * KS * TILEF;                      // blocks per level | list (rows whose list the kernel makes)
+  static constexpr int END = OFF_LIST + 4 * PSA_MAX_LEVELS + 2 * ROW_LISTS_NK;
+  static constexpr size_t BYTES = END > 4 * MERGEF ? END : 4 * MERGEF;
 };
 
 // dQ.  Operand roles, tiles and teams as in attn_f32_kernel: S^T = K Q^T and dP^T = V dO^T put one query row in
@@ -76,7 +78,7 @@ struct BwdDqShape {
 template <typename T, int D, int TEAM>
 __global__ __launch_bounds__(256, (D == 64 && TEAM > 1 ? 2 : 1))
 void bwd_dq_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ Kp,
-                   const T* __restrict__ Vp, const uint16_t* __restrict__ idx, const int32_t* __restrict__ cnt,
+                   const T* __restrict__ Vp, const uint8_t* __restrict__ M, const uint16_t* __restrict__ idx, const int32_t* __restrict__ cnt,
                    const T* __restrict__ O, const float* __restrict__ lse, float* __restrict__ Dr, const T* __restrict__ dO,
                    T* __restrict__ dQ, BwdArgs a) {
   using S = BwdDqShape<D, TEAM>;
@@ -135,9 +137,15 @@ void bwd_dq_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* __
   const int64_t srow = qhead * a.nq + i;
   const uint16_t* my_idx = idx + srow * a.nk;
   const int32_t* my_cnt = cnt + srow * CNT_STRIDE;
+  int* cnt_s = reinterpret_cast<int*>(reinterpret_cast<unsigned char*>(fsm) + S::OFF_LIST);
+  uint16_t* list_s = reinterpret_cast<uint16_t*>(cnt_s + PSA_MAX_LEVELS);
+  if (M) {                                               // (short rows, see lists_in_kernel)
+    row_lists<4>(M + srow * a.nk, a.nk, a.H, false, list_s, cnt_s, wave, lane);
+    __syncthreads();
+  }
   struct Tile { int h, tl, ntl, nblk, start; bool ok; };
   auto enter = [&](Tile& t) __attribute__((always_inline)) {
-    t.nblk = my_cnt[t.h - 1];
+    t.nblk = M ? __builtin_amdgcn_readfirstlane(cnt_s[t.h - 1]) : my_cnt[t.h - 1];
     t.ntl = ((t.nblk << (a.lg_bk - (t.h - 1))) + 31) >> 5;
   };
   auto settle = [&](Tile& t) __attribute__((always_inline)) {          // carry tl over to the level that holds it
@@ -152,7 +160,7 @@ void bwd_dq_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* __
   auto locate = [&](const Tile& t) __attribute__((always_inline)) -> int {   // pooled row of tile row l32; -1: none
     if (!t.ok) return -1;
     const int lg_th = a.lg_bk - (t.h - 1), g = (t.tl << 5) + l32, e = g >> lg_th;
-    return e < t.nblk ? ((int)my_idx[t.start + e] << lg_th) | (g & ((1 << lg_th) - 1)) : -1;
+    return e < t.nblk ? ((M ? (int)list_s[t.start + e] : (int)my_idx[t.start + e]) << lg_th) | (g & ((1 << lg_th) - 1)) : -1;
   };
   typename Four<T>::raw kreg[NCH], vreg[NCH];
   auto fetch = [&](const Tile& t, int prow) __attribute__((always_inline)) {
@@ -566,14 +574,14 @@ size_t bwd_pooled_grad_elems(const Plan& pl) {      // one tensor: levels 1..H, 
 
 template <typename T, int D, int TEAM>
 static hipError_t launch_dq_t(const Plan& pl, const BwdArgs& a, const T* q, const T* k, const T* v, const T* kp, const T* vp,
-                              const uint16_t* idx, const int32_t* cnt, const T* o, const float* lse, float* Dr, const T* go,
+                              const uint8_t* M, const uint16_t* idx, const int32_t* cnt, const T* o, const float* lse, float* Dr, const T* go,
                               T* dq, hipStream_t s) {
   using S = BwdDqShape<D, TEAM>;
   auto kern = bwd_dq_kernel<T, D, TEAM>;
   static LdsOptIn optin;
   const hipError_t e = allow_max_lds(reinterpret_cast<const void*>(kern), &optin);
   if (e != hipSuccess) return e;
-  kern<<<dim3(pl.nq * ((pl.bq + S::ROWS - 1) / S::ROWS), pl.Hq, pl.B), 256, S::BYTES, s>>>(q, k, v, kp, vp, idx, cnt, o, lse, Dr, go, dq, a);
+  kern<<<dim3(pl.nq * ((pl.bq + S::ROWS - 1) / S::ROWS), pl.Hq, pl.B), 256, S::BYTES, s>>>(q, k, v, kp, vp, M, idx, cnt, o, lse, Dr, go, dq, a);
   return hipGetLastError();
 }
 
@@ -615,9 +623,10 @@ static hipError_t launch_bwd_t(const Plan& pl, const void* Q, const void* K, con
     auto groups = [&](int rows_wg) { return blocks * ((pl.bq + rows_wg - 1) / rows_wg); };
     const int team = pl.bq > 64 && groups(128) >= 256 ? 4 : (pl.bq > 32 && groups(64) >= 192 ? 2 : 1);
     T* dq = static_cast<T*>(dQ);
-    e = team == 4 ? launch_dq_t<T, D, 4>(pl, a, q, k, v, kp, vp, idx, cnt, o, lse, Dr, go, dq, s)
-      : team == 2 ? launch_dq_t<T, D, 2>(pl, a, q, k, v, kp, vp, idx, cnt, o, lse, Dr, go, dq, s)
-                  : launch_dq_t<T, D, 1>(pl, a, q, k, v, kp, vp, idx, cnt, o, lse, Dr, go, dq, s);
+    const uint8_t* own = lists_in_kernel(pl, false) ? M : nullptr;
+    e = team == 4 ? launch_dq_t<T, D, 4>(pl, a, q, k, v, kp, vp, own, idx, cnt, o, lse, Dr, go, dq, s)
+      : team == 2 ? launch_dq_t<T, D, 2>(pl, a, q, k, v, kp, vp, own, idx, cnt, o, lse, Dr, go, dq, s)
+                  : launch_dq_t<T, D, 1>(pl, a, q, k, v, kp, vp, own, idx, cnt, o, lse, Dr, go, dq, s);
     if (e != hipSuccess) return e;
     static LdsOptIn optin;
     e = allow_max_lds(reinterpret_cast<const void*>(bwd_dkv_kernel<T, D>), &optin);

@@ -98,15 +98,16 @@ template <int D> __host__ __device__ constexpr int row_swizzle(int row) {
 template <int D>
 __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                                              const bf16_t* __restrict__ V, const bf16_t* __restrict__ Kp,
-                                                             const bf16_t* __restrict__ Vp, const uint16_t* __restrict__ idx,
+                                                             const bf16_t* __restrict__ Vp, const uint8_t* __restrict__ M,
+                                                             const uint16_t* __restrict__ idx,
                                                              const int32_t* __restrict__ cnt, const bf16_t* __restrict__ O,
                                                              const float* __restrict__ lse, float* __restrict__ Dr,
                                                              const bf16_t* __restrict__ dO, bf16_t* __restrict__ dQ, BwdMfmaArgs a) {
   constexpr int ROWB = D * 2, TILEB = 64 * ROWB, BUFB = 2 * TILEB, CPR = D / 8, RPI = 64 / CPR, NI = 16 / RPI, KS = D / 16, MD = D / 32;
   // two buffers (Kbar rows [64][ROWB] | Vbar rows [64][ROWB]), a table per wavefront for irregular tiles (term [64] | last token [64])
-  constexpr int OFF_FIX = 2 * BUFB, OFF_CNT = OFF_FIX + 4 * 512;   // and the row's blocks per level
+  constexpr int OFF_FIX = 2 * BUFB, OFF_CNT = OFF_FIX + 4 * 512, OFF_LIST = OFF_CNT + 4 * PSA_MAX_LEVELS;   // and the row's blocks per level, a short row's list
   // The kernel's only LDS object: the addresses in the assembly are offsets into it, so it has to start at LDS address 0.
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[OFF_CNT + 4 * PSA_MAX_LEVELS];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[OFF_LIST + 2 * ROW_LISTS_NK];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slices = (a.bq + 127) / 128, per_head = a.nq * slices;
@@ -172,7 +173,9 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_mfma_kernel(const
   const uint16_t* my_idx = idx + srow * a.nk;
   // (in LDS: read from memory at a change of level it would wait for the rows that are under way)
   int* my_cnt = reinterpret_cast<int*>(smem + OFF_CNT);
-  if (tid < a.H) my_cnt[tid] = cnt[srow * CNT_STRIDE + tid];
+  uint16_t* list_s = reinterpret_cast<uint16_t*>(smem + OFF_LIST);
+  if (M) row_lists<4>(M + srow * a.nk, a.nk, a.H, false, list_s, my_cnt, wave, lane);   // (short rows, see lists_in_kernel)
+  else if (tid < a.H) my_cnt[tid] = cnt[srow * CNT_STRIDE + tid];
   __syncthreads();
 
   // ---- the tiles of 64 pooled keys, level after level down the row's list
@@ -198,7 +201,8 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_mfma_kernel(const
   // the block that tile row `lane` is of (rows past the level's last block: that block)
   auto block_of = [&](const Tile& t) __attribute__((always_inline)) -> int {
     const int e = ((t.tl << 6) + lane) >> (a.lg_bk - (t.h - 1));
-    return (int)my_idx[t.start + (e < t.nblk ? e : t.nblk - 1)];
+    const int at = t.start + (e < t.nblk ? e : t.nblk - 1);
+    return M ? (int)list_s[at] : (int)my_idx[at];
   };
   // its row in the level's array, from the block's id
   auto row_of = [&](const Tile& t, int block) __attribute__((always_inline)) -> int {
@@ -952,7 +956,7 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
   a.dq_runs = dq_runs(dq_items);
   const int dq_slot_count = pl.causal ? xcd_slots(heads, dq_items) : dq_slots(heads, dq_items);
   const unsigned dq_grid = 8u * (unsigned)dq_slot_count;
-  bwd_dq_mfma_kernel<D><<<dq_grid, 256, 0, s>>>(q, k, v, kp, vp, idx, cnt, static_cast<const bf16_t*>(O), lse, Dr, go, static_cast<bf16_t*>(dQ), a);
+  bwd_dq_mfma_kernel<D><<<dq_grid, 256, 0, s>>>(q, k, v, kp, vp, lists_in_kernel(pl, false) ? M : nullptr, idx, cnt, static_cast<const bf16_t*>(O), lse, Dr, go, static_cast<bf16_t*>(dQ), a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   auto groups = [&](int small_keys) {            // workgroups of an XCD, as the kernel counts them

@@ -51,7 +51,9 @@ struct F32Shape {
   static constexpr int TILEB = OFF_TAB + TEAM * 256;                   // K | V | (term [32] | last token [32]) per wavefront
   static constexpr int MERGEB = 4 * (2 * KS * ROWS + KS * ROWS * PITCH);   // m, l | O of every team
   static constexpr int OFF_FLAG = KS * TILEB;                          // behind the teams' tiles: one flag per wavefront
-  static constexpr size_t BYTES = OFF_FLAG + 16 > MERGEB ? OFF_FLAG + 16 : MERGEB;
+  static constexpr int OFF_LIST = OFF_FLAG + 16;                       // blocks per level | list (rows whose list the kernel makes)
+  static constexpr int END = OFF_LIST + 4 * PSA_MAX_LEVELS + 2 * ROW_LISTS_NK;
+  static constexpr size_t BYTES = END > MERGEB ? END : MERGEB;
 };
 
 // Four consecutive elements as their planes: put(plane, its four bfloat16).  NaN comes back if one is not finite (0 times its remainder otherwise).
@@ -79,7 +81,7 @@ typedef __attribute__((address_space(3))) f32_s16x4 f32_lds_s16x4;
 template <typename T, int D, int TEAM>
 __global__ __launch_bounds__(256, (F32Shape<T, D, TEAM>::BYTES <= 80 * 1024 ? 2 : 1))
 void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ Kp,
-                     const T* __restrict__ Vp, const uint16_t* __restrict__ idx, const int32_t* __restrict__ cnt,
+                     const T* __restrict__ Vp, const uint8_t* __restrict__ M, const uint16_t* __restrict__ idx, const int32_t* __restrict__ cnt,
                      T* __restrict__ O, float* __restrict__ lse, F32Args a) {
   using S = F32Shape<T, D, TEAM>;
   constexpr int KS = S::KS, ROWS = S::ROWS, PITCH = S::PITCH, NPL = S::NPL, ROWB = S::ROWB, PLANEB = S::PLANEB, CPR = D / 4, MD = D / 32, KSTEPS = D / 16;
@@ -94,7 +96,9 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
   int* last_s = reinterpret_cast<int*>(term_s + 32);
   int* flag_s = reinterpret_cast<int*>(fsm + S::OFF_FLAG);               // did the wavefront meet a value that is not finite
 
-  const bool dense = idx == nullptr;
+  const bool own_list = M != nullptr, dense = !own_list && idx == nullptr;
+  int* cnt_s = reinterpret_cast<int*>(fsm + S::OFF_LIST);
+  uint16_t* list_s = reinterpret_cast<uint16_t*>(cnt_s + PSA_MAX_LEVELS);
   const int slice = blockIdx.x % a.slices;
   int i = blockIdx.x / a.slices;
   if (a.causal) i = a.nq - 1 - i;                        // longest rows first
@@ -131,8 +135,12 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
   float m = -INFINITY, l = 0.f;                          // reference of the weights (log2, a whole number), sum of the weights
 
   const int64_t srow = qhead * a.nq + i;
-  const uint16_t* my_idx = dense ? nullptr : idx + srow * a.nk;
-  const int32_t* my_cnt = dense ? nullptr : cnt + srow * CNT_STRIDE;
+  const uint16_t* my_idx = idx + srow * a.nk;
+  const int32_t* my_cnt = cnt + srow * CNT_STRIDE;
+  if (own_list) {
+    row_lists<4>(M + srow * a.nk, a.nk, a.H, false, list_s, cnt_s, wave, lane);
+    __syncthreads();
+  }
   const int H = dense ? 1 : a.H;
   int dense_blocks = a.nk;                               // dense and causal: blocks that start at or before the last row
   if (a.causal) dense_blocks = (row_end - 1) / a.bk + 1;
@@ -140,7 +148,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
   // The pooled tokens of a level's kept blocks, in list order, are one stream that is cut into tiles of 32.
   struct Tile { int h, tl, ntl, nblk, start, ok; };      // (no padding: its bytes were copied through memory)
   auto enter = [&](Tile& t) __attribute__((always_inline)) {
-    t.nblk = dense ? dense_blocks : my_cnt[t.h - 1];
+    t.nblk = dense ? dense_blocks : own_list ? __builtin_amdgcn_readfirstlane(cnt_s[t.h - 1]) : my_cnt[t.h - 1];
     t.ntl = (int)((((int64_t)t.nblk << (a.lg_bk - (t.h - 1))) + 31) >> 5);
   };
   auto settle = [&](Tile& t) __attribute__((always_inline)) {   // carry tl over to the level that holds it
@@ -155,7 +163,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
   // The block of tile row l32 (past the level's last block: that block) is requested a step before its row is worked out.
   auto block_of = [&](const Tile& t) __attribute__((always_inline)) -> int {
     const int e = ((t.tl << 5) + l32) >> (a.lg_bk - (t.h - 1)), f = e < t.nblk ? e : t.nblk - 1;
-    return dense ? f : (int)my_idx[t.start + f];
+    return dense ? f : own_list ? (int)list_s[t.start + f] : (int)my_idx[t.start + f];
   };
   auto row_of = [&](const Tile& t, int block) __attribute__((always_inline)) -> int {   // pooled row of tile row l32; -1: none
     const int lg_th = a.lg_bk - (t.h - 1), g = (t.tl << 5) + l32, pr = (block << lg_th) | (g & ((1 << lg_th) - 1));
@@ -490,7 +498,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
 
 template <typename T, int D, int TEAM>
 static hipError_t launch_f32_t(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp, const void* Vp,
-                               const uint16_t* idx, const int32_t* cnt, void* O, float* lse, hipStream_t s) {
+                               const uint8_t* M, const uint16_t* idx, const int32_t* cnt, void* O, float* lse, hipStream_t s) {
   using S = F32Shape<T, D, TEAM>;
   F32Args a;
   a.N = pl.N; a.Hq = pl.Hq; a.Hkv = pl.Hkv; a.nq = pl.nq; a.nk = pl.nk; a.bq = pl.bq; a.bk = pl.bk;
@@ -509,13 +517,13 @@ static hipError_t launch_f32_t(const Plan& pl, const void* Q, const void* K, con
   if (e != hipSuccess) return e;
   kern<<<dim3(pl.nq * a.slices, pl.Hq, pl.B), 256, S::BYTES, s>>>(
       static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V), static_cast<const T*>(Kp),
-      static_cast<const T*>(Vp), idx, cnt, static_cast<T*>(O), lse, a);
+      static_cast<const T*>(Vp), M, idx, cnt, static_cast<T*>(O), lse, a);
   return hipGetLastError();
 }
 
 template <typename T, int D>
 static hipError_t launch_f32_d(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp, const void* Vp,
-                               const uint16_t* idx, const int32_t* cnt, void* O, float* lse, hipStream_t s) {
+                               const uint8_t* M, const uint16_t* idx, const int32_t* cnt, void* O, float* lse, hipStream_t s) {
   // The largest team that still fills the chip: fewer rows per team cost more reads (and conversions) of the same keys, fewer
   // workgroups leave compute units idle.  Measured with 12 heads at d = 128 (128-row blocks of the problem: us for team 1 / 2 / 4, pyramid and
   // block lists included): 48: 25 / 31 / 33, 96: 55 / 38 / 45, 192: 106 / 93 / 80, 252: 183 / 127 / 107, 288: 225 / 190 / 151, 432: 415 / 328 / 240,
@@ -524,18 +532,18 @@ static hipError_t launch_f32_d(const Plan& pl, const void* Q, const void* K, con
   const int64_t blocks = (int64_t)pl.B * pl.Hq * pl.nq;
   auto groups = [&](int rows) { return blocks * ((pl.bq + rows - 1) / rows); };
   const int team = pl.bq > 64 && groups(128) >= (D == 128 ? 150 : 256) ? 4 : (pl.bq > 32 && groups(64) >= 192 ? 2 : 1);
-  if (team == 4) return launch_f32_t<T, D, 4>(pl, Q, K, V, Kp, Vp, idx, cnt, O, lse, s);
-  if (team == 2) return launch_f32_t<T, D, 2>(pl, Q, K, V, Kp, Vp, idx, cnt, O, lse, s);
-  return launch_f32_t<T, D, 1>(pl, Q, K, V, Kp, Vp, idx, cnt, O, lse, s);
+  if (team == 4) return launch_f32_t<T, D, 4>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, s);
+  if (team == 2) return launch_f32_t<T, D, 2>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, s);
+  return launch_f32_t<T, D, 1>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, s);
 }
 
 hipError_t launch_attn_f32(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp, const void* Vp,
-                           const uint16_t* idx, const int32_t* cnt, void* O, float* lse, hipStream_t s) {
+                           const uint8_t* M, const uint16_t* idx, const int32_t* cnt, void* O, float* lse, hipStream_t s) {
   if (pl.dtype == PSA_F32)
-    return pl.d == 64 ? launch_f32_d<float, 64>(pl, Q, K, V, Kp, Vp, idx, cnt, O, lse, s)
-                      : launch_f32_d<float, 128>(pl, Q, K, V, Kp, Vp, idx, cnt, O, lse, s);
-  return pl.d == 64 ? launch_f32_d<bf16_t, 64>(pl, Q, K, V, Kp, Vp, idx, cnt, O, lse, s)
-                    : launch_f32_d<bf16_t, 128>(pl, Q, K, V, Kp, Vp, idx, cnt, O, lse, s);
+    return pl.d == 64 ? launch_f32_d<float, 64>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, s)
+                      : launch_f32_d<float, 128>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, s);
+  return pl.d == 64 ? launch_f32_d<bf16_t, 64>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, s)
+                    : launch_f32_d<bf16_t, 128>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, s);
 }
 
 }  // namespace psa

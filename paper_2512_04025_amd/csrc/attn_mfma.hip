@@ -93,7 +93,7 @@ template <int D, int NW, bool SC, int BN, int BUFS>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu((least_waves(D, NW, SC, BN, BUFS)), most_waves(D, NW, SC, BN, BUFS))))
 void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
                       const bf16_t* __restrict__ Kp, const bf16_t* __restrict__ Vp,
-                      const uint16_t* __restrict__ idx, const int32_t* __restrict__ cnt,
+                      const uint8_t* __restrict__ M, const uint16_t* __restrict__ idx, const int32_t* __restrict__ cnt,
                       const uint32_t* __restrict__ desc, bf16_t* __restrict__ O, float* __restrict__ lse, MfmaArgs a) {
   constexpr int NT = NW * 64;
   constexpr int ROWS = NW * 32;              // query rows per workgroup
@@ -118,9 +118,9 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   static_assert(BN == 64 || (BN == 32 && NW < 4), "tile width");
   static_assert(NINST % NW == 0, "tile rows must split evenly over the wavefronts");
   static_assert(MPC * NB == NPAIR, "chunking of the softmax work");
-  // LDS map: K[2] | V[2] | per-wavefront table for irregular tiles | block list
+  // LDS map: K[2] | V[2] | per-wavefront table for irregular tiles | blocks per level | block list
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  constexpr int OFF_K = 0, OFF_V = BUFS * TILEB, OFF_FIX = 2 * BUFS * TILEB, OFF_LIST = OFF_FIX + NW * 512;
+  constexpr int OFF_K = 0, OFF_V = BUFS * TILEB, OFF_FIX = 2 * BUFS * TILEB, OFF_CNT = OFF_FIX + NW * 512, OFF_LIST = OFF_CNT + 4 * PSA_MAX_LEVELS;
   uint16_t* list = reinterpret_cast<uint16_t*>(smem + OFF_LIST);    // kept block ids, level-major
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -160,11 +160,19 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   const int64_t srow = qhead * a.nq + i;
   const uint16_t* my_idx = idx + srow * a.nk;
   const int32_t* my_cnt = cnt + srow * CNT_STRIDE;
+  const bool back = BACK && !a.causal && (((int)(blockIdx.x >> 3) / GENERATION) & 1);
 
-  // ---- totals and the block list into LDS
+  // ---- totals and the block list into LDS.  With a level map the workgroup makes the list itself (short rows, see lists_in_kernel).
+  int* cnt_s = reinterpret_cast<int*>(smem + OFF_CNT);
+  const bool own_list = !DESC && M;
+  if (own_list) {
+    row_lists<NW>(M + srow * a.nk, a.nk, a.H, back, list, cnt_s, wave, lane);
+    __syncthreads();
+  }
+  auto kept = [&](int h) __attribute__((always_inline)) -> int { return own_list ? __builtin_amdgcn_readfirstlane(cnt_s[h - 1]) : my_cnt[h - 1]; };
   int total_blocks = 0, total_tiles = 0;
   for (int h = 1; h <= a.H; ++h) {
-    const int nb = my_cnt[h - 1];
+    const int nb = kept(h);
     const int lg_th = a.lg_bk - (h - 1);
     total_blocks += nb;
     total_tiles += ((nb << lg_th) + BN - 1) >> LG_BN;
@@ -172,14 +180,14 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   // Where the rows in flight on an XCD outgrow its L2 (d = 128, 32-row blocks, not causal) every second generation of workgroups walks its lists backwards:
   // a workgroup that follows one which has just reached the end of the sequence begins where that one's neighbours still are.  12 heads x 24000 tokens
   // 1260 -> 1215 us, x 32760 2430 -> 2260, 4 x 30000 730 -> 638; no change at 18000, none at d = 64 or with 64-row blocks.
-  if (BACK && !a.causal && (((int)(blockIdx.x >> 3) / GENERATION) & 1)) {
+  if (back && !own_list) {
     int first = 0;
     for (int h = 1; h <= a.H; ++h) {
       const int nb = my_cnt[h - 1];
       for (int x = tid; x < nb; x += NT) list[first + x] = my_idx[first + nb - 1 - x];
       first += nb;
     }
-  } else {
+  } else if (!own_list) {
     for (int x = tid; x < total_blocks; x += NT) list[x] = my_idx[x];
   }
   {  // tile buffers start as zeros (a lane whose source row is out of range was seen to store zeros, but
@@ -197,7 +205,7 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
       return;
     }
     ls.lg_th = a.lg_bk - (h - 1);
-    ls.nblk = my_cnt[h - 1];
+    ls.nblk = kept(h);
     ls.ntl = ((ls.nblk << ls.lg_th) + BN - 1) >> LG_BN;
     int lim = a.N >> (h - 1);                                  // rows below cover 2^(h-1) valid tokens
     if (a.causal) {
@@ -501,7 +509,7 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   auto fixup_special = [&](f32x16 (&sc)[HALVES], int t) __attribute__((always_inline)) {
     int h = 1, start = 0, tl = t, nb = 0, lg_th = a.lg_bk;
     for (;; ++h) {
-      nb = my_cnt[h - 1];
+      nb = kept(h);
       lg_th = a.lg_bk - (h - 1);
       const int ntl = ((nb << lg_th) + BN - 1) >> LG_BN;
       if (tl < ntl || h == a.H) break;
@@ -825,12 +833,12 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
 }
 
 size_t attn_mfma_smem_bytes(int d, int nk, int bn, int bufs, int nw) {
-  return 2 * bufs * (size_t)bn * d * sizeof(bf16_t) + nw * 512 + (((size_t)nk * 2 + 15) & ~(size_t)15);
+  return 2 * bufs * (size_t)bn * d * sizeof(bf16_t) + nw * 512 + 4 * PSA_MAX_LEVELS + (((size_t)nk * 2 + 15) & ~(size_t)15);
 }
 
 template <int D, int NW, bool SC, int BN, int BUFS>
 static hipError_t launch_mfma_t(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp,
-                                const void* Vp, const uint16_t* idx, const int32_t* cnt, const uint32_t* desc, void* O,
+                                const void* Vp, const uint8_t* M, const uint16_t* idx, const int32_t* cnt, const uint32_t* desc, void* O,
                                 float* lse, hipStream_t s) {
   MfmaArgs a;
   a.N = pl.N; a.Hq = pl.Hq; a.Hkv = pl.Hkv; a.nq = pl.nq; a.nk = pl.nk; a.bq = pl.bq; a.bk = pl.bk;
@@ -853,17 +861,17 @@ static hipError_t launch_mfma_t(const Plan& pl, const void* Q, const void* K, co
   const unsigned grid = 8u * (unsigned)(pl.causal ? xcd_slots(a.heads, per_head) : a.runs ? (a.heads * per_head + 7) / 8 : a.heads * ((per_head + 7) / 8));
   kern<<<grid, NW * 64, smem, s>>>(
       static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),
-      static_cast<const bf16_t*>(Kp), static_cast<const bf16_t*>(Vp), idx, cnt, desc, static_cast<bf16_t*>(O), lse, a);
+      static_cast<const bf16_t*>(Kp), static_cast<const bf16_t*>(Vp), M, idx, cnt, desc, static_cast<bf16_t*>(O), lse, a);
   return hipGetLastError();
 }
 
 template <int D, int NW>
 static hipError_t launch_mfma_d(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp,
-                                const void* Vp, const uint16_t* idx, const int32_t* cnt, const uint32_t* desc, void* O,
+                                const void* Vp, const uint8_t* M, const uint16_t* idx, const int32_t* cnt, const uint32_t* desc, void* O,
                                 float* lse, hipStream_t s) {
   constexpr int RPI = 64 / (D / 8);           // tile rows per wave-wide 16 B/lane load
   // (the scalar-plan variant of full workgroups reads tile descriptors; without them take the general one)
-  const bool blocks_cover_a_load = (pl.bk >> (pl.H - 1)) >= RPI && (NW != 4 || pl.desc_pitch > 0);
+  const bool blocks_cover_a_load = (pl.bk >> (pl.H - 1)) >= RPI && (NW != 4 || (pl.desc_pitch > 0 && !M));
   // Key columns per tile.  64 for workgroups of four wavefronts.  The tiles of smaller workgroups serve fewer rows, and of 32
   // columns twice as many workgroups fit the LDS of a compute unit (d = 128: four instead of two; d = 64: eight instead of four):
   // what counts once the chip is full.  While all workgroups are resident at once either way, twice the tiles are only twice
@@ -884,7 +892,7 @@ static hipError_t launch_mfma_d(const Plan& pl, const void* Q, const void* K, co
   const int64_t in_one = 256 * 2 * most_waves(D, 2, true, 32, 1), in_two = 256 * 2 * most_waves(D, 2, true, 32, 2);
   const bool one_buffer = (wgs + in_one - 1) / in_one * in_one <= (wgs + in_two - 1) / in_two * in_two;
   auto launch = [&](auto sc, auto bn, auto bufs) {
-    return launch_mfma_t<D, NW, decltype(sc)::value, decltype(bn)::value, decltype(bufs)::value>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s);
+    return launch_mfma_t<D, NW, decltype(sc)::value, decltype(bn)::value, decltype(bufs)::value>(pl, Q, K, V, Kp, Vp, M, idx, cnt, desc, O, lse, s);
   };
   const std::integral_constant<int, 64> c64;
   const std::integral_constant<int, 32> c32;
@@ -908,20 +916,20 @@ static hipError_t launch_mfma_d(const Plan& pl, const void* Q, const void* K, co
 }
 
 hipError_t launch_attn_mfma(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp,
-                            const void* Vp, const uint16_t* idx, const int32_t* cnt, const uint32_t* desc, void* O,
+                            const void* Vp, const uint8_t* M, const uint16_t* idx, const int32_t* cnt, const uint32_t* desc, void* O,
                             float* lse, hipStream_t s) {
   const int rows = pl.bq < 128 ? pl.bq : 128;   // rows per workgroup
   if (pl.d == 128) {
     switch (rows) {
-      case 32: return launch_mfma_d<128, 1>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s);
-      case 64: return launch_mfma_d<128, 2>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s);
-      case 128: return launch_mfma_d<128, 4>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s);
+      case 32: return launch_mfma_d<128, 1>(pl, Q, K, V, Kp, Vp, M, idx, cnt, desc, O, lse, s);
+      case 64: return launch_mfma_d<128, 2>(pl, Q, K, V, Kp, Vp, M, idx, cnt, desc, O, lse, s);
+      case 128: return launch_mfma_d<128, 4>(pl, Q, K, V, Kp, Vp, M, idx, cnt, desc, O, lse, s);
     }
   } else if (pl.d == 64) {
     switch (rows) {
-      case 32: return launch_mfma_d<64, 1>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s);
-      case 64: return launch_mfma_d<64, 2>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s);
-      case 128: return launch_mfma_d<64, 4>(pl, Q, K, V, Kp, Vp, idx, cnt, desc, O, lse, s);
+      case 32: return launch_mfma_d<64, 1>(pl, Q, K, V, Kp, Vp, M, idx, cnt, desc, O, lse, s);
+      case 64: return launch_mfma_d<64, 2>(pl, Q, K, V, Kp, Vp, M, idx, cnt, desc, O, lse, s);
+      case 128: return launch_mfma_d<64, 4>(pl, Q, K, V, Kp, Vp, M, idx, cnt, desc, O, lse, s);
     }
   }
   return hipErrorInvalidValue;

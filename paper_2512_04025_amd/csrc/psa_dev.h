@@ -147,6 +147,34 @@ __device__ __forceinline__ Split2 split2(float a, float b, float& rest) {
 
 __device__ __forceinline__ int ilog2(int x) { return 31 - __clz(x); }
 
+// A row of the level map -> its kept blocks grouped by level (ascending inside a level, descending with `back`) and the number per level, in LDS, by
+// the NW wavefronts of a workgroup (which then wait for each other).  Rows of at most ROW_LISTS_NK blocks.
+constexpr int ROW_LISTS_NK = 128;
+template <int NW>
+__device__ __forceinline__ void row_lists(const uint8_t* __restrict__ m, int nk, int H, bool back, uint16_t* list, int* cnt, int wave, int lane) {
+  int lv[ROW_LISTS_NK / 64];
+#pragma unroll
+  for (int c = 0; c < ROW_LISTS_NK / 64; ++c) lv[c] = c * 64 + lane < nk ? (int)m[c * 64 + lane] : 0;
+  const uint64_t below = (1ull << lane) - 1ull;
+  int first = 0;
+  for (int h = 1; h <= H; ++h) {
+    int before[ROW_LISTS_NK / 64], n = 0;
+#pragma unroll
+    for (int c = 0; c < ROW_LISTS_NK / 64; ++c) {
+      const uint64_t mask = __ballot(lv[c] == h);
+      before[c] = n + __popcll(mask & below);
+      n += __popcll(mask);
+    }
+    if (NW == 1 || h % NW == wave) {
+#pragma unroll
+      for (int c = 0; c < ROW_LISTS_NK / 64; ++c)
+        if (lv[c] == h) list[first + (back ? n - 1 - before[c] : before[c])] = (uint16_t)(c * 64 + lane);
+      if (lane == 0) cnt[h - 1] = n;
+    }
+    first += n;
+  }
+}
+
 // Causal work on the 8 XCDs, whose rows (or columns) differ in length by up to the whole sequence: every XCD takes as many whole heads as
 // all can have, one after the other, and of the heads that are left every eighth item.  (Contiguous runs gave one XCD the long half
 // of a shared head and its neighbour the short one.)

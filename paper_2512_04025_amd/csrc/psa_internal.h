@@ -78,12 +78,18 @@ hipError_t launch_rho(const Plan& pl, const uint32_t* rowcnt, float* rho, hipStr
 // Per query block its level-sorted block list and level counts and, unless desc is null or Plan::desc_pitch is 0, per
 // 64-column tile of that list the source-row offsets of the tile's load instructions, level and irregularity (Plan::off_desc)
 hipError_t launch_lists(const Plan& pl, const uint8_t* M, uint16_t* idx, int32_t* cnt, uint32_t* desc, hipStream_t s);
-// idx == nullptr selects dense attention (every key block at level 1)
+// Whether the kernels that walk a row's list make it from the level map themselves (M given, idx and cnt unused) instead of reading what
+// launch_lists has made (M null): short rows, for which a launch of 4 us counts.  descriptors: the caller would get tile descriptors with the lists
+// (the forward's 128-row workgroups), which save 3 to 7 % of the attention: there only up to 40000 block pairs.  Whole call, us with a launch /
+// without: 12 heads x 1000 tokens 44.0 / 42.0, x 4000 56.2 / 53.6 (24000 pairs), x 8000 138 / 141 (94000), 28 causal x 8000 187 / 200; f32 2 x 1024 45.6 / 44.0;
+// 32-row blocks 12 x 4000 58.5 / 52.2; gradients 8 x 745 49.7 / 47.2.
+bool lists_in_kernel(const Plan& pl, bool descriptors);
+// M and idx both null: dense attention (every key block at level 1)
 hipError_t launch_attn_f32(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp,
-                            const void* Vp, const uint16_t* idx, const int32_t* cnt, void* O, float* lse,
+                            const void* Vp, const uint8_t* M, const uint16_t* idx, const int32_t* cnt, void* O, float* lse,
                             hipStream_t s);
 hipError_t launch_attn_mfma(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp,
-                            const void* Vp, const uint16_t* idx, const int32_t* cnt, const uint32_t* desc, void* O,
+                            const void* Vp, const uint8_t* M, const uint16_t* idx, const int32_t* cnt, const uint32_t* desc, void* O,
                             float* lse, hipStream_t s);
 
 // Backward of the pyramid attention.  Dr: [B*Hq*N] floats; dKp, dVp: pooled gradients of levels 1..H
