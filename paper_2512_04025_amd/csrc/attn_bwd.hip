@@ -25,6 +25,7 @@ namespace psa {
 
 struct BwdArgs {
   int N, Hq, Hkv, nq, nk, bq, bk, lg_bk, H, causal;
+  int parts;                             // workgroups that share a column of the level map (bwd_dkv_kernel)
   float scale;
   int64_t lvl_off[PSA_MAX_LEVELS + 2];   // level h >= 2 inside one pyramid buffer (elements)
   int64_t glvl_off[PSA_MAX_LEVELS + 2];  // level h >= 1 inside one pooled-gradient buffer (elements)
@@ -315,7 +316,7 @@ void bwd_dkv_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* _
   float* D_s = lse_s + 32;
   int* kept = reinterpret_cast<int*>(fsm + 4 * S::WAVEF);
   int* wcount = kept + S::LIST;
-  const int hk = blockIdx.y, b = blockIdx.z, group = a.Hq / a.Hkv;
+  const int hk = blockIdx.y / a.parts, part = blockIdx.y % a.parts, b = blockIdx.z, group = a.Hq / a.Hkv;
   int h = a.H, pieces = 1, bx = blockIdx.x;
   for (;; --h) {
     const int th = a.bk >> (h - 1);
@@ -357,7 +358,9 @@ void bwd_dkv_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* _
 #pragma unroll
     for (int u = 0; u < 16; ++u) { dk[md][u] = 0.f; dv[md][u] = 0.f; }
 
-  const int E = group * a.nq, nchunk = (a.bq + 31) / 32;
+  // this workgroup's share of the column: entries (query head of the group, query block)
+  const int E_all = group * a.nq, share = (E_all + a.parts - 1) / a.parts, nchunk = (a.bq + 31) / 32;
+  const int E_lo = part * share, E = E_lo + share < E_all ? E_lo + share : E_all;
   struct Chunk { int64_t row0; int r0, seg; };
   typename Four<T>::raw reg[NCH];                                      // the Q or dO rows on their way into LDS
   float lreg = INFINITY, dreg = 0.f;
@@ -413,7 +416,7 @@ void bwd_dkv_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* _
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  for (int e0 = 0; e0 < E; e0 += S::LIST) {
+  for (int e0 = E_lo; e0 < E; e0 += S::LIST) {
     // which of the next column entries (query head of the group, query block) use this block at this level
     const int e = e0 + tid;
     const bool hit = e < E && (int)M[(((int64_t)b * a.Hq + hk * group) * a.nq + e) * a.nk + j] == h;
@@ -493,7 +496,7 @@ void bwd_dkv_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* _
         *reinterpret_cast<f32x4*>(fsm + (wave * 32 + l32) * PITCH + md * 32 + g * 8 + hf * 4) = x;
       }
     __syncthreads();
-    float* dst = (which ? dVp : dKp) + a.glvl_off[h] + (khead * ((int64_t)a.nk << lg_th) + ((int64_t)j << lg_th) + koff) * D;
+    float* dst = (which ? dVp : dKp) + a.glvl_off[h] + ((khead * a.parts + part) * ((int64_t)a.nk << lg_th) + ((int64_t)j << lg_th) + koff) * D;
     const float mul = which ? 1.f : a.scale;
     for (int x = tid; x < 32 * CPR; x += 256) {
       const int kk = x / CPR, c = (x % CPR) * 4;
@@ -563,8 +566,28 @@ hipError_t launch_attn_bwd_mfma(const Plan& pl, const void* Q, const void* K, co
                                 const uint8_t* M, const uint16_t* idx, const int32_t* cnt, const void* O, const float* lse,
                                 const void* dO, float* Dr, float* dKp, float* dVp, void* dQ, hipStream_t s);
 
-// partial pooled-gradient tensors per key head: the matrix-core kernel writes one per query head of the group
-int bwd_parts(const Plan& pl) { return bwd_uses_mfma(pl) ? pl.group : 1; }
+// workgroups of bwd_dkv_kernel for one key head and part, as the kernel counts them
+static int dkv_groups(const Plan& pl) {
+  int n = 0;
+  for (int h = 1; h <= pl.H; ++h) {
+    const int th = pl.bk >> (h - 1);
+    n += (th > 32 ? th / 32 : 1) * pl.nk;
+  }
+  return n;
+}
+
+// Partial pooled-gradient tensors per key head.  The matrix-core kernel writes one per query head of the group.
+int bwd_parts(const Plan& pl) {
+  if (bwd_uses_mfma(pl)) return pl.group;
+  // The other one splits the columns of short launches over several workgroups, whose sums unpool_kernel adds: until there are 600 workgroups (the chip
+  // holds 256 at d = 128, 512 at d = 64) while a column has 24 chunks of 32 rows for each part, or 1200 while it has 100.  Whole call, us by parts
+  // (1 / 2 / 4 / 8): 8 heads in groups of four x 1185 tokens, d = 128 409 / 270 / 209 / 193, x 600 122 / - / 75 / 85, x 2500 at d = 64 260 / 219 / 202 / 212;
+  // 2 heads x 1000 at d = 64 62 / 49 / 50 / 60, x 3000 120 / 111 / 121 / 144; 12 x 1000 at d = 128 145 / 169.
+  const int64_t wgs = (int64_t)pl.B * pl.Hkv * dkv_groups(pl), chunks = (int64_t)pl.group * pl.nq * ((pl.bq + 31) / 32);
+  int parts = 1;
+  while ((wgs * parts < 600 && chunks >= 24 * parts) || (wgs * parts < 1200 && chunks >= 100 * parts)) parts *= 2;
+  return parts;
+}
 
 size_t bwd_pooled_grad_elems(const Plan& pl) {      // one tensor: levels 1..H, every part
   size_t n = 0;
@@ -595,7 +618,8 @@ static hipError_t launch_bwd_t(const Plan& pl, const void* Q, const void* K, con
   a.H = pl.H; a.causal = pl.causal; a.scale = pl.scale;
   a.lg_bk = 0;
   while ((1 << a.lg_bk) < pl.bk) ++a.lg_bk;
-  const int parts = use_mfma ? pl.group : 1;
+  const int parts = bwd_parts(pl);
+  a.parts = parts;
   int64_t off = 0;
   for (int h = 0; h < PSA_MAX_LEVELS + 2; ++h) { a.lvl_off[h] = pl.lvl_off[h]; a.glvl_off[h] = 0; }
   for (int h = 1; h <= pl.H; ++h) {
@@ -631,12 +655,8 @@ static hipError_t launch_bwd_t(const Plan& pl, const void* Q, const void* K, con
     static LdsOptIn optin;
     e = allow_max_lds(reinterpret_cast<const void*>(bwd_dkv_kernel<T, D>), &optin);
     if (e != hipSuccess) return e;
-    int wgs = 0;                                   // as the kernel counts them
-    for (int h = 1; h <= pl.H; ++h) {
-      const int th = pl.bk >> (h - 1);
-      wgs += (th > 32 ? th / 32 : 1) * pl.nk;
-    }
-    bwd_dkv_kernel<T, D><<<dim3(wgs, pl.Hkv, pl.B), 256, BwdDkvShape<D>::BYTES, s>>>(q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, a);
+    const int wgs = dkv_groups(pl);
+    bwd_dkv_kernel<T, D><<<dim3(wgs, pl.Hkv * parts, pl.B), 256, BwdDkvShape<D>::BYTES, s>>>(q, k, v, kp, vp, M, lse, Dr, go, dKp, dVp, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -205,3 +205,10 @@ def test_infinite_keys_and_values_act_as_in_float32(N, Hq, bq, d):
     rest = [c for c in range(d) if c not in (5, 6)]
     assert np.abs(got[sees][:, rest] - want[sees][:, rest]).max() <= 1e-5
     assert np.abs(lse[sees] - (top + np.log(total))[..., 0][sees]).max() <= 1e-4
+
+
+@pytest.mark.parametrize("shape", [("f32", 1, 8, 2, 611, 128, 128, 64, 3, True), ("f32", 1, 8, 1, 1201, 64, 128, 64, 4, False), ("f32", 1, 2, 2, 1000, 64, 64, 64, 4, False)],
+                         ids=lambda s: "-".join(map(str, s)))
+def test_gradients_of_split_columns(shape):
+    """Short launches whose columns of the level map are shared by four, eight and two workgroups (same bars)."""
+    test_backward_at_the_edges(shape)
