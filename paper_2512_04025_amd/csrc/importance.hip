@@ -129,8 +129,7 @@ __global__ __launch_bounds__(256) void importance_kernel(const T* __restrict__ Q
                                                          float* __restrict__ S, ImpArgs a) {
   constexpr int VEC = Elem<T>::VEC;
   extern __shared__ float smem[];
-  float* qs = smem;                                 // [IMP_ROWS][D]
-  float* rowstat = qs + IMP_ROWS * D;               // [sq][2]: row max, row sum
+  float* rowstat = smem;                            // [sq][2]: row max, row sum
   float* bmax = rowstat + 2 * a.sq;                 // [sq][nk]
   float* bsum = bmax + (size_t)a.sq * a.nk;         // [sq][nk]
   const int tid = threadIdx.x;
@@ -143,16 +142,15 @@ __global__ __launch_bounds__(256) void importance_kernel(const T* __restrict__ Q
 
   for (int r0 = 0; r0 < a.sq; r0 += IMP_ROWS) {
     const int nr = a.sq - r0 < IMP_ROWS ? a.sq - r0 : IMP_ROWS;
-    __syncthreads();
-    for (int x = tid; x < IMP_ROWS * D; x += 256) {
-      const int r = x / D, e = x % D;
-      qs[x] = r < nr ? Elem<T>::to_f32(qbase[(int64_t)(r0 + r) * D + e]) : 0.f;
-    }
+    // The rows' channels are the same for all threads: through the scalar cache, as scalar operands of the multiply-adds.  (From LDS each was waited for:
+    // 226 LDS instructions a wavefront and three quarters of its time, 18 us for 32 workgroups.)  Rows past the end: the last one, results not used.
+    const T* qrow[IMP_ROWS];
     int qpos[IMP_ROWS];
 #pragma unroll
-    for (int r = 0; r < IMP_ROWS; ++r)
+    for (int r = 0; r < IMP_ROWS; ++r) {
+      qrow[r] = qbase + (int64_t)(r0 + (r < nr ? r : nr - 1)) * D;
       qpos[r] = r < nr ? rep_pos(a.mode, i, r0 + r, a.bq, a.sq, a.N) : -1;
-    __syncthreads();
+    }
 
     for (int c = tid; c < nkeys_pad; c += 256) {
       const int j = c / a.sk;
@@ -162,14 +160,17 @@ __global__ __launch_bounds__(256) void importance_kernel(const T* __restrict__ Q
       for (int r = 0; r < IMP_ROWS; ++r) acc[r] = 0.f;
       if (kpos >= 0) {
         const T* kp = kbase + (int64_t)c * D;
-#pragma unroll 16
-        for (int ch = 0; ch < D / VEC; ++ch) {
-          float kv[VEC];
-          Elem<T>::load(kp + ch * VEC, kv);
+        constexpr int BATCH = 64 / VEC;                  // 64 channels of the key in flight
+        for (int c0 = 0; c0 < D / VEC; c0 += BATCH) {
+          float kv[BATCH][VEC];
 #pragma unroll
-          for (int r = 0; r < IMP_ROWS; ++r)
+          for (int x = 0; x < BATCH; ++x) Elem<T>::load(kp + (c0 + x) * VEC, kv[x]);
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) acc[r] = fmaf(qs[r * D + ch * VEC + e], kv[e], acc[r]);
+          for (int x = 0; x < BATCH; ++x)
+#pragma unroll
+            for (int r = 0; r < IMP_ROWS; ++r)
+#pragma unroll
+              for (int e = 0; e < VEC; ++e) acc[r] = fmaf(Elem<T>::to_f32(qrow[r][(c0 + x) * VEC + e]), kv[x][e], acc[r]);
         }
       }
       // The rows side by side, so that a step waits once for the lane exchanges of all of them: latency decides here (32
@@ -234,6 +235,7 @@ __global__ __launch_bounds__(256) void importance_kernel(const T* __restrict__ Q
 }
 
 size_t importance_smem_bytes(int sq, int nk, int d) {
+  // (IMP_ROWS * d: rows that were kept here once; the limit on row lengths that follows from it stays where callers know it)
   return sizeof(float) * ((size_t)IMP_ROWS * d + 2 * (size_t)sq + 2 * (size_t)sq * nk);
 }
 
