@@ -85,26 +85,47 @@ __device__ __forceinline__ uint64_t lane_xor64(uint64_t v, int m) {
 // KPL keys each; the three merge steps whose partner lane sits in another wavefront go through LDS.
 // (One wavefront with 32 or 64 keys per lane needs 140+ registers: three wavefronts per SIMD, and the
 // sort, a chain of short dependent steps, then runs 6.8 times longer per row than with 16 keys per lane.)
-template <int KPL, bool FACTORED, int NW>
-__global__ __launch_bounds__((FACTORED || NW == 4) ? 256 : 64) void alloc_kernel(const float* __restrict__ S, const uint8_t* __restrict__ cap,
-                                                                    uint8_t* __restrict__ M, uint32_t* __restrict__ rowcnt,
+// HEAD (rows of up to 128 blocks, heads of up to HEAD_ROWS of them): one workgroup per head, a wavefront per row from the scores to the levels, and the
+// compute ratio of Eq. 9 at the end: a launch less for short calls.  Whole forward, us: 40 heads x 402 tokens (four rows) 35.7 -> 30.1, 12 x 1000 (eight) 42.2 -> 41.3;
+// with 16 rows, on one compute unit, the kernel itself takes 9.8 us instead of 4.7 and 2.5 (2 x 1024 43.9 -> 47.0).
+constexpr int HEAD_ROWS = 8;
+template <int KPL, bool FACTORED, int NW, bool HEAD>
+__global__ __launch_bounds__(HEAD ? 64 * HEAD_ROWS : (FACTORED || NW == 4) ? 256 : 64) void alloc_kernel(const float* __restrict__ S, const uint8_t* __restrict__ cap,
+                                                                    uint8_t* __restrict__ M, uint32_t* __restrict__ rowcnt, float* __restrict__ rho,
                                                                     AllocArgs a) {
-  __shared__ int cnt_s[PSA_MAX_LEVELS + 1];
-  __shared__ float lse_s[8];
-  __shared__ float srow_s[FACTORED ? KPL * 64 * NW : 1];
+  static_assert(!HEAD || NW == 1, "a wavefront per row");
+  constexpr int RPW = HEAD ? HEAD_ROWS : 1;              // rows of a workgroup, each with its part of the LDS
+  __shared__ int cnt_all[RPW][PSA_MAX_LEVELS + 1];
+  __shared__ float lse_all[RPW][8];
+  __shared__ float srow_all[RPW][FACTORED ? KPL * 64 * NW : 1];
+  __shared__ int vis_all[RPW];
+  const int mine = HEAD ? (int)threadIdx.x >> 6 : 0;
+  int* cnt_s = cnt_all[mine];
+  float *lse_s = lse_all[mine], *srow_s = srow_all[mine];
   __shared__ uint64_t xbuf[NW == 4 ? KPL * 256 : 1];
   __shared__ double wave_d[4];
   __shared__ int wave_i[4];
   constexpr int LANES = 64 * NW;
   const int lane = threadIdx.x & 63;
   const int glane = NW == 1 ? lane : (int)threadIdx.x;   // position of this lane among the sorting lanes
-  const int i = blockIdx.x, hq = blockIdx.y, b = blockIdx.z;
+  const int i = HEAD ? mine : (int)blockIdx.x, hq = blockIdx.y, b = blockIdx.z;
   const int64_t head = (int64_t)b * a.Hq + hq;
   const int64_t row = head * a.nq + i;
   const float* s_row = FACTORED ? nullptr : S + row * a.nk;
-  if (threadIdx.x <= PSA_MAX_LEVELS) cnt_s[threadIdx.x] = 0;
+  const int tid = HEAD ? lane : (int)threadIdx.x;        // among the threads that evaluate the row's scores
+  constexpr int EVAL = HEAD ? 64 : 256;
+  // (LDS serves one wavefront's accesses in order: a row of its own needs the fence only)
+  auto row_sync = [&]() __attribute__((always_inline)) {
+    if constexpr (HEAD) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+      __syncthreads();
+    }
+  };
+  if (tid <= PSA_MAX_LEVELS) cnt_s[tid] = 0;
   if (FACTORED) {
-    const int tid = threadIdx.x;
     if (tid < 8) {      // lse of the block's 8 representative rows from the key slices' partial results
       const float2* pr = a.fs.part + ((head * a.nq + i) * 8 + tid) * 8;
       float mrow = -INFINITY, lrow = 0.f;
@@ -115,9 +136,9 @@ __global__ __launch_bounds__((FACTORED || NW == 4) ? 256 : 64) void alloc_kernel
       }
       lse_s[tid] = lrow > 0.f ? mrow + __log2f(lrow) : INFINITY;   // no visible key: all scores 0
     }
-    __syncthreads();
+    row_sync();
     const float* __restrict__ bm0 = a.fs.bmax + (head * a.fs.bm_rows + (int64_t)i * 8) * a.fs.bm_pitch;
-    for (int j = tid; j < a.nk; j += 256) {
+    for (int j = tid; j < a.nk; j += EVAL) {
       float v = -INFINITY;
 #pragma unroll
       for (int r = 0; r < 8; ++r) v = fmaxf(v, bm0[(int64_t)r * a.fs.bm_pitch + j] - lse_s[r]);
@@ -125,10 +146,10 @@ __global__ __launch_bounds__((FACTORED || NW == 4) ? 256 : 64) void alloc_kernel
       srow_s[j] = sc;
       if (a.S_out) a.S_out[row * a.nk + j] = sc;
     }
-    __syncthreads();
-    if (NW == 1 && tid >= 64) return;   // no workgroup barrier follows in that instantiation
+    row_sync();
+    if (!HEAD && NW == 1 && tid >= 64) return;   // no workgroup barrier follows in that instantiation
   } else {
-    __syncthreads();
+    row_sync();
   }
   uint8_t* m_row = M + row * a.nk;
   const uint8_t* cap_row = cap ? cap + ((int64_t)b * a.Hkv + hq / (a.Hq / a.Hkv)) * a.nk : nullptr;
@@ -290,22 +311,46 @@ __global__ __launch_bounds__((FACTORED || NW == 4) ? 256 : 64) void alloc_kernel
   }
   // the counters are complete: one wavefront is left here in either instantiation and its LDS
   // operations complete in order, so a fence is enough where the other wavefronts have retired
-  if (FACTORED && NW == 1) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-  else __syncthreads();
+  if (FACTORED && NW == 1 && !HEAD) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+  else row_sync();
+  if constexpr (HEAD) {
+    if (lane == 0) vis_all[mine] = n_vis;
+    __syncthreads();
+    if (rho && threadIdx.x == 0) {
+      double num = 0.0, den = 0.0;                       // (whole numbers and halves: exact in any order)
+      for (int r = 0; r < a.nq; ++r) {
+        den += (double)vis_all[r];
+        for (int h = 1; h <= a.H; ++h) num += (double)cnt_all[r][h] / (double)(1u << (h - 1));
+      }
+      rho[head] = (float)(num / den);
+    }
+    return;
+  }
   if (glane <= a.H) rowcnt[row * ROWCNT_STRIDE + lane] = lane == 0 ? (uint32_t)n_vis : (uint32_t)cnt_s[lane];
 }
 
+static hipError_t launch_rho(const Plan& pl, const uint32_t* rowcnt, float* rho, hipStream_t s);
+
 template <int KPL, int NW>
 static hipError_t launch_alloc_t(const Plan& pl, const AllocArgs& a, const float* S, const uint8_t* cap, uint8_t* M,
-                                 uint32_t* rowcnt, hipStream_t s) {
+                                 uint32_t* rowcnt, float* rho, hipStream_t s) {
+  if constexpr (NW == 1) {
+    if (pl.nq <= HEAD_ROWS) {
+      const dim3 heads(1, pl.Hq, pl.B);
+      if (a.fs.bmax) alloc_kernel<KPL, true, 1, true><<<heads, 64 * pl.nq, 0, s>>>(S, cap, M, rowcnt, rho, a);
+      else alloc_kernel<KPL, false, 1, true><<<heads, 64 * pl.nq, 0, s>>>(S, cap, M, rowcnt, rho, a);
+      return hipGetLastError();
+    }
+  }
   dim3 grid(pl.nq, pl.Hq, pl.B);
-  if (a.fs.bmax) alloc_kernel<KPL, true, NW><<<grid, 256, 0, s>>>(S, cap, M, rowcnt, a);
-  else alloc_kernel<KPL, false, NW><<<grid, 64 * NW, 0, s>>>(S, cap, M, rowcnt, a);
-  return hipGetLastError();
+  if (a.fs.bmax) alloc_kernel<KPL, true, NW, false><<<grid, 256, 0, s>>>(S, cap, M, rowcnt, nullptr, a);
+  else alloc_kernel<KPL, false, NW, false><<<grid, 64 * NW, 0, s>>>(S, cap, M, rowcnt, nullptr, a);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess && rho ? launch_rho(pl, rowcnt, rho, s) : e;
 }
 
 hipError_t launch_allocate(const Plan& pl, const float* S, const FactoredScores* factored, float* S_out,
-                           const uint8_t* cap, uint8_t* M, uint32_t* rowcnt, hipStream_t s) {
+                           const uint8_t* cap, uint8_t* M, uint32_t* rowcnt, float* rho, hipStream_t s) {
   AllocArgs a;
   if (factored) a.fs = *factored;
   else { a.fs.part = nullptr; a.fs.bmax = nullptr; a.fs.ksplit = 0; a.fs.bm_rows = 0; a.fs.bm_pitch = 0; }
@@ -317,13 +362,13 @@ hipError_t launch_allocate(const Plan& pl, const float* S, const FactoredScores*
   int kpl = 1;                       // keys per lane: the row padded to a power of two >= 64
   while (64 * kpl < pl.nk) kpl <<= 1;
   switch (kpl) {
-    case 1:  return launch_alloc_t<1, 1>(pl, a, S, cap, M, rowcnt, s);
-    case 2:  return launch_alloc_t<2, 1>(pl, a, S, cap, M, rowcnt, s);
-    case 4:  return launch_alloc_t<1, 4>(pl, a, S, cap, M, rowcnt, s);    // from 256 keys on: four wavefronts per row
-    case 8:  return launch_alloc_t<2, 4>(pl, a, S, cap, M, rowcnt, s);    //   (5 us of 41 at 512 keys, 30 of 330 at 1024)
-    case 16: return launch_alloc_t<4, 4>(pl, a, S, cap, M, rowcnt, s);
-    case 32: return launch_alloc_t<8, 4>(pl, a, S, cap, M, rowcnt, s);    // 2048 keys: 256 lanes x 8
-    case 64: return launch_alloc_t<16, 4>(pl, a, S, cap, M, rowcnt, s);   // 4096 keys: 256 lanes x 16
+    case 1:  return launch_alloc_t<1, 1>(pl, a, S, cap, M, rowcnt, rho, s);
+    case 2:  return launch_alloc_t<2, 1>(pl, a, S, cap, M, rowcnt, rho, s);
+    case 4:  return launch_alloc_t<1, 4>(pl, a, S, cap, M, rowcnt, rho, s);    // from 256 keys on: four wavefronts per row
+    case 8:  return launch_alloc_t<2, 4>(pl, a, S, cap, M, rowcnt, rho, s);    //   (5 us of 41 at 512 keys, 30 of 330 at 1024)
+    case 16: return launch_alloc_t<4, 4>(pl, a, S, cap, M, rowcnt, rho, s);
+    case 32: return launch_alloc_t<8, 4>(pl, a, S, cap, M, rowcnt, rho, s);    // 2048 keys: 256 lanes x 8
+    case 64: return launch_alloc_t<16, 4>(pl, a, S, cap, M, rowcnt, rho, s);   // 4096 keys: 256 lanes x 16
     default: return hipErrorInvalidValue;   // more than PSA_MAX_NK key blocks: refused before any launch
   }
 }
@@ -349,7 +394,7 @@ __global__ __launch_bounds__(256) void rho_kernel(const uint32_t* __restrict__ r
   if (tid == 0) rho[blockIdx.x] = (float)(num_s[0] / den_s[0]);
 }
 
-hipError_t launch_rho(const Plan& pl, const uint32_t* rowcnt, float* rho, hipStream_t s) {
+static hipError_t launch_rho(const Plan& pl, const uint32_t* rowcnt, float* rho, hipStream_t s) {
   rho_kernel<<<pl.B * pl.Hq, 256, 0, s>>>(rowcnt, rho, pl.nq, pl.H);
   return hipGetLastError();
 }

@@ -240,9 +240,7 @@ int psa_allocate_levels(const psa_params* p, const void* Q, const void* K, const
       const size_t bytes = (size_t)pl.B * pl.Hq * pl.nq * pl.nk * sizeof(float);
       if (hipMemcpyAsync(scores_out, scores_in, bytes, hipMemcpyDeviceToDevice, s) != hipSuccess) return PSA_ELAUNCH;
     }
-    if (launch_allocate(pl, scores_in, nullptr, nullptr, level_cap, M, rowcnt, s) != hipSuccess) return PSA_ELAUNCH;
-    if (rho_out && launch_rho(pl, rowcnt, rho_out, s) != hipSuccess) return PSA_ELAUNCH;
-    return PSA_OK;
+    return launch_allocate(pl, scores_in, nullptr, nullptr, level_cap, M, rowcnt, rho_out, s) == hipSuccess ? PSA_OK : PSA_ELAUNCH;
   }
   if (!Q) return PSA_EINVAL;
   if (pl.krep_is_pyramid ? !Kpyr : !K) return PSA_EINVAL;
@@ -257,8 +255,7 @@ int psa_allocate_levels(const psa_params* p, const void* Q, const void* K, const
   if (launch_importance(pl, qrep, krep, at(scratch, pl.off_part), at(scratch, pl.off_bmax), sdst, &fs, s) != hipSuccess) return PSA_ELAUNCH;
   const bool factored = fs.bmax != nullptr;
   if (launch_allocate(pl, factored ? nullptr : sdst, factored ? &fs : nullptr, factored ? scores_out : nullptr, level_cap, M,
-                      rowcnt, s) != hipSuccess) return PSA_ELAUNCH;
-  if (rho_out && launch_rho(pl, rowcnt, rho_out, s) != hipSuccess) return PSA_ELAUNCH;
+                      rowcnt, rho_out, s) != hipSuccess) return PSA_ELAUNCH;
   return PSA_OK;
 }
 
