@@ -86,9 +86,10 @@ __device__ __forceinline__ uint64_t lane_xor64(uint64_t v, int m) {
 // (One wavefront with 32 or 64 keys per lane needs 140+ registers: three wavefronts per SIMD, and the
 // sort, a chain of short dependent steps, then runs 6.8 times longer per row than with 16 keys per lane.)
 // HEAD (rows of up to 128 blocks, heads of up to HEAD_ROWS of them): one workgroup per head, a wavefront per row from the scores to the levels, and the
-// compute ratio of Eq. 9 at the end: a launch less for short calls.  Whole forward, us: 40 heads x 402 tokens (four rows) 35.7 -> 30.1, 12 x 1000 (eight) 42.2 -> 41.3;
-// with 16 rows, on one compute unit, the kernel itself takes 9.8 us instead of 4.7 and 2.5 (2 x 1024 43.9 -> 47.0).
-constexpr int HEAD_ROWS = 8;
+// compute ratio of Eq. 9 at the end: a launch less for short calls.  Whole forward, us, row per workgroup and ratio kernel -> this: 40 heads x 402
+// tokens (four rows) 35.7 -> 28.3, 12 x 1000 (eight) 42.2 -> 37.4; with eight rows at most -> sixteen: 8 x 542 in 64-row blocks (nine) 39.3 -> 38.1, 12 x 2000 44.4 -> 44.0,
+// float32 2 x 1024 36.7 -> 36.0.
+constexpr int HEAD_ROWS = 16;
 template <int KPL, bool FACTORED, int NW, bool HEAD>
 __global__ __launch_bounds__(HEAD ? 64 * HEAD_ROWS : (FACTORED || NW == 4) ? 256 : 64) void alloc_kernel(const float* __restrict__ S, const uint8_t* __restrict__ cap,
                                                                     uint8_t* __restrict__ M, uint32_t* __restrict__ rowcnt, float* __restrict__ rho,
@@ -316,13 +317,16 @@ __global__ __launch_bounds__(HEAD ? 64 * HEAD_ROWS : (FACTORED || NW == 4) ? 256
   if constexpr (HEAD) {
     if (lane == 0) vis_all[mine] = n_vis;
     __syncthreads();
-    if (rho && threadIdx.x == 0) {
-      double num = 0.0, den = 0.0;                       // (whole numbers and halves: exact in any order)
-      for (int r = 0; r < a.nq; ++r) {
-        den += (double)vis_all[r];
-        for (int h = 1; h <= a.H; ++h) num += (double)cnt_all[r][h] / (double)(1u << (h - 1));
+    if (rho && mine == 0) {
+      // in units of 2^-(H-1): whole numbers (at most 8 rows x 128 blocks x 128), a row per lane
+      int num = 0, den = lane < a.nq ? vis_all[lane & (RPW - 1)] : 0;
+      for (int h = 1; h <= a.H; ++h) num += lane < a.nq ? cnt_all[lane & (RPW - 1)][h] << (a.H - h) : 0;
+#pragma unroll
+      for (int off = RPW / 2; off; off >>= 1) {
+        num += __shfl_xor(num, off, 64);
+        den += __shfl_xor(den, off, 64);
       }
-      rho[head] = (float)(num / den);
+      if (lane == 0) rho[head] = (float)((double)num / (double)(1 << (a.H - 1)) / (double)den);
     }
     return;
   }
