@@ -19,33 +19,31 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
 __device__ __forceinline__ float bf16_to_f32(bf16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 
-// round-to-nearest-even; NaN stays NaN
-__device__ __forceinline__ bf16_t f32_to_bf16(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (bf16_t)((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (bf16_t)(u >> 16);
+// round-to-nearest-even; NaN stays NaN.  Two at a time: one conversion instruction.
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+__device__ __forceinline__ uint32_t f32_to_bf16_pair(float x, float y) {   // x in the low half
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x, y}), bf16x2));
 }
+__device__ __forceinline__ bf16_t f32_to_bf16(float f) { return (bf16_t)f32_to_bf16_pair(f, f); }
 
 // Element-type traits: a 16-byte vector of VEC elements, widened to float and narrowed back.
 template <typename T> struct Elem;
 template <> struct Elem<float> {
   static constexpr int VEC = 4;
-  __device__ static __forceinline__ void load(const float* p, float* out) {
-    f32x4 v = *reinterpret_cast<const f32x4*>(p);
+  __device__ static __forceinline__ void load(const float* p, float* out) { widen(*reinterpret_cast<const u32x4*>(p), out); }
+  __device__ static __forceinline__ void widen(u32x4 x, float* out) {
+    f32x4 v = __builtin_bit_cast(f32x4, x);
     out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
   }
-  __device__ static __forceinline__ void store(float* p, const float* in) {
-    f32x4 v = {in[0], in[1], in[2], in[3]};
-    *reinterpret_cast<f32x4*>(p) = v;
-  }
+  __device__ static __forceinline__ u32x4 pack(const float* in) { return __builtin_bit_cast(u32x4, (f32x4{in[0], in[1], in[2], in[3]})); }
+  __device__ static __forceinline__ void store(float* p, const float* in) { *reinterpret_cast<u32x4*>(p) = pack(in); }
   __device__ static __forceinline__ float to_f32(float x) { return x; }
   __device__ static __forceinline__ float from_f32(float x) { return x; }
 };
 template <> struct Elem<bf16_t> {
   static constexpr int VEC = 8;
-  __device__ static __forceinline__ void load(const bf16_t* p, float* out) {
-    u32x4 v = *reinterpret_cast<const u32x4*>(p);
+  __device__ static __forceinline__ void load(const bf16_t* p, float* out) { widen(*reinterpret_cast<const u32x4*>(p), out); }
+  __device__ static __forceinline__ void widen(u32x4 v, float* out) {
     uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -53,14 +51,13 @@ template <> struct Elem<bf16_t> {
       out[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
     }
   }
-  __device__ static __forceinline__ void store(bf16_t* p, const float* in) {
+  __device__ static __forceinline__ u32x4 pack(const float* in) {
     uint32_t w[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      w[i] = (uint32_t)f32_to_bf16(in[2 * i]) | ((uint32_t)f32_to_bf16(in[2 * i + 1]) << 16);
-    u32x4 v = {w[0], w[1], w[2], w[3]};
-    *reinterpret_cast<u32x4*>(p) = v;
+    for (int i = 0; i < 4; ++i) w[i] = f32_to_bf16_pair(in[2 * i], in[2 * i + 1]);
+    return u32x4{w[0], w[1], w[2], w[3]};
   }
+  __device__ static __forceinline__ void store(bf16_t* p, const float* in) { *reinterpret_cast<u32x4*>(p) = pack(in); }
   __device__ static __forceinline__ float to_f32(bf16_t x) { return bf16_to_f32(x); }
   __device__ static __forceinline__ bf16_t from_f32(float x) { return f32_to_bf16(x); }
 };
@@ -84,7 +81,7 @@ template <> struct Four<bf16_t> {
     return f32x4{bf16_to_f32(r[0]), bf16_to_f32(r[1]), bf16_to_f32(r[2]), bf16_to_f32(r[3])};
   }
   __device__ static __forceinline__ void store(bf16_t* p, f32x4 x) {
-    *reinterpret_cast<u16x4_any*>(p) = u16x4_any{f32_to_bf16(x[0]), f32_to_bf16(x[1]), f32_to_bf16(x[2]), f32_to_bf16(x[3])};
+    *reinterpret_cast<u16x4_any*>(p) = __builtin_bit_cast(u16x4_any, (u32x2{f32_to_bf16_pair(x[0], x[1]), f32_to_bf16_pair(x[2], x[3])}));
   }
 };
 
@@ -129,18 +126,14 @@ template <int D> __host__ __device__ constexpr int row_swizzle32(int row) {
 // Not for values that are not finite (or round to infinity): their m and l are NaN.
 struct Split2 { uint32_t h, m, l; };                 // of two neighbours: the first in the low halves
 __device__ __forceinline__ Split2 split2(float a, float b, float& rest) {
-  typedef __attribute__((ext_vector_type(2))) float f32x2;
-  auto pack = [](float x, float y) __attribute__((always_inline)) {   // (as a vector: one conversion for the pair)
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x, y}), bf16x2));
-  };
   Split2 s;
-  s.h = pack(a, b);
+  s.h = f32_to_bf16_pair(a, b);
   a -= __uint_as_float(s.h << 16);
   b -= __uint_as_float(s.h & 0xffff0000u);
-  s.m = pack(a, b);
+  s.m = f32_to_bf16_pair(a, b);
   a -= __uint_as_float(s.m << 16);
   b -= __uint_as_float(s.m & 0xffff0000u);
-  s.l = pack(a, b);
+  s.l = f32_to_bf16_pair(a, b);
   rest += a + b;                                     // NaN if either was not finite
   return s;
 }

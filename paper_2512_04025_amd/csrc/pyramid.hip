@@ -211,7 +211,8 @@ __device__ __forceinline__ void pyramid_body(const T* __restrict__ K, const T* _
   constexpr int VEC = Elem<T>::VEC;
   constexpr int BATCH = G < 8 ? G : 8;
   // (32-bit arithmetic: a grid has fewer than 2^32 threads.  64-bit divisions here and a division per element and level below were half of the kernel's
-  // 1500 vector instructions a wavefront: 12 heads x 1000 tokens 8.6 -> 7.4 us, float32 2 x 1024 4.8 -> 3.6, 12 x 32760 75 -> 64 = 5.9 TB/s.)
+  // 1500 vector instructions a wavefront: 12 heads x 1000 tokens 8.6 -> 7.4 us, float32 2 x 1024 4.8 -> 3.6, 12 x 32760 75 -> 64; roundings by the conversion
+  // instruction another 7.4 -> 5.5 and 64 -> 62 = 6.1 TB/s.)
   const uint32_t rest = gid / (uint32_t)a.chunks;
   const int c = (int)(gid - rest * (uint32_t)a.chunks);
   const int bh = (int)(rest / (uint32_t)a.groups);
@@ -270,10 +271,7 @@ __device__ __forceinline__ void pyramid_body(const T* __restrict__ K, const T* _
           // streaming store: the pooled levels are not read again by this kernel, so they bypass the
           // cache write-allocate path (measured 4.3 -> 5.4 TB/s on the 32760-token workload)
           T* dp = dst + a.lvl_off[h] + ((int64_t)bh * rows_h + row) * a.d + (int64_t)c * VEC;
-          T packed[VEC];
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) packed[e] = Elem<T>::from_f32(out[e]);
-          __builtin_nontemporal_store(*reinterpret_cast<u32x4*>(packed), reinterpret_cast<u32x4*>(dp));
+          __builtin_nontemporal_store(Elem<T>::pack(out), reinterpret_cast<u32x4*>(dp));
         }
       }
     }
