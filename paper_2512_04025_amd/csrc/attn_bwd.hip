@@ -562,6 +562,7 @@ __global__ __launch_bounds__(256) void unpool_kernel(const float* __restrict__ d
 }
 
 bool bwd_uses_mfma(const Plan& pl);
+int dkv_split(const Plan& pl);
 hipError_t launch_attn_bwd_mfma(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp, const void* Vp,
                                 const uint8_t* M, const uint16_t* idx, const int32_t* cnt, const void* O, const float* lse,
                                 const void* dO, float* Dr, float* dKp, float* dVp, void* dQ, hipStream_t s);
@@ -576,9 +577,9 @@ static int dkv_groups(const Plan& pl) {
   return n;
 }
 
-// Partial pooled-gradient tensors per key head.  The matrix-core kernel writes one per query head of the group.
+// Partial pooled-gradient tensors per key head.  The matrix-core kernel writes one per query head of the group and share of a walk.
 int bwd_parts(const Plan& pl) {
-  if (bwd_uses_mfma(pl)) return pl.group;
+  if (bwd_uses_mfma(pl)) return pl.group * dkv_split(pl);
   // The other one splits the columns of short launches over several workgroups, whose sums unpool_kernel adds: until there are 600 workgroups (the chip
   // holds 256 at d = 128, 512 at d = 64) while a column has 24 chunks of 32 rows for each part, or 1200 while it has 100.  Whole call, us by parts
   // (1 / 2 / 4 / 8): 8 heads in groups of four x 1185 tokens, d = 128 409 / 270 / 209 / 193, x 600 122 / - / 75 / 85, x 2500 at d = 64 260 / 219 / 202 / 212;

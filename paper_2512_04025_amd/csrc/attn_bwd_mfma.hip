@@ -24,6 +24,7 @@ namespace psa {
 
 struct BwdMfmaArgs {
   int B, N, Hq, Hkv, group, nq, nk, bq, bk, lg_bk, H, causal;
+  int split;                             // dK, dV: workgroups that share a walk (the query blocks of a column), each with a partial gradient
   int one_head;                          // dK, dV: all XCDs work on one head's neighbouring keys
   int dq_runs;                           // dQ: each XCD takes a contiguous run of all heads' query blocks
   int small_keys;                        // dK, dV: keys of a workgroup where blocks have fewer than 64
@@ -419,7 +420,7 @@ struct DkvPtrs {
   const float *lse, *Dr;
   float *dKp, *dVp;
 };
-// What a workgroup does: level, (batch, query head), number among the head's workgroups of this level
+// What a workgroup does: level, (batch, query head, share of its query blocks), number among the head's workgroups of this level
 struct DkvItem { int h, head, bx; };
 
 template <int D, int RH, bool FULL, bool CAUSAL>
@@ -443,7 +444,7 @@ __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr
   const bf16_t *Q = ptr.Q, *K = ptr.K, *V = ptr.V, *Kp = ptr.Kp, *Vp = ptr.Vp, *dO = ptr.dO;
   const uint8_t* M = ptr.M;
   const float *lse = ptr.lse, *Dr = ptr.Dr;
-  const int h = it.h, head = it.head, bx = it.bx;
+  const int h = it.h, head = it.head / a.split, share = it.head % a.split, bx = it.bx;
   const DkvGroup grp = dkv_group(a.lg_bk - (h - 1), a.nk, a.small_keys);
   const int G = 1 << grp.lg_G, keys = FULL ? KEYS : grp.keys;
   const int hq = head % a.Hq, b = head / a.Hq;
@@ -698,13 +699,14 @@ __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr
     at ^= 1;
   };
 
-  for (int e_lo = 0; e_lo < a.nq; e_lo += DKV_LIST) {
+  const int per_share = (a.nq + a.split - 1) / a.split, e_end = (share + 1) * per_share < a.nq ? (share + 1) * per_share : a.nq;
+  for (int e_lo = share * per_share; e_lo < e_end; e_lo += DKV_LIST) {
     const int tid = wave * 64 + lane_again(), lane = tid & 63;
     // The columns of the level map: which of the next query blocks of this query head use any of the group's key blocks
     // at this level, as an ordered list in LDS with the blocks used as a bit mask (one round of independent
     // loads per NT entries; a walk that tests one entry after the other spends a memory latency on each of them).
     int nkept = 0;
-    const int e_hi = e_lo + DKV_LIST < a.nq ? e_lo + DKV_LIST : a.nq;
+    const int e_hi = e_lo + DKV_LIST < e_end ? e_lo + DKV_LIST : e_end;
     for (int e0 = e_lo; e0 < e_hi; e0 += NT) {
       const int e = e0 + tid;
       uint32_t bits = 0u;
@@ -768,7 +770,7 @@ __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr
       for (int md = 0; md < MD; ++md)              // (rows spread over the banks)
         *reinterpret_cast<f32x4*>(red(rh, pair, u) + (l16e * D + ((md * 16 + ge * 4) ^ (l16e << 2)))) = which ? dv[u][md] : dk[u][md];
     __syncthreads();
-    float* dst = (which ? ptr.dVp : ptr.dKp) + a.glvl_off[h] + (qhead * ((int64_t)a.nk << lg_th) + ((int64_t)j0 << lg_th)) * D;
+    float* dst = (which ? ptr.dVp : ptr.dKp) + a.glvl_off[h] + ((qhead * a.split + share) * ((int64_t)a.nk << lg_th) + ((int64_t)j0 << lg_th)) * D;
     for (int x = tid; x < keys * (D / 4); x += NT) {
       const int kk = x / (D / 4), c4 = x % (D / 4);     // key of the workgroup, group of four channels
       const int blk = (koff + kk) >> lg_th;
@@ -790,14 +792,14 @@ __device__ __forceinline__ void dkv_body(unsigned char* smem, const DkvPtrs& ptr
 // launch_bwd_mfma_t).  An XCD's items, level after level from the coarsest down, are its slots.
 __device__ __forceinline__ bool dkv_item(const BwdMfmaArgs& a, int xcd, int slot, DkvItem& it) {
   for (int h = a.H; h >= 1; --h) {
-    const int ng = dkv_group(a.lg_bk - (h - 1), a.nk, a.small_keys).ng, items = a.B * a.Hq * ng, run = a.causal ? xcd_slots(a.B * a.Hq, ng) : (items + 7) >> 3;
+    const int heads = a.B * a.Hq * a.split, ng = dkv_group(a.lg_bk - (h - 1), a.nk, a.small_keys).ng, items = heads * ng, run = a.causal ? xcd_slots(heads, ng) : (items + 7) >> 3;
     if (slot >= run) {
       slot -= run;
       continue;
     }
     if (a.causal) {
       it.h = h;
-      return xcd_item(a.B * a.Hq, ng, xcd, slot, it.head, it.bx);
+      return xcd_item(heads, ng, xcd, slot, it.head, it.bx);
     }
     const int item = a.one_head ? slot * 8 + xcd : xcd * run + slot;
     it = {h, item / ng, item % ng};
@@ -908,6 +910,26 @@ __global__ __launch_bounds__(1024) void bwd_dkv_order_kernel(const uint32_t* __r
 
 // (32-bit byte offsets reach every row of a head: at most 65535 key blocks of 128 keys of 256 bytes are less than 2^31.
 // Addresses need no more than element alignment, in the direct-to-LDS loads as in all others.)
+// Workgroups that share a walk of dK, dV, each with a share of the query blocks and a partial gradient (added up with those of the query heads): while
+// workgroups (of 32 keys) are fewer than four fifths of what the chip holds and a share has 32 chunks of 32 rows; two where several levels make walks of
+// different lengths, up to twice what the chip holds, if they have 128 chunks.  Whole call, us, one / two / four, d = 128: 2 heads x 1000 tokens
+// 41.0 / 38.8 / 43.0, x 3000 87.5 / 74.0, x 8000 189 / 164, in one level x 2000 54.3 / - / 43.7, x 8000 141 / 134; d = 64 4 x 2000 58.5 / 49.6, 2 x 7026 in one level
+// 176 / - / 131, causal 8 x 4000 in groups of four 96.3 / 92.8; not on a nearly full chip, 2 x 14837 in one level 282 / - / 292, 12 x 1000 54.7 / 61, 28 x 1716 57.4 / 64.
+int dkv_split(const Plan& pl) {
+  int64_t groups = 0;
+  for (int h = 1; h <= pl.H; ++h) {
+    int lg_th = 0;
+    while ((1 << (lg_th + 1)) <= (pl.bk >> (h - 1))) ++lg_th;
+    groups += (int64_t)pl.B * pl.Hq * dkv_group(lg_th, pl.nk, 32).ng;
+  }
+  const int64_t chunks = (int64_t)pl.nq * ((pl.bq + 31) / 32);
+  int split = 1;
+  const int64_t resident = 256 * (pl.d == 64 ? 3 : 2);
+  while (5 * groups * split < 4 * resident && chunks >= 32 * split) split *= 2;
+  if (split == 1 && pl.H > 1 && groups < 2 * resident && chunks >= 128) split = 2;
+  return split;
+}
+
 bool bwd_uses_mfma(const Plan& pl) {
   return pl.dtype == PSA_BF16 && pl.bk >= 8 && pl.bk <= 128 && (pl.d == 64 || pl.d == 128) &&
          pl.nq <= 8192;                            // (the bound that the header states)
@@ -935,11 +957,12 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
   // heads to a key head, 28 x 16000 3.70 / 4.25, x 32760 15.3 / 16.5 (single level 11.0 / 11.7), x 40000 23.1 / 24.5.  One head is better for few
   // heads: 1 x 40000 0.929 / 0.924, 2 x 100000 in a single level 8.04 / 7.55, d = 64 4 x 120000 11.4 / 11.0 (2 x 40000 1.61 / 1.63).  The line has yet to be moved.
   a.one_head = !pl.causal && (int64_t)pl.N * pl.d >= (pl.group > 1 ? 4000000 : 5000000);
+  a.split = dkv_split(pl);
   int64_t off = 0;
   for (int h = 0; h < PSA_MAX_LEVELS + 2; ++h) { a.lvl_off[h] = pl.lvl_off[h]; a.glvl_off[h] = 0; }
   for (int h = 1; h <= pl.H; ++h) {
     a.glvl_off[h] = off;
-    off += (int64_t)pl.B * pl.Hq * pl.nk * (pl.bk >> (h - 1)) * pl.d;   // one partial tensor per QUERY head
+    off += (int64_t)pl.B * pl.Hq * a.split * pl.nk * (pl.bk >> (h - 1)) * pl.d;   // partial tensors of every QUERY head
   }
   const bf16_t* q = static_cast<const bf16_t*>(Q);
   const bf16_t* k = static_cast<const bf16_t*>(K);
@@ -963,7 +986,7 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
     int64_t n = 0;
     for (int h = 1; h <= pl.H; ++h) {
       const int ng = dkv_group(a.lg_bk - (h - 1), pl.nk, small_keys).ng;
-      n += pl.causal ? (int64_t)xcd_slots(pl.B * pl.Hq, ng) : ((int64_t)pl.B * pl.Hq * ng + 7) / 8;
+      n += pl.causal ? (int64_t)xcd_slots(heads * a.split, ng) : ((int64_t)heads * a.split * ng + 7) / 8;
     }
     return n;
   };
@@ -971,13 +994,13 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
   // the query blocks, say) would end after the work that there is for every resident workgroup (walks of a fifth of the query blocks,
   // a tenth if causal; what a workgroup costs besides is worth four).  Whole call, us for 64 / 32, d = 128, four levels: 2 heads x 3000 tokens 112 / 90,
   // x 8000 241 / 193, x 20000 644 / 505; 12 x 3000 148 / 147, x 8000 489 / 512, 28 grouped causal x 8000 674 / 709; d = 64 2 x 8000 164 / 129, 12 x 8000 256 / 266.
-  const int64_t walk = pl.nq / (pl.causal ? 10 : 5) + 4;
+  const int64_t nq = (pl.nq + a.split - 1) / a.split, walk = nq / (pl.causal ? 10 : 5) + 4;   // of a workgroup's share
   // Workgroups of two wavefronts (twice as many resident, each walk twice as long) where the work for every resident one is at least the
   // longest walk that there can be.  Whole call, time in four wavefronts over time in two, 70 shapes, by that work over that walk: up to
   // 0.2 0.60-0.91, 0.2-0.5 0.63-0.97 (32-row blocks up to 1.07), 0.5-0.95 0.71-1.08, from 1.0 on 1.01-1.06.
-  const bool pairs = groups(64) * 8 * walk >= 256 * DkvShape<D, 1>::WPS * 2 * (int64_t)pl.nq;
+  const bool pairs = groups(64) * 8 * walk >= 256 * DkvShape<D, 1>::WPS * 2 * nq;
   const int64_t resident = 256 * DkvShape<D, 2>::WPS * (pairs ? 2 : 1);
-  a.small_keys = groups(64) * 8 * walk < resident * (pl.nq / 2 + 4) ? 32 : 64;
+  a.small_keys = groups(64) * 8 * walk < resident * (nq / 2 + 4) ? 32 : 64;
   const DkvPtrs ptr = {q, k, v, kp, vp, go, M, lse, Dr, dKp, dVp};
   const int pitch = (int)groups(a.small_keys);
   // Started in the order of their lengths once they are more than fit at a time and the launch is long enough to gain more than the two
@@ -986,7 +1009,7 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
   // 281 / 274, x 8000 690 / 674; 40 x 3000 392 / 342, which the line leaves in the order of the keys.  The dQ kernel was the last to read the block
   // lists: their place takes the lengths and the order.
   uint32_t* order = nullptr;
-  if (8 * pitch > resident && 8 * pitch * walk > 36 * resident && (size_t)pitch * 8 * 2 * sizeof(uint32_t) <= (size_t)pl.B * pl.Hq * pl.nq * pl.nk * sizeof(uint16_t)) {
+  if (a.split == 1 && 8 * pitch > resident && 8 * pitch * walk > 36 * resident && (size_t)pitch * 8 * 2 * sizeof(uint32_t) <= (size_t)pl.B * pl.Hq * pl.nq * pl.nk * sizeof(uint16_t)) {
     uint32_t* len = const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(idx));
     order = len + 8 * pitch;
     bwd_dkv_length_kernel<<<dim3((pl.nk + 63) / 64, pl.Hq, pl.B), LEN_WAVES * 64, 0, s>>>(M, len, pitch, a);

@@ -52,3 +52,31 @@ def test_short_rows(N, dtype, d, bq, levels, causal):
     for name, x, want in zip(("dQ", "dK", "dV"), grads, orc.psa_attention_backward(Q64, *pyramids, M, dO64, op)):
         bar = (2e-2 if bf16 else 1e-5) * max(1.0, float(np.abs(want).max()))
         assert np.abs(from_dev(x, dtype) - want).max() <= bar, name
+
+
+@pytest.mark.parametrize("N,d,bq,levels,causal", [(2601, 128, 128, 3, False), (2601, 64, 64, 2, True), (4301, 64, 128, 1, False)])
+def test_gradients_of_shared_walks(N, d, bq, levels, causal):
+    """Few key blocks under long columns: four and eight workgroups share a walk of the bfloat16 dK, dV kernel."""
+    import torch
+    op = orc.Params(B=1, Hq=2, Hkv=1, N=N, d=d, bq=bq, bk=64, levels=levels, dtype="bf16", causal=causal, sq=8, sk=1)
+    gp = gpu_params(op)
+    host = si.random_qkv(N + d, 1, 2, 1, N, d, "bf16")
+    dO = si.random_qkv(9, 1, 2, 2, N, d, "bf16")[0]
+    rng = np.random.default_rng(N)
+    vis = orc.block_visibility(op)
+    M = rng.integers(1, levels + 1, size=(1, 2, op.nq, op.nk)) * (rng.random((1, 2, op.nq, op.nk)) < 0.2)
+    M[..., 0] = 1
+    M[:, :, -1, -1] = 1
+    M = np.where(vis[None, None] == 0, 0, np.where(vis[None, None] == 2, 1, M)).astype(np.uint8)
+    Qd, Kd, Vd, dOd = (to_dev(x, "bf16") for x in (*host, dO))
+    Q64, K64, V64, dO64 = (si.to_f64(x, "bf16") for x in (*host, dO))
+    buf, Md = Buffers(gp), torch.from_numpy(M).cuda()
+    psa.psa_build_pyramid(gp, Kd, Vd, buf.Kpyr, buf.Vpyr)
+    psa.psa_attention_fwd(gp, Qd, Kd, Vd, buf.Kpyr, buf.Vpyr, Md, buf.O, buf.scratch, lse=buf.lse)
+    grads = [torch.full_like(x, float("nan")) for x in (Qd, Kd, Vd)]
+    scratch = torch.full((psa.psa_query_bwd_sizes(gp),), 255, dtype=torch.uint8, device="cuda")
+    psa.psa_attention_bwd(gp, Qd, Kd, Vd, buf.Kpyr, buf.Vpyr, Md, buf.O, buf.lse, dOd, *grads, scratch)
+    torch.cuda.synchronize()
+    want = orc.psa_attention_backward(Q64, orc.build_pyramid(K64, op), orc.build_pyramid(V64, op), M, dO64, op)
+    for name, x, w in zip(("dQ", "dK", "dV"), grads, want):
+        assert np.abs(from_dev(x, "bf16") - w).max() <= 2e-2 * max(1.0, float(np.abs(w).max())), name
