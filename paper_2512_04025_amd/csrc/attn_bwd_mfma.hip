@@ -949,14 +949,12 @@ static hipError_t launch_bwd_mfma_t(const Plan& pl, const void* Q, const void* K
   a.lg_cpe = 0;
   while ((1 << a.lg_cpe) < cpe) ++a.lg_cpe;
   if ((1 << a.lg_cpe) != cpe) a.lg_cpe = -1;
-  // With a run of items to each XCD the Q and dO of eight heads are in flight, which the memory-side cache (256 MB) has to
-  // hold; with all XCDs on one head it holds them at any length.  The line was drawn for the kernels before the 16-key tiles, for which
-  // one head was up to 12 % better behind it.  With these runs are better on most of both sides.  Whole call, ms for runs / one head, not causal,
-  // d = 128: 12 heads x 16000 tokens 1.53 / 1.80, x 32760 6.25 / 6.94, x 40000 9.40 / 10.48, 24 x 60000 43.1 / 46.8, 40 x 75600 116 / 125,
-  // 24 x 100000 123 / 131, single level 16 x 60000 21.1 / 21.7; d = 64: 12 x 40000 4.81 / 5.22, x 75600 17.3 / 18.4, 32 x 131072 127 / 135.  Seven query
-  // heads to a key head, 28 x 16000 3.70 / 4.25, x 32760 15.3 / 16.5 (single level 11.0 / 11.7), x 40000 23.1 / 24.5.  One head is better for few
-  // heads: 1 x 40000 0.929 / 0.924, 2 x 100000 in a single level 8.04 / 7.55, d = 64 4 x 120000 11.4 / 11.0 (2 x 40000 1.61 / 1.63).  The line has yet to be moved.
-  a.one_head = !pl.causal && (int64_t)pl.N * pl.d >= (pl.group > 1 ? 4000000 : 5000000);
+  // With a run of items to each XCD the Q and dO of eight heads are in flight, next to which the memory-side cache (256 MB) has little room from 5 million
+  // elements a head on (4 million with grouped heads); with all XCDs on one head it has room at any length.  Runs are better all the same, but for few
+  // heads, of which they leave an XCD less than a whole one.  Whole call, ms for runs / one head, not causal, d = 128: 5 heads x 60000 tokens 8.92 / 10.0, 12 x 40000 9.52 / 10.6,
+  // 40 x 75600 116 / 125, single level 8 x 42000 5.22 / 5.46; 64-row blocks 16 x 40000 7.90 / 9.05; d = 64 6 x 100000 15.0 / 16.7, 32 x 131072 127 / 135; grouped 28 x 32000
+  // 7.48 / 8.45, 8 x 40000 6.20 / 7.17.  One head: 1 x 40000 0.929 / 0.924, 2 x 100000 in a single level 8.04 / 7.55, d = 64 4 x 120000 11.4 / 11.0 (2 x 40000 1.61 / 1.63).
+  a.one_head = !pl.causal && pl.B * pl.Hq <= 4 && (int64_t)pl.N * pl.d >= (pl.group > 1 ? 4000000 : 5000000);
   a.split = dkv_split(pl);
   int64_t off = 0;
   for (int h = 0; h < PSA_MAX_LEVELS + 2; ++h) { a.lvl_off[h] = pl.lvl_off[h]; a.glvl_off[h] = 0; }
