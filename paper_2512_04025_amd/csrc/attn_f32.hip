@@ -4,7 +4,7 @@
 // (psa_dev.h), and a product of two is six products of planes on v_mfma_f32_32x32x16_bf16: 192 cycles of the matrix pipe for
 // 16 channels where v_mfma_f32_32x32x2_f32 needs 512.  A bfloat16 operand is one plane, the weights are three either way.
 // In S the products of the leading planes and all others are two sums that are added at the end; error against 64 bits
-// of 12 heads x 4680 tokens 3.9e-7 (float32 instructions) -> 3.3e-7, of 2 x 1024 at d = 64 1.4e-7 -> 1.1e-7.
+// of 12 heads x 4680 tokens 4.1e-7 (float32 instructions) -> 1.0e-7, of 2 x 1024 at d = 64 1.4e-7 -> 0.9e-7, of lse 4.8e-8 -> 2.4e-8.
 //
 // What bounds it: 12 heads x 4680 tokens, d = 128, a fifth of the keys: a wavefront issues about 830 vector instructions a
 // tile (72 conversions and what belongs to them, addresses, softmax) next to 96 MFMAs, two wavefronts on a SIMD: the vector port is
@@ -21,8 +21,8 @@
 // stream of keys, and there are 4 / TEAM such teams over the SAME 32 * TEAM rows, each taking every
 // (4 / TEAM)-th tile of the row's list; their (maximum, sum, output) are merged through LDS at the end.
 //
-// Measured (pyramid and block lists included), products on v_mfma_f32_32x32x2_f32 -> here: 12 heads x 4680 tokens, d = 128, a fifth of the
-// keys 353 -> 205 us, x 1000 49 -> 38, x 6000 at d = 64 430 -> 227; causal 2 x 2435 154 -> 97; 4 x 3433 at d = 64 81 -> 53.
+// Measured (pyramid and block lists included, a quarter of the keys), products on v_mfma_f32_32x32x2_f32 -> here: 12 heads x 4680 tokens, d = 128,
+// a fifth of the keys 353 -> 215 us, x 1000 57 -> 39, x 6000 at d = 64 527 -> 277; causal 2 x 2435 69 -> 48; 4 x 3433 at d = 64 87 -> 59.
 #include <math.h>
 
 #include "psa_dev.h"
@@ -262,8 +262,14 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
 #pragma unroll
       for (int v = 0; v < 16; ++v) sc[v] = __builtin_amdgcn_exp2f(fmaf(sc[v], a.scale_lo, fmaf(sc[v], a.scale_hi, shift)));
     }
+    float sum[8];                                        // pairwise: l is rounded once a tile, the parts at their own size
 #pragma unroll
-    for (int v = 0; v < 16; ++v) l += sc[v];
+    for (int v = 0; v < 8; ++v) sum[v] = sc[2 * v] + sc[2 * v + 1];
+#pragma unroll
+    for (int w = 1; w < 8; w *= 2)
+#pragma unroll
+      for (int v = 0; v < 8; v += 2 * w) sum[v] += sum[v + w];
+    l += sum[0];
   };
   // a team of one wavefront owns its buffer: its LDS operations complete in order, nothing to wait for
   auto barrier = [&]() __attribute__((always_inline)) {
@@ -369,8 +375,8 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
       }
       const int trow = hf * 4 + ((lane & 15) >> 2);
       const uint32_t taddr = (uint32_t)(trow * ROWB + (((((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) ^ row_swizzle32<D>(trow)) << 4) + (lane & 1) * 8);
-      auto read_v = [&](bf16x8 (&dst)[NPL], auto tag) __attribute__((always_inline)) {   // 16 keys j / MD, channels (j % MD) * 32 ..
-        constexpr int j = decltype(tag)::value, down = (j / MD) * 16 * ROWB, md = j % MD;
+      auto read_v = [&](bf16x8 (&dst)[NPL], auto tag) __attribute__((always_inline)) {   // 16 keys j % 2, channels (j / 2) * 32 ..
+        constexpr int j = decltype(tag)::value, down = (j % 2) * 16 * ROWB, md = j / 2;
         unsigned char *at = Vs + flip<md * 64>(taddr), *at8 = Vs + flip<(md * 64) ^ 32>(taddr);   // (eight rows further down the swizzle differs in one bit)
 #pragma unroll
         for (int pl = 0; pl < NPL; ++pl) {
@@ -379,20 +385,28 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
           dst[pl] = __builtin_bit_cast(bf16x8, (f32_s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
         }
       };
-      bf16x8 fr[2][NPL];
-      read_v(fr[0], std::integral_constant<int, 0>{});
+      // The tile's twelve products for 32 channels are summed from zero and join o in one addition: twelve roundings a tile at the size of o made
+      // the error against 64 bits of causal 12 heads x 2634 tokens 3.5e-7, where one makes it 1.1e-7 (float32 instructions 2.5e-7).  It costs 223 -> 240 us at
+      // 12 heads x 4680 tokens: `part` takes the registers of a second set of V fragments, the other wavefront of the SIMD covers their loads.
+      bf16x8 va[NPL];
+      f32x16 part;
       each<2 * MD>([&](auto tag) __attribute__((always_inline)) {
-        constexpr int j = decltype(tag)::value, f = j / MD, md = j % MD;
-        if constexpr (j + 1 < 2 * MD) read_v(fr[(j + 1) & 1], std::integral_constant<int, j + 1>{});
-        const bf16x8(&va)[NPL] = fr[j & 1];
-        if constexpr (NPL == 3) o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[2], p[0][f], o[md], 0, 0, 0);
-        o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[0], p[2][f], o[md], 0, 0, 0);
+        constexpr int j = decltype(tag)::value, f = j % 2, md = j / 2;
+        read_v(va, tag);
+        if constexpr (f == 0)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) part[v] = 0.f;
+        if constexpr (NPL == 3) part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[2], p[0][f], part, 0, 0, 0);
+        part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[0], p[2][f], part, 0, 0, 0);
         if constexpr (NPL == 3) {
-          o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[1], p[1][f], o[md], 0, 0, 0);
-          o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[1], p[0][f], o[md], 0, 0, 0);
+          part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[1], p[1][f], part, 0, 0, 0);
+          part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[1], p[0][f], part, 0, 0, 0);
         }
-        o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[0], p[1][f], o[md], 0, 0, 0);
-        o[md] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[0], p[0][f], o[md], 0, 0, 0);
+        part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[0], p[1][f], part, 0, 0, 0);
+        part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[0], p[0][f], part, 0, 0, 0);
+        if constexpr (f == 1)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) o[md][v] += part[v];
         __builtin_amdgcn_sched_barrier(0x7);             // (arithmetic may pass: the next weights' planes, addresses; 237 -> 228 us at 12 heads x 4680 tokens)
       });
     }
@@ -492,7 +506,11 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
     }
     const float inv = 1.f / ll;                          // no visible key at all: NaN
     Four<T>::store(O + (qhead * a.N + row0 + r) * D + c, acc * inv);
-    if (lse && c == 0) lse[qhead * a.N + row0 + r] = fmaf(mm, 0.69314718055994531f, logf(ll));
+    if (lse && c == 0) {
+      int e;                                             // the sum's power of two joins the reference: ln 2 in two parts, one rounding at the size of lse
+      const float f = frexpf(ll, &e), w = mm + (float)e;
+      lse[qhead * a.N + row0 + r] = fmaf(w, 0.693145751953125f, fmaf(w, 1.42860677e-6f, logf(f)));
+    }
   }
 }
 
