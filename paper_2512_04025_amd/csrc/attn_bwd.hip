@@ -9,8 +9,8 @@
 // float32 and the bfloat16 shapes that attn_bwd_mfma.hip does not take:
 //   bwd_dq_kernel   one workgroup per 32, 64 or 128 query rows, walking the row's level-sorted block list; also
 //                   leaves D = dO . O per query row for the next kernel
-//   bwd_dkv_kernel  one workgroup per (key head, up to 32 pooled keys of a block, level), walking the column
-//                   of the level map; writes the gradient of every pooled token of every level (fp32)
+//   bwd_dkv_kernel  one workgroup (short launches: several, see bwd_parts) per (key head, up to 32 pooled keys of a block, level), walking
+//                   the column of the level map; writes the gradient of every pooled token of every level (fp32)
 //   unpool_kernel   dK, dV = sum over the levels of the pooled gradients / c_g
 // The products run on v_mfma_f32_32x32x2_f32 and are bound by its rate (64 FLOP per cycle and SIMD); the
 // operands of a 32 x 32 tile are read from LDS in an eighth of that time, so tiles are staged through registers

@@ -388,7 +388,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_mfma_kernel(const
   }
 }
 
-// One workgroup per (64 adjacent pooled keys, QUERY head, level): the query heads that share a key
+// One workgroup (short launches: a few, see dkv_split) per (64 adjacent pooled keys, QUERY head, level): the query heads that share a key
 // head each write a partial gradient of their own (added up when the levels are folded back into dK, dV),
 // so that a key block which every query block uses is not one workgroup's walk over the whole group.
 // A block of 128 pooled keys is shared by two workgroups; smaller blocks are packed to a workgroup (at most 32).
