@@ -141,7 +141,7 @@ void bwd_dq_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* __
   int* cnt_s = reinterpret_cast<int*>(reinterpret_cast<unsigned char*>(fsm) + S::OFF_LIST);
   uint16_t* list_s = reinterpret_cast<uint16_t*>(cnt_s + PSA_MAX_LEVELS);
   if (M) {                                               // (short rows, see lists_in_kernel)
-    row_lists<4>(M + srow * a.nk, a.nk, a.H, false, list_s, cnt_s, wave, lane);
+    row_lists<4>(M + srow * a.nk, a.nk, a.H, list_s, cnt_s, wave, lane);
     __syncthreads();
   }
   struct Tile { int h, tl, ntl, nblk, start; bool ok; };

@@ -175,7 +175,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_dq_mfma_kernel(const
   // (in LDS: read from memory at a change of level it would wait for the rows that are under way)
   int* my_cnt = reinterpret_cast<int*>(smem + OFF_CNT);
   uint16_t* list_s = reinterpret_cast<uint16_t*>(smem + OFF_LIST);
-  if (M) row_lists<4>(M + srow * a.nk, a.nk, a.H, false, list_s, my_cnt, wave, lane);   // (short rows, see lists_in_kernel)
+  if (M) row_lists<4>(M + srow * a.nk, a.nk, a.H, list_s, my_cnt, wave, lane);   // (short rows, see lists_in_kernel)
   else if (tid < a.H) my_cnt[tid] = cnt[srow * CNT_STRIDE + tid];
   __syncthreads();
 

@@ -138,7 +138,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
   const uint16_t* my_idx = idx + srow * a.nk;
   const int32_t* my_cnt = cnt + srow * CNT_STRIDE;
   if (own_list) {
-    row_lists<4>(M + srow * a.nk, a.nk, a.H, false, list_s, cnt_s, wave, lane);
+    row_lists<4>(M + srow * a.nk, a.nk, a.H, list_s, cnt_s, wave, lane);
     __syncthreads();
   }
   const int H = dense ? 1 : a.H;

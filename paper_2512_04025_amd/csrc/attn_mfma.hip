@@ -84,7 +84,7 @@ struct LevelState {
 // V(t)) a load has half a step to arrive instead of one and a half, but a workgroup's LDS is half as large and one more wavefront
 // fits on every SIMD: a lone wavefront issues for 1400 of the 2100 cycles that a 32-column tile took and waits for the rest.  Pyramid and attention, 12 heads,
 // a fifth of the keys, us for two buffers / one (both with the work order below): 32-row blocks d = 128 x 4000 tokens 78 / 59, x 9000 266 / 203, x 18000 799 / 651,
-// x 32760 (back and forth, see the list) 2290 / 2250; d = 64 x 6000 81 / 69, x 24000 658 / 612; 64-row blocks d = 128 x 6000 105 / 91, x 13000 357 / 312, x 24000 998 / 916.
+// x 32760 2330 (one head at a time) / 2285; d = 64 x 6000 81 / 69, x 24000 658 / 612; 64-row blocks d = 128 x 6000 105 / 91, x 13000 357 / 312, x 24000 998 / 916.
 constexpr int most_waves(int d, int nw, bool sc, int bn, int bufs) {
   return bn == 64 ? (d == 64 ? 3 : 2) : bufs == 2 ? (d == 64 ? nw + 1 : nw) : d == 64 ? nw + 2 : sc ? nw + 1 : 2;
 }
@@ -113,8 +113,6 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   // Full-size workgroups on shapes whose load instructions never straddle a pooled block read their
   // load plan from per-tile descriptors made by lists_kernel instead of deriving it per tile.
   constexpr bool DESC = SC && NW == 4;
-  constexpr bool BACK = BUFS == 1 && NW == 1 && D == 128;
-  constexpr int GENERATION = 32 * 4 * most_waves(D, NW, SC, BN, BUFS) / NW;   // workgroups of an XCD that run at one time
   static_assert(BN == 64 || (BN == 32 && NW < 4), "tile width");
   static_assert(NINST % NW == 0, "tile rows must split evenly over the wavefronts");
   static_assert(MPC * NB == NPAIR, "chunking of the softmax work");
@@ -160,13 +158,12 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   const int64_t srow = qhead * a.nq + i;
   const uint16_t* my_idx = idx + srow * a.nk;
   const int32_t* my_cnt = cnt + srow * CNT_STRIDE;
-  const bool back = BACK && !a.causal && (((int)(blockIdx.x >> 3) / GENERATION) & 1);
 
   // ---- totals and the block list into LDS.  With a level map the workgroup makes the list itself (short rows, see lists_in_kernel).
   int* cnt_s = reinterpret_cast<int*>(smem + OFF_CNT);
   const bool own_list = !DESC && M;
   if (own_list) {
-    row_lists<NW>(M + srow * a.nk, a.nk, a.H, back, list, cnt_s, wave, lane);
+    row_lists<NW>(M + srow * a.nk, a.nk, a.H, list, cnt_s, wave, lane);
     __syncthreads();
   }
   auto kept = [&](int h) __attribute__((always_inline)) -> int { return own_list ? __builtin_amdgcn_readfirstlane(cnt_s[h - 1]) : my_cnt[h - 1]; };
@@ -177,19 +174,10 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
     total_blocks += nb;
     total_tiles += ((nb << lg_th) + BN - 1) >> LG_BN;
   }
-  // Where the rows in flight on an XCD outgrow its L2 (d = 128, 32-row blocks, not causal) every second generation of workgroups walks its lists backwards:
-  // a workgroup that follows one which has just reached the end of the sequence begins where that one's neighbours still are.  12 heads x 24000 tokens
-  // 1260 -> 1215 us, x 32760 2430 -> 2260, 4 x 30000 730 -> 638; no change at 18000, none at d = 64 or with 64-row blocks.
-  if (back && !own_list) {
-    int first = 0;
-    for (int h = 1; h <= a.H; ++h) {
-      const int nb = my_cnt[h - 1];
-      for (int x = tid; x < nb; x += NT) list[first + x] = my_idx[first + nb - 1 - x];
-      first += nb;
-    }
-  } else if (!own_list) {
+  // (In the order of the keys for every workgroup: walks that turn round with the workgroup's place gain 4 % at some sizes, 12 heads x 32760 tokens 2290 -> 2180 us, nothing or 2 %
+  // less at others, and give a head other bits behind other heads; turned by the query block's number they lose up to 25 %, 6 x 50000 3260 -> 4000.)
+  if (!own_list)
     for (int x = tid; x < total_blocks; x += NT) list[x] = my_idx[x];
-  }
   {  // tile buffers start as zeros (a lane whose source row is out of range was seen to store zeros, but
      // nothing here relies on that: an out-of-range row may as well keep what its slot held)
     const u32x4 z = {0u, 0u, 0u, 0u};

@@ -140,11 +140,11 @@ __device__ __forceinline__ Split2 split2(float a, float b, float& rest) {
 
 __device__ __forceinline__ int ilog2(int x) { return 31 - __clz(x); }
 
-// A row of the level map -> its kept blocks grouped by level (ascending inside a level, descending with `back`) and the number per level, in LDS, by
+// A row of the level map -> its kept blocks grouped by level (ascending inside a level) and the number per level, in LDS, by
 // the NW wavefronts of a workgroup (which then wait for each other).  Rows of at most ROW_LISTS_NK blocks.
 constexpr int ROW_LISTS_NK = 128;
 template <int NW>
-__device__ __forceinline__ void row_lists(const uint8_t* __restrict__ m, int nk, int H, bool back, uint16_t* list, int* cnt, int wave, int lane) {
+__device__ __forceinline__ void row_lists(const uint8_t* __restrict__ m, int nk, int H, uint16_t* list, int* cnt, int wave, int lane) {
   int lv[ROW_LISTS_NK / 64];
 #pragma unroll
   for (int c = 0; c < ROW_LISTS_NK / 64; ++c) lv[c] = c * 64 + lane < nk ? (int)m[c * 64 + lane] : 0;
@@ -161,7 +161,7 @@ __device__ __forceinline__ void row_lists(const uint8_t* __restrict__ m, int nk,
     if (NW == 1 || h % NW == wave) {
 #pragma unroll
       for (int c = 0; c < ROW_LISTS_NK / 64; ++c)
-        if (lv[c] == h) list[first + (back ? n - 1 - before[c] : before[c])] = (uint16_t)(c * 64 + lane);
+        if (lv[c] == h) list[first + before[c]] = (uint16_t)(c * 64 + lane);
       if (lane == 0) cnt[h - 1] = n;
     }
     first += n;

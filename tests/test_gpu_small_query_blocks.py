@@ -73,8 +73,8 @@ def test_attention_small_query_blocks_on_an_idle_chip(bq, N, d, bk, levels, caus
 @pytest.mark.parametrize("bq,d", [(32, 128), (32, 64), (64, 128), (64, 64)])
 @pytest.mark.parametrize("bk,levels", [(32, 3), (16, 4)])
 def test_attention_small_query_blocks_on_a_full_chip(bq, d, bk, levels):
-    """More workgroups than run at one time: single buffers and, for 32-row blocks at d = 128, lists that are walked backwards
-    from the 257th workgroup of an XCD on (heads 3 and 4 of 40 lie before and behind it)."""
+    """More workgroups than run at one time (heads 3 and 4 of 40): one buffer each for K and V, but two at (64, 64), whose 2640
+    workgroups would leave more of the last of two rounds of 2048 empty than of two of 1536."""
     import torch
     N, Hq = (2100 if bq == 32 else 4200) + 13, 40
     op = orc.Params(B=1, Hq=Hq, Hkv=1, N=N, d=d, bq=bq, bk=bk, levels=levels, dtype="bf16", sq=8, sk=1)
@@ -96,3 +96,26 @@ def test_attention_small_query_blocks_on_a_full_chip(bq, d, bk, levels):
     assert not np.isnan(got).any()
     assert np.abs(got[:, 3:5] - O).max() <= 2e-2 and rel_l2(got[:, 3:5], O) <= 1e-2
     assert np.abs(buf.lse.cpu().numpy()[:, 3:5] - lse).max() <= 2e-2
+
+
+@pytest.mark.parametrize("bq,d", [(32, 128), (32, 64), (64, 128), (64, 64)])
+def test_a_heads_result_does_not_depend_on_the_heads_before_it(bq, d):
+    """The last of twelve heads alone and behind the others, the same bits: rows of more query blocks than an XCD runs at one time,
+    enough heads in either call that both take the kernel of 32-column tiles."""
+    import torch
+    N = 260 * bq + 5
+    host = si.random_qkv(2, 1, 12, 12, N, d, "bf16")
+    nq, nk = -(-N // bq), -(-N // 32)
+    M = torch.from_numpy((np.random.default_rng(3).random((1, 12, nq, nk)) < 0.1).astype(np.uint8)).cuda()
+    M[..., 0] = 1
+    outs = []
+    for heads in (slice(0, 12), slice(6, 12)):
+        Hq = heads.stop - heads.start
+        op = orc.Params(B=1, Hq=Hq, Hkv=Hq, N=N, d=d, bq=bq, bk=32, levels=1, dtype="bf16", sq=8, sk=8)
+        gp = gpu_params(op)
+        buf = Buffers(gp)
+        psa.psa_attention_fwd(gp, *(to_dev(x[:, heads], "bf16") for x in host), None, None, M[:, heads].contiguous(), buf.O, buf.scratch, lse=buf.lse)
+        torch.cuda.synchronize()
+        outs.append((buf.O[:, -6:], buf.lse[:, -6:]))
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
