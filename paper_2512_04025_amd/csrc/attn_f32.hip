@@ -23,6 +23,7 @@
 //
 // Measured (pyramid and block lists included, a quarter of the keys), products on v_mfma_f32_32x32x2_f32 -> here: 12 heads x 4680 tokens, d = 128,
 // a fifth of the keys 353 -> 215 us, x 1000 57 -> 39, x 6000 at d = 64 527 -> 277; causal 2 x 2435 69 -> 48; 4 x 3433 at d = 64 87 -> 59.
+#include <limits.h>
 #include <math.h>
 
 #include "psa_dev.h"
@@ -43,6 +44,7 @@ template <> struct Planes<float> { static constexpr int N = 3; };
 
 // A tile: its planes one after the other, rows of D bfloat16, 16-byte chunks at chunk ^ row_swizzle32(row).  A team of one wavefront puts V
 // where K was (it has nobody to wait for), so that four such teams fit the LDS at d = 128.
+constexpr int LATER_TILES = 2048;
 template <typename T, int D, int TEAM>
 struct F32Shape {
   static constexpr int KS = 4 / TEAM, ROWS = 32 * TEAM, PITCH = D + 4, NPL = Planes<T>::N;
@@ -51,7 +53,8 @@ struct F32Shape {
   static constexpr int TILEB = OFF_TAB + TEAM * 256;                   // K | V | (term [32] | last token [32]) per wavefront
   static constexpr int MERGEB = 4 * (2 * KS * ROWS + KS * ROWS * PITCH);   // m, l | O of every team
   static constexpr int OFF_FLAG = KS * TILEB;                          // behind the teams' tiles: one flag per wavefront
-  static constexpr int OFF_LIST = OFF_FLAG + 16;                       // blocks per level | list (rows whose list the kernel makes)
+  static constexpr int OFF_LATER = OFF_FLAG + 16;                      // a bit per tile and wavefront: left for the end
+  static constexpr int OFF_LIST = OFF_LATER + 4 * LATER_TILES / 8;                        // blocks per level | list (rows whose list the kernel makes)
   static constexpr int END = OFF_LIST + 4 * PSA_MAX_LEVELS + 2 * ROW_LISTS_NK;
   static constexpr size_t BYTES = END > MERGEB ? END : MERGEB;
 };
@@ -94,7 +97,8 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
   unsigned char* Vs = Ks + S::OFF_V;
   float* term_s = reinterpret_cast<float*>(Ks + S::OFF_TAB + wr * 256);   // irregular tiles: additive term per key, its last token
   int* last_s = reinterpret_cast<int*>(term_s + 32);
-  int* flag_s = reinterpret_cast<int*>(fsm + S::OFF_FLAG);               // did the wavefront meet a value that is not finite
+  int* flag_s = reinterpret_cast<int*>(fsm + S::OFF_FLAG);               // did the wavefront stage a value of V that is not finite
+  uint32_t* later_s = reinterpret_cast<uint32_t*>(fsm + S::OFF_LATER) + wave * (LATER_TILES / 32);
 
   const bool own_list = M != nullptr, dense = !own_list && idx == nullptr;
   int* cnt_s = reinterpret_cast<int*>(fsm + S::OFF_LIST);
@@ -201,8 +205,8 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
     }
     return !(rest == rest);
   };
-  // scores of tile t -> weights of its keys for this lane's row; reference, sum and output follow
-  auto weights = [&](const Tile& t, int prow, f32x16& sc) __attribute__((always_inline)) {
+  // scores of tile t -> weights of its keys for this lane's row and their sum; reference, sum and output so far follow
+  auto weights = [&](const Tile& t, int prow, f32x16& sc) __attribute__((always_inline)) -> float {
     // log2 of the tokens under a key: one constant, unless the tile holds keys that do not exist, cover fewer tokens than others of the level
     // or (causal) are hidden from a row of this wavefront
     const int hm1 = t.h - 1;
@@ -269,7 +273,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
     for (int w = 1; w < 8; w *= 2)
 #pragma unroll
       for (int v = 0; v < 8; v += 2 * w) sum[v] += sum[v + w];
-    l += sum[0];
+    return sum[0];
   };
   // a team of one wavefront owns its buffer: its LDS operations complete in order, nothing to wait for
   auto barrier = [&]() __attribute__((always_inline)) {
@@ -297,9 +301,12 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
     if (nxt.ok) id = block_of(nxt);
     deposit(Ks, pc);
   }
+#pragma unroll
+  for (int x = 0; x < LATER_TILES / 32; x += 64) if (x + lane < LATER_TILES / 32) later_s[x + lane] = 0u;
   barrier();
-  bool finite = true;
-  for (int step = 0; step < total; step += KS) {
+  int n = 0, later_from = INT_MAX;                       // tiles of the team so far; the first of those that are all left for the end
+  bool later = false;
+  for (int step = 0; step < total; step += KS, ++n) {
     const int pn = row_of(nxt, id);
     Tile nn = nxt;
     if (nxt.ok) {
@@ -309,6 +316,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
     }
     if (cur.ok) fetch(V, Vp, cur, pc);
     f32x16 sc;
+    float sum = 0.f;
     bool bad = false;
     if (cur.ok) {
       // S: the large terms in one sum, the others in another that is added at the end (fewer roundings than one chain of D products).  One k-step's
@@ -346,18 +354,25 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
         }
         bad = __any(!(fabsf(any) < INFINITY));           // a row or key that is not finite, or a product that overflows
       }
-      weights(cur, pc, sc);
-      bad |= (bool)__any(deposit(Vs, pc));
+      if (!bad) sum = weights(cur, pc, sc);
+      const bool bad_v = __any(deposit(Vs, pc));
+      if constexpr (TEAM == 1) bad |= bad_v;
+      else if (lane == 0) flag_s[wave] = bad_v ? 1 : 0;
     }
-    if (lane == 0) flag_s[wave] = bad ? 1 : 0;
     barrier();                                           // V rows in LDS; everyone is done with the K rows
-    int stop = 0;
+    if constexpr (TEAM > 1) {
+      int any = 0;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) stop |= TEAM == 1 && w != wave ? 0 : flag_s[w];
-    finite = __builtin_amdgcn_readfirstlane(stop) == 0;
-    if (!finite) break;
+      for (int w = 0; w < TEAM; ++w) any |= flag_s[team * TEAM + w];
+      bad |= __builtin_amdgcn_readfirstlane(any) != 0;
+    }
     if (nxt.ok) fetch(K, Kp, nxt, pn);
-    if (cur.ok) {
+    if (cur.ok && (bad || n >= later_from)) {
+      later = true;
+      if (n >= LATER_TILES) later_from = n < later_from ? n : later_from;
+      else if (lane == 0) later_s[n >> 5] |= 1u << (n & 31);
+    } else if (cur.ok) {
+      l += sum;
       bf16x8 p[3][2];                                    // planes of the weights: keys f * 16 .. as they stand in the registers
 #pragma unroll
       for (int f = 0; f < 2; ++f) {
@@ -416,58 +431,65 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
     pc = pn;
     nxt = nn;
   }
-  if (!finite) {
-    // A value that is not finite was met: the planes of an infinity give NaN where the product has a sign, and (causal) a row must not see 0 * inf of
-    // a key that is hidden from it.  The row's list is walked again from memory, S in float32, the outputs key by key on the vector unit (rare).
-    // (Of the workgroup or, where a team is a wavefront that waits for nobody, of the team.)
-    m = -INFINITY;
-    l = 0.f;
-#pragma unroll
-    for (int md = 0; md < MD; ++md)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) o[md][v] = 0.f;
-    Tile t = {1, team, 0, 0, 0, 0};
-    enter(t);
-    settle(t);
+  if (later) {
+    // Tiles with values that are not finite: the planes of an infinity give NaN where the product has a sign.  They are taken from memory in float32, at the end
+    // (a wavefront's sums do not ask for an order), since next to the planes in the loop above this would take registers from it (12 heads x 4680 tokens
+    // 229 -> 255 us with no such tile).
+    const int tiles = (total + KS - 1 - team) / KS;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll 1
-    while (t.ok) {
+    for (int x = 0; x < tiles; ++x) {
+      if (x < LATER_TILES ? !((__builtin_amdgcn_readfirstlane(later_s[x >> 5]) >> (x & 31)) & 1u) : x < later_from) continue;
+      Tile t = {1, team + x * KS, 0, 0, 0, 0};
+      enter(t);
+      settle(t);
       const int prow = row_of(t, block_of(t));
       f32x16 sc;
 #pragma unroll
       for (int v = 0; v < 16; ++v) sc[v] = 0.f;
       const T* krow = base_of(K, Kp, t) + (int64_t)(prow < 0 ? 0 : prow) * D + hf * 4;
       const T* qrow = Q + (qhead * a.N + (active ? row : row0)) * D + hf * 4;
-#pragma unroll 1
+#pragma unroll 4
       for (int c = 0; c < D; c += 8) {
-        f32x4 x = Four<T>::widen(Four<T>::load(krow + c)), y = Four<T>::widen(Four<T>::load(qrow + c));
-        if (prow < 0) x = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (!active) y = f32x4{0.f, 0.f, 0.f, 0.f};
+        f32x4 kk = Four<T>::widen(Four<T>::load(krow + c)), qq = Four<T>::widen(Four<T>::load(qrow + c));
+        if (prow < 0) kk = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (!active) qq = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], sc, 0, 0, 0);
+        for (int e = 0; e < 4; ++e) sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kk[e], qq[e], sc, 0, 0, 0);
       }
-      weights(t, prow, sc);
-      const T* vbase = base_of(V, Vp, t) + hf * 4;
+      l += weights(t, prow, sc);
+      const T* vbase = base_of(V, Vp, t);
+      if (a.causal && __any(prow >= (row0 + wr * 32 + 1) >> (t.h - 1))) {
+        // A row must not see 0 * inf of a key that is hidden from it: hidden keys are left out one by one, on the vector unit.
 #pragma unroll 1
-      for (int kk = 0; kk < 32; ++kk) {
-        const int vi = (kk >> 3) * 4 + (kk & 3), from = l32 + ((kk >> 2) & 1) * 32, pr = __shfl(prow, kk, 64);
-        if (pr < 0) continue;                            // no such key
-        float pv = 0.f;
+        for (int kk = 0; kk < 32; ++kk) {
+          const int vi = (kk >> 3) * 4 + (kk & 3), from = l32 + ((kk >> 2) & 1) * 32, pr = __shfl(prow, kk, 64);
+          if (pr < 0) continue;                          // no such key
+          float pv = 0.f;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) pv = v == vi ? sc[v] : pv;
-        pv = __shfl(pv, from, 64);
-        const int64_t end = ((int64_t)pr + 1) << (t.h - 1);
-        const bool hidden = a.causal && (end < a.N ? end : a.N) - 1 > row;
+          for (int v = 0; v < 16; ++v) pv = v == vi ? sc[v] : pv;
+          pv = __shfl(pv, from, 64);
+          const int64_t end = ((int64_t)pr + 1) << (t.h - 1);
+          const bool hidden = (end < a.N ? end : a.N) - 1 > row;
 #pragma unroll
-        for (int md = 0; md < MD; ++md)
+          for (int md = 0; md < MD; ++md)
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const f32x4 x = Four<T>::widen(Four<T>::load(vbase + (int64_t)pr * D + md * 32 + g * 8));
+            for (int g = 0; g < 4; ++g) {
+              const f32x4 y = Four<T>::widen(Four<T>::load(vbase + (int64_t)pr * D + md * 32 + g * 8 + hf * 4));
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[md][g * 4 + e] = hidden ? o[md][g * 4 + e] : fmaf(pv, x[e], o[md][g * 4 + e]);
-          }
+              for (int e = 0; e < 4; ++e) o[md][g * 4 + e] = hidden ? o[md][g * 4 + e] : fmaf(pv, y[e], o[md][g * 4 + e]);
+            }
+        }
+      } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {                   // the key of register v, and the one four rows further down
+          const int pr = __shfl(prow, (v >> 2) * 8 + hf * 4 + (v & 3), 64);
+          const T* vrow = vbase + (int64_t)(pr < 0 ? 0 : pr) * D + l32;
+#pragma unroll
+          for (int md = 0; md < MD; ++md)
+            o[md] = __builtin_amdgcn_mfma_f32_32x32x2f32(pr < 0 ? 0.f : Elem<T>::to_f32(vrow[md * 32]), sc[v], o[md], 0, 0, 0);
+        }
       }
-      t.tl += KS;
-      settle(t);
     }
   }
 

@@ -1,0 +1,65 @@
+"""float32 attention and dense attention: what one value that is not finite costs the rest of a call.
+
+Tolerance: the fp32 bar of the parity tests."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+from oracle import psa_oracle as orc
+from tests.psa_testlib import Buffers, from_dev, gpu_params, to_dev
+
+pytestmark = pytest.mark.gpu
+
+psa = pytest.importorskip("paper_2512_04025_amd")
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("what", ["key", "value"])
+def test_one_infinity_does_not_slow_the_call(what, causal):
+    """The first token's key or value is infinite in one channel and every row keeps its block: one tile of a row's list.  The
+    two calls are timed in turn, the shortest of 20 each, so that what else the machine does drops out."""
+    import torch
+    op = orc.Params(B=1, Hq=12, Hkv=12, N=4680, d=128, bq=128, bk=64, levels=4, dtype="f32", causal=causal, sq=8, sk=8)
+    gp = gpu_params(op)
+    Q, K, V = (to_dev(x, "f32") for x in si.random_qkv(6, 1, 12, 12, op.N, 128, "f32"))
+    rng = np.random.default_rng(7)
+    vis = orc.block_visibility(op)
+    M = rng.integers(1, 5, size=(1, 12, op.nq, op.nk)) * (rng.random((1, 12, op.nq, op.nk)) < 0.4)
+    M[..., 0] = 1
+    M = torch.from_numpy(np.where(vis[None, None] == 0, 0, np.where(vis[None, None] == 2, 1, M)).astype(np.uint8)).cuda()
+    problems = []
+    for bad in (False, True):
+        k, v = K.clone(), V.clone()
+        if bad:
+            (k if what == "key" else v)[:, :, 0, 0] = float("inf")
+        buf = Buffers(gp)
+        psa.psa_build_pyramid(gp, k, v, buf.Kpyr, buf.Vpyr)
+        problems.append((k, v, buf))
+    best = [float("inf")] * 2
+    for _ in range(20):
+        for x, (k, v, buf) in enumerate(problems):
+            start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            start.record()
+            psa.psa_attention_fwd(gp, Q, k, v, buf.Kpyr, buf.Vpyr, M, buf.O, buf.scratch)
+            end.record()
+            torch.cuda.synchronize()
+            best[x] = min(best[x], start.elapsed_time(end))
+    assert best[1] <= 1.5 * best[0]
+
+
+def test_infinities_far_down_a_row():
+    """A row of 2195 tiles of 32 keys: infinite values in the first tile, in the 2063rd and in the last.  The channels without one stay
+    what they are, here of three rows in torch at 64 bits."""
+    import torch
+    op = orc.Params(B=1, Hq=1, Hkv=1, N=70219, d=128, bq=128, bk=64, levels=1, dtype="f32", sq=8, sk=8)
+    Q, K, V = (to_dev(x, "f32") for x in si.random_qkv(8, 1, 1, 1, op.N, 128, "f32"))
+    for token, channel in ((3, 5), (66007, 6), (70218, 7)):
+        V[:, :, token, channel] = float("inf")
+    O = torch.full_like(Q, float("nan"))
+    psa.psa_dense_ref(gpu_params(op), Q, K, V, O)
+    torch.cuda.synchronize()
+    assert bool((O[..., 5:8] == float("inf")).all()) and bool(torch.isfinite(O[..., 8:]).all())
+    rows = torch.tensor([0, 35000, 70218], device="cuda")
+    P = torch.softmax(Q[0, 0, rows].double() @ K[0, 0].double().T.contiguous() / np.sqrt(128), 1)
+    want = P @ V[0, 0, :, 8:].double()
+    assert float((O[0, 0, rows, 8:].double() - want).abs().max()) <= 1e-5
