@@ -246,8 +246,8 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
       tmax = fmaf(tmax, a.scale_hi, (float)hm1);
     }
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-    // The reference is a whole number, so that changing it rounds nothing, and is raised when a weight would pass 2^8.
-    if (__any(tmax - m > 8.f)) {
+    // The reference is a whole number, so that changing it rounds nothing, and no weight is more than one: values up to the largest float32 can be summed.
+    if (__any(tmax > m)) {
       const float mn = fmaxf(m, ceilf(tmax));
       const float alpha = mn == -INFINITY ? 1.f : exp2f(m - mn);      // m = -inf: 0
       l *= alpha;

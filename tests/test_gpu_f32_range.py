@@ -1,6 +1,8 @@
-"""float32 attention and dense attention: what one value that is not finite costs the rest of a call.
+"""float32 attention and dense attention over the range of float32: values near its largest, and what one value that is not finite
+costs the rest of a call.
 
-Tolerance: the fp32 bar of the parity tests."""
+Tolerance: the fp32 bar of the parity tests, relative to the largest entry of the result (which is of the order of the scaled
+operand), unless a test derives its own."""
 import numpy as np
 import pytest
 
@@ -11,6 +13,56 @@ from tests.psa_testlib import Buffers, from_dev, gpu_params, to_dev
 pytestmark = pytest.mark.gpu
 
 psa = pytest.importorskip("paper_2512_04025_amd")
+
+TEAMS = [(289, 2, 64), (993, 12, 64), (993, 32, 128)]       # (tokens, heads, block): teams of one, two and four wavefronts
+
+
+def _run(op, Q, K, V):
+    """Every block kept at level 1: the sparse call and the dense one, which are the same attention."""
+    import torch
+    gp = gpu_params(op)
+    buf = Buffers(gp)
+    buf.M.fill_(1)
+    dev = [to_dev(x, "f32") for x in (Q, K, V)]
+    out = []
+    for call in ("sparse", "dense"):
+        buf.O.fill_(float("nan"))
+        if call == "sparse":
+            psa.psa_attention_fwd(gp, *dev, None, None, buf.M, buf.O, buf.scratch, lse=buf.lse)
+        else:
+            psa.psa_dense_ref(gp, *dev, buf.O, lse=buf.lse)
+        torch.cuda.synchronize()
+        out.append((from_dev(buf.O, "f32"), buf.lse.cpu().numpy()))
+    return out
+
+
+def _single_level(N, Hq, d, bq):
+    return orc.Params(B=1, Hq=Hq, Hkv=1, N=N, d=d, bq=bq, bk=32, levels=1, dtype="f32", sq=8, sk=1)
+
+
+def _scored(op, scores, seed):
+    """Q and K whose scores are `scores` (natural, one per key) for every row, all in the first channel."""
+    Q = np.zeros((1, op.Hq, op.N, op.d), np.float32)
+    K = np.zeros((1, 1, op.N, op.d), np.float32)
+    Q[..., 0] = 1
+    K[0, 0, :, 0] = scores * np.sqrt(op.d)
+    V = np.random.default_rng(seed).uniform(0.5, 1.0, K.shape)
+    return Q, K, V
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("N,Hq,bq", TEAMS)
+def test_values_whose_weighted_sum_just_fits(N, Hq, bq, d):
+    """128 keys of value 0, then keys of almost 2^8 times their weight and values whose plain sum is a little below 2^127:
+    finite as long as no weight on the way is more than one."""
+    op = _single_level(N, Hq, d, bq)
+    Q, K, V = _scored(op, np.where(np.arange(N) < 128, 0.0, 7.9 * np.log(2)), 1)
+    V = (V * 2.0 ** (127 - np.ceil(np.log2(N)))).astype(np.float32)
+    V[:, :, :128] = 0
+    want, lse = orc.dense_attention(*(x.astype(np.float64) for x in (Q, K, V)), op)
+    for got, l in _run(op, Q, K, V):
+        assert np.abs(got - want).max() <= 1e-5 * np.abs(want).max()
+        assert np.abs(l - lse).max() <= 1e-4
 
 
 @pytest.mark.parametrize("causal", [False, True])
