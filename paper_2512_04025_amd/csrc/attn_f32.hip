@@ -59,22 +59,20 @@ struct F32Shape {
   static constexpr size_t BYTES = END > MERGEB ? END : MERGEB;
 };
 
-// Four consecutive elements as their planes: put(plane, its four bfloat16).  NaN comes back if one is not finite (0 times its remainder otherwise).
-template <typename F> __device__ __forceinline__ float to_planes(f32x4 x, F&& put) {
-  float rest = 0.f;
-  const Split2 a = split2(x[0], x[1], rest), b = split2(x[2], x[3], rest);
+// Four consecutive elements as their planes: put(plane, its four bfloat16); their leading planes' range is added to `range`.
+template <typename F> __device__ __forceinline__ void to_planes(f32x4 x, PairRange& range, F&& put) {
+  const Split2 a = split2(x[0], x[1]), b = split2(x[2], x[3]);
+  range.add(a.h);
+  range.add(b.h);
   put(0, u32x2{a.h, b.h});
   put(1, u32x2{a.m, b.m});
   put(2, u32x2{a.l, b.l});
-  return rest;
 }
-template <typename F> __device__ __forceinline__ float to_planes(Four<bf16_t>::raw x, F&& put) {
+template <typename F> __device__ __forceinline__ void to_planes(Four<bf16_t>::raw x, PairRange& range, F&& put) {
   const u32x2 w = __builtin_bit_cast(u32x2, x);
+  range.add(w[0]);
+  range.add(w[1]);
   put(0, w);
-  bool bad = false;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) bad |= (x[e] & 0x7f80u) == 0x7f80u;
-  return bad ? __builtin_nanf("") : 0.f;
 }
 
 typedef short f32_s16x4 __attribute__((ext_vector_type(4)));
@@ -97,7 +95,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
   unsigned char* Vs = Ks + S::OFF_V;
   float* term_s = reinterpret_cast<float*>(Ks + S::OFF_TAB + wr * 256);   // irregular tiles: additive term per key, its last token
   int* last_s = reinterpret_cast<int*>(term_s + 32);
-  int* flag_s = reinterpret_cast<int*>(fsm + S::OFF_FLAG);               // did the wavefront stage a value of V that is not finite
+  int* flag_s = reinterpret_cast<int*>(fsm + S::OFF_FLAG);               // what the wavefront staged of V: NOT_FINITE, SMALL
   uint32_t* later_s = reinterpret_cast<uint32_t*>(fsm + S::OFF_LATER) + wave * (LATER_TILES / 32);
 
   const bool own_list = M != nullptr, dense = !own_list && idx == nullptr;
@@ -115,6 +113,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
   const int row = row0 + wr * 32 + l32;
   const bool active = row < row_end;
 
+  PairRange q_range;
   bf16x8 q[NPL][KSTEPS];                                 // planes of channels ks * 16 + hf * 8 .. +7 of this lane's row
 #pragma unroll
   for (int ks = 0; ks < KSTEPS; ++ks) {
@@ -123,7 +122,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
     for (int u = 0; u < 2; ++u) {
       typename Four<T>::raw x = {0, 0, 0, 0};
       if (active) x = Four<T>::load(Q + (qhead * a.N + row) * D + ks * 16 + hf * 8 + u * 4);
-      to_planes(x, [&](int plane, u32x2 v) __attribute__((always_inline)) {
+      to_planes(x, q_range, [&](int plane, u32x2 v) __attribute__((always_inline)) {
         w[plane][2 * u] = v[0];
         w[plane][2 * u + 1] = v[1];
       });
@@ -189,21 +188,21 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
       reg[c] = Four<T>::load(base + (int64_t)__shfl(at, x / CPR, 64) * D + (x % CPR) * 4);
     }
   };
-  auto deposit = [&](unsigned char* tensor, int prow) __attribute__((always_inline)) -> bool {   // whether a value is not finite
+  auto deposit = [&](unsigned char* tensor, int prow) __attribute__((always_inline)) -> PairRange {
     const int x0 = place();
     if (__any(prow < 0)) {
 #pragma unroll
       for (int c = 0; c < NCH; ++c)
         if (__shfl(prow, (x0 + TT * c) / CPR, 64) < 0) reg[c] = typename Four<T>::raw{0, 0, 0, 0};
     }
-    float rest = 0.f;
+    PairRange range;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
       const int x = x0 + TT * c, r = x / CPR, ch = x % CPR;
       unsigned char* at = tensor + r * ROWB + (((ch >> 1) ^ row_swizzle32<D>(r)) << 4) + (ch & 1) * 8;
-      rest += to_planes(reg[c], [&](int plane, u32x2 v) __attribute__((always_inline)) { *reinterpret_cast<u32x2*>(at + plane * PLANEB) = v; });
+      to_planes(reg[c], range, [&](int plane, u32x2 v) __attribute__((always_inline)) { *reinterpret_cast<u32x2*>(at + plane * PLANEB) = v; });
     }
-    return !(rest == rest);
+    return range;
   };
   // scores of tile t -> weights of its keys for this lane's row and their sum; reference, sum and output so far follow
   auto weights = [&](const Tile& t, int prow, f32x16& sc) __attribute__((always_inline)) -> float {
@@ -281,6 +280,11 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
     else asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   };
 
+  // Of float32 operands below 2^-109 the planes may hold all but 2^-134.  Of keys this counts next to large queries only, of queries it is not asked whether
+  // there are large keys: such rows leave every tile for the end.  Of values it counts where the output is as small: SMALL is noted, and looked into at the end.
+  const bool far_q = NPL == 3 && __any(q_range.small() || q_range.large());
+  constexpr int NOT_FINITE = 1, SMALL = 2;
+  bool small_v = false;
   int total = 0;                                         // tiles of the row: the same for every team
   for (int h = 1; h <= H; ++h) {
     Tile t;
@@ -305,7 +309,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
   for (int x = 0; x < LATER_TILES / 32; x += 64) if (x + lane < LATER_TILES / 32) later_s[x + lane] = 0u;
   barrier();
   int n = 0, later_from = INT_MAX;                       // tiles of the team so far; the first of those that are all left for the end
-  bool later = false;
+  bool later = false, again = false;                     // there are such tiles; all are
   for (int step = 0; step < total; step += KS, ++n) {
     const int pn = row_of(nxt, id);
     Tile nn = nxt;
@@ -317,7 +321,8 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
     if (cur.ok) fetch(V, Vp, cur, pc);
     f32x16 sc;
     float sum = 0.f;
-    bool bad = false;
+    int v_state = 0;
+    bool bad = far_q;
     if (cur.ok) {
       // S: the large terms in one sum, the others in another that is added at the end (fewer roundings than one chain of D products).  One k-step's
       // fragments ahead of the products, no more.
@@ -352,35 +357,35 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
           sc[v] += low[v];
           any += sc[v];
         }
-        bad = __any(!(fabsf(any) < INFINITY));           // a row or key that is not finite, or a product that overflows
+        bad |= (bool)__any(!(fabsf(any) < INFINITY));          // a row or key that is not finite, or a product that overflows
       }
       if (!bad) sum = weights(cur, pc, sc);
-      const bool bad_v = __any(deposit(Vs, pc));
-      if constexpr (TEAM == 1) bad |= bad_v;
-      else if (lane == 0) flag_s[wave] = bad_v ? 1 : 0;
+      const PairRange range = deposit(Vs, pc);
+      v_state = (__any(!range.finite()) ? NOT_FINITE : 0) | (NPL == 3 && __any(range.small()) ? SMALL : 0);
+      if (TEAM > 1 && lane == 0) flag_s[wave] = v_state;
     }
     barrier();                                           // V rows in LDS; everyone is done with the K rows
     if constexpr (TEAM > 1) {
-      int any = 0;
+      v_state = 0;
 #pragma unroll
-      for (int w = 0; w < TEAM; ++w) any |= flag_s[team * TEAM + w];
-      bad |= __builtin_amdgcn_readfirstlane(any) != 0;
+      for (int w = 0; w < TEAM; ++w) v_state |= flag_s[team * TEAM + w];
+      v_state = __builtin_amdgcn_readfirstlane(v_state);
     }
     if (nxt.ok) fetch(K, Kp, nxt, pn);
-    if (cur.ok && (bad || n >= later_from)) {
+    if (cur.ok && (bad || (v_state & NOT_FINITE) || n >= later_from)) {
       later = true;
       if (n >= LATER_TILES) later_from = n < later_from ? n : later_from;
       else if (lane == 0) later_s[n >> 5] |= 1u << (n & 31);
     } else if (cur.ok) {
       l += sum;
+      small_v |= v_state & SMALL;
       bf16x8 p[3][2];                                    // planes of the weights: keys f * 16 .. as they stand in the registers
 #pragma unroll
       for (int f = 0; f < 2; ++f) {
         u32x4 w[3];
-        float rest = 0.f;
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
-          const Split2 t = split2(sc[8 * f + 2 * x], sc[8 * f + 2 * x + 1], rest);
+          const Split2 t = split2(sc[8 * f + 2 * x], sc[8 * f + 2 * x + 1]);
           w[0][x] = t.h;
           w[1][x] = t.m;
           w[2][x] = t.l;
@@ -431,15 +436,32 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
     pc = pn;
     nxt = nn;
   }
+  if (small_v) {                                         // an output so small that 2^-134 of a value is more than 2^-25 of it: the whole row again, in float32
+    const float bar = (l + __shfl_xor(l, 32, 64)) * 0x1p-109f;
+    bool below = false;
+#pragma unroll
+    for (int md = 0; md < MD; ++md)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) below |= fabsf(o[md][v]) < bar;
+    if (__any(below)) {
+      later = again = true;
+      m = -INFINITY;
+      l = 0.f;
+#pragma unroll
+      for (int md = 0; md < MD; ++md)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[md][v] = 0.f;
+    }
+  }
   if (later) {
-    // Tiles with values that are not finite: the planes of an infinity give NaN where the product has a sign.  They are taken from memory in float32, at the end
-    // (a wavefront's sums do not ask for an order), since next to the planes in the loop above this would take registers from it (12 heads x 4680 tokens
-    // 229 -> 255 us with no such tile).
+    // Tiles with values that are not finite (the planes of an infinity give NaN where the product has a sign), and rows of small operands.  They are taken from memory in
+    // float32, at the end (a wavefront's sums do not ask for an order), since next to the planes in the loop above this would take registers from it (12 heads x 4680
+    // tokens 229 -> 255 us with no such tile).
     const int tiles = (total + KS - 1 - team) / KS;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll 1
     for (int x = 0; x < tiles; ++x) {
-      if (x < LATER_TILES ? !((__builtin_amdgcn_readfirstlane(later_s[x >> 5]) >> (x & 31)) & 1u) : x < later_from) continue;
+      if (!again && (x < LATER_TILES ? !((__builtin_amdgcn_readfirstlane(later_s[x >> 5]) >> (x & 31)) & 1u) : x < later_from)) continue;
       Tile t = {1, team + x * KS, 0, 0, 0, 0};
       enter(t);
       settle(t);
@@ -449,7 +471,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
       for (int v = 0; v < 16; ++v) sc[v] = 0.f;
       const T* krow = base_of(K, Kp, t) + (int64_t)(prow < 0 ? 0 : prow) * D + hf * 4;
       const T* qrow = Q + (qhead * a.N + (active ? row : row0)) * D + hf * 4;
-#pragma unroll 4
+#pragma unroll
       for (int c = 0; c < D; c += 8) {
         f32x4 kk = Four<T>::widen(Four<T>::load(krow + c)), qq = Four<T>::widen(Four<T>::load(qrow + c));
         if (prow < 0) kk = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -481,14 +503,23 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
             }
         }
       } else {
+        f32x16 part[MD];                                 // (from zero for every tile, as above)
+#pragma unroll
+        for (int md = 0; md < MD; ++md)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) part[md][v] = 0.f;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {                   // the key of register v, and the one four rows further down
           const int pr = __shfl(prow, (v >> 2) * 8 + hf * 4 + (v & 3), 64);
           const T* vrow = vbase + (int64_t)(pr < 0 ? 0 : pr) * D + l32;
 #pragma unroll
           for (int md = 0; md < MD; ++md)
-            o[md] = __builtin_amdgcn_mfma_f32_32x32x2f32(pr < 0 ? 0.f : Elem<T>::to_f32(vrow[md * 32]), sc[v], o[md], 0, 0, 0);
+            part[md] = __builtin_amdgcn_mfma_f32_32x32x2f32(pr < 0 ? 0.f : Elem<T>::to_f32(vrow[md * 32]), sc[v], part[md], 0, 0, 0);
         }
+#pragma unroll
+        for (int md = 0; md < MD; ++md)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) o[md][v] += part[md][v];
       }
     }
   }

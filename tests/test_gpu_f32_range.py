@@ -1,5 +1,5 @@
-"""float32 attention and dense attention over the range of float32: values near its largest, and what one value that is not finite
-costs the rest of a call.
+"""float32 attention and dense attention over the range of float32: values near its largest, operands near its smallest, and what one
+value that is not finite costs the rest of a call.
 
 Tolerance: the fp32 bar of the parity tests, relative to the largest entry of the result (which is of the order of the scaled
 operand), unless a test derives its own."""
@@ -65,11 +65,30 @@ def test_values_whose_weighted_sum_just_fits(N, Hq, bq, d):
         assert np.abs(l - lse).max() <= 1e-4
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("N,Hq,bq", TEAMS)
+@pytest.mark.parametrize("which", ["V", "K", "Q"])
+@pytest.mark.parametrize("power", [104, 112, 116, 120])
+def test_small_operands(N, Hq, bq, d, which, power):
+    """One operand scaled by 2^-power (keys and queries: the other one by 2^power, so that the scores stay)."""
+    op = _single_level(N, Hq, d, bq)
+    host = dict(zip("QKV", si.random_qkv(power, 1, Hq, 1, N, d, "f32")))
+    host[which] = np.ldexp(host[which], -power)
+    if which != "V":
+        other = "K" if which == "Q" else "Q"
+        host[other] = np.ldexp(host[other], power)
+    want, lse = orc.dense_attention(*(host[x].astype(np.float64) for x in "QKV"), op)
+    for got, l in _run(op, *(host[x] for x in "QKV")):
+        assert np.abs(got - want).max() <= 1e-5 * np.abs(want).max()
+        assert np.abs(l - lse).max() <= 1e-4
+
+
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("what", ["key", "value"])
-def test_one_infinity_does_not_slow_the_call(what, causal):
-    """The first token's key or value is infinite in one channel and every row keeps its block: one tile of a row's list.  The
-    two calls are timed in turn, the shortest of 20 each, so that what else the machine does drops out."""
+@pytest.mark.parametrize("what", ["key", "value", "small values"])
+def test_single_values_do_not_slow_the_call(what, causal):
+    """The first token's key or value is infinite in one channel and every row keeps its block: one tile of a row's list.  Or
+    every seventh token has a value of 1e-36 among ordinary ones.  The two calls are timed in turn, the shortest of 20 each, so that
+    what else the machine does drops out."""
     import torch
     op = orc.Params(B=1, Hq=12, Hkv=12, N=4680, d=128, bq=128, bk=64, levels=4, dtype="f32", causal=causal, sq=8, sk=8)
     gp = gpu_params(op)
@@ -82,7 +101,9 @@ def test_one_infinity_does_not_slow_the_call(what, causal):
     problems = []
     for bad in (False, True):
         k, v = K.clone(), V.clone()
-        if bad:
+        if bad and what == "small values":
+            v[:, :, ::7, 3] = 1e-36
+        elif bad:
             (k if what == "key" else v)[:, :, 0, 0] = float("inf")
         buf = Buffers(gp)
         psa.psa_build_pyramid(gp, k, v, buf.Kpyr, buf.Vpyr)
