@@ -95,7 +95,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
   unsigned char* Vs = Ks + S::OFF_V;
   float* term_s = reinterpret_cast<float*>(Ks + S::OFF_TAB + wr * 256);   // irregular tiles: additive term per key, its last token
   int* last_s = reinterpret_cast<int*>(term_s + 32);
-  int* flag_s = reinterpret_cast<int*>(fsm + S::OFF_FLAG);               // what the wavefront staged of V: NOT_FINITE, SMALL
+  int* flag_s = reinterpret_cast<int*>(fsm + S::OFF_FLAG);               // what the wavefront staged of V: NOT_FINITE, SMALL, LARGE
   uint32_t* later_s = reinterpret_cast<uint32_t*>(fsm + S::OFF_LATER) + wave * (LATER_TILES / 32);
 
   const bool own_list = M != nullptr, dense = !own_list && idx == nullptr;
@@ -204,8 +204,13 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
     }
     return range;
   };
-  // scores of tile t -> weights of its keys for this lane's row and their sum; reference, sum and output so far follow
-  auto weights = [&](const Tile& t, int prow, f32x16& sc) __attribute__((always_inline)) -> float {
+  // scores of tile t -> weights of its keys for this lane's row and their sum; reference, sum and output so far follow.  Weights below 2^-109, whose planes would not
+  // hold them (and those below 2^-126, which v_exp_f32 makes 0): the tile's weights and their sum are 2^24 times what they are, `unscale` takes that back (scores of 16
+  // heads x 3000 tokens with a deviation of 16: 598 -> 630 us, error 2.01e-6 as before, 5.1e-6 with float32 instructions).  EXACT: never, by exp2f.
+  float unscale = 1.f;
+  auto weights = [&](const Tile& t, int prow, f32x16& sc, auto exact) __attribute__((always_inline)) -> float {
+    constexpr bool EXACT = decltype(exact)::value;
+    constexpr float TINY = -109.f;
     // log2 of the tokens under a key: one constant, unless the tile holds keys that do not exist, cover fewer tokens than others of the level
     // or (causal) are hidden from a row of this wavefront
     const int hm1 = t.h - 1;
@@ -215,7 +220,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
       lim = vis < lim ? vis : lim;
     }
     const bool irregular = __any(prow < 0 || prow >= lim);
-    float tmax = -INFINITY;
+    float tmax = -INFINITY, tmin = INFINITY;
     if (irregular) {
       const int span = 1 << hm1;
       const int64_t first = (int64_t)prow << hm1;
@@ -237,12 +242,17 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
           if (a.causal && last_s[g4 * 8 + hf * 4 + e] > row) s = -INFINITY;
           sc[g4 * 4 + e] = s;
           tmax = fmaxf(tmax, s);
+          if (!EXACT) tmin = fminf(tmin, s == -INFINITY ? INFINITY : s);
         }
       }
     } else {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) tmax = fmaxf(tmax, sc[v]);
+      for (int v = 0; v < 16; ++v) {
+        tmax = fmaxf(tmax, sc[v]);
+        tmin = fminf(tmin, sc[v]);
+      }
       tmax = fmaf(tmax, a.scale_hi, (float)hm1);
+      tmin = fmaf(tmin, a.scale_hi, (float)hm1);
     }
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
     // The reference is a whole number, so that changing it rounds nothing, and no weight is more than one: values up to the largest float32 can be summed.
@@ -257,11 +267,24 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
       m = mn;
     }
     const float ref = m == -INFINITY ? 0.f : m;
-    if (irregular) {
+    const float shift = irregular ? -ref : (float)hm1 - ref;
+    auto power = [&](int v) __attribute__((always_inline)) { return irregular ? sc[v] + shift : fmaf(sc[v], a.scale_lo, fmaf(sc[v], a.scale_hi, shift)); };
+    const bool tiny = !EXACT && __any(tmin - ref < TINY);
+    unscale = tiny ? 0x1p-24f : 1.f;
+    if (EXACT) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) sc[v] = __builtin_amdgcn_exp2f(sc[v] - ref);
+      for (int v = 0; v < 16; ++v) sc[v] = exp2f(power(v));
+    } else if (tiny) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const float x = power(v);
+        const bool down = x < -64.f;
+        sc[v] = __builtin_amdgcn_exp2f(down ? x + 24.f : x) * (down ? 1.f : 0x1p24f);
+      }
+    } else if (irregular) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sc[v] = __builtin_amdgcn_exp2f(sc[v] + shift);
     } else {
-      const float shift = (float)hm1 - ref;
 #pragma unroll
       for (int v = 0; v < 16; ++v) sc[v] = __builtin_amdgcn_exp2f(fmaf(sc[v], a.scale_lo, fmaf(sc[v], a.scale_hi, shift)));
     }
@@ -283,7 +306,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
   // Of float32 operands below 2^-109 the planes may hold all but 2^-134.  Of keys this counts next to large queries only, of queries it is not asked whether
   // there are large keys: such rows leave every tile for the end.  Of values it counts where the output is as small: SMALL is noted, and looked into at the end.
   const bool far_q = NPL == 3 && __any(q_range.small() || q_range.large());
-  constexpr int NOT_FINITE = 1, SMALL = 2;
+  constexpr int NOT_FINITE = 1, SMALL = 2, LARGE = 4;
   bool small_v = false;
   int total = 0;                                         // tiles of the row: the same for every team
   for (int h = 1; h <= H; ++h) {
@@ -359,9 +382,9 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
         }
         bad |= (bool)__any(!(fabsf(any) < INFINITY));          // a row or key that is not finite, or a product that overflows
       }
-      if (!bad) sum = weights(cur, pc, sc);
+      if (!bad) sum = weights(cur, pc, sc, std::false_type{});
       const PairRange range = deposit(Vs, pc);
-      v_state = (__any(!range.finite()) ? NOT_FINITE : 0) | (NPL == 3 && __any(range.small()) ? SMALL : 0);
+      v_state = (__any(!range.finite()) ? NOT_FINITE : 0) | (NPL == 3 && __any(range.small()) ? SMALL : 0) | (__any(range.large()) ? LARGE : 0);
       if (TEAM > 1 && lane == 0) flag_s[wave] = v_state;
     }
     barrier();                                           // V rows in LDS; everyone is done with the K rows
@@ -371,13 +394,14 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
       for (int w = 0; w < TEAM; ++w) v_state |= flag_s[team * TEAM + w];
       v_state = __builtin_amdgcn_readfirstlane(v_state);
     }
+    bad |= (v_state & LARGE) && unscale != 1.f;          // (2^24 times a weight times a large value may overflow)
     if (nxt.ok) fetch(K, Kp, nxt, pn);
     if (cur.ok && (bad || (v_state & NOT_FINITE) || n >= later_from)) {
       later = true;
       if (n >= LATER_TILES) later_from = n < later_from ? n : later_from;
       else if (lane == 0) later_s[n >> 5] |= 1u << (n & 31);
     } else if (cur.ok) {
-      l += sum;
+      l = fmaf(sum, unscale, l);
       small_v |= v_state & SMALL;
       bf16x8 p[3][2];                                    // planes of the weights: keys f * 16 .. as they stand in the registers
 #pragma unroll
@@ -426,7 +450,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
         part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[0], p[0][f], part, 0, 0, 0);
         if constexpr (f == 1)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) o[md][v] += part[v];
+          for (int v = 0; v < 16; ++v) o[md][v] = fmaf(part[v], unscale, o[md][v]);
         __builtin_amdgcn_sched_barrier(0x7);             // (arithmetic may pass: the next weights' planes, addresses; 237 -> 228 us at 12 heads x 4680 tokens)
       });
     }
@@ -479,7 +503,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
 #pragma unroll
         for (int e = 0; e < 4; ++e) sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kk[e], qq[e], sc, 0, 0, 0);
       }
-      l += weights(t, prow, sc);
+      l += weights(t, prow, sc, std::true_type{});
       const T* vbase = base_of(V, Vp, t);
       if (a.causal && __any(prow >= (row0 + wr * 32 + 1) >> (t.h - 1))) {
         // A row must not see 0 * inf of a key that is hidden from it: hidden keys are left out one by one, on the vector unit.

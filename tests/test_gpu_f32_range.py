@@ -1,5 +1,5 @@
-"""float32 attention and dense attention over the range of float32: values near its largest, operands near its smallest, and what one
-value that is not finite costs the rest of a call.
+"""float32 attention and dense attention over the range of float32: values near its largest, operands and weights near its
+smallest, and what one value that is not finite costs the rest of a call.
 
 Tolerance: the fp32 bar of the parity tests, relative to the largest entry of the result (which is of the order of the scaled
 operand), unless a test derives its own."""
@@ -81,6 +81,22 @@ def test_small_operands(N, Hq, bq, d, which, power):
     for got, l in _run(op, *(host[x] for x in "QKV")):
         assert np.abs(got - want).max() <= 1e-5 * np.abs(want).max()
         assert np.abs(l - lse).max() <= 1e-4
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("N,Hq,bq", TEAMS)
+@pytest.mark.parametrize("log2_weight", [-112, -118, -130])
+def test_small_weights(N, Hq, bq, d, log2_weight):
+    """128 keys of weight 1 and value 0, all others of weight 2^-112 and less and values of 2^120.  A score of 130 is rounded
+    to 2^-17 (twice: the product, the maximum taken off), which moves its weight by 1.1e-5; a weight of 2^-130 is a
+    subnormal number of 20 bits (1e-6): 2e-5."""
+    op = _single_level(N, Hq, d, bq)
+    Q, K, V = _scored(op, np.where(np.arange(N) < 128, 0.0, log2_weight * np.log(2)), 2)
+    V = (V * 2.0 ** 120).astype(np.float32)
+    V[:, :, :128] = 0
+    want, _ = orc.dense_attention(*(x.astype(np.float64) for x in (Q, K, V)), op)
+    for got, _ in _run(op, Q, K, V):
+        assert np.abs(got - want).max() <= 2e-5 * np.abs(want).max()
 
 
 @pytest.mark.parametrize("causal", [False, True])
