@@ -116,9 +116,10 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   static_assert(BN == 64 || (BN == 32 && NW < 4), "tile width");
   static_assert(NINST % NW == 0, "tile rows must split evenly over the wavefronts");
   static_assert(MPC * NB == NPAIR, "chunking of the softmax work");
-  // LDS map: K[2] | V[2] | per-wavefront table for irregular tiles | blocks per level | block list
+  // LDS map: K[BUFS] | V[BUFS] | per-wavefront table for irregular tiles | block list, of a row whose list is made here (at most ROW_LISTS_NK blocks) with
+  // the blocks per level behind it
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  constexpr int OFF_K = 0, OFF_V = BUFS * TILEB, OFF_FIX = 2 * BUFS * TILEB, OFF_CNT = OFF_FIX + NW * 512, OFF_LIST = OFF_CNT + 4 * PSA_MAX_LEVELS;
+  constexpr int OFF_K = 0, OFF_V = BUFS * TILEB, OFF_FIX = 2 * BUFS * TILEB, OFF_LIST = OFF_FIX + NW * 512, OFF_CNT = OFF_LIST + 2 * ROW_LISTS_NK;
   uint16_t* list = reinterpret_cast<uint16_t*>(smem + OFF_LIST);    // kept block ids, level-major
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -821,7 +822,8 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
 }
 
 size_t attn_mfma_smem_bytes(int d, int nk, int bn, int bufs, int nw) {
-  return 2 * bufs * (size_t)bn * d * sizeof(bf16_t) + nw * 512 + 4 * PSA_MAX_LEVELS + (((size_t)nk * 2 + 15) & ~(size_t)15);
+  const size_t list = nk <= ROW_LISTS_NK ? 2 * ROW_LISTS_NK + 4 * PSA_MAX_LEVELS : ((size_t)nk * 2 + 15) & ~(size_t)15;
+  return 2 * bufs * (size_t)bn * d * sizeof(bf16_t) + nw * 512 + list;
 }
 
 template <int D, int NW, bool SC, int BN, int BUFS>

@@ -687,3 +687,31 @@ def test_measurement_probes_run():
         torch.cuda.synchronize()
         assert flops == 8 * 4 * 3 * 16 * 2.0 * 32 * 32 * 16
         assert bool(torch.isfinite(sink).all())
+
+
+@pytest.mark.parametrize("d,nk", [(128, 48128), (64, 64512)])
+def test_longest_rows_of_the_matrix_core_kernel(d, nk):
+    """As many key blocks as the LDS takes next to the tiles (160 KB less four tiles of 64 rows and four tables of 512 bytes, two bytes a
+    block), of which a row keeps 40; eight more are refused.  Against torch in float32, bfloat16 bars."""
+    import torch
+    N, bk = nk * 8, 8
+    assert 4 * 64 * d * 2 + 4 * 512 + 2 * nk == 160 * 1024
+    gp = psa.make_params(1, 1, 1, N, d, N, bk, 1, sq=8, sk=8)
+    more = psa.make_params(1, 1, 1, N + 64, d, N + 128, bk, 1, sq=8, sk=8)
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    Q, K, V = (torch.randn((1, 1, N, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    buf = Buffers(gp)
+    buf.M.zero_()
+    blocks = torch.linspace(0, nk - 1, 40, device="cuda").round().long()
+    buf.M[..., blocks] = 1
+    buf.O.fill_(float("nan"))
+    psa.psa_attention_fwd(gp, Q, K, V, None, None, buf.M, buf.O, buf.scratch, lse=buf.lse)
+    torch.cuda.synchronize()
+    keys = (blocks[:, None] * bk + torch.arange(bk, device="cuda")).flatten()
+    x = Q[0, 0].float() @ K[0, 0, keys].float().T.contiguous() / d ** 0.5
+    want = torch.softmax(x, 1) @ V[0, 0, keys].float()
+    assert float((buf.O[0, 0].float() - want).abs().max()) <= 2e-2
+    assert float((buf.lse[0, 0] - torch.logsumexp(x, 1)).abs().max()) <= 2e-2
+    with pytest.raises(psa.PsaError) as e:
+        psa.psa_attention_fwd(more, Q, K, V, None, None, buf.M, buf.O, buf.scratch)
+    assert e.value.status == 2
