@@ -1,4 +1,4 @@
-// Which work a workgroup of the backward kernels takes and which rows the dK, dV walk over the query blocks touches (attn_bwd_mfma.hip).  Plain arithmetic, the same on host and device, so
+// Which work a workgroup of the backward kernels takes and which rows the dK, dV walk over the query blocks touches (attn_bwd_mfma.hip), and what fits one launch.  Plain arithmetic, the same on host and device, so
 // that its bounds can be checked without a GPU (tests/test_bwd_walk_host.py).
 #ifndef PSA_BWD_WALK_H
 #define PSA_BWD_WALK_H
@@ -42,6 +42,9 @@ constexpr bool dq_item(int heads, int per_head, bool runs, int xcd, int slot, in
   item = xcd * run + slot % run;
   return item < per_head;
 }
+
+// Whether the work of two launches, in workgroups of 256 threads each, may go out as one: a launch has fewer than 2^32 threads
+constexpr bool one_launch(long long first, long long second) { return (first + second) * 256 < (1ll << 32); }
 
 // log2 of the most key blocks of a workgroup: one bit each
 constexpr int DKV_LG_MAXG = 5;

@@ -13,6 +13,7 @@
 // tile statistics follow from those, so no logit is stored or recomputed.
 #include <type_traits>
 
+#include "bwd_walk.h"
 #include "psa_dev.h"
 #include "psa_internal.h"
 
@@ -115,14 +116,23 @@ hipError_t launch_representatives(const Plan& pl, const void* Q, void* Rq, const
   a.chunks = pl.d / (pl.dtype == PSA_F32 ? 4 : 8);
   a.b = pl.bq; a.s = pl.sq; a.nb = pl.nq; a.heads = pl.B * pl.Hq;
   a.b2 = pl.bk; a.s2 = pl.sk; a.nb2 = pl.nk; a.heads2 = pl.B * pl.Hkv;
-  auto groups = [&](int heads, int nb, int reps) { return (unsigned)(((int64_t)heads * nb * reps * a.chunks + 255) / 256); };
-  a.first2 = groups(a.heads, a.nb, a.s);
-  const unsigned grid = a.first2 + (Rk ? groups(a.heads2, a.nb2, a.s2) : 0u);
-  if (pl.dtype == PSA_F32)
-    reps_kernel<float><<<grid, 256, 0, s>>>(static_cast<const float*>(Q), static_cast<float*>(Rq), static_cast<const float*>(K), static_cast<float*>(Rk), a);
-  else
-    reps_kernel<bf16_t><<<grid, 256, 0, s>>>(static_cast<const bf16_t*>(Q), static_cast<bf16_t*>(Rq), static_cast<const bf16_t*>(K), static_cast<bf16_t*>(Rk), a);
-  return hipGetLastError();
+  auto groups = [&](int heads, int nb, int reps) { return ((long long)heads * nb * reps * a.chunks + 255) / 256; };
+  const long long first = groups(a.heads, a.nb, a.s), second = Rk ? groups(a.heads2, a.nb2, a.s2) : 0;
+  const bool both = one_launch(first, second);
+  a.first2 = (uint32_t)first;
+  auto launch = [&](const void* X, void* R, long long n) {
+    const unsigned grid = (unsigned)n;
+    if (pl.dtype == PSA_F32)
+      reps_kernel<float><<<grid, 256, 0, s>>>(static_cast<const float*>(X), static_cast<float*>(R), static_cast<const float*>(K), static_cast<float*>(Rk), a);
+    else
+      reps_kernel<bf16_t><<<grid, 256, 0, s>>>(static_cast<const bf16_t*>(X), static_cast<bf16_t*>(R), static_cast<const bf16_t*>(K), static_cast<bf16_t*>(Rk), a);
+    return hipGetLastError();
+  };
+  const hipError_t e = launch(Q, Rq, both ? first + second : first);
+  if (e != hipSuccess || both || !Rk) return e;
+  a.b = a.b2; a.s = a.s2; a.nb = a.nb2; a.heads = a.heads2;
+  a.first2 = (uint32_t)second;
+  return launch(K, Rk, second);
 }
 
 // ------------------------------------------------------------------------------------------------

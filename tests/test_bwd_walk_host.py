@@ -18,6 +18,10 @@ int main(int argc, char** argv) {
     printf("group %d %d\ngroup %d %d\n", g.keys, g.lg_G, g.lg_pieces, g.ng);
     return 0;
   }
+  if (argc == 5) {
+    printf("first 0 %d\n", one_launch(atoll(argv[1]) * atoll(argv[2]), atoll(argv[3]) * atoll(argv[4])));
+    return 0;
+  }
   if (argc == 3 && atoi(argv[1]) < 0) {
     const int heads = -atoi(argv[1]), per_head = atoi(argv[2]);
     for (int xcd = 0; xcd < 8; ++xcd)
@@ -90,3 +94,10 @@ def test_query_blocks_are_dealt_once_and_evenly(walk, heads, per_head):
     assert sorted(sum(shares, [])) == [(h, i) for h in range(heads) for i in range(per_head)]
     most = -(-heads * per_head // 8) if per_head < 32 else heads * -(-per_head // 8)
     assert max(map(len, shares)) <= most                              # from 32 blocks on: at most a quarter more than an even share
+
+
+@pytest.mark.parametrize("first,second,fits", [((1, 1), (0, 0), 1), ((4096, 4095), (1, 4095), 1), ((4096, 4095), (1, 4096), 0), ((1024, 12000), (1024, 6000), 0),
+                                               ((65536, 65536), (0, 0), 0)])
+def test_two_launches_go_out_as_one_below_the_limit_of_a_launch(walk, first, second, fits):
+    """Workgroups of 256 threads: 2^24 of them are 2^32 threads, which no launch has."""
+    assert walk(*first, *second)["first"] == [(0, fits)]
