@@ -8,7 +8,7 @@
 
 namespace psa {
 
-size_t importance_smem_bytes(int sq, int nk, int d);
+bool importance_row_fits(int sq, int nk, int d);
 bool importance_uses_mfma(const Plan& pl);
 
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -244,7 +244,7 @@ int psa_allocate_levels(const psa_params* p, const void* Q, const void* K, const
   }
   if (!Q) return PSA_EINVAL;
   if (pl.krep_is_pyramid ? !Kpyr : !K) return PSA_EINVAL;
-  if (!importance_uses_mfma(pl) && importance_smem_bytes(pl.sq, pl.nk, pl.d) > LDS_LIMIT) return PSA_EUNSUPPORTED;
+  if (!importance_uses_mfma(pl) && !importance_row_fits(pl.sq, pl.nk, pl.d)) return PSA_EUNSUPPORTED;
   void* qrep = at(scratch, pl.off_qrep);
   void* kr = pl.krep_is_pyramid ? nullptr : at(scratch, pl.off_krep);
   if (launch_representatives(pl, Q, qrep, K, kr, s) != hipSuccess) return PSA_ELAUNCH;

@@ -253,10 +253,9 @@ __global__ __launch_bounds__(256) void importance_kernel(const T* __restrict__ Q
   }
 }
 
-size_t importance_smem_bytes(int sq, int nk, int d) {
-  // (IMP_ROWS * d: rows that were kept here once; the limit on row lengths that follows from it stays where callers know it)
-  return sizeof(float) * ((size_t)IMP_ROWS * d + 2 * (size_t)sq + 2 * (size_t)sq * nk);
-}
+static size_t importance_smem_bytes(int sq, int nk) { return sizeof(float) * (2 * (size_t)sq + 2 * (size_t)sq * nk); }
+// Rows are refused where IMP_ROWS query rows, which were kept in LDS once, would no longer fit next to that: the limit that callers know.
+bool importance_row_fits(int sq, int nk, int d) { return importance_smem_bytes(sq, nk) + sizeof(float) * IMP_ROWS * d <= LDS_LIMIT; }
 
 template <typename T, int D>
 static hipError_t launch_imp_t(const Plan& pl, const void* Qrep, const void* Krep, float* S, hipStream_t s) {
@@ -264,7 +263,7 @@ static hipError_t launch_imp_t(const Plan& pl, const void* Qrep, const void* Kre
   a.N = pl.N; a.Hq = pl.Hq; a.Hkv = pl.Hkv; a.nq = pl.nq; a.nk = pl.nk; a.bq = pl.bq; a.bk = pl.bk;
   a.sq = pl.sq; a.sk = pl.sk; a.mode = pl.rep_mode; a.causal = pl.causal; a.est_pool = pl.est_pool;
   a.scale = pl.scale;
-  const size_t smem = importance_smem_bytes(pl.sq, pl.nk, D);
+  const size_t smem = importance_smem_bytes(pl.sq, pl.nk);
   auto kern = importance_kernel<T, D>;
   static LdsOptIn optin;                       // one per kernel instantiation
   const hipError_t e = allow_max_lds(reinterpret_cast<const void*>(kern), &optin);
