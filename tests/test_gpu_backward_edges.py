@@ -104,7 +104,11 @@ def _before_nan(x):
 
 
 @pytest.mark.parametrize("N,d,bq,bk,levels,causal", [
-    (321, 128, 128, 64, 4, False), (450, 64, 128, 128, 4, True), (449, 128, 128, 128, 1, False), (290, 128, 32, 32, 3, True), (1000, 64, 128, 64, 2, False)])
+    (321, 128, 128, 64, 4, False), (450, 64, 128, 128, 4, True), (449, 128, 128, 128, 1, False), (290, 128, 32, 32, 3, True), (1000, 64, 128, 64, 2, False),
+    # more than 128 key blocks: the forward's 128-row workgroups read lists and tile descriptors made by a launch of their own, as all long calls do;
+    # with 256-row blocks two of them share a set
+    (2099, 128, 128, 16, 2, False), (2099, 128, 128, 16, 2, True), (2099, 64, 128, 16, 2, False), (2099, 64, 128, 16, 2, True), (2081, 128, 256, 16, 2, False),
+    (2081, 64, 256, 16, 2, True)])
 def test_what_lies_behind_the_tensors_does_not_count(N, d, bq, bk, levels, causal):
     """Ragged lengths whose last tiles, stages and chunks reach far past the last row: the same bits with NaN behind every input."""
     import torch

@@ -86,13 +86,14 @@ def test_small_operands(N, Hq, bq, d, which, power):
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("N,Hq,bq", TEAMS)
 @pytest.mark.parametrize("log2_weight", [-112, -118, -130])
-def test_small_weights(N, Hq, bq, d, log2_weight):
-    """128 keys of weight 1 and value 0, all others of weight 2^-112 and less and values of 2^120.  A score of 130 is rounded
+@pytest.mark.parametrize("log2_value", [80, 120])
+def test_small_weights(N, Hq, bq, d, log2_weight, log2_value):
+    """128 keys of weight 1 and value 0, all others of weight 2^-112 and less and values of 2^80 or 2^120.  A score of 130 is rounded
     to 2^-17 (twice: the product, the maximum taken off), which moves its weight by 1.1e-5; a weight of 2^-130 is a
     subnormal number of 20 bits (1e-6): 2e-5."""
     op = _single_level(N, Hq, d, bq)
     Q, K, V = _scored(op, np.where(np.arange(N) < 128, 0.0, log2_weight * np.log(2)), 2)
-    V = (V * 2.0 ** 120).astype(np.float32)
+    V = (V * 2.0 ** log2_value).astype(np.float32)
     V[:, :, :128] = 0
     want, _ = orc.dense_attention(*(x.astype(np.float64) for x in (Q, K, V)), op)
     for got, _ in _run(op, Q, K, V):

@@ -50,9 +50,9 @@ def _case(name):
             "edge_bq96": base.with_(N=700, grid=(1, 20, 35), bq=96, bk=64, levels=3),     # rows kernel fallback
             "edge_eight_levels": base.with_(N=2048, grid=(2, 32, 32), bq=128, bk=128, levels=8),
         }[name], {}
-    if name == "bq256":           # query blocks of two 128-row workgroup slices sharing one block list and one set of tile descriptors
+    if name == "bq256":           # query blocks of two 128-row workgroup slices, which make the same block list (from 129 key blocks on they share one, with its descriptors: test_short_rows)
         return si.small_variant(C["dit1p3b"], 1531, Hq=2, Hkv=2).with_(bq=256), {}
-    if name == "bq256_causal":    # the same, causal + grouped-query: the descriptors' visibility bound is the block's first row
+    if name == "bq256_causal":    # the same, causal + grouped-query: the visibility bound of a tile is that of the slice
         return si.small_variant(C["vlm_prefill"], 1500, Hq=4, Hkv=2).with_(bq=256), {}
     if name.startswith("wide_"):  # rows of int(name[5:]) key blocks of 32 tokens, full 128-row workgroups, sparse caller-made masks
         return si.small_variant(C["dit1p3b"], int(name[5:]) * 32 - 5, Hq=1, Hkv=1).with_(bq=128, bk=32, levels=3), {}

@@ -16,7 +16,8 @@ psa = pytest.importorskip("paper_2512_04025_amd")
 
 @pytest.mark.parametrize("N", [1021, 1030])
 @pytest.mark.parametrize("dtype,d,bq,levels,causal", [("bf16", 128, 128, 2, False), ("bf16", 64, 128, 1, True), ("bf16", 128, 32, 2, False), ("bf16", 128, 64, 2, True),
-                                                      ("bf16", 64, 32, 3, True), ("f32", 64, 64, 3, True), ("f32", 128, 128, 2, False), ("bf16", 64, 96, 2, False)])
+                                                      ("bf16", 64, 32, 3, True), ("f32", 64, 64, 3, True), ("f32", 128, 128, 2, False), ("bf16", 64, 96, 2, False),
+                                                      ("bf16", 128, 256, 2, False), ("bf16", 128, 256, 2, True), ("bf16", 64, 256, 1, True)])   # two workgroups to a row's list and descriptors
 def test_short_rows(N, dtype, d, bq, levels, causal):
     import torch
     op = orc.Params(B=1, Hq=2, Hkv=1, N=N, d=d, bq=bq, bk=8, levels=levels, dtype=dtype, causal=causal, sq=8, sk=1)

@@ -70,32 +70,53 @@ def test_attention_small_query_blocks_on_an_idle_chip(bq, N, d, bk, levels, caus
     assert np.abs(buf.lse.cpu().numpy() - lse)[:, :, rows].max() <= 2e-2
 
 
-@pytest.mark.parametrize("bq,d", [(32, 128), (32, 64), (64, 128), (64, 64)])
-@pytest.mark.parametrize("bk,levels", [(32, 3), (16, 4)])
-def test_attention_small_query_blocks_on_a_full_chip(bq, d, bk, levels):
-    """More workgroups than run at one time (heads 3 and 4 of 40): one buffer each for K and V, but two at (64, 64), whose 2640
-    workgroups would leave more of the last of two rounds of 2048 empty than of two of 1536."""
+def _heads_three_and_four(N, Hq, bq, d, bk, levels, causal):
     import torch
-    N, Hq = (2100 if bq == 32 else 4200) + 13, 40
-    op = orc.Params(B=1, Hq=Hq, Hkv=1, N=N, d=d, bq=bq, bk=bk, levels=levels, dtype="bf16", sq=8, sk=1)
+    op = orc.Params(B=1, Hq=Hq, Hkv=1, N=N, d=d, bq=bq, bk=bk, levels=levels, dtype="bf16", causal=causal, sq=8, sk=1)
     gp = gpu_params(op)
     host = si.random_qkv(N + bk, 1, Hq, 1, N, d, "bf16")
     rng = np.random.default_rng(N)
     M = (rng.integers(1, levels + 1, size=(1, Hq, op.nq, op.nk)) * (rng.random((1, Hq, op.nq, op.nk)) < 0.2)).astype(np.uint8)
-    M[..., -1] = 1
+    M[..., 0 if causal else -1] = 1
+    vis = orc.block_visibility(op)
+    M = np.where(vis[None, None] == 0, 0, np.where(vis[None, None] == 2, 1, M)).astype(np.uint8)
     Qd, Kd, Vd = (to_dev(x, "bf16") for x in host)
     buf = Buffers(gp)
     psa.psa_build_pyramid(gp, Kd, Vd, buf.Kpyr, buf.Vpyr)
     buf.O.fill_(float("nan"))
     psa.psa_attention_fwd(gp, Qd, Kd, Vd, buf.Kpyr, buf.Vpyr, torch.from_numpy(M).cuda(), buf.O, buf.scratch, lse=buf.lse)
     torch.cuda.synchronize()
-    two = orc.Params(B=1, Hq=2, Hkv=1, N=N, d=d, bq=bq, bk=bk, levels=levels, dtype="bf16", sq=8, sk=1)
+    two = orc.Params(B=1, Hq=2, Hkv=1, N=N, d=d, bq=bq, bk=bk, levels=levels, dtype="bf16", causal=causal, sq=8, sk=1)
     Q64, K64, V64 = (si.to_f64(x, "bf16") for x in (host[0][:, 3:5], host[1], host[2]))
     O, lse = orc.psa_attention(Q64, orc.build_pyramid(K64, two), orc.build_pyramid(V64, two), M[:, 3:5], two)
     got = from_dev(buf.O, "bf16")
     assert not np.isnan(got).any()
     assert np.abs(got[:, 3:5] - O).max() <= 2e-2 and rel_l2(got[:, 3:5], O) <= 1e-2
     assert np.abs(buf.lse.cpu().numpy()[:, 3:5] - lse).max() <= 2e-2
+
+
+def _one_buffer(wgs):
+    """Whether 64-row blocks at d = 64 take one buffer each for K and V: their rounds of the chip, four wavefronts on a SIMD, then
+    hold no more wavefronts than those of two buffers and three."""
+    return -(-wgs // 2048) * 2048 <= -(-wgs // 1536) * 1536
+
+
+@pytest.mark.parametrize("bq,d", [(32, 128), (32, 64), (64, 128), (64, 64)])
+@pytest.mark.parametrize("bk,levels", [(32, 3), (16, 4)])
+def test_attention_small_query_blocks_on_a_full_chip(bq, d, bk, levels):
+    """More workgroups than run at one time (heads 3 and 4 of 40): one buffer each for K and V, but two at (64, 64)."""
+    N, Hq = (2100 if bq == 32 else 4200) + 13, 40
+    assert (bq, d) != (64, 64) or not _one_buffer(Hq * -(-N // 64))
+    _heads_three_and_four(N, Hq, bq, d, bk, levels, False)
+
+
+@pytest.mark.parametrize("N,Hq", [(4213, 28), (5013, 40)])
+@pytest.mark.parametrize("bk,levels", [(32, 3), (16, 4)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_attention_single_buffers_of_64_row_blocks(N, Hq, bk, levels, causal):
+    """Numbers of workgroups with which 64-row blocks at d = 64 take one buffer each for K and V."""
+    assert Hq * -(-N // 64) > 1024 and _one_buffer(Hq * -(-N // 64))
+    _heads_three_and_four(N, Hq, 64, 64, bk, levels, causal)
 
 
 @pytest.mark.parametrize("bq,d", [(32, 128), (32, 64), (64, 128), (64, 64)])
