@@ -95,7 +95,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
   unsigned char* Vs = Ks + S::OFF_V;
   float* term_s = reinterpret_cast<float*>(Ks + S::OFF_TAB + wr * 256);   // irregular tiles: additive term per key, its last token
   int* last_s = reinterpret_cast<int*>(term_s + 32);
-  int* flag_s = reinterpret_cast<int*>(fsm + S::OFF_FLAG);               // what the wavefront staged of V: NOT_FINITE, SMALL, LARGE
+  int* flag_s = reinterpret_cast<int*>(fsm + S::OFF_FLAG);               // what the wavefront staged of V: FAR, SMALL
   uint32_t* later_s = reinterpret_cast<uint32_t*>(fsm + S::OFF_LATER) + wave * (LATER_TILES / 32);
 
   const bool own_list = M != nullptr, dense = !own_list && idx == nullptr;
@@ -207,6 +207,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
   // scores of tile t -> weights of its keys for this lane's row and their sum; reference, sum and output so far follow.  Weights below 2^-109, whose planes would not
   // hold them (and those below 2^-126, which v_exp_f32 makes 0): the tile's weights and their sum are 2^24 times what they are, `unscale` takes that back (scores of 16
   // heads x 3000 tokens with a deviation of 16: 598 -> 630 us, error 2.01e-6 as before, 5.1e-6 with float32 instructions).  EXACT: never, by exp2f.
+  constexpr float LAG = 8.f;
   float unscale = 1.f;
   auto weights = [&](const Tile& t, int prow, f32x16& sc, auto exact) __attribute__((always_inline)) -> float {
     constexpr bool EXACT = decltype(exact)::value;
@@ -255,8 +256,9 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
       tmin = fmaf(tmin, a.scale_hi, (float)hm1);
     }
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-    // The reference is a whole number, so that changing it rounds nothing, and no weight is more than one: values up to the largest float32 can be summed.
-    if (__any(tmax > m)) {
+    // The reference is a whole number, so that changing it rounds nothing, and is raised when a weight would pass 2^LAG (with every
+    // larger score 12 heads x 4680 tokens take 244 us instead of 240): no sum overflows as long as values are below 2^80, and tiles with others are EXACT.
+    if (__any(EXACT ? tmax > m : tmax - m > LAG)) {
       const float mn = fmaxf(m, ceilf(tmax));
       const float alpha = mn == -INFINITY ? 1.f : exp2f(m - mn);      // m = -inf: 0
       l *= alpha;
@@ -306,7 +308,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
   // Of float32 operands below 2^-109 the planes may hold all but 2^-134.  Of keys this counts next to large queries only, of queries it is not asked whether
   // there are large keys: such rows leave every tile for the end.  Of values it counts where the output is as small: SMALL is noted, and looked into at the end.
   const bool far_q = NPL == 3 && __any(q_range.small() || q_range.large());
-  constexpr int NOT_FINITE = 1, SMALL = 2, LARGE = 4;
+  constexpr int FAR = 1, SMALL = 2;                      // of the rows of V: one is large or not finite, one is small
   bool small_v = false;
   int total = 0;                                         // tiles of the row: the same for every team
   for (int h = 1; h <= H; ++h) {
@@ -384,7 +386,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
       }
       if (!bad) sum = weights(cur, pc, sc, std::false_type{});
       const PairRange range = deposit(Vs, pc);
-      v_state = (__any(!range.finite()) ? NOT_FINITE : 0) | (NPL == 3 && __any(range.small()) ? SMALL : 0) | (__any(range.large()) ? LARGE : 0);
+      v_state = (__any(range.large()) ? FAR : 0) | (NPL == 3 && __any(range.small()) ? SMALL : 0);
       if (TEAM > 1 && lane == 0) flag_s[wave] = v_state;
     }
     barrier();                                           // V rows in LDS; everyone is done with the K rows
@@ -394,9 +396,9 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
       for (int w = 0; w < TEAM; ++w) v_state |= flag_s[team * TEAM + w];
       v_state = __builtin_amdgcn_readfirstlane(v_state);
     }
-    bad |= (v_state & LARGE) && unscale != 1.f;          // (2^24 times a weight times a large value may overflow)
+    bad |= v_state & FAR;
     if (nxt.ok) fetch(K, Kp, nxt, pn);
-    if (cur.ok && (bad || (v_state & NOT_FINITE) || n >= later_from)) {
+    if (cur.ok && (bad || n >= later_from)) {
       later = true;
       if (n >= LATER_TILES) later_from = n < later_from ? n : later_from;
       else if (lane == 0) later_s[n >> 5] |= 1u << (n & 31);
@@ -478,9 +480,15 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
     }
   }
   if (later) {
-    // Tiles with values that are not finite (the planes of an infinity give NaN where the product has a sign), and rows of small operands.  They are taken from memory in
-    // float32, at the end (a wavefront's sums do not ask for an order), since next to the planes in the loop above this would take registers from it (12 heads x 4680
-    // tokens 229 -> 255 us with no such tile).
+    // Tiles with scores or values that are not finite (the planes of an infinity give NaN where the product has a sign) or values that are large, and rows of small
+    // operands: taken from memory in float32, at the end (a wavefront's sums do not ask for an order), since next to the planes in the loop above this would take
+    // registers from it (12 heads x 4680 tokens 229 -> 255 us with no such tile).  No weight is more than one here, so that values up to the largest float32 can be summed.
+    m += LAG;
+    l *= exp2f(-LAG);
+#pragma unroll
+    for (int md = 0; md < MD; ++md)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) o[md][v] *= exp2f(-LAG);
     const int tiles = (total + KS - 1 - team) / KS;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll 1
