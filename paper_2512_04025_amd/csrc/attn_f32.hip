@@ -204,12 +204,13 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
     }
     return range;
   };
-  // scores of tile t -> weights of its keys for this lane's row and their sum; reference, sum and output so far follow.  Weights below 2^-109, whose planes would not
-  // hold them (and those below 2^-126, which v_exp_f32 makes 0): the tile's weights and their sum are 2^24 times what they are, `unscale` takes that back (scores of 16
-  // heads x 3000 tokens with a deviation of 16: 598 -> 630 us, error 2.01e-6 as before, 5.1e-6 with float32 instructions).  EXACT: never, by exp2f.
+  // scores of tile t -> weights of its keys for this lane's row and their sum; reference, sum and output so far follow.  Weights below 2^-109, whose planes would
+  // not hold them (and those below 2^-126, which v_exp_f32 makes 0): the tile's weights and their sum are 2^24 times what they are, `unscale` takes that back (dense
+  // 16 heads x 3000 tokens, scores of deviation 1 / 16: 619 / 624 us, error 2.9e-7 / 1.0e-6; float32 instructions 1011 / 1013 us, 1.2e-6 / 2.6e-6).  EXACT: never,
+  // by exp2f.  With `discard` the scores may be anything: reference, sum and output stay.
   constexpr float LAG = 8.f;
   float unscale = 1.f;
-  auto weights = [&](const Tile& t, int prow, f32x16& sc, auto exact) __attribute__((always_inline)) -> float {
+  auto weights = [&](const Tile& t, int prow, f32x16& sc, auto exact, bool discard) __attribute__((always_inline)) -> float {
     constexpr bool EXACT = decltype(exact)::value;
     constexpr float TINY = -109.f;
     // log2 of the tokens under a key: one constant, unless the tile holds keys that do not exist, cover fewer tokens than others of the level
@@ -258,8 +259,10 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
     // The reference is a whole number, so that changing it rounds nothing, and is raised when a weight would pass 2^LAG (with every
     // larger score 12 heads x 4680 tokens take 244 us instead of 240): no sum overflows as long as values are below 2^80, and tiles with others are EXACT.
-    if (__any(EXACT ? tmax > m : tmax - m > LAG)) {
-      const float mn = fmaxf(m, ceilf(tmax));
+    // (One test for all that is rare, and `discard` only behind it: what a step waits for before its weights counts.)
+    bool tiny = false;
+    if (__any(EXACT ? tmax > m : tmax - m > LAG || tmin - m < TINY) && !discard) {
+      const float mn = tmax - m > LAG || EXACT ? fmaxf(m, ceilf(tmax)) : m;
       const float alpha = mn == -INFINITY ? 1.f : exp2f(m - mn);      // m = -inf: 0
       l *= alpha;
 #pragma unroll
@@ -267,12 +270,12 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[md][v] *= alpha;
       m = mn;
+      tiny = !EXACT && __any(tmin - (m == -INFINITY ? 0.f : m) < TINY);
     }
+    unscale = tiny ? 0x1p-24f : 1.f;
     const float ref = m == -INFINITY ? 0.f : m;
     const float shift = irregular ? -ref : (float)hm1 - ref;
     auto power = [&](int v) __attribute__((always_inline)) { return irregular ? sc[v] + shift : fmaf(sc[v], a.scale_lo, fmaf(sc[v], a.scale_hi, shift)); };
-    const bool tiny = !EXACT && __any(tmin - ref < TINY);
-    unscale = tiny ? 0x1p-24f : 1.f;
     if (EXACT) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) sc[v] = exp2f(power(v));
@@ -376,15 +379,16 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
         __builtin_amdgcn_sched_barrier(0);
       });
       if constexpr (NPL == 3) {
-        float any = 0.f;
+        float any[16];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          sc[v] += low[v];
-          any += sc[v];
-        }
-        bad |= (bool)__any(!(fabsf(any) < INFINITY));          // a row or key that is not finite, or a product that overflows
+        for (int v = 0; v < 16; ++v) any[v] = sc[v] += low[v];
+#pragma unroll
+        for (int w = 1; w < 16; w *= 2)
+#pragma unroll
+          for (int v = 0; v < 16; v += 2 * w) any[v] += any[v + w];
+        bad |= (bool)__any(!(fabsf(any[0]) < INFINITY));       // a row or key that is not finite, or a product that overflows
       }
-      if (!bad) sum = weights(cur, pc, sc, std::false_type{});
+      sum = weights(cur, pc, sc, std::false_type{}, bad);
       const PairRange range = deposit(Vs, pc);
       v_state = (__any(range.large()) ? FAR : 0) | (NPL == 3 && __any(range.small()) ? SMALL : 0);
       if (TEAM > 1 && lane == 0) flag_s[wave] = v_state;
@@ -511,7 +515,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
 #pragma unroll
         for (int e = 0; e < 4; ++e) sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kk[e], qq[e], sc, 0, 0, 0);
       }
-      l += weights(t, prow, sc, std::true_type{});
+      l += weights(t, prow, sc, std::true_type{}, false);
       const T* vbase = base_of(V, Vp, t);
       if (a.causal && __any(prow >= (row0 + wr * 32 + 1) >> (t.h - 1))) {
         // A row must not see 0 * inf of a key that is hidden from it: hidden keys are left out one by one, on the vector unit.
