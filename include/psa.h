@@ -183,7 +183,9 @@ int psa_allocate_levels(const psa_params* p, const void* Q, const void* K, const
  *   scratch     workspace of psa_query_sizes' scratch_bytes (per-row level-sorted block lists and per-tile
  *               load descriptors, rebuilt from M by every call)
  * bfloat16: QK^T and PV run on MFMA with fp32 accumulation, P is rounded to bfloat16 before PV.
- * float32: all arithmetic in fp32 with an accurate exp.
+ * float32: fp32 sums.  A product takes each operand as three bfloat16 parts (24 bits), of whose nine products the three smallest are left out, below 2^-24 of
+ * it; weights are accurate to one unit in the last place.  Where that would lose bits or range (rows with queries below 2^-109 or above 2^80, rows whose output is that small, values above
+ * 2^80, scores or values that are not finite) the products are single fp32 ones.  Relative error against 64 bits 1e-7 to 4e-7 on ordinary inputs.
  * A row whose kept blocks contain no visible key produces NaN.
  * Errors: PSA_EINVAL (null required pointer, misaligned scratch), PSA_EUNSUPPORTED (bfloat16 with more
  *         key blocks per row than fit the kernel's LDS: about 48 000 at d = 128), PSA_ELAUNCH.
@@ -205,8 +207,9 @@ int psa_attention_fwd(const psa_params* p, const void* Q, const void* K, const v
  *   dO          [B, Hq, N, d], dtype
  *   dQ          out [B, Hq, N, d];  dK, dV  out [B, Hkv, N, d], dtype (every element is written)
  *   scratch     workspace of psa_query_bwd_sizes' scratch_bytes (256-byte aligned): D, block lists, and the
- *               fp32 gradients of the pooled tokens of every level (bfloat16 on the matrix cores: one
- *               partial tensor per query head, added up in a fixed order)
+ *               fp32 gradients of the pooled tokens of every level, in one or more partial tensors per key
+ *               head that are added up in a fixed order (bfloat16 on the matrix cores: at least one per
+ *               query head; small problems: several, so that more of the GPU has work)
  * bfloat16: the products run on MFMA with fp32 accumulation, P and dS rounded to bfloat16 for the products
  * that consume them (dQ per query block; the pooled dK, dV per key block and level, walking the level
  * map's column).  float32, and bfloat16 shapes the matrix-core kernels do not take (b_k < 8, more than

@@ -318,7 +318,8 @@ __global__ __launch_bounds__(HEAD ? 64 * HEAD_ROWS : (FACTORED || NW == 4) ? 256
     if (lane == 0) vis_all[mine] = n_vis;
     __syncthreads();
     if (rho && mine == 0) {
-      // in units of 2^-(H-1): whole numbers (at most 8 rows x 128 blocks x 128), a row per lane
+      // in units of 2^-(H-1): whole numbers, a row per lane
+      static_assert((long long)HEAD_ROWS * KPL * 64 << (PSA_MAX_LEVELS - 1) < 1ll << 31, "32 bits hold the sum over the rows");
       int num = 0, den = lane < a.nq ? vis_all[lane & (RPW - 1)] : 0;
       for (int h = 1; h <= a.H; ++h) num += lane < a.nq ? cnt_all[lane & (RPW - 1)][h] << (a.H - h) : 0;
 #pragma unroll

@@ -1,12 +1,13 @@
-// Attention in fp32 arithmetic on the gfx950 matrix cores: psa_attention_fwd in float32 (Alg. 1 with accurate
-// exp, the 1e-5 mode), psa_dense_ref (Eq. 1) for both element types, and the bfloat16 block sizes that
-// attn_mfma_kernel does not take.  Sums are fp32 throughout; a float32 operand is the exact sum of three bfloat16 planes
-// (psa_dev.h), and a product of two is six products of planes on v_mfma_f32_32x32x16_bf16: 192 cycles of the matrix pipe for
-// 16 channels where v_mfma_f32_32x32x2_f32 needs 512.  A bfloat16 operand is one plane, the weights are three either way.
+// Attention with float32 operands and sums on the gfx950 matrix cores: psa_attention_fwd in float32 (Alg. 1, the 1e-5 mode),
+// psa_dense_ref (Eq. 1) for both element types, and the bfloat16 block sizes that
+// attn_mfma_kernel does not take.  Sums are fp32 throughout; a float32 operand is the sum of three bfloat16 planes (psa_dev.h: exact but for
+// small values, see far_q and small_v below), and a product of two is six of the nine products of planes on v_mfma_f32_32x32x16_bf16 (what is left out is below
+// 2^-24 of it): 192 cycles of the matrix pipe for 16 channels where v_mfma_f32_32x32x2_f32 needs 512.  A bfloat16 operand is one plane, the weights, by
+// v_exp_f32 (1 ulp), are three either way.  Scores or values that are not finite, values of 2^80 and more and rows of small operands take float32 instructions.
 // In S the products of the leading planes and all others are two sums that are added at the end; error against 64 bits
 // of 12 heads x 4680 tokens 4.1e-7 (float32 instructions) -> 1.0e-7, of 2 x 1024 at d = 64 1.4e-7 -> 0.9e-7, of lse 4.8e-8 -> 2.4e-8.
 //
-// What bounds it: 12 heads x 4680 tokens, d = 128, a fifth of the keys: a wavefront issues about 830 vector instructions a
+// What bounds it: 12 heads x 4680 tokens, d = 128, a fifth of the keys: a wavefront issues about 1040 vector instructions a
 // tile (72 conversions and what belongs to them, addresses, softmax) next to 96 MFMAs, two wavefronts on a SIMD: the vector port is
 // busy as long as the matrix pipe, and 444 workgroups take one and a half rounds of the chip.  The V rows of a tile travel through registers into LDS during its
 // first product, the K rows of the next one during its second, and each product is followed by one barrier; the block ids that say
@@ -21,8 +22,10 @@
 // stream of keys, and there are 4 / TEAM such teams over the SAME 32 * TEAM rows, each taking every
 // (4 / TEAM)-th tile of the row's list; their (maximum, sum, output) are merged through LDS at the end.
 //
-// Measured (pyramid and block lists included, a quarter of the keys), products on v_mfma_f32_32x32x2_f32 -> here: 12 heads x 4680 tokens, d = 128,
-// a fifth of the keys 353 -> 215 us, x 1000 57 -> 39, x 6000 at d = 64 527 -> 277; causal 2 x 2435 69 -> 48; 4 x 3433 at d = 64 87 -> 59.
+// Registers: float32 at d = 128 in teams of four spills 16 (68 bytes), some of them stored and reloaded inside the tile loop; no other instantiation spills vector registers.
+//
+// Measured (pyramid and block lists included, a fifth of the keys), products on v_mfma_f32_32x32x2_f32 -> here, us: 12 heads x 4680 tokens, d = 128,
+// 342 -> 236, x 1000 46.8 -> 35.2, x 6000 at d = 64 417 -> 228; causal 12 x 2634 133 -> 107, 2 x 2435 58.5 -> 43.0; 4 x 3433 at d = 64 70.8 -> 50.9.
 #include <limits.h>
 #include <math.h>
 
@@ -436,7 +439,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
         }
       };
       // The tile's twelve products for 32 channels are summed from zero and join o in one addition: twelve roundings a tile at the size of o made
-      // the error against 64 bits of causal 12 heads x 2634 tokens 3.5e-7, where one makes it 1.1e-7 (float32 instructions 2.5e-7).  It costs 223 -> 240 us at
+      // the error against 64 bits of causal 12 heads x 2634 tokens 3.5e-7, where one makes it 1.1e-7 (float32 instructions 2.5e-7).  It costs 223 -> 236 us at
       // 12 heads x 4680 tokens: `part` takes the registers of a second set of V fragments, the other wavefront of the SIMD covers their loads.
       bf16x8 va[NPL];
       f32x16 part;
@@ -457,7 +460,7 @@ void attn_f32_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* 
         if constexpr (f == 1)
 #pragma unroll
           for (int v = 0; v < 16; ++v) o[md][v] = fmaf(part[v], unscale, o[md][v]);
-        __builtin_amdgcn_sched_barrier(0x7);             // (arithmetic may pass: the next weights' planes, addresses; 237 -> 228 us at 12 heads x 4680 tokens)
+        __builtin_amdgcn_sched_barrier(0x7);             // (arithmetic may pass: the next weights' planes, addresses; causal 12 heads x 2634 tokens 110 -> 107 us)
       });
     }
     if (nxt.ok) deposit(Ks, pn);

@@ -10,9 +10,9 @@
 // One workgroup = one slice of up to 128 query rows, one wavefront per 32 rows; 128-row workgroups run two
 // (d = 64: three) to a compute unit, as many wavefronts per SIMD, ~256 (~168) registers each.  Per tile:
 //   K/V rows go HBM/L2 -> LDS directly (buffer_load ... lds, 16 B per lane; the descriptor's range
-//   check drops rows past the end of the unpadded level-1 arrays), two buffers each; a tile's K rows
+//   check drops rows past the end of the unpadded level-1 arrays), two buffers each for 128-row workgroups: a tile's K rows
 //   are requested one and a half steps before its first product, its V rows one and a half steps
-//   before its second product.  The 16-byte chunks of a row are XOR-swizzled on the way in so that
+//   before its second product (smaller workgroups mostly have one buffer each and half a step, see BUFS).  The 16-byte chunks of a row are XOR-swizzled on the way in so that
 //   the MFMA operand reads are bank-conflict free without padding.
 //   S^T = K_tile Q^T        (A = K rows from LDS, B = Q fragments held in registers)
 //   online softmax in the log2 domain; the accumulator layout of S^T puts ONE query row in each
@@ -74,9 +74,8 @@ struct LevelState {
 // block holds at least as many rows as one load instruction covers
 // BN: key columns per tile, 64 or 32 (see launch_mfma_d).
 // Wavefronts per SIMD: with tiles of 64 as many as the registers of the loop allow.  Workgroups of one or two wavefronts
-// with tiles of 32: NOT more registers free than for one or two (d = 64: two or three) wavefronts per SIMD, since with
-// room for more the workgroups of a compute unit were put on few of its four SIMDs.  (LDS would take four per SIMD at
-// d = 64 and two wavefronts a workgroup; three is what was measured.)  Measured, 12 heads x 32760
+// with tiles of 32: registers for just as many wavefronts per SIMD as the LDS takes (most_waves: with two buffers one or two, d = 64 two or three; with one buffer
+// two or three, d = 64 three or four), since with room for more the workgroups of a compute unit were put on few of its four SIMDs.  Measured with two buffers, 12 heads x 32760
 // tokens (pyramid included), tiles of 64 and two wavefronts per SIMD allowed -> tiles of 32, no tight limit -> this:
 // 32-row blocks d = 128 4104 -> 3915 -> 2360 us, d = 64 1752 -> 1685 -> 1180; 64-row blocks d = 128 2142 -> 1777 -> 1765,
 // d = 64 1160 -> 1118 -> 1040.
@@ -303,7 +302,7 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
   auto load_rows = [&](__amdgpu_buffer_rsrc_t rsrc, unsigned char* to, uint32_t row_off, uint32_t lane_off) __attribute__((always_inline)) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)to, 16, (int)(SC ? lane_off : row_off + lane_off), (int)(SC ? row_off : 0u), 0, 0);
   };
-  auto fire_k = [&](int t) __attribute__((always_inline)) {      // K rows of tile t -> K buffer t & 1
+  auto fire_k = [&](int t) __attribute__((always_inline)) {      // K rows of tile t -> K buffer t & (BUFS - 1)
     // rows past the end of the unpadded level-1 array are out of the descriptor's range: such lanes
     // read nothing (the scores of those columns are masked, see fixup_special)
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)planK_kbase, 0, (int)planK_nrec, RSRC_FLAGS);
@@ -311,7 +310,7 @@ void attn_mfma_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K
     for (int k = 0; k < RI; ++k)
       load_rows(rsrc, smem + OFF_K + (t & (BUFS - 1)) * TILEB + (k * NW + wave) * RPI * ROWB, planK[k], klane[k % KP]);
   };
-  auto fire_v = [&](int t) __attribute__((always_inline)) {      // V rows of tile t -> V buffer t & 1
+  auto fire_v = [&](int t) __attribute__((always_inline)) {      // V rows of tile t -> V buffer t & (BUFS - 1)
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)planV1_vbase, 0, (int)planV1_nrec, RSRC_FLAGS);
 #pragma unroll
     for (int k = 0; k < RI; ++k)

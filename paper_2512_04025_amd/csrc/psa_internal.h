@@ -69,10 +69,10 @@ hipError_t launch_representatives(const Plan& pl, const void* Q, void* Rq, const
 hipError_t launch_importance(const Plan& pl, const void* Qrep, const void* Krep, void* part, void* bmax, float* S,
                              FactoredScores* factored, hipStream_t s);
 // Scores come from S, or (factored != null) are evaluated from the factored form and, if S_out is given,
-// written there as well.  rowcnt: per-row counters [n_visible, c_1..c_H] (scratch).
-// (Eq. 9 per head stays a kernel of its own: summing the rows' counters with atomics from the allocation
-// kernel's 256+ workgroups per head onto a handful of addresses was measured 70 us slower than that 4 us kernel.)
-// rho (nullable): Eq. 9 per head.
+// written there as well.  rho (nullable): Eq. 9 per head.  Heads of few short rows are one workgroup, which sums up Eq. 9 itself; for all others it is a
+// kernel of its own that reads rowcnt, the per-row counters [n_visible, c_1..c_H] (scratch, left alone otherwise).
+// (Summing the rows' counters with atomics from the allocation kernel's 256+ workgroups per head onto a handful of addresses was measured 70 us slower than that
+// 4 us kernel.)
 hipError_t launch_allocate(const Plan& pl, const float* S, const FactoredScores* factored, float* S_out,
                            const uint8_t* cap, uint8_t* M, uint32_t* rowcnt, float* rho, hipStream_t s);
 // Per query block its level-sorted block list and level counts and, unless desc is null or Plan::desc_pitch is 0, per
