@@ -143,12 +143,20 @@ struct ImpArgs {
 
 constexpr int IMP_ROWS = 8;  // representative query rows processed per sweep over the keys
 
+// The channels of the query rows are the same for all threads.  float32: through the scalar cache, as scalar operands of the multiply-adds (from LDS each was
+// waited for: 226 LDS instructions a wavefront and three quarters of its time, 18 us for 32 workgroups of 2 heads x 1024 tokens, 9 so).  bfloat16: a scalar
+// instruction would widen each of them for each multiply-add (16 heads x 11049 causal tokens in 32-token blocks, four representatives, 820 us), so they are
+// widened once, into LDS (606).
+template <typename T> constexpr bool rows_staged = sizeof(T) == 2;
+
 template <typename T, int D>
 __global__ __launch_bounds__(256) void importance_kernel(const T* __restrict__ Qrep, const T* __restrict__ Krep,
                                                          float* __restrict__ S, ImpArgs a) {
   constexpr int VEC = Elem<T>::VEC;
   extern __shared__ float smem[];
-  float* rowstat = smem;                            // [sq][2]: row max, row sum
+  constexpr bool STAGED = rows_staged<T>;
+  float* qs = smem;                                 // STAGED: query rows [IMP_ROWS][D]
+  float* rowstat = qs + (STAGED ? IMP_ROWS * D : 0);   // [sq][2]: row max, row sum
   float* bmax = rowstat + 2 * a.sq;                 // [sq][nk]
   float* bsum = bmax + (size_t)a.sq * a.nk;         // [sq][nk]
   const int tid = threadIdx.x;
@@ -161,14 +169,19 @@ __global__ __launch_bounds__(256) void importance_kernel(const T* __restrict__ Q
 
   for (int r0 = 0; r0 < a.sq; r0 += IMP_ROWS) {
     const int nr = a.sq - r0 < IMP_ROWS ? a.sq - r0 : IMP_ROWS;
-    // The rows' channels are the same for all threads: through the scalar cache, as scalar operands of the multiply-adds.  (From LDS each was waited for:
-    // 226 LDS instructions a wavefront and three quarters of its time, 18 us for 32 workgroups.)  Rows past the end: the last one, results not used.
+    // (rows past the end: the last one, results not used)
     const T* qrow[IMP_ROWS];
     int qpos[IMP_ROWS];
 #pragma unroll
     for (int r = 0; r < IMP_ROWS; ++r) {
       qrow[r] = qbase + (int64_t)(r0 + (r < nr ? r : nr - 1)) * D;
       qpos[r] = r < nr ? rep_pos(a.mode, i, r0 + r, a.bq, a.sq, a.N) : -1;
+    }
+
+    if constexpr (STAGED) {
+      __syncthreads();
+      for (int x = tid; x < IMP_ROWS * D; x += 256) qs[x] = Elem<T>::to_f32(qbase[(int64_t)(r0 + (x / D < nr ? x / D : nr - 1)) * D + x % D]);
+      __syncthreads();
     }
 
     for (int c = tid; c < nkeys_pad; c += 256) {
@@ -181,15 +194,31 @@ __global__ __launch_bounds__(256) void importance_kernel(const T* __restrict__ Q
         const T* kp = kbase + (int64_t)c * D;
         constexpr int BATCH = 64 / VEC;                  // 64 channels of the key in flight
         for (int c0 = 0; c0 < D / VEC; c0 += BATCH) {
-          float kv[BATCH][VEC];
+          if constexpr (STAGED) {
+            u32x4 raw[BATCH];
 #pragma unroll
-          for (int x = 0; x < BATCH; ++x) Elem<T>::load(kp + (c0 + x) * VEC, kv[x]);
+            for (int x = 0; x < BATCH; ++x) raw[x] = *reinterpret_cast<const u32x4*>(kp + (c0 + x) * VEC);
+            __builtin_amdgcn_sched_barrier(0);           // (widened when they are used, not before: half the registers, 414 -> 363 us at 28 heads x 11060)
 #pragma unroll
-          for (int x = 0; x < BATCH; ++x)
+            for (int x = 0; x < BATCH; ++x) {
+              float kv[VEC];
+              Elem<T>::widen(raw[x], kv);
 #pragma unroll
-            for (int r = 0; r < IMP_ROWS; ++r)
+              for (int r = 0; r < IMP_ROWS; ++r)
 #pragma unroll
-              for (int e = 0; e < VEC; ++e) acc[r] = fmaf(Elem<T>::to_f32(qrow[r][(c0 + x) * VEC + e]), kv[x][e], acc[r]);
+                for (int e = 0; e < VEC; ++e) acc[r] = fmaf(qs[r * D + (c0 + x) * VEC + e], kv[e], acc[r]);
+            }
+          } else {
+            float kv[BATCH][VEC];
+#pragma unroll
+            for (int x = 0; x < BATCH; ++x) Elem<T>::load(kp + (c0 + x) * VEC, kv[x]);
+#pragma unroll
+            for (int x = 0; x < BATCH; ++x)
+#pragma unroll
+              for (int r = 0; r < IMP_ROWS; ++r)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) acc[r] = fmaf(qrow[r][(c0 + x) * VEC + e], kv[x][e], acc[r]);
+          }
         }
       }
       // The rows side by side, so that a step waits once for the lane exchanges of all of them: latency decides here (32
@@ -253,9 +282,9 @@ __global__ __launch_bounds__(256) void importance_kernel(const T* __restrict__ Q
   }
 }
 
-static size_t importance_smem_bytes(int sq, int nk) { return sizeof(float) * (2 * (size_t)sq + 2 * (size_t)sq * nk); }
-// Rows are refused where IMP_ROWS query rows, which were kept in LDS once, would no longer fit next to that: the limit that callers know.
-bool importance_row_fits(int sq, int nk, int d) { return importance_smem_bytes(sq, nk) + sizeof(float) * IMP_ROWS * d <= LDS_LIMIT; }
+static size_t importance_smem_bytes(int sq, int nk, int staged_d) { return sizeof(float) * ((size_t)IMP_ROWS * staged_d + 2 * (size_t)sq + 2 * (size_t)sq * nk); }
+// (float32 rows are refused at the same length, though theirs are not in LDS: the limit that callers know)
+bool importance_row_fits(int sq, int nk, int d) { return importance_smem_bytes(sq, nk, d) <= LDS_LIMIT; }
 
 template <typename T, int D>
 static hipError_t launch_imp_t(const Plan& pl, const void* Qrep, const void* Krep, float* S, hipStream_t s) {
@@ -263,7 +292,7 @@ static hipError_t launch_imp_t(const Plan& pl, const void* Qrep, const void* Kre
   a.N = pl.N; a.Hq = pl.Hq; a.Hkv = pl.Hkv; a.nq = pl.nq; a.nk = pl.nk; a.bq = pl.bq; a.bk = pl.bk;
   a.sq = pl.sq; a.sk = pl.sk; a.mode = pl.rep_mode; a.causal = pl.causal; a.est_pool = pl.est_pool;
   a.scale = pl.scale;
-  const size_t smem = importance_smem_bytes(pl.sq, pl.nk);
+  const size_t smem = importance_smem_bytes(pl.sq, pl.nk, rows_staged<T> ? D : 0);
   auto kern = importance_kernel<T, D>;
   static LdsOptIn optin;                       // one per kernel instantiation
   const hipError_t e = allow_max_lds(reinterpret_cast<const void*>(kern), &optin);
