@@ -134,8 +134,12 @@ static int plan_allocation(const psa_params* p, Plan* o) {
   return PSA_OK;
 }
 
-static bool few_pairs(const Plan& pl) { return (int64_t)pl.B * pl.Hq * pl.nq * pl.nk <= 40000; }
-bool lists_in_kernel(const Plan& pl, bool descriptors) { return pl.nk <= ROW_LISTS_NK && (!descriptors || pl.desc_pitch == 0 || few_pairs(pl)); }
+bool lists_in_kernel(const Plan& pl, bool descriptors) {
+  if (pl.nk > ROW_LISTS_NK) return false;
+  if (!descriptors || pl.desc_pitch == 0) return true;
+  const int64_t workgroups = (int64_t)pl.B * pl.Hq * pl.nq * ((pl.bq + 127) / 128);
+  return pl.N <= 5120 && pl.N * (workgroups > 512 ? workgroups : 512) <= 5120 * 512;
+}
 
 static inline char* at(void* base, size_t off) { return static_cast<char*>(base) + off; }
 

@@ -80,9 +80,10 @@ hipError_t launch_allocate(const Plan& pl, const float* S, const FactoredScores*
 hipError_t launch_lists(const Plan& pl, const uint8_t* M, uint16_t* idx, int32_t* cnt, uint32_t* desc, hipStream_t s);
 // Whether the kernels that walk a row's list make it from the level map themselves (M given, idx and cnt unused) instead of reading what
 // launch_lists has made (M null): short rows, for which a launch of 4 us counts.  descriptors: the caller would get tile descriptors with the lists
-// (the forward's 128-row workgroups), which save 3 to 7 % of the attention: there only up to 40000 block pairs.  Whole call, us with a launch /
-// without: 12 heads x 1000 tokens 44.0 / 42.0, x 4000 56.2 / 53.6 (24000 pairs), x 8000 138 / 141 (94000), 28 causal x 8000 187 / 200; f32 2 x 1024 45.6 / 44.0;
-// 32-row blocks 12 x 4000 58.5 / 52.2; gradients 8 x 745 49.7 / 47.2.
+// (the forward's 128-row workgroups), which save up to 10 % of the attention: there only up to 5120 tokens times rounds of the chip (512 workgroups), where
+// none of 250 shapes is more than 3 % slower for it.  Attention call, us with a launch / without: 1 head x 1280 tokens 13.5 / 11.1, 40 x 1150 14.3 / 11.9, 12 x 2000
+// 14.7 / 12.0, 3 x 4100 24.4 / 23.5, 4 x 5240 34.6 / 36.4, 40 x 3033 74.3 / 80.3, 1 x 12875 71.6 / 78.9, 40 x 7998 at d = 64 173 / 188.  Others, whole call: f32 2 x 1024
+// 45.6 / 44.0; 32-row blocks 12 x 4000 58.5 / 52.2; gradients 8 x 745 49.7 / 47.2.
 bool lists_in_kernel(const Plan& pl, bool descriptors);
 // M and idx both null: dense attention (every key block at level 1)
 hipError_t launch_attn_f32(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp,

@@ -81,3 +81,21 @@ def test_gradients_of_shared_walks(N, d, bq, levels, causal):
     want = orc.psa_attention_backward(Q64, orc.build_pyramid(K64, op), orc.build_pyramid(V64, op), M, dO64, op)
     for name, x, w in zip(("dQ", "dK", "dV"), grads, want):
         assert np.abs(from_dev(x, "bf16") - w).max() <= 2e-2 * max(1.0, float(np.abs(w).max())), name
+
+
+@pytest.mark.parametrize("Hq,N,bk,bq,own", [(12, 1000, 64, 128, True), (1, 5100, 64, 128, True), (1, 14634, 128, 128, False), (40, 3033, 128, 128, False),
+                                            (1, 14634, 128, 64, True), (1, 8200, 64, 64, False)])
+def test_which_calls_make_their_lists_themselves(Hq, N, bk, bq, own):
+    """Rows of up to 128 blocks; 128-row query blocks, which lose their tile descriptors with it, only where tokens times rounds of the
+    chip are few.  Calls that make them write nothing into the workspace."""
+    import torch
+    gp = psa.make_params(1, Hq, 1, N, 128, bq, bk, 1, causal=True, sq=8, sk=8)
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    Q, K, V = (torch.randn((1, h, N, 128), generator=gen, device="cuda").to(torch.bfloat16) for h in (Hq, 1, 1))
+    buf = Buffers(gp)
+    buf.M.zero_()
+    buf.M[..., 0] = 1
+    buf.scratch.fill_(255)
+    psa.psa_attention_fwd(gp, Q, K, V, None, None, buf.M, buf.O, buf.scratch)
+    torch.cuda.synchronize()
+    assert bool((buf.scratch == 255).all()) == own
