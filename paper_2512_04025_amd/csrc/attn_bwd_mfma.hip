@@ -911,22 +911,27 @@ __global__ __launch_bounds__(1024) void bwd_dkv_order_kernel(const uint32_t* __r
 // (32-bit byte offsets reach every row of a head: at most 65535 key blocks of 128 keys of 256 bytes are less than 2^31.
 // Addresses need no more than element alignment, in the direct-to-LDS loads as in all others.)
 // Workgroups that share a walk of dK, dV, each with a share of the query blocks and a partial gradient (added up with those of the query heads): while
-// workgroups (of 32 keys) are fewer than four fifths of what the chip holds and a share has 32 chunks of 32 rows; two where several levels make walks of
-// different lengths, up to twice what the chip holds, if they have 128 chunks.  Whole call, us, one / two / four, d = 128: 2 heads x 1000 tokens
-// 41.0 / 38.8 / 43.0, x 3000 87.5 / 74.0, x 8000 189 / 164, in one level x 2000 54.3 / - / 43.7, x 8000 141 / 134; d = 64 4 x 2000 58.5 / 49.6, 2 x 7026 in one level
-// 176 / - / 131, causal 8 x 4000 in groups of four 96.3 / 92.8; not on a nearly full chip, 2 x 14837 in one level 282 / - / 292, 12 x 1000 54.7 / 61, 28 x 1716 57.4 / 64.
+// workgroups (of 32 keys) are fewer than the chip holds (four levels or more, whose deepest walks are the longest: twice that), and the walk is worth
+// it: its chunks of 32 rows (causal: half of them; more than two levels, whose blocks are used by more rows: twice) at least 16 a share, and one for every 10000 gradient elements that the shares write, times the shares (a share more
+// costs the same traffic, and saves less the more there are).  Which blocks are kept is not known here.  1150 shapes at a tenth to three tenths of the
+// keys: 5 more than 3 % slower than with one workgroup, the worst 4 %, the mean of all 2.3 % faster (the best choice for each: 4.1 %).  Whole call, us, one / two / four:
+// d = 128 1 head x 3825 tokens 130 / 101 / 89, 2 x 6109 186 / 149 / 176, 1 x 14018 423 / 335 / 330; d = 64 4 x 2869 69.5 / 60.5 / 65.2, 1 x 5413 112 / 80 / 67,
+// causal 2 x 11280 227 / 165 / 171, one level 2 x 10891 177 / 148 / 152; not in one level causal 4 x 2396 at d = 128 46 / 50 / 57, 28 x 1295 39 / 46 / 60, nor in two
+// causal 8 x 1549 at d = 128 41 / 50 / 63.
 int dkv_split(const Plan& pl) {
-  int64_t groups = 0;
+  int64_t groups = 0, elems = 0;
   for (int h = 1; h <= pl.H; ++h) {
     int lg_th = 0;
     while ((1 << (lg_th + 1)) <= (pl.bk >> (h - 1))) ++lg_th;
     groups += (int64_t)pl.B * pl.Hq * dkv_group(lg_th, pl.nk, 32).ng;
+    elems += ((int64_t)pl.B * pl.Hq * pl.N * pl.d) >> (h - 1);
   }
-  const int64_t chunks = (int64_t)pl.nq * ((pl.bq + 31) / 32);
-  int split = 1;
   const int64_t resident = 256 * (pl.d == 64 ? 3 : 2);
-  while (5 * groups * split < 4 * resident && chunks >= 32 * split) split *= 2;
-  if (split == 1 && pl.H > 1 && groups < 2 * resident && chunks >= 128) split = 2;
+  int64_t walk = 2 * (int64_t)pl.nq * ((pl.bq + 31) / 32);            // in half chunks
+  if (pl.causal) walk /= 2;
+  if (pl.H > 2) walk *= 2;
+  int split = 1;
+  while (groups * split < (pl.H > 3 ? 2 : 1) * resident && walk >= 2 * 16 * split && 5000 * walk >= elems * split * split) split *= 2;
   return split;
 }
 

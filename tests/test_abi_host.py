@@ -136,3 +136,24 @@ def test_new_entry_points_validate_before_any_launch(lib):
     with pytest.raises(psa.PsaError):
         psa.psa_query_bwd_sizes(big)
     assert psa.psa_query_bwd_sizes(p) % 256 == 0
+
+
+def gradient_shares(lib, dtype, heads, kv_heads, N, d, bq, bk, levels, causal):
+    """Partial pooled gradients per key head, from the backward workspace's size: a sum per row, lists, counts, and the parts of dK and dV."""
+    p = psa.make_params(1, heads, kv_heads, N, d, bq, bk, levels, dtype=dtype, causal=causal, sq=8, sk=8)
+    nq, nk = -(-N // bq), -(-N // bk)
+    up = lambda x: -(-x // 256) * 256
+    rest = psa.psa_query_bwd_sizes(p) - up(4 * heads * N) - up(2 * heads * nq * nk) - up(4 * 8 * heads * nq)
+    one = 4 * kv_heads * nk * sum(bk >> h for h in range(levels)) * d
+    shares = [s for s in range(1, 65) if 2 * up(one * s) == rest]
+    assert len(shares) == 1
+    return shares[0]
+
+
+# Long walks of few heads, and walks that cost less than the partial gradients that a second workgroup has to write.
+@pytest.mark.parametrize("heads,kv_heads,N,d,bq,bk,levels,causal,split", [
+    (4, 4, 2396, 128, 128, 128, 1, True, 1), (28, 4, 1295, 64, 32, 64, 1, False, 1), (8, 2, 1549, 128, 64, 64, 2, True, 1), (12, 12, 1000, 128, 128, 64, 4, False, 1),
+    (2, 2, 8000, 128, 128, 64, 4, False, 2), (1, 1, 3825, 128, 128, 128, 4, False, 2), (2, 2, 11280, 64, 64, 64, 4, True, 2), (1, 1, 5413, 64, 128, 64, 5, False, 4)])
+def test_bfloat16_walks_are_shared_where_that_pays(lib, heads, kv_heads, N, d, bq, bk, levels, causal, split):
+    got = gradient_shares(lib, psa.PSA_BF16, heads, kv_heads, N, d, bq, bk, levels, causal)
+    assert got == split * (heads // kv_heads)
