@@ -580,18 +580,20 @@ static int dkv_groups(const Plan& pl) {
 // Partial pooled-gradient tensors per key head.  The matrix-core kernel writes one per query head of the group and share of a walk.
 int bwd_parts(const Plan& pl) {
   if (bwd_uses_mfma(pl)) return pl.group * dkv_split(pl);
-  // The other one splits the columns of short launches over up to eight workgroups, whose sums unpool_kernel adds: while there are fewer than 400 workgroups (d = 64:
-  // 800; the chip holds 256 and 512) and the column is worth it: its chunks of 32 rows (causal: a third of them) at least eight a part, and one for every
-  // 15000 gradient elements that the parts write, times the parts (a part more costs the same traffic, and saves less the more there are).  Which blocks are
-  // kept is not known here.  950 shapes at a tenth to three tenths of the keys: 11 more than 3 % slower than with one workgroup, the worst 15 %, the mean of all 10.6 %
-  // faster (the best choice for each: 15 %).  Whole call, us, one / two / four / eight, one level: 8 heads in groups of four x 1258 tokens, d = 64 176 / 115 / 82 / 76; 28 in
-  // groups of seven x 902 112 / 85 / 84 / 87, x 900 causal at d = 128 141 / 114 / 123 / 142; 2 x 697 54 / 43 / 38 / 40; four levels 8 in groups of four x 1185, d = 128
-  // 409 / 270 / 209 / 193; not two levels 2 x 1721 causal 35 / 42 / 47 / 55, one level 16 x 928 at d = 128 130 / 159 / 177 / 226.
+  // The other one splits the columns of short launches over up to eight workgroups, whose sums unpool_kernel adds: while there are fewer than 500 workgroups (d = 64:
+  // 1000; the chip holds 256 and 512) and the column is worth it.  A part more saves less the more there are, and costs each time what the workgroups write (a
+  // block of fewer than 32 pooled keys takes as long as a full one) and what is added again: the column's length, squared where it is long, against both sums, times
+  // the parts squared.  Length: chunks of 32 rows, of which a causal column sees about a third; which blocks are kept is not known here.  950 shapes at a tenth to
+  // three tenths of the keys: 4 more than 3 % slower than with one workgroup, the worst 8 %, the mean of all 9.6 % faster (the best choice for each: 15 %).  Whole call,
+  // us, one / two / four / eight, one level: 8 heads in groups of four x 1258 tokens, d = 64 176 / 115 / 82 / 76; 28 in groups of seven x 902 112 / 85 / 84 / 87, x 900
+  // causal at d = 128 141 / 114 / 123 / 142; 2 x 697 54 / 43 / 38 / 40; four levels 8 in groups of four x 1185, d = 128 409 / 270 / 209 / 193; not two levels
+  // 2 x 1721 causal 35 / 42 / 47 / 55, one level 16 x 928 at d = 128 130 / 159 / 177 / 226, blocks of 8 keys 4 x 1047 in pairs causal 43 / 50.
   const int64_t wgs = (int64_t)pl.B * pl.Hkv * dkv_groups(pl), walk = (int64_t)pl.group * pl.nq * ((pl.bq + 31) / 32) * (pl.causal ? 1 : 3);   // (in thirds of a chunk)
-  int64_t elems = 0;
-  for (int h = 1; h <= pl.H; ++h) elems += ((int64_t)pl.B * pl.Hkv * pl.N * pl.d) >> (h - 1);
+  int64_t cost = wgs * 32 * pl.d;
+  for (int h = 1; h <= pl.H; ++h) cost += ((int64_t)pl.B * pl.Hkv * pl.N * pl.d) >> (h - 1);
+  const double gain = 40.0 * walk * std::max<int64_t>(walk, 200);
   int parts = 1;
-  while (parts < 8 && wgs * parts < (pl.d == 64 ? 800 : 400) && walk >= 24 * parts && 5000 * walk >= elems * parts * parts) parts *= 2;
+  while (parts < 8 && wgs * parts < (pl.d == 64 ? 1000 : 500) && walk >= 12 * parts && gain >= (double)cost * parts * parts) parts *= 2;
   return parts;
 }
 

@@ -161,6 +161,6 @@ def test_bfloat16_walks_are_shared_where_that_pays(lib, heads, kv_heads, N, d, b
 
 @pytest.mark.parametrize("heads,kv_heads,N,d,bq,bk,levels,causal,parts", [
     (2, 2, 1721, 64, 128, 64, 2, True, 1), (16, 16, 928, 128, 256, 64, 1, False, 1), (12, 12, 1000, 128, 128, 64, 4, False, 1),
-    (28, 4, 900, 128, 128, 64, 1, True, 2), (8, 2, 1185, 128, 128, 64, 4, False, 4), (8, 2, 1258, 64, 128, 64, 1, False, 4), (8, 1, 1201, 64, 128, 64, 4, False, 8)])
+    (28, 4, 900, 128, 128, 64, 1, True, 2), (8, 2, 1185, 128, 128, 64, 4, False, 4), (8, 2, 1258, 64, 128, 64, 1, False, 8), (4, 2, 1047, 64, 64, 8, 2, True, 1), (8, 1, 1201, 64, 128, 64, 4, False, 8)])
 def test_float32_columns_are_shared_where_that_pays(lib, heads, kv_heads, N, d, bq, bk, levels, causal, parts):
     assert gradient_shares(lib, psa.PSA_F32, heads, kv_heads, N, d, bq, bk, levels, causal) == parts

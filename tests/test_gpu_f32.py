@@ -207,7 +207,7 @@ def test_infinite_keys_and_values_act_as_in_float32(N, Hq, bq, d):
     assert np.abs(lse[sees] - (top + np.log(total))[..., 0][sees]).max() <= 1e-4
 
 
-@pytest.mark.parametrize("shape", [("f32", 1, 8, 2, 611, 128, 128, 64, 3, True), ("f32", 1, 8, 2, 611, 128, 128, 64, 3, False), ("f32", 1, 8, 1, 1201, 64, 128, 64, 4, False), ("f32", 1, 2, 2, 1000, 64, 64, 64, 4, False)],
+@pytest.mark.parametrize("shape", [("f32", 1, 8, 2, 611, 128, 128, 64, 3, True), ("f32", 1, 8, 2, 611, 64, 128, 64, 3, False), ("f32", 1, 8, 1, 1201, 64, 128, 64, 4, False), ("f32", 1, 2, 2, 1000, 64, 64, 64, 4, False)],
                          ids=lambda s: "-".join(map(str, s)))
 def test_gradients_of_split_columns(shape):
     """Short launches whose columns of the level map are shared by two, four, eight and two workgroups (same bars)."""
