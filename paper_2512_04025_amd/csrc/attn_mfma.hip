@@ -83,7 +83,7 @@ struct LevelState {
 // V(t)) a load has half a step to arrive instead of one and a half, but a workgroup's LDS is half as large and one more wavefront
 // fits on every SIMD: a lone wavefront issues for 1400 of the 2100 cycles that a 32-column tile took and waits for the rest.  Pyramid and attention, 12 heads,
 // a fifth of the keys, us for two buffers / one (both with the work order below): 32-row blocks d = 128 x 4000 tokens 78 / 59, x 9000 266 / 203, x 18000 799 / 651,
-// x 32760 2330 (one head at a time) / 2285; d = 64 x 6000 81 / 69, x 24000 658 / 612; 64-row blocks d = 128 x 6000 105 / 91, x 13000 357 / 312, x 24000 998 / 916.
+// x 32760 2330 (one head at a time) / 2285 (longer launches: see launch_mfma_d); d = 64 x 6000 81 / 69, x 24000 658 / 612; 64-row blocks d = 128 x 6000 105 / 91, x 13000 357 / 312, x 24000 998 / 916.
 constexpr int most_waves(int d, int nw, bool sc, int bn, int bufs) {
   return bn == 64 ? (d == 64 ? 3 : 2) : bufs == 2 ? (d == 64 ? nw + 1 : nw) : d == 64 ? nw + 2 : sc ? nw + 1 : 2;
 }
@@ -875,11 +875,22 @@ static hipError_t launch_mfma_d(const Plan& pl, const void* Q, const void* K, co
   const int64_t wgs = (int64_t)pl.B * pl.Hq * pl.nq * ((pl.bq + NW * 32 - 1) / (NW * 32));
   const int64_t resident = 256 * (int64_t)(LDS_LIMIT / attn_mfma_smem_bytes(D, pl.nk, 64, 2, NW));
   const bool wide = NW == 4 || (wgs <= resident && pl.N >= (NW == 1 ? 6144 : 2 * wgs <= resident ? 3000 : 4096));
-  // Buffers of a narrow tile (see the kernel): two only for d = 64 in 64-row blocks, where three wavefronts fit a SIMD with two buffers and four with one,
+  // Buffers of a narrow tile (see the kernel).  64-row blocks: two only for d = 64, where three wavefronts fit a SIMD with two buffers and four with one,
   // if the rounds of the chip then hold fewer wavefronts.  12 heads, us for two / one: x 6000 68.5 / 69.5, x 9000 124 / 113, x 13000 210 / 218, x 18000
   // 376 / 366, x 32760 1035 / 1011, pooled blocks of four keys x 8000 89 / 102.
+  // 32-row blocks: one buffer while the workgroups on an XCD walk a head's keys closely enough together for its L2 to serve them.  With twice as many of
+  // them, and half a step for a load to arrive, they fall apart over the rounds of a long launch and then wait for the memory behind the L2, which two buffers
+  // hide.  Where that begins goes by the launch's workgroups times the keys and values of a head, levels included; causal (each XCD on heads of its own) and at
+  // d = 128 by the length.  Attention, us for two / one: d = 128 12 heads x 16145 tokens at 0.3 of the keys 1.33 times as fast with one, 40 grouped x 12365 at 0.2
+  // 1.37 times; 8 grouped x 30169 at 0.2 1.24 times slower, 40 grouped x 24041 at 0.3 6036 / 9113, 28 grouped x 34953 at 0.3 8737 / 15401, 8 grouped x 66597 at 0.2
+  // 6363 / 11601, causal 40 x 31561 at 0.2 3577 / 3084; d = 64 16 x 62042 at 0.3 8130 / 11268, 40 x 45812 at 0.2 8000 / 10962, 40 x 38760 at 0.3 8236 / 8080.
   const int64_t in_one = 256 * 2 * most_waves(D, 2, true, 32, 1), in_two = 256 * 2 * most_waves(D, 2, true, 32, 2);
-  const bool one_buffer = (wgs + in_one - 1) / in_one * in_one <= (wgs + in_two - 1) / in_two * in_two;
+  bool one_buffer = D == 128 || (wgs + in_one - 1) / in_one * in_one <= (wgs + in_two - 1) / in_two * in_two;
+  if (NW == 1) {
+    int64_t elems = 0;
+    for (int h = 1; h <= pl.H; ++h) elems += ((int64_t)pl.N * D) >> (h - 1);
+    one_buffer = (pl.causal || 4.0 * elems * wgs < (D == 64 ? 250e9 : 150e9)) && (D == 64 || pl.N <= 32768);
+  }
   auto launch = [&](auto sc, auto bn, auto bufs) {
     return launch_mfma_t<D, NW, decltype(sc)::value, decltype(bn)::value, decltype(bufs)::value>(pl, Q, K, V, Kp, Vp, M, idx, cnt, desc, O, lse, s);
   };
@@ -891,7 +902,7 @@ static hipError_t launch_mfma_d(const Plan& pl, const void* Q, const void* K, co
     return blocks_cover_a_load ? launch(std::true_type{}, c64, c2) : launch(std::false_type{}, c64, c2);
   } else {
     auto narrow = [&](auto sc) {
-      if constexpr (D == 64 && NW == 2) {
+      if constexpr (D == 64 || NW == 1) {
         if (!one_buffer) return launch(sc, c32, c2);
       }
       return launch(sc, c32, c1);
