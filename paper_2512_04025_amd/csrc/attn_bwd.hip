@@ -588,7 +588,7 @@ int bwd_parts(const Plan& pl) {
   // us, one / two / four / eight, one level: 8 heads in groups of four x 1258 tokens, d = 64 176 / 115 / 82 / 76; 28 in groups of seven x 902 112 / 85 / 84 / 87, x 900
   // causal at d = 128 141 / 114 / 123 / 142; 2 x 697 54 / 43 / 38 / 40; four levels 8 in groups of four x 1185, d = 128 409 / 270 / 209 / 193; not two levels
   // 2 x 1721 causal 35 / 42 / 47 / 55, one level 16 x 928 at d = 128 130 / 159 / 177 / 226, blocks of 8 keys 4 x 1047 in pairs causal 43 / 50.
-  const int64_t wgs = (int64_t)pl.B * pl.Hkv * dkv_groups(pl), walk = (int64_t)pl.group * pl.nq * ((pl.bq + 31) / 32) * (pl.causal ? 1 : 3);   // (in thirds of a chunk)
+  const int64_t wgs = (int64_t)pl.B * pl.Hkv * dkv_groups(pl), walk = pl.group * column_chunks(pl) * (pl.causal ? 1 : 3);   // (in thirds of a chunk)
   int64_t cost = wgs * 32 * pl.d;
   for (int h = 1; h <= pl.H; ++h) cost += ((int64_t)pl.B * pl.Hkv * pl.N * pl.d) >> (h - 1);
   const double gain = 40.0 * walk * std::max<int64_t>(walk, 200);

@@ -927,7 +927,7 @@ int dkv_split(const Plan& pl) {
     elems += ((int64_t)pl.B * pl.Hq * pl.N * pl.d) >> (h - 1);
   }
   const int64_t resident = 256 * (pl.d == 64 ? 3 : 2);
-  int64_t walk = 2 * (int64_t)pl.nq * ((pl.bq + 31) / 32);            // in half chunks
+  int64_t walk = 2 * column_chunks(pl);            // in half chunks
   if (pl.causal) walk /= 2;
   if (pl.H > 2) walk *= 2;
   int split = 1;

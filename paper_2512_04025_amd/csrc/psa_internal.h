@@ -96,6 +96,11 @@ hipError_t launch_attn_mfma(const Plan& pl, const void* Q, const void* K, const 
 // Backward of the pyramid attention.  Dr: [B*Hq*N] floats; dKp, dVp: pooled gradients of levels 1..H
 // (bwd_pooled_grad_elems floats each); idx / cnt: the level-sorted block lists of launch_lists.
 size_t bwd_pooled_grad_elems(const Plan& pl);
+// Chunks of 32 query rows in a column of the level map, the last query block's only as far as it has rows.
+inline int64_t column_chunks(const Plan& pl) {
+  const int64_t full = pl.nq - 1;
+  return full * ((pl.bq + 31) / 32) + (pl.N - full * pl.bq + 31) / 32;
+}
 hipError_t launch_attn_bwd(const Plan& pl, const void* Q, const void* K, const void* V, const void* Kp, const void* Vp,
                            const uint8_t* M, const uint16_t* idx, const int32_t* cnt, const void* O, const float* lse,
                            const void* dO, float* Dr, float* dKp, float* dVp, void* dQ, void* dK, void* dV, hipStream_t s);

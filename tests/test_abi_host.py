@@ -152,7 +152,7 @@ def gradient_shares(lib, dtype, heads, kv_heads, N, d, bq, bk, levels, causal):
 
 # Long walks of few heads, and walks that cost less than the partial gradients that a second workgroup has to write.
 @pytest.mark.parametrize("heads,kv_heads,N,d,bq,bk,levels,causal,split", [
-    (4, 4, 2396, 128, 128, 128, 1, True, 1), (28, 4, 1295, 64, 32, 64, 1, False, 1), (8, 2, 1549, 128, 64, 64, 2, True, 1), (12, 12, 1000, 128, 128, 64, 4, False, 1),
+    (4, 4, 2396, 128, 128, 128, 1, True, 1), (28, 4, 1295, 64, 32, 64, 1, False, 1), (28, 4, 57, 64, 512, 64, 5, False, 1), (8, 2, 1549, 128, 64, 64, 2, True, 1), (12, 12, 1000, 128, 128, 64, 4, False, 1),
     (2, 2, 8000, 128, 128, 64, 4, False, 2), (1, 1, 3825, 128, 128, 128, 4, False, 2), (2, 2, 11280, 64, 64, 64, 4, True, 2), (1, 1, 5413, 64, 128, 64, 5, False, 4)])
 def test_bfloat16_walks_are_shared_where_that_pays(lib, heads, kv_heads, N, d, bq, bk, levels, causal, split):
     got = gradient_shares(lib, psa.PSA_BF16, heads, kv_heads, N, d, bq, bk, levels, causal)
@@ -161,6 +161,6 @@ def test_bfloat16_walks_are_shared_where_that_pays(lib, heads, kv_heads, N, d, b
 
 @pytest.mark.parametrize("heads,kv_heads,N,d,bq,bk,levels,causal,parts", [
     (2, 2, 1721, 64, 128, 64, 2, True, 1), (16, 16, 928, 128, 256, 64, 1, False, 1), (12, 12, 1000, 128, 128, 64, 4, False, 1),
-    (28, 4, 900, 128, 128, 64, 1, True, 2), (8, 2, 1185, 128, 128, 64, 4, False, 4), (8, 2, 1258, 64, 128, 64, 1, False, 8), (4, 2, 1047, 64, 64, 8, 2, True, 1), (8, 1, 1201, 64, 128, 64, 4, False, 8)])
+    (28, 4, 900, 128, 128, 64, 1, True, 2), (8, 2, 1185, 128, 128, 64, 4, False, 4), (8, 2, 1258, 64, 128, 64, 1, False, 8), (4, 2, 1047, 64, 64, 8, 2, True, 1), (2, 2, 57, 64, 512, 64, 1, False, 1), (8, 1, 1201, 64, 128, 64, 4, False, 8)])
 def test_float32_columns_are_shared_where_that_pays(lib, heads, kv_heads, N, d, bq, bk, levels, causal, parts):
     assert gradient_shares(lib, psa.PSA_F32, heads, kv_heads, N, d, bq, bk, levels, causal) == parts
