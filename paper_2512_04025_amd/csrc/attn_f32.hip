@@ -639,9 +639,10 @@ static hipError_t launch_f32_d(const Plan& pl, const void* Q, const void* K, con
   // block lists included): 48: 25 / 31 / 33, 96: 55 / 38 / 45, 192: 106 / 93 / 80, 252: 183 / 127 / 107, 288: 225 / 190 / 151, 432: 415 / 328 / 240,
   // 564: 673 / 515 / 417; d = 64: 48: 20 / 28 / 29, 96: 28 / 31 / 32, 192: 52 / 47 / 53, 252: 77 / 61 / 66, 288: 97 / 94 / 87, 432: 177 / 151 / 129,
   // 564: 284 / 242 / 232.  So teams of four from 150 such blocks on at d = 128 and from 256 on at d = 64, where a row of keys is converted in half the time.
-  const int64_t blocks = (int64_t)pl.B * pl.Hq * pl.nq;
-  auto groups = [&](int rows) { return blocks * ((pl.bq + rows - 1) / rows); };
-  const int team = pl.bq > 64 && groups(128) >= (D == 128 ? 150 : 256) ? 4 : (pl.bq > 32 && groups(64) >= 192 ? 2 : 1);
+  // Counted in parts of 64 rows, so that a part of 128 rows that is half empty counts as half: blocks of 192 rows, dense, teams of four / two: 16 heads x 926 tokens
+  // 156 / 88, 8 x 2000 298 / 162, 28 x 926 at d = 64 113 / 69 (but 16 x 1024 153 / 163).
+  const int64_t parts = (int64_t)pl.B * pl.Hq * pl.nq * ((pl.bq + 63) / 64);
+  const int team = pl.bq > 64 && parts >= (D == 128 ? 300 : 512) ? 4 : (pl.bq > 32 && parts >= 192 ? 2 : 1);
   if (team == 4) return launch_f32_t<T, D, 4>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, s);
   if (team == 2) return launch_f32_t<T, D, 2>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, s);
   return launch_f32_t<T, D, 1>(pl, Q, K, V, Kp, Vp, M, idx, cnt, O, lse, s);

@@ -212,3 +212,27 @@ def test_infinite_keys_and_values_act_as_in_float32(N, Hq, bq, d):
 def test_gradients_of_split_columns(shape):
     """Short launches whose columns of the level map are shared by two, four, eight and two workgroups (same bars)."""
     test_backward_at_the_edges(shape)
+
+
+@pytest.mark.parametrize("Hq,N,d", [(16, 926, 128), (28, 926, 64)])
+def test_half_empty_parts_of_a_query_block_do_not_count_as_work(Hq, N, d):
+    """Blocks of 192 rows: with teams of four wavefronts every second part of 128 rows is half empty, and these calls, too short to fill
+    the chip with them, took 1.7 times as long as in blocks of 128 rows; with teams of two as long."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    Q, K, V, O = (torch.randn((1, Hq, N, d), generator=gen, device="cuda") for _ in range(4))
+
+    def best(bq):
+        gp = psa.make_params(1, Hq, Hq, N, d, bq, 64, 1, dtype=psa.PSA_F32, sq=8, sk=8)
+        times = []
+        for _ in range(8):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(10):
+                psa.psa_dense_ref(gp, Q, K, V, O)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end))
+        return min(times)
+
+    assert best(192) <= 1.3 * best(128)
